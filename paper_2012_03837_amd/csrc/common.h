@@ -62,7 +62,13 @@ struct GemmArgs {
   const void* dact_src = nullptr; int dact = ACT_NONE; int64_t ldd = 0;
   const void* res = nullptr; int64_t ldr = 0;
   int accumulate = 0;
+  // Rows of A / B that exist in memory where that differs from M / N (0: the same).  More than M: an operand stored
+  // k-major whose row pitch is padded, so that whole 16-byte chunks can be read past row M.  Fewer than N: the last
+  // columns of C are padding, computed from a repeated row.
+  int a_rows = 0, b_rows = 0;
 };
+static inline int rows_of_a(const GemmArgs& g) { return g.a_rows ? g.a_rows : g.M; }
+static inline int rows_of_b(const GemmArgs& g) { return g.b_rows ? g.b_rows : g.N; }
 
 // Convolution as an implicit GEMM over NHWC activations and [O,R,S,C] filters.
 struct ConvArgs {
@@ -126,8 +132,8 @@ hipError_t op_fill_f32(const OpCtx& c, float* p, size_t n, float v);
 hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, float* out);
 hipError_t op_copy(const OpCtx& c, const void* src, void* dst, size_t bytes);   // bytes % 16 == 0
 hipError_t op_cast_to_compute(const OpCtx& c, const float* src, void* dst, size_t n);
-// dst[C][R] = src[R][C]^T, bf16, R and C multiples of 8 and both pointers 16-byte aligned
-hipError_t op_transpose_bf16(const OpCtx& c, const void* src, void* dst, int R, int C);
+// dst[C][ldd] = src[R][C]^T, bf16, columns R .. ldd - 1 of dst zero; C and ldd multiples of 8, both pointers 16-byte aligned
+hipError_t op_transpose_bf16(const OpCtx& c, const void* src, void* dst, int R, int C, int ldd);
 
 hipError_t op_embed_fwd(const OpCtx& c, const int32_t* ids, const float* emb, const float* pe, void* out,
                         int T, int S, int d, int V);
@@ -154,9 +160,9 @@ hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const flo
 
 // Row-wise softmax cross-entropy over logits z [rows, n] (compute dtype, leading dim ld).
 // loss_rows[r] = logsumexp(z_r) - z[r, y_r].  If write_grad: z is overwritten by
-// (softmax(z_r) - onehot(y_r)) * inv_rows.
+// (softmax(z_r) - onehot(y_r)) * inv_rows, and columns n .. pad_to - 1 (pad_to <= ld; 0: none) by zeros.
 hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows,
-                         int n, int write_grad, float inv_rows);
+                         int n, int write_grad, float inv_rows, int pad_to = 0);
 hipError_t op_mean(const OpCtx& c, const float* v, int n, float* out);
 
 struct OptArgs {

@@ -68,6 +68,7 @@ struct HeadState {
   lp_head_spec s;
   size_t p_begin = 0, p_end = 0;
   int s_lo = 0, e = 0;               // window (s_lo, e]
+  int ldz = 0;                       // row pitch of the logits (and of dZ): n_classes, padded in vocabulary heads
   std::map<std::string, int> t;
 };
 
@@ -121,11 +122,13 @@ struct lp_ctx : lp_scratch {
   hipStream_t stream = nullptr;
   // device memory (borrowed)
   float* master = nullptr; void* lowp = nullptr;
-  // transposed bf16 copy [in][out] of a weight [out][in], per tensor (null: none).  Kept for the vocabulary
+  // transposed bf16 copy [in][wt_ld] of a weight [out][in], per tensor (null: none; wt_ld = out rounded up to 64, the
+  // padding zero, so that any vocabulary is a whole number of 64-deep k-tiles).  Kept for the vocabulary
   // heads: their input-gradient GEMM then has the reduction index fastest in both operands, which the
   // direct-to-LDS kernel runs 18 % faster than with a k-major operand (ds_read_b128 instead of two
   // transposing 8-byte reads per fragment).
   std::vector<void*> wt;
+  static int wt_ld(const lp::Tensor& w) { return (int)((w.shape[0] + 63) & ~(int64_t)63); }
   // running statistics of every batch normalisation: for the gain tensor with index i and C channels,
   // run_off[i] >= 0 and bn_run + run_off[i] holds the running mean, the next C floats the running variance
   float* bn_run = nullptr;

@@ -46,7 +46,7 @@ static GemmArgs lin_dgrad(const lp_ctx* c, const void* dy, int rows, int ti_w, v
   const Tensor& w = c->tensors[ti_w];
   GemmArgs g;
   g.A = dy; g.lda = w.shape[0]; g.a_kc = 1;
-  if (c->wt[ti_w]) { g.B = c->wt[ti_w]; g.ldb = w.shape[0]; g.b_kc = 1; }     // transposed copy [in][out]
+  if (c->wt[ti_w]) { g.B = c->wt[ti_w]; g.ldb = lp_ctx::wt_ld(w); g.b_kc = 1; }     // transposed copy [in][out]
   else { g.B = c->W(ti_w); g.ldb = w.shape[1]; g.b_kc = 0; }
   g.C = dx; g.ldc = w.shape[1];
   g.M = rows; g.N = (int)w.shape[1]; g.K = (int)w.shape[0];
@@ -331,6 +331,29 @@ int drv_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool 
 }
 
 // ===================================================================================== heads
+// The three products of a vocabulary head, whose logits have a padded pitch (HeadState::ldz): the forward product
+// fills whole 8-column chunks (columns past the vocabulary come from a repeated weight row and are never used), the
+// weight gradient reads whole chunks of dZ's rows, and the input gradient runs over the padding too where the
+// transposed weight copy has the same one (zeros in both).
+static GemmArgs head_fwd(const lp_ctx* c, const HeadState& Hd, int rows, int ti_w, void* z) {
+  GemmArgs g = lin_fwd(c, c->feat, rows, ti_w, -1, z);
+  g.ldc = Hd.ldz;
+  if (Hd.ldz > g.N && g.K % 8 == 0) { g.b_rows = g.N; g.N = (g.N + 7) & ~7; }
+  return g;
+}
+static GemmArgs head_wgrad(const lp_ctx* c, const HeadState& Hd, const void* dz, int rows, int ti_w) {
+  GemmArgs g = lin_wgrad(c, dz, c->feat, rows, ti_w, 0);
+  g.lda = Hd.ldz;
+  if (Hd.ldz > g.M) g.a_rows = (g.M + 7) & ~7;
+  return g;
+}
+static GemmArgs head_dgrad(const lp_ctx* c, const HeadState& Hd, const void* dz, int rows, int ti_w, void* dx) {
+  GemmArgs g = lin_dgrad(c, dz, rows, ti_w, dx);
+  g.lda = Hd.ldz;
+  if (g.b_kc) g.K = Hd.ldz;
+  return g;
+}
+
 // The vocabulary head (LayerNorm, projection, cross-entropy) in stages, like the decoder layer: stage 0 ends in the
 // logits product, stage 1 (loss, dZ) in the head's weight gradient, stage 2 in its input gradient, stage 3 is the
 // LayerNorm backward.  Without `backward` only stages 0 and 1 do anything, and stage 1 hands back no product.
@@ -343,13 +366,13 @@ int vocab_head_stage(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss
   out->n = 0;
   if (stage == 0) {
     DO(op_layernorm_fwd(o, L.out, c->P32(Hd.t["ln.g"]), c->P32(Hd.t["ln.b"]), c->feat, c->hmean, c->hrstd, rows, in_dim));
-    out->g[out->n++] = lin_fwd(c, c->feat, rows, Hd.t["w"], -1, c->logits);
+    out->g[out->n++] = head_fwd(c, Hd, rows, Hd.t["w"], c->logits);
   } else if (stage == 1) {
-    DO(op_softmax_ce(o, c->logits, ncls, y, c->loss_rows, rows, ncls, backward ? 1 : 0, 1.0f / (float)rows));
+    DO(op_softmax_ce(o, c->logits, Hd.ldz, y, c->loss_rows, rows, ncls, backward ? 1 : 0, 1.0f / (float)rows, Hd.ldz));
     DO(op_mean(o, c->loss_rows, rows, loss_out));
-    if (backward) out->g[out->n++] = lin_wgrad(c, c->logits, c->feat, rows, Hd.t["w"], 0);    // logits now hold dZ
+    if (backward) out->g[out->n++] = head_wgrad(c, Hd, c->logits, rows, Hd.t["w"]);    // logits now hold dZ
   } else if (stage == 2) {
-    if (backward) out->g[out->n++] = lin_dgrad(c, c->logits, rows, Hd.t["w"], c->dfeat);
+    if (backward) out->g[out->n++] = head_dgrad(c, Hd, c->logits, rows, Hd.t["w"], c->dfeat);
   } else if (backward) {
     DO(op_layernorm_bwd(o, c->dfeat, L.out, c->hmean, c->hrstd, c->P32(Hd.t["ln.g"]), nullptr, dh,
                         c->G32(Hd.t["ln.g"]), c->G32(Hd.t["ln.b"]), rows, in_dim, 0));

@@ -12,7 +12,7 @@ hipError_t ln_bwd_fast(const OpCtx& c, const void* dy, const void* x, const floa
                        const float* g, const void* add, void* dx, int rows, int d, int* nblk_out);
 bool ce_fast_ok(const OpCtx& c, const void* z, int64_t ld, int n);
 hipError_t ce_fast(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows, int n,
-                   int write_grad, float inv_rows);
+                   int write_grad, float inv_rows, int pad_to);
 
 #define LP_LAUNCH_CHECK() hipGetLastError()
 
@@ -532,7 +532,7 @@ hipError_t op_colsum_batched(const OpCtx& c, int count, const void* const* dy, c
 // write_grad): z <- (exp(z - lse) - [j == y]) * inv_rows.
 template <typename T>
 __global__ void k_softmax_ce(T* z, int64_t ld, const int32_t* y, float* loss_rows, int n, int write_grad,
-                             float inv_rows) {
+                             float inv_rows, int pad_to) {
   __shared__ float sh[4];
   int row = blockIdx.x;
   T* zr = z + (size_t)row * ld;
@@ -556,15 +556,18 @@ __global__ void k_softmax_ce(T* z, int64_t ld, const int32_t* y, float* loss_row
       if (j == yy) p -= 1.f;
       zr[j] = from_f<T>(p * inv_rows);
     }
+    for (int j = n + threadIdx.x; j < pad_to; j += 256) zr[j] = from_f<T>(0.f);
   }
 }
 hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows, int n,
-                         int write_grad, float inv_rows) {
+                         int write_grad, float inv_rows, int pad_to) {
   ProfScope prof_(c, KC_SOFTMAX_CE);
   if (rows == 0) return hipSuccess;
-  if (ce_fast_ok(c, z, ld, n)) return ce_fast(c, z, ld, y, loss_rows, rows, n, write_grad, inv_rows);
-  if (c.dt == BF16) k_softmax_ce<bf16_t><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows);
-  else k_softmax_ce<float><<<rows, 256, 0, c.stream>>>((float*)z, ld, y, loss_rows, n, write_grad, inv_rows);
+  if (pad_to > ld) return hipErrorInvalidValue;
+  // a row that does not end on a 16-byte chunk needs its padding: the last chunk is read and written whole
+  if (ce_fast_ok(c, z, ld, n) && (n % 8 == 0 || pad_to >= n)) return ce_fast(c, z, ld, y, loss_rows, rows, n, write_grad, inv_rows, pad_to);
+  if (c.dt == BF16) k_softmax_ce<bf16_t><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
+  else k_softmax_ce<float><<<rows, 256, 0, c.stream>>>((float*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
   return LP_LAUNCH_CHECK();
 }
 
@@ -675,7 +678,7 @@ hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float*
 
 // ------------------------------------------------------------------------------------ transpose
 // 64 x 64 tiles through LDS: 16-byte loads of 8 columns, 16-byte stores of 8 rows gathered from a padded tile.
-__global__ void __launch_bounds__(256) k_transpose_bf16(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, int R, int C) {
+__global__ void __launch_bounds__(256) k_transpose_bf16(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, int R, int C, int ldd) {
   __shared__ bf16_t tile[64][64 + 2];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int tr = threadIdx.x >> 3, tc = (threadIdx.x & 7) * 8;
@@ -695,20 +698,20 @@ __global__ void __launch_bounds__(256) k_transpose_bf16(const bf16_t* __restrict
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int c = c0 + tr + 32 * i, r = r0 + tc;      // output row c, output columns r .. r+7
-    if (c < C && r < R) {
+    if (c < C && r < ldd) {       // rows past R were fetched as zeros
       bf16x8 v;
 #pragma unroll
       for (int x = 0; x < 8; ++x) v[x] = tile[tc + x][tr + 32 * i];
-      *reinterpret_cast<bf16x8*>(dst + (size_t)c * R + r) = v;
+      *reinterpret_cast<bf16x8*>(dst + (size_t)c * ldd + r) = v;
     }
   }
 }
-hipError_t op_transpose_bf16(const OpCtx& c, const void* src, void* dst, int R, int C) {
+hipError_t op_transpose_bf16(const OpCtx& c, const void* src, void* dst, int R, int C, int ldd) {
   ProfScope prof_(c, KC_OTHER);
   if (R <= 0 || C <= 0) return hipSuccess;
-  if (R % 8 || C % 8 || (((uintptr_t)src | (uintptr_t)dst) & 15)) return hipErrorInvalidValue;
-  dim3 grid((C + 63) / 64, (R + 63) / 64);
-  k_transpose_bf16<<<grid, 256, 0, c.stream>>>((const bf16_t*)src, (bf16_t*)dst, R, C);
+  if (ldd < R || ldd % 8 || C % 8 || (((uintptr_t)src | (uintptr_t)dst) & 15)) return hipErrorInvalidValue;
+  dim3 grid((C + 63) / 64, (ldd + 63) / 64);
+  k_transpose_bf16<<<grid, 256, 0, c.stream>>>((const bf16_t*)src, (bf16_t*)dst, R, C, ldd);
   return LP_LAUNCH_CHECK();
 }
 

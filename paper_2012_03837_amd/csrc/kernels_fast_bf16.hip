@@ -185,13 +185,16 @@ __global__ void __launch_bounds__(256) k_ln_bwd_v(const bf16_t* __restrict__ dy,
   }
 }
 
-// Softmax cross-entropy with the whole row in registers (<= 16 chunks of 8 logits per thread).
+// Softmax cross-entropy with the whole row in registers (<= 16 chunks of 8 logits per thread).  TAIL: n is not a
+// multiple of 8; the last chunk reaches into the row's padding, whose values count as -inf.  Chunks from n up to
+// pad_to are cleared together with the gradient's write (a padded dZ is read whole by the products behind it).
 constexpr int kCeChunks = 16;
+template <bool TAIL>
 __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, int64_t ld, const int32_t* __restrict__ y,
                                                         float* __restrict__ loss_rows, int n, int write_grad,
-                                                        float inv_rows) {
+                                                        float inv_rows, int pad_to) {
   __shared__ float sh[8];
-  const int row = blockIdx.x, nch = n >> 3;
+  const int row = blockIdx.x, nch = TAIL ? (n + 7) >> 3 : n >> 3;
   bf16_t* zr = z + (size_t)row * ld;
   bf16x8 v[kCeChunks];
   float m = -INFINITY;
@@ -200,6 +203,11 @@ __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, 
     int c = threadIdx.x + 256 * i;
     if (c < nch) {
       v[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(zr + 8 * c));
+      if (TAIL) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (8 * c + e >= n) v[i][e] = (bf16_t)(-INFINITY);
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) m = fmaxf(m, (float)v[i][e]);
     }
@@ -235,10 +243,12 @@ __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, 
         float p = __expf((float)v[i][e] - lse);
         if (8 * c + e == yy) p -= 1.f;
         o[e] = (bf16_t)(p * inv_rows);
+        if (TAIL && 8 * c + e >= n) o[e] = (bf16_t)0.f;
       }
       __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(zr + 8 * c));
     }
   }
+  for (int j = 8 * nch + threadIdx.x; j < pad_to; j += 256) zr[j] = (bf16_t)0.f;
 }
 
 bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -271,11 +281,12 @@ hipError_t ln_bwd_fast(const OpCtx& c, const void* dy, const void* x, const floa
   return hipGetLastError();
 }
 bool ce_fast_ok(const OpCtx& c, const void* z, int64_t ld, int n) {
-  return c.dt == BF16 && n % 8 == 0 && ld % 8 == 0 && n <= kCeChunks * 256 * 8 && al16(z);
+  return c.dt == BF16 && ld % 8 == 0 && n <= kCeChunks * 256 * 8 && al16(z);
 }
 hipError_t ce_fast(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows, int n,
-                   int write_grad, float inv_rows) {
-  k_softmax_ce_reg<<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows);
+                   int write_grad, float inv_rows, int pad_to) {
+  if (n % 8) k_softmax_ce_reg<true><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
+  else k_softmax_ce_reg<false><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
   return hipGetLastError();
 }
 

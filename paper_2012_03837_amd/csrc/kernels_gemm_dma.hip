@@ -25,7 +25,8 @@
 // finished item is written.  Hand-pipelined main loop (PIPE): the k-tiles of all of a block's items form
 // one stream through the ring of stages, so the loader stays NSTAGE-1 k-tiles ahead across item boundaries
 // and the next item's first k-tiles are in flight while a finished item is written; see the comment in the kernel.
-// Requires K % 32 == 0 (no zero fill on this path).
+// The 32-deep shapes require K % 32 == 0 (no zero fill on their path); the 64-deep one takes any K >= 64, a
+// multiple of 8 if an operand is stored with k contiguous.
 #include <stdio.h>
 #include <stdlib.h>
 #include <type_traits>
@@ -119,13 +120,17 @@ __device__ __forceinline__ void epilogue8(const Epilogue& e, int m, int n, float
 }
 
 // Per-lane global pointers of the direct-to-LDS loads of one operand: NI loads per thread per k-tile.
-// ROWS = tile rows of this operand.  The pointers are for k-tile 0; a k-tile step adds `kstep` elements.
+// ROWS = tile rows of this operand.  The pointers are for the item's first k-tile; a later one adds its k.
+// A last k-tile that would reach past the end of the reduction is loaded KT - K % KT earlier (k >= klim never
+// starts a tile): everything stays inside the operand, and the kernel clears what an earlier k-tile has counted.
 template <bool KC, int ROWS, int NI, int KT = 32>
 struct DmaPlan {
   const bf16_t* g[NI];
   int lds_off[NI];      // byte offset of the wave's 1 KB destination inside the operand's stage region
-  int64_t kstep;
-  __device__ __forceinline__ void init(const Operand& o, int r0, int wave, int lane, int kbase) {
+  int64_t kmul;
+  int klim;
+  __device__ __forceinline__ void init(const Operand& o, int r0, int wave, int lane, int kbase, int K) {
+    klim = K - KT - kbase;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       int q = wave * NI + i;              // which 1 KB of the tile
@@ -154,12 +159,13 @@ struct DmaPlan {
         g[i] = o.p + (size_t)(kbase + k) * o.ld + rg;
       }
     }
-    kstep = KC ? (int64_t)KT : (int64_t)KT * o.ld;
+    kmul = KC ? 1 : o.ld;
   }
   __device__ __forceinline__ void issue(char* stage_base, int tile) const {
+    const int64_t off = (int64_t)(tile * KT < klim ? tile * KT : klim) * kmul;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const bf16_t* src = g[i] + (int64_t)tile * kstep;
+      const bf16_t* src = g[i] + off;
       __builtin_amdgcn_global_load_lds((glb_void*)src, (lds_void*)(stage_base + lds_off[i]), 16, 0, 0);
     }
   }
@@ -206,6 +212,7 @@ __device__ __forceinline__ bf16x8 frag_t(const char* sm, int rowbase, int k) {
 struct SkPlan {
   int tiles_m, tiles_n, kt;
   int full, tail_tiles, upb, G;
+  int K;        // length of the reduction (the last k-tile may be partly past it, see DmaPlan)
   int sib;      // 0: ordinary; otherwise tiles_n (panel mode)
   int ngrp;     // 0: one problem; otherwise the number of problems of a grouped launch (see GroupTable)
 };
@@ -495,6 +502,25 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
                      : frag_t<BM>(as, wm + 32 * j + m_rowbase_t, 16 * kk + 8 * hf + kq);
     };
     constexpr int NDS = (A_KC ? 4 : 8) + (B_KC ? TN : 2 * TN);
+    // The reduction's last k-tile, if it is partial, holds the last 64 of k: the first `skip` of them belong to the
+    // k-tile before it and are cleared in the m-side operand (finite values times zero).  Once per output tile, by
+    // all waves, between the barrier that says the k-tile has landed and its first fragment reads.
+    const int skip = p.kt * KT - p.K;
+    auto clear_counted = [&](int stage) {
+      char* as = smem + stage * STAGE_BYTES;
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      if (A_KC) {              // K is a multiple of 8: whole 16-byte chunks
+#pragma unroll 1
+        for (int i = threadIdx.x; i < BM * 8; i += 64 * NWAVES) {
+          const int row = i >> 3, c = i & 7;
+          if (8 * c < skip) *reinterpret_cast<f32x4*>(as + row * 128 + 16 * (c ^ ((row >> 1) & 7))) = zero;
+        }
+      } else {
+#pragma unroll 1
+        for (int i = threadIdx.x; i < skip * (BM * 2 / 16); i += 64 * NWAVES) *reinterpret_cast<f32x4*>(as + 16 * i) = zero;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
     ItemIter L = first_item(), C = L;
     int lt = 0, l_left = 0, lstage = 0, cstage = 0, inflight = 0;
     auto loader_ready = [&]() -> bool {
@@ -503,12 +529,12 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       int tm, tn;
       if (p.ngrp) {
         const int g = __builtin_amdgcn_readfirstlane(group_tile_coords(gt, p.ngrp, L.q, tm, tn));
-        pa.init(gt.A[g], tm * BM, wave, lane, L.ks * KT);
-        pb.init(gt.B[g], tn * BN, wave, lane, L.ks * KT);
+        pa.init(gt.A[g], tm * BM, wave, lane, L.ks * KT, p.K);
+        pb.init(gt.B[g], tn * BN, wave, lane, L.ks * KT, p.K);
       } else {
         plan_tile_coords(p, L.q, tm, tn);
-        pa.init(A, tm * BM, wave, lane, L.ks * KT);
-        pb.init(B, tn * BN, wave, lane, L.ks * KT);
+        pa.init(A, tm * BM, wave, lane, L.ks * KT, p.K);
+        pb.init(B, tn * BN, wave, lane, L.ks * KT, p.K);
       }
       lt = 0; l_left = L.ke - L.ks;
       return true;
@@ -527,6 +553,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
     bf16x8 fn0[TN], fm0[4], fn1[TN], fm1[4];
     if (inflight >= 2) wait_loads_and_barrier<LPT>(); else wait_loads_and_barrier<0>();
     --inflight;
+    if (skip > 0 && C.ks == p.kt - 1) clear_counted(0);
     read(smem, smem + A_BYTES, 0, fn0, fm0);
     for (;;) {
       f32x16 acc[TN][4];
@@ -547,7 +574,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       // item, so everything is unconditional: the A half of k-tile t + 2 goes out in t's last substep (behind the
       // barrier), its B half in the first substep of t + 1, so that a wave's eight loads do not reach the memory
       // pipeline in one burst.  Otherwise (0) the whole k-tile goes out in the last substep, if there is one.
-      auto step = [&](auto steady, bool last) {
+      auto step = [&](auto steady, bool last, bool tail_next) {
         constexpr int ST = decltype(steady)::value;
         const char* as = smem + cstage * STAGE_BYTES;
         const char* bs = as + A_BYTES;
@@ -589,6 +616,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
             --inflight;
             cstage ^= 1;
             if (load) issue_tile();
+            if (tail_next) clear_counted(cstage);
             if (!last) read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
           }
           mma(fn1, fm1);
@@ -600,15 +628,16 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       int t = 0;
       typedef std::integral_constant<int, 0> General;
       if (nt >= 3) {           // k-tiles 0 .. nt - 3 have their k-tile t + 2 inside this item
-        step(std::integral_constant<int, 1>{}, false);
-        for (t = 1; t + 3 <= nt; ++t) step(std::integral_constant<int, 2>{}, false);
+        step(std::integral_constant<int, 1>{}, false, false);
+        for (t = 1; t + 3 <= nt; ++t) step(std::integral_constant<int, 2>{}, false, false);
         pb.issue(smem + (lstage ^ 1) * STAGE_BYTES + A_BYTES, lt - 1);
       }
-      for (; t < nt; ++t) step(General{}, t + 1 == nt);
+      for (; t < nt; ++t) step(General{}, t + 1 == nt, skip > 0 && t + 1 < nt && C.ks + t + 2 == p.kt);
       const ItemIter done = C;
       const bool have = advance(C);
       write_item(acc, done);
       if (!have) break;
+      if (skip > 0 && C.ks == p.kt - 1) clear_counted(cstage);
       read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
     }
   } else if constexpr (PIPE) {
@@ -648,12 +677,12 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       int tm, tn;
       if (p.ngrp) {
         const int g = __builtin_amdgcn_readfirstlane(group_tile_coords(gt, p.ngrp, L.q, tm, tn));
-        pa.init(gt.A[g], tm * BM, wave, lane, L.ks * KT);
-        pb.init(gt.B[g], tn * BN, wave, lane, L.ks * KT);
+        pa.init(gt.A[g], tm * BM, wave, lane, L.ks * KT, p.K);
+        pb.init(gt.B[g], tn * BN, wave, lane, L.ks * KT, p.K);
       } else {
         plan_tile_coords(p, L.q, tm, tn);
-        pa.init(A, tm * BM, wave, lane, L.ks * KT);
-        pb.init(B, tn * BN, wave, lane, L.ks * KT);
+        pa.init(A, tm * BM, wave, lane, L.ks * KT, p.K);
+        pb.init(B, tn * BN, wave, lane, L.ks * KT, p.K);
       }
       lt = 0; l_left = L.ke - L.ks;
       return true;
@@ -771,12 +800,12 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       nt = I.ke - I.ks;
       if (p.ngrp) {
         const int g = __builtin_amdgcn_readfirstlane(group_tile_coords(gt, p.ngrp, I.q, tm, tn));
-        pa.init(gt.A[g], tm * BM, wave, lane, I.ks * KT);
-        pb.init(gt.B[g], tn * BN, wave, lane, I.ks * KT);
+        pa.init(gt.A[g], tm * BM, wave, lane, I.ks * KT, p.K);
+        pb.init(gt.B[g], tn * BN, wave, lane, I.ks * KT, p.K);
       } else {
         plan_tile_coords(p, I.q, tm, tn);
-        pa.init(A, tm * BM, wave, lane, I.ks * KT);
-        pb.init(B, tn * BN, wave, lane, I.ks * KT);
+        pa.init(A, tm * BM, wave, lane, I.ks * KT, p.K);
+        pb.init(B, tn * BN, wave, lane, I.ks * KT, p.K);
       }
 #pragma unroll
       for (int s = 0; s < NSTAGE - 1; ++s)
@@ -901,7 +930,7 @@ hipError_t launch(const OpCtx& c, const GemmArgs& g, const SkPlan& p, bool parti
     if (e != hipSuccess) return e;
     configured = true;
   }
-  Operand A{(const bf16_t*)g.A, g.lda, g.M}, B{(const bf16_t*)g.B, g.ldb, g.N};
+  Operand A{(const bf16_t*)g.A, g.lda, rows_of_a(g)}, B{(const bf16_t*)g.B, g.ldb, rows_of_b(g)};
   Epilogue e = make_epilogue(g);
   static char kname[64];
   if (!kname[0])
@@ -922,24 +951,26 @@ hipError_t launch(const OpCtx& c, const GemmArgs& g, const SkPlan& p, bool parti
 
 }  // namespace
 
-// The DMA kernel takes: K a multiple of 32, and an operand stored k-major needs at least one full
-// 8-row chunk column set (rows >= 8, rows % 8 == 0 is already required by the caller's checks).
-bool gemm_dma_ok(const GemmArgs& g) { return g.K % 32 == 0 && g.K >= 32 && g.M >= 8 && g.N >= 8; }
+// The 64-deep kernel takes any reduction of at least 64 (K % 8 == 0 with a k-contiguous operand is already
+// required by the caller's checks, and so are the whole 8-row chunks of an operand stored k-major); the 32-deep
+// shapes need whole k-tiles (gemm_dma_plan).
+bool gemm_dma_ok(const GemmArgs& g) { return (g.K >= 64 || g.K == 32) && g.M >= 8 && g.N >= 8; }
 
 // Distribution of an M x N x K problem over the persistent grid of one tile shape
 // (kind 0: 256 x 128, two blocks per CU; 1: 256 x 256 with 8 waves; 2: 256 x 256 with 4 waves).
 // mode 0: every tile whole, one per block per wave; 1: the last, partial wave of tiles cut along k;
 // 2: panel mode (see SkPlan).  Modes 1 and 2 need workspace.  Returns false if the mode does not apply.
 bool gemm_dma_plan(const OpCtx& c, const GemmArgs& g, int kind, int mode, DmaGemmPlan* out) {
-  // kind 3: 256 x 256 with 8 waves and 64-deep k-tiles (K a multiple of 64)
-  if (kind == 3 && g.K % 64 != 0) return false;
+  // kind 3: 256 x 256 with 8 waves and 64-deep k-tiles
+  if (kind == 3 ? g.K < 64 : g.K % BK != 0) return false;
   const int bk = kind == 3 ? 64 : BK;
   const int bn = kind == 0 ? 128 : 256, per_cu = kind == 0 ? 2 : 1;
   SkPlan p;
   p.G = (device_cus() * per_cu) & ~7;
   p.tiles_m = (g.M + BM - 1) / BM;
   p.tiles_n = (g.N + bn - 1) / bn;
-  p.kt = g.K / bk;
+  p.kt = (g.K + bk - 1) / bk;
+  p.K = g.K;
   p.sib = 0;
   p.ngrp = 0;
   const long T = (long)p.tiles_m * p.tiles_n;
@@ -1000,7 +1031,7 @@ bool gemm_dma_plan(const OpCtx& c, const GemmArgs& g, int kind, int mode, DmaGem
 hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d) {
   SkPlan p;
   p.tiles_m = d.tiles_m; p.tiles_n = d.tiles_n; p.kt = d.kt; p.full = d.full; p.tail_tiles = d.tail_tiles;
-  p.upb = d.upb; p.G = d.G; p.sib = d.sib; p.ngrp = 0;
+  p.upb = d.upb; p.G = d.G; p.sib = d.sib; p.ngrp = 0; p.K = g.K;
   const bool partials = d.partial_bytes > 0;
 #define LP_DMA(AK, BK_)                                                    \
   (d.kind == 3 ? launch<AK, BK_, 4, 2, 2, true, 64>(c, g, p, partials)            \
@@ -1015,7 +1046,7 @@ hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d) {
 }
 
 // Grouped launch of n products (see GroupTable).  Returns hipErrorInvalidValue, with nothing launched, if the set
-// does not qualify (the caller then launches them one by one): bf16 operands, the same K (a multiple of 32) and the
+// does not qualify (the caller then launches them one by one): bf16 operands, the same K (at least 128, or a multiple of 32) and the
 // same operand layouts for all, every pointer and leading dimension fit for 16-byte accesses, at most kMaxGroup
 // problems, workspace for the cut tail.  Epilogues and output types may differ from problem to problem.
 hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
@@ -1028,7 +1059,7 @@ hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
     if (!gemm_dma_ok(g) || g.K != g0.K || g.a_kc != g0.a_kc || g.b_kc != g0.b_kc) return hipErrorInvalidValue;
-    if (g.M % 8 || g.N % 8 || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || !al16(g.A) || !al16(g.B) || !al16(g.C) ||
+    if (g.a_rows || g.b_rows || (!g.a_kc && g.M % 8) || g.N % 8 || ((g.a_kc || g.b_kc) && g.K % 8) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || !al16(g.A) || !al16(g.B) || !al16(g.C) ||
         (g.bias && !al16(g.bias)) || (g.pre && !al16(g.pre)) || (g.dact_src && (!al16(g.dact_src) || g.ldd % 8)) ||
         (g.res && (!al16(g.res) || g.ldr % 8)))
       return hipErrorInvalidValue;
@@ -1047,10 +1078,12 @@ hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   p.tiles_m = (int)T; p.tiles_n = 1;                 // only the product is used outside the tile numbering
   static int deep_ok = -1;           // LP_GROUP_K64=0 keeps the 32-deep k-tiles (for measurements)
   if (deep_ok < 0) { const char* e = getenv("LP_GROUP_K64"); deep_ok = (e && e[0] == '0') ? 0 : 1; }
-  const bool deep = deep_ok && g0.K % 64 == 0 && g0.K >= 128;
+  const bool deep = (deep_ok || g0.K % BK != 0) && g0.K >= 128;
+  if (!deep && g0.K % BK != 0) return hipErrorInvalidValue;
   const int bk = deep ? 64 : BK;
   const long min_len = deep ? 2 : 4;
-  p.kt = g0.K / bk;
+  p.kt = (g0.K + bk - 1) / bk;
+  p.K = g0.K;
   p.sib = 0; p.ngrp = n;
   p.full = (int)(T / p.G);
   p.tail_tiles = (int)(T - (long)p.full * p.G);

@@ -252,7 +252,9 @@ static hipError_t gemm_plain_t(const OpCtx& c, const GemmArgs& g) {
   }
   return launch_plain<T>(c.stream, A, B, make_epilogue(g), g.M, g.N, g.K);
 }
-hipError_t gemm_plain(const OpCtx& c, const GemmArgs& g) {
+hipError_t gemm_plain(const OpCtx& c, const GemmArgs& ga) {
+  GemmArgs g = ga;
+  if (g.b_rows && g.b_rows < g.N) g.N = g.b_rows;      // element by element: no padding columns
   return c.dt == BF16 ? gemm_plain_t<bf16_t>(c, g) : gemm_plain_t<float>(c, g);
 }
 

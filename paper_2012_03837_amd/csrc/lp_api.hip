@@ -310,7 +310,11 @@ static void plan(lp_ctx* c, const lp_buffers* buf, lp_sizes* sizes) {
   for (auto& Hd : c->heads) {
     const lp_layer_spec& l = c->layers[Hd.e].s;
     size_t rows = kind0 == LP_LAYER_DECODER ? (size_t)B * l.seq_len : (size_t)B;
-    if (rows * Hd.s.n_classes > max_head_logits) max_head_logits = rows * Hd.s.n_classes;
+    // A vocabulary head's logits have a pitch of whole 64-deep k-tiles (128-byte lines) whatever the vocabulary: the
+    // products on either side take 16-byte chunks, and the cross-entropy clears the padding of dZ.
+    Hd.ldz = Hd.s.n_classes;
+    if (dt == BF16 && Hd.s.kind == LP_HEAD_LN_LINEAR_CE) Hd.ldz = (Hd.ldz + 63) & ~63;
+    if (rows * Hd.ldz > max_head_logits) max_head_logits = rows * Hd.ldz;
     if (rows * Hd.s.in_dim > max_feat) max_feat = rows * Hd.s.in_dim;
     if (rows > max_rows) max_rows = rows;
     if ((size_t)Hd.s.in_dim > max_rows) max_rows = Hd.s.in_dim;      // per-channel statistics of a BatchNorm head
@@ -328,7 +332,7 @@ static void plan(lp_ctx* c, const lp_buffers* buf, lp_sizes* sizes) {
     for (auto& Hd : c->heads)
       if (Hd.s.kind == LP_HEAD_LN_LINEAR_CE && Hd.t.count("w")) {
         const Tensor& w = c->tensors[Hd.t["w"]];
-        if (w.shape[0] % 8 == 0 && w.shape[1] % 8 == 0) c->wt[Hd.t["w"]] = wa.take(w.numel * 2);
+        if (w.shape[1] % 8 == 0) c->wt[Hd.t["w"]] = wa.take((size_t)lp_ctx::wt_ld(w) * w.shape[1] * 2);
       }
   if (sp.schedule != LP_SCHED_SYNC) {
     const int J = sp.n_heads;
@@ -421,7 +425,7 @@ static int refresh_wt(lp_ctx* c, size_t off, size_t n) {
   for (size_t ti = 0; ti < c->wt.size(); ++ti) {
     const Tensor& t = c->tensors[ti];
     if (!c->wt[ti] || t.off < off || t.off >= off + n) continue;
-    CK(op_transpose_bf16(c->op(), c->W((int)ti), c->wt[ti], (int)t.shape[0], (int)t.shape[1]));
+    CK(op_transpose_bf16(c->op(), c->W((int)ti), c->wt[ti], (int)t.shape[0], (int)t.shape[1], lp_ctx::wt_ld(t)));
   }
   return LP_OK;
 }
@@ -497,7 +501,7 @@ extern "C" int lp_init_blocks(const lp_model_spec* spec, const lp_buffers* buffe
   if (c->dt == BF16) {
     CKI(op_cast_to_compute(o, c->master, c->lowp, c->P));
     for (size_t ti = 0; ti < c->wt.size(); ++ti)
-      if (c->wt[ti]) CKI(op_transpose_bf16(o, c->W((int)ti), c->wt[ti], (int)c->tensors[ti].shape[0], (int)c->tensors[ti].shape[1]));
+      if (c->wt[ti]) CKI(op_transpose_bf16(o, c->W((int)ti), c->wt[ti], (int)c->tensors[ti].shape[0], (int)c->tensors[ti].shape[1], lp_ctx::wt_ld(c->tensors[ti])));
   }
   if (c->pe) CKI(op_posenc_init(o, c->pe, spec->layers[0].seq_len, spec->layers[0].width));
   CKI(hipStreamSynchronize(c->stream));
