@@ -200,8 +200,25 @@ __global__ void k_avgpool_bwd(const T* dfeat, T* dx, size_t n, int HW, int C) {
     dx[i] = from_f<T>(to_f(dfeat[img * C + c]) * inv);
   }
 }
+// The same, 16 bytes per thread (C a multiple of the vector): 262144 x 64 bf16 (33.6 MB written), 15 -> 6.5 us averaged over the stages.
+template <typename T>
+__global__ void __launch_bounds__(256) k_avgpool_bwd_v(const T* __restrict__ dfeat, T* __restrict__ dx, size_t nv, int HW, int C) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  const size_t st = (size_t)gridDim.x * 256;
+  const unsigned CV = C / VEC;
+  const float inv = 1.f / (float)HW;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nv; i += st) {
+    const size_t row = i / CV, img = row / (unsigned)HW;
+    vec_t v = *reinterpret_cast<const vec_t*>(dfeat + img * C + (i - row * CV) * VEC);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] = from_f<T>(to_f(v[e]) * inv);
+    *reinterpret_cast<vec_t*>(dx + i * VEC) = v;
+  }
+}
 // One block per image, 16-byte loads: thread (p, cv) sums channel vector cv over pixels p, p + P, ...
-// (P = 256 / channel vectors), then the P partial sums of a channel are added in order of p.
+// (P = floor(256 / channel vectors), the threads left over idle), then the P partial sums of a channel are added in
+// order of p.
 template <typename T>
 __global__ void __launch_bounds__(256) k_avgpool_fwd_v(const T* __restrict__ x, T* __restrict__ out, int HW, int C) {
   constexpr int VEC = 16 / (int)sizeof(T);
@@ -213,13 +230,14 @@ __global__ void __launch_bounds__(256) k_avgpool_fwd_v(const T* __restrict__ x, 
   float a[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) a[e] = 0.f;
-  for (int i = p; i < HW; i += P) {
+  for (int i = p < P ? p : HW; i < HW; i += P) {
     vec_t v = *reinterpret_cast<const vec_t*>(xi + (size_t)i * C);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a[e] += to_f(v[e]);
   }
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) part[p * C + cv * VEC + e] = a[e];
+  for (int e = 0; e < VEC; ++e)
+    if (p < P) part[p * C + cv * VEC + e] = a[e];
   __syncthreads();
   for (int ch = threadIdx.x; ch < C; ch += 256) {
     float t = 0.f;
@@ -231,7 +249,7 @@ hipError_t op_avgpool_fwd(const OpCtx& c, const void* x, void* out, int N, int H
   ProfScope prof_(c, KC_OTHER);
   if (N == 0) return hipSuccess;
   const int vec = c.dt == BF16 ? 8 : 4;
-  if (C % vec == 0 && C / vec <= 256 && 256 % (C / vec) == 0 && ((uintptr_t)x & 15) == 0) {
+  if (C % vec == 0 && C / vec <= 256 && ((uintptr_t)x & 15) == 0) {
     if (c.dt == BF16) k_avgpool_fwd_v<bf16_t><<<N, 256, 0, c.stream>>>((const bf16_t*)x, (bf16_t*)out, HW, C);
     else k_avgpool_fwd_v<float><<<N, 256, 0, c.stream>>>((const float*)x, (float*)out, HW, C);
     return hipGetLastError();
@@ -244,6 +262,13 @@ hipError_t op_avgpool_bwd(const OpCtx& c, const void* dfeat, void* dx, int N, in
   ProfScope prof_(c, KC_OTHER);
   size_t n = (size_t)N * HW * C;
   if (n == 0) return hipSuccess;
+  const int vec = c.dt == BF16 ? 8 : 4;
+  if (C % vec == 0 && (((uintptr_t)dfeat | (uintptr_t)dx) & 15) == 0) {
+    const size_t nv = n / vec;
+    if (c.dt == BF16) k_avgpool_bwd_v<bf16_t><<<ew_blocks(nv), 256, 0, c.stream>>>((const bf16_t*)dfeat, (bf16_t*)dx, nv, HW, C);
+    else k_avgpool_bwd_v<float><<<ew_blocks(nv), 256, 0, c.stream>>>((const float*)dfeat, (float*)dx, nv, HW, C);
+    return hipGetLastError();
+  }
   if (c.dt == BF16) k_avgpool_bwd<bf16_t><<<ew_blocks(n), 256, 0, c.stream>>>((const bf16_t*)dfeat, (bf16_t*)dx, n, HW, C);
   else k_avgpool_bwd<float><<<ew_blocks(n), 256, 0, c.stream>>>((const float*)dfeat, (float*)dx, n, HW, C);
   return hipGetLastError();
