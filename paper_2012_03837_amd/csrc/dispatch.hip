@@ -24,6 +24,9 @@ hipError_t conv_bwd_data_mfma(const OpCtx& c, const ConvArgs& a, const void* dou
                               const void* add);
 hipError_t conv_bwd_weight_mfma(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
                                 int accumulate);
+bool conv_stem_ok(const OpCtx& c, const ConvArgs& a, const void* p0, const void* p1);
+hipError_t conv_stem_fwd(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* st);
+hipError_t conv_stem_wgrad(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw, int accumulate);
 static bool plain_conv() {
   static int v = -1;
   if (v < 0) { const char* s = getenv("LP_PLAIN_CONV"); v = (s && s[0] == '1') ? 1 : 0; }
@@ -51,6 +54,7 @@ hipError_t op_conv_fwd(const OpCtx& c, const ConvArgs& a, const void* x, const v
   ProfScope prof_(c, KC_CONV, 2.0 * a.N * a.P * a.Q * a.O * a.R * a.S * a.C);
   if (stats) { stats->nslab = 0; stats->slab_rows = 0; }
   if (!plain_conv() && conv_mfma_ok(c, a, x, w, out)) return conv_fwd_mfma(c, a, x, w, out, stats);
+  if (!plain_conv() && conv_stem_ok(c, a, out, out)) return conv_stem_fwd(c, a, x, w, out, stats);
   return conv_fwd_plain(c, a, x, w, out);
 }
 hipError_t op_conv_bwd_data(const OpCtx& c, const ConvArgs& a, const void* dout, const void* w, void* dx,
@@ -64,6 +68,10 @@ hipError_t op_conv_bwd_weight(const OpCtx& c, const ConvArgs& a, const void* dou
                               int accumulate) {
   ProfScope prof_(c, KC_CONV, 2.0 * a.N * a.P * a.Q * a.O * a.R * a.S * a.C);
   if (!plain_conv() && conv_mfma_ok(c, a, dout, x, dw)) return conv_bwd_weight_mfma(c, a, dout, x, dw, accumulate);
+  if (!plain_conv() && conv_stem_ok(c, a, dout, dw)) {
+    hipError_t e = conv_stem_wgrad(c, a, dout, x, dw, accumulate);
+    if (e != hipErrorInvalidValue) return e;
+  }
   return conv_bwd_weight_plain(c, a, dout, x, dw, accumulate);
 }
 

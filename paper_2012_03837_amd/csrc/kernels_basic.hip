@@ -318,6 +318,10 @@ k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out
     out[j] = accumulate ? out[j] + t : t;
   }
 }
+hipError_t op_reduce_partials(const OpCtx& c, const float* partial, int nblk, int n, float* out, int accumulate) {
+  k_reduce_partials<<<(n + 63) / 64, 64 * kReduceGroups, 0, c.stream>>>(partial, nblk, n, out, accumulate);
+  return LP_LAUNCH_CHECK();
+}
 hipError_t op_layernorm_bwd(const OpCtx& c, const void* dy, const void* x, const float* mean, const float* rstd,
                             const float* g, const void* add, void* dx, float* dg, float* db, int rows, int d,
                             int accumulate) {

@@ -68,3 +68,73 @@ def test_vocabulary_of_any_size(K, vocab):
     x, y = data_for(cfg)
     compare_step(tr, cfg, generic_params(cfg), x, y, label=f"vocab {vocab}")
     tr.close()
+
+
+@pytest.mark.parametrize("N,H,C,O", [(2, 32, 3, 64), (3, 28, 1, 24), (5, 5, 3, 8), (1, 33, 2, 72), (40, 16, 3, 64), (2, 150, 3, 16),
+                                     (1, 1, 1, 8)])
+def test_stem_convolution(K, N, H, C, O):
+    """The 3x3 convolution of a few-channel image: forward (also in front of a normalisation, whose statistics it leaves
+    where the bands of rows are equal: 16 and 32 wide images) and filter gradient with and without accumulation; twice."""
+    import torch
+    rng = np.random.default_rng(N * H + C)
+    x, w = rnd(rng, (N, H, H, C), 1), rnd(rng, (O, 3, 3, C), 1, 0.3)
+    dout = rnd(rng, (N, H, H, O), 1)
+    ref = ops.conv2d_fwd(x.astype(np.float64), w.astype(np.float64), 1, 1)
+    _, rdw = ops.conv2d_bwd(x.astype(np.float64), w.astype(np.float64), 1, 1, dout.astype(np.float64))
+    ws = zeros(1 << 22)
+    scratch = zeros((2 * 1024 + 2) * O + 3 * N * H * H + 64)
+    seen = []
+    for _ in range(2):
+        z = torch.zeros(N, H, H, O, device="cuda", dtype=torch.bfloat16)
+        y, mean, rstd = torch.zeros_like(z), zeros(O), zeros(O)
+        K.lpk_conv_bn_fwd(1, dev(x, 1), dev(w, 1), z, dev(np.ones(O, np.float32), 0), zeros(O), None, y, mean, rstd, N, H, H,
+                          C, O, 3, 1, 1, 0, scratch)
+        dw = zeros(O, 3, 3, C)
+        for acc in (0, 1):
+            K.lpk_conv_bwd_weight_ws(1, dev(dout, 1), dev(x, 1), dw, N, H, H, C, O, 3, 1, 1, ws, accumulate=acc)
+        seen.append((z, y, mean, rstd, dw))
+    for a, b in zip(*seen):
+        assert torch.equal(a, b)
+    z, y, mean, rstd, dw = seen[0]
+    assert relerr(host(z), ref) <= 4e-3              # one rounding to bf16
+    zs = host(z).reshape(-1, O)
+    assert np.max(np.abs(host(mean) - zs.mean(0))) <= 1e-5 * max(1.0, np.max(np.abs(zs.mean(0))))
+    assert relerr(host(rstd), 1.0 / np.sqrt(zs.var(0) + 1e-5)) <= 1e-5
+    assert relerr(host(dw), 2 * rdw) <= 5e-6         # fp32 sums of exact products
+
+
+@pytest.mark.parametrize("rows,C", [(7, 8), (39200, 24), (1000, 48), (777, 96), (129, 1032), (300, 2048), (64, 200)])
+def test_batchnorm_any_channel_chunks(K, rows, C):
+    """Channel counts whose 8-wide chunks do not divide a block, forward and backward."""
+    import torch
+    rng = np.random.default_rng(rows + C)
+    z, res, dy = rnd(rng, (rows, C), 1), rnd(rng, (rows, C), 1), rnd(rng, (rows, C), 1)
+    g, b = rng.standard_normal(C).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    scratch = zeros((2 * 1024 + 2) * C + 64)
+    y = torch.zeros(rows, C, device="cuda", dtype=torch.bfloat16)
+    mean, rstd = zeros(C), zeros(C)
+    K.lpk_batchnorm_fwd(1, dev(z, 1), dev(g, 0), dev(b, 0), dev(res, 1), y, mean, rstd, rows, C, 1, scratch)
+    z64 = z.astype(np.float64)
+    mu, var = z64.mean(0), z64.var(0)
+    xh = (z64 - mu) / np.sqrt(var + 1e-5)
+    want = np.maximum(xh * g + b + res, 0)
+    assert relerr(host(y), want) <= 4e-3
+    assert np.max(np.abs(host(mean) - mu)) <= 1e-5 * max(1.0, np.max(np.abs(mu)))
+    dz, dres, dg, db = torch.zeros_like(y), torch.zeros_like(y), zeros(C), zeros(C)
+    K.lpk_batchnorm_bwd(1, dev(dy, 1), y, dev(z, 1), mean, rstd, dev(g, 0), dz, dres, dg, db, rows, C, 1, 0, scratch)
+    d = dy * (host(y) > 0)
+    rdb, rdg = d.sum(0), (d * xh).sum(0)
+    rdz = g / np.sqrt(var + 1e-5) * (d - rdb / rows - xh * rdg / rows)
+    assert relerr(host(db), rdb) <= 1e-5 and relerr(host(dg), rdg) <= 1e-4
+    assert relerr(host(dz), rdz) <= 4e-3 and relerr(host(dres), d) == 0
+
+
+def test_resnet_step_off_tile_channels(K):
+    """A step of a two-stage network whose channel counts fit no tile (pooling, normalisation, stem, convolutions)."""
+    import paper_2012_03837_amd as lp
+    from gpu_util import stored_for
+    cfg = LI.configs.resnet_config("t", channels=(24, 48), in_hw=12, in_ch=1, n_classes=5, batch=7, n_basic_blocks=1)
+    tr = lp.LocalTrainer(cfg)
+    x, y = data_for(cfg)
+    compare_step(tr, cfg, generic_params(cfg), x, y, label="24, 48", stored=stored_for(cfg))
+    tr.close()
