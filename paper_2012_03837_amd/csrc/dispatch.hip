@@ -14,9 +14,10 @@ hipError_t conv_bwd_data_plain(const OpCtx& c, const ConvArgs& a, const void* do
 hipError_t conv_bwd_weight_plain(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
                                  int accumulate);
 
-hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal);
+bool attn_mfma_ok(int dh);
+hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
 hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
-                         void* dqkv, float* delta, int B, int S, int H, int causal);
+                         void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
 
 bool conv_mfma_ok(const OpCtx& c, const ConvArgs& a, const void* p0, const void* p1, const void* p2);
 hipError_t conv_fwd_mfma(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* st);
@@ -36,18 +37,18 @@ static bool plain_conv() {
 static bool use_mfma_attn(const OpCtx& c, int dh) {
   static int plain = -1;
   if (plain < 0) { const char* s = getenv("LP_PLAIN_ATTN"); plain = (s && s[0] == '1') ? 1 : 0; }
-  return c.dt == BF16 && dh == 64 && !plain;
+  return c.dt == BF16 && attn_mfma_ok(dh) && !plain;
 }
 
 hipError_t op_attn_fwd(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal) {
   ProfScope prof_(c, KC_ATTN_FWD);
-  if (use_mfma_attn(c, dh)) return attn_fwd_mfma(c, qkv, o, lse, B, S, H, causal);
+  if (use_mfma_attn(c, dh)) return attn_fwd_mfma(c, qkv, o, lse, B, S, H, dh, causal);
   return attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
 }
 hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv,
                        float* delta, int B, int S, int H, int dh, int causal) {
   ProfScope prof_(c, KC_ATTN_BWD);
-  if (use_mfma_attn(c, dh)) return attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
+  if (use_mfma_attn(c, dh)) return attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
   return attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
 }
 hipError_t op_conv_fwd(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* stats) {

@@ -1,5 +1,9 @@
 // Causal multi-head attention on the CDNA4 matrix cores (bf16 operands, fp32 accumulation and
-// softmax), head size 64, flash-style: the S x S score matrix lives only in registers.
+// softmax), head sizes 16, 32 and 64, flash-style: the S x S score matrix lives only in registers.
+// (Head sizes 16 and 32 at 64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward
+// 149 + 287 us.  Here, DH = 16: 11 us, 12 + 15 us.  The head size only changes the number of 16-deep products of a
+// score tile and of 32-row output tiles; a 16-wide head leaves half of its one output tile unused, which costs
+// nothing that counts, since the exponentials bound the kernels.)
 //
 // All three kernels keep the score tile transposed where that puts one query per lane column, so
 // that the running max / sum / log-sum-exp of a query are lane-uniform scalars:
@@ -12,12 +16,15 @@
 // never pass through LDS.  Operands whose reduction index is the slow one in memory (V for the
 // forward, K for dQ, Q and dO for dK/dV) sit in LDS as in memory and are read with the transposing LDS
 // read (ds_read_b64_tr_b16).  The next tile's global loads are issued before the current tile's MFMAs.
-// Layout: qkv [B*S, 3*H*64] (q | k | v, head h at columns h*64..), o [B*S, H*64], lse [B, H, S].
+// Layout: qkv [B*S, 3*H*DH] (q | k | v, head h at columns h*DH..), o [B*S, H*DH], lse [B, H, S].
 #include "common.h"
 
 namespace lp {
 
-constexpr int ALD = 72;                  // padded LDS row: 64 + 8 elements (144 bytes)
+// Padded LDS row: the head size + 8 elements (144 or 80 bytes); a 16-wide head takes the 32-wide row, because the
+// transposing reads cover 32 columns (what they find past the head lands in output rows that are not written).
+template <int DH> constexpr int kAld = DH == 64 ? 72 : 40;
+template <int DH> constexpr float kScale = DH == 64 ? 0.125f : (DH == 32 ? 0.17677669529663687f : 0.25f);
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -48,6 +55,7 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 // MFMA's accumulator holds P / dS.  Done with the transposing LDS read (ds_read_b64_tr_b16): within a
 // 16-lane group, lane 4r+c supplies the 8-byte chunk s[row + r][4c..4c+3] and lane 4c+e receives element e
 // of the four chunks r = 0..3, so nothing is ever stored transposed.
+template <int ALD>
 __device__ __forceinline__ bf16x8 frag_tr(const bf16_t (*s)[ALD], int r0, int c0, int lane) {
   const int g = lane >> 4, l16 = lane & 15, hf = g >> 1;
   const bf16_t* p = &s[r0 + 4 * hf + (l16 >> 2)][c0 + 16 * (g & 1) + 4 * (l16 & 3)];
@@ -58,26 +66,32 @@ __device__ __forceinline__ bf16x8 frag_tr(const bf16_t (*s)[ALD], int r0, int c0
   for (int e = 0; e < 4; ++e) { r[e] = lo[e]; r[4 + e] = hi[e]; }
   return r;
 }
-// A [64 rows][64 cols] bf16 tile (rows r0.., row stride ld, rows >= nrows read as zero) on its way into
-// LDS: 256 threads, 16 elements each, held in registers between the global load and the LDS store so that
-// the next tile's loads fly while the current tile is computed.
-struct TileRegs { bf16x8 v0, v1; };
-__device__ __forceinline__ TileRegs load_tile(const bf16_t* src, size_t ld, int r0, int nrows) {
-  const int r = threadIdx.x >> 2, ch = (threadIdx.x & 3) * 16;
-  TileRegs t;
-  t.v0 = zero8(); t.v1 = zero8();
-  if (r0 + r < nrows) {
-    const bf16_t* p = src + (size_t)(r0 + r) * ld + ch;
-    t.v0 = *reinterpret_cast<const bf16x8*>(p);
-    t.v1 = *reinterpret_cast<const bf16x8*>(p + 8);
+// A [64 rows][DH cols] bf16 tile (rows r0.., row stride ld, rows >= nrows read as zero) on its way into
+// LDS: 256 threads (128 for DH = 16), one or two 16-byte chunks each, held in registers between the global load and
+// the LDS store so that the next tile's loads fly while the current tile is computed.
+template <int DH>
+struct TileRegs {
+  static constexpr int NCH = DH == 64 ? 2 : 1, TPR = DH / (8 * NCH);      // chunks per thread, threads per row
+  bf16x8 v[NCH];
+  __device__ __forceinline__ void load(const bf16_t* src, size_t ld, int r0, int nrows) {
+    const int r = threadIdx.x / TPR, ch = (threadIdx.x % TPR) * 8 * NCH;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) v[i] = zero8();
+    if (r < 64 && r0 + r < nrows) {
+      const bf16_t* p = src + (size_t)(r0 + r) * ld + ch;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) v[i] = *reinterpret_cast<const bf16x8*>(p + 8 * i);
+    }
   }
-  return t;
-}
-__device__ __forceinline__ void store_tile(const TileRegs& t, bf16_t (*dst)[ALD]) {
-  const int r = threadIdx.x >> 2, ch = (threadIdx.x & 3) * 16;
-  *reinterpret_cast<bf16x8*>(&dst[r][ch]) = t.v0;
-  *reinterpret_cast<bf16x8*>(&dst[r][ch + 8]) = t.v1;
-}
+  template <int ALD>
+  __device__ __forceinline__ void store(bf16_t (*dst)[ALD]) const {
+    const int r = threadIdx.x / TPR, ch = (threadIdx.x % TPR) * 8 * NCH;
+    if (r < 64) {
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) *reinterpret_cast<bf16x8*>(&dst[r][ch + 8 * i]) = v[i];
+    }
+  }
+};
 
 // Work order.  The grid is one-dimensional: block L takes sequence block L / (B*H) (counted from the heavy end)
 // of head-and-batch index L % (B*H).  With causal masking the work of a 128-row block grows with its position
@@ -96,38 +110,43 @@ __device__ __forceinline__ AttnBlock attn_block(int H, int BH, int nblk, bool he
 }
 
 // ================================================================================= forward
+template <int DH>
 __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
                                                        float* __restrict__ lse, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][ALD];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][ALD];
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
-  const int h = ab.h, b = ab.b, d = H * 64;
+  const int h = ab.h, b = ab.b, d = H * DH;
+  constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
   const int q0 = bx * 128 + wave * 32, qi = q0 + n;
-  bf16x8 qf[4];
+  bf16x8 qf[NK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-    qf[kk] = qi < S ? *reinterpret_cast<const bf16x8*>(base + (size_t)qi * ld + h * 64 + 16 * kk + 8 * hf) : zero8();
+  for (int kk = 0; kk < NK; ++kk)
+    qf[kk] = qi < S ? *reinterpret_cast<const bf16x8*>(base + (size_t)qi * ld + h * DH + 16 * kk + 8 * hf) : zero8();
   float m = -INFINITY, l = 0.f;
-  f32x16 oacc[2];
-  zero16(oacc[0]); zero16(oacc[1]);
-  const float c = 0.125f * kLog2e;
+  f32x16 oacc[ND];
+#pragma unroll
+  for (int dh = 0; dh < ND; ++dh) zero16(oacc[dh]);
+  const float c = kScale<DH> * kLog2e;
   int q_hi = bx * 128 + 127;
   if (q_hi > S - 1) q_hi = S - 1;
   const int n_tiles = causal ? q_hi / 64 + 1 : (S + 63) / 64;
-  TileRegs kr = load_tile(base + d + h * 64, ld, 0, S), vr = load_tile(base + 2 * d + h * 64, ld, 0, S);
+  TileRegs<DH> kr, vr;
+  kr.load(base + d + h * DH, ld, 0, S);
+  vr.load(base + 2 * d + h * DH, ld, 0, S);
   for (int jt = 0; jt < n_tiles; ++jt) {
     const int k0 = jt * 64;
     __syncthreads();
-    store_tile(kr, Ks);
-    store_tile(vr, Vs);
+    kr.store(Ks);
+    vr.store(Vs);
     __syncthreads();
     if (jt + 1 < n_tiles) {      // the next key tile's loads fly during this tile's MFMAs
-      kr = load_tile(base + d + h * 64, ld, k0 + 64, S);
-      vr = load_tile(base + 2 * d + h * 64, ld, k0 + 64, S);
+      kr.load(base + d + h * DH, ld, k0 + 64, S);
+      vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
     }
     const bool active = q0 < S && (!causal || k0 <= q0 + 31);
     if (!active) continue;
@@ -136,12 +155,12 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
     for (int i = 0; i < 2; ++i) {
       zero16(st[i]);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < NK; ++kk) {
         bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Ks[32 * i + n][16 * kk + 8 * hf]);
         st[i] = MFMA32(kf, qf[kk], st[i]);
       }
     }
-    // The scale 1/sqrt(64) * log2(e) is positive: the running maximum is taken over the raw scores and scaled once,
+    // The scale 1/sqrt(DH) * log2(e) is positive: the running maximum is taken over the raw scores and scaled once,
     // and the scaling of every score rides in the fused multiply-add that feeds the exponential.
     float mt = -INFINITY;
     // only tiles that touch the diagonal or the end of the sequence need the mask (wave-uniform test)
@@ -181,7 +200,7 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
     // once the running maxima have settled every lane's alpha is exactly 1: skip the rescale then (wave-uniform)
     if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
 #pragma unroll
-      for (int dh = 0; dh < 2; ++dh)
+      for (int dh = 0; dh < ND; ++dh)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[dh][v] *= alpha;
     }
@@ -191,17 +210,17 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
       for (int kk = 0; kk < 2; ++kk) {
         bf16x8 pf = pack8(st[i], kk);
 #pragma unroll
-        for (int dh = 0; dh < 2; ++dh) oacc[dh] = MFMA32(frag_tr(Vs, 32 * i + 16 * kk, 32 * dh, lane), pf, oacc[dh]);
+        for (int dh = 0; dh < ND; ++dh) oacc[dh] = MFMA32(frag_tr(Vs, 32 * i + 16 * kk, 32 * dh, lane), pf, oacc[dh]);
       }
   }
   float lt = l + __shfl_xor(l, 32, 64);
   if (qi < S) {
     float inv = 1.f / lt;
-    bf16_t* op = o + ((size_t)b * S + qi) * d + h * 64;
+    bf16_t* op = o + ((size_t)b * S + qi) * d + h * DH;
 #pragma unroll
-    for (int dh = 0; dh < 2; ++dh)
+    for (int dh = 0; dh < ND; ++dh)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NG; ++g) {
         bf16x4 w;
 #pragma unroll
         for (int j = 0; j < 4; ++j) w[j] = (bf16_t)(oacc[dh][4 * g + j] * inv);
@@ -212,26 +231,28 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
 }
 
 // ================================================================================= backward: dQ
+template <int DH>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                           const float* __restrict__ lse,
                                                           const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv,
                                                           float* __restrict__ delta, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][ALD];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][ALD];
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
-  const int h = ab.h, b = ab.b, d = H * 64;
+  const int h = ab.h, b = ab.b, d = H * DH;
+  constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
   const int q0 = bx * 128 + wave * 32, qi = q0 + n;
-  bf16x8 qf[4], dof[4];
+  bf16x8 qf[NK], dof[NK];
   float D = 0.f, lse2 = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
+  for (int kk = 0; kk < NK; ++kk) {
     if (qi < S) {
-      qf[kk] = *reinterpret_cast<const bf16x8*>(base + (size_t)qi * ld + h * 64 + 16 * kk + 8 * hf);
-      size_t off = ((size_t)b * S + qi) * d + h * 64 + 16 * kk + 8 * hf;
+      qf[kk] = *reinterpret_cast<const bf16x8*>(base + (size_t)qi * ld + h * DH + 16 * kk + 8 * hf);
+      size_t off = ((size_t)b * S + qi) * d + h * DH + 16 * kk + 8 * hf;
       dof[kk] = *reinterpret_cast<const bf16x8*>(dout + off);
       bf16x8 ov = *reinterpret_cast<const bf16x8*>(o + off);
 #pragma unroll
@@ -246,22 +267,25 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
     lse2 = lse[si] * kLog2e;
     if (hf == 0) delta[si] = D;
   }
-  f32x16 dqa[2];
-  zero16(dqa[0]); zero16(dqa[1]);
-  const float scale = 0.125f, c = 0.125f * kLog2e;
+  f32x16 dqa[ND];
+#pragma unroll
+  for (int dh = 0; dh < ND; ++dh) zero16(dqa[dh]);
+  const float scale = kScale<DH>, c = scale * kLog2e;
   int q_hi = bx * 128 + 127;
   if (q_hi > S - 1) q_hi = S - 1;
   const int n_tiles = causal ? q_hi / 64 + 1 : (S + 63) / 64;
-  TileRegs kr = load_tile(base + d + h * 64, ld, 0, S), vr = load_tile(base + 2 * d + h * 64, ld, 0, S);
+  TileRegs<DH> kr, vr;
+  kr.load(base + d + h * DH, ld, 0, S);
+  vr.load(base + 2 * d + h * DH, ld, 0, S);
   for (int jt = 0; jt < n_tiles; ++jt) {
     const int k0 = jt * 64;
     __syncthreads();
-    store_tile(kr, Ks);
-    store_tile(vr, Vs);
+    kr.store(Ks);
+    vr.store(Vs);
     __syncthreads();
     if (jt + 1 < n_tiles) {
-      kr = load_tile(base + d + h * 64, ld, k0 + 64, S);
-      vr = load_tile(base + 2 * d + h * 64, ld, k0 + 64, S);
+      kr.load(base + d + h * DH, ld, k0 + 64, S);
+      vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
     }
     const bool active = q0 < S && (!causal || k0 <= q0 + 31);
     if (!active) continue;
@@ -270,7 +294,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
     for (int i = 0; i < 2; ++i) {
       zero16(st[i]); zero16(dp[i]);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < NK; ++kk) {
         bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Ks[32 * i + n][16 * kk + 8 * hf]);
         bf16x8 vf = *reinterpret_cast<const bf16x8*>(&Vs[32 * i + n][16 * kk + 8 * hf]);
         st[i] = MFMA32(kf, qf[kk], st[i]);
@@ -294,7 +318,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           float p = __builtin_amdgcn_exp2f(st[i][v] * c - lse2);
-          st[i][v] = p * (dp[i][v] - D);        // the factor 1/sqrt(64) of dS is applied once, to the finished dQ
+          st[i][v] = p * (dp[i][v] - D);        // the factor 1/sqrt(DH) of dS is applied once, to the finished dQ
         }
     }
 #pragma unroll
@@ -303,15 +327,15 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
       for (int kk = 0; kk < 2; ++kk) {
         bf16x8 dsf = pack8(st[i], kk);
 #pragma unroll
-        for (int dh = 0; dh < 2; ++dh) dqa[dh] = MFMA32(frag_tr(Ks, 32 * i + 16 * kk, 32 * dh, lane), dsf, dqa[dh]);
+        for (int dh = 0; dh < ND; ++dh) dqa[dh] = MFMA32(frag_tr(Ks, 32 * i + 16 * kk, 32 * dh, lane), dsf, dqa[dh]);
       }
   }
   if (qi < S) {
-    bf16_t* dqp = dqkv + ((size_t)b * S + qi) * ld + h * 64;
+    bf16_t* dqp = dqkv + ((size_t)b * S + qi) * ld + h * DH;
 #pragma unroll
-    for (int dh = 0; dh < 2; ++dh)
+    for (int dh = 0; dh < ND; ++dh)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NG; ++g) {
         bf16x4 w;
 #pragma unroll
         for (int j = 0; j < 4; ++j) w[j] = (bf16_t)(dqa[dh][4 * g + j] * scale);
@@ -321,48 +345,53 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
 }
 
 // ================================================================================= backward: dK, dV
+template <int DH>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv,
                                                            const float* __restrict__ lse,
                                                            const float* __restrict__ delta,
                                                            const bf16_t* __restrict__ dout,
                                                            bf16_t* __restrict__ dqkv, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[64][ALD];
-  __shared__ __attribute__((aligned(16))) bf16_t dOs[64][ALD];
+  __shared__ __attribute__((aligned(16))) bf16_t Qs[64][kAld<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t dOs[64][kAld<DH>];
   __shared__ __attribute__((aligned(16))) float lse2s[64];
   __shared__ __attribute__((aligned(16))) float deltas[64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, false);
   const int bx = ab.x;
-  const int h = ab.h, b = ab.b, d = H * 64;
+  const int h = ab.h, b = ab.b, d = H * DH;
+  constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
   const bf16_t* dob = dout + (size_t)b * S * d;
   const int k0w = bx * 128 + wave * 32, kj = k0w + n;
-  bf16x8 kf[4], vf[4];
+  bf16x8 kf[NK], vf[NK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
+  for (int kk = 0; kk < NK; ++kk) {
     if (kj < S) {
-      const bf16_t* kp = base + (size_t)kj * ld + d + h * 64 + 16 * kk + 8 * hf;
+      const bf16_t* kp = base + (size_t)kj * ld + d + h * DH + 16 * kk + 8 * hf;
       kf[kk] = *reinterpret_cast<const bf16x8*>(kp);
       vf[kk] = *reinterpret_cast<const bf16x8*>(kp + d);
     } else {
       kf[kk] = zero8(); vf[kk] = zero8();
     }
   }
-  f32x16 dka[2], dva[2];
-  zero16(dka[0]); zero16(dka[1]); zero16(dva[0]); zero16(dva[1]);
-  const float scale = 0.125f, c = 0.125f * kLog2e;
+  f32x16 dka[ND], dva[ND];
+#pragma unroll
+  for (int dh = 0; dh < ND; ++dh) { zero16(dka[dh]); zero16(dva[dh]); }
+  const float scale = kScale<DH>, c = scale * kLog2e;
   const int t_begin = causal ? (bx * 128) / 64 : 0;
   const int t_end = (S + 63) / 64;
-  TileRegs qr = load_tile(base + h * 64, ld, t_begin * 64, S), dor = load_tile(dob + h * 64, (size_t)d, t_begin * 64, S);
+  TileRegs<DH> qr, dor;
+  qr.load(base + h * DH, ld, t_begin * 64, S);
+  dor.load(dob + h * DH, (size_t)d, t_begin * 64, S);
   for (int it = t_begin; it < t_end; ++it) {
     const int q0 = it * 64;
     __syncthreads();
-    store_tile(qr, Qs);
-    store_tile(dor, dOs);
+    qr.store(Qs);
+    dor.store(dOs);
     if (it + 1 < t_end) {
-      qr = load_tile(base + h * 64, ld, q0 + 64, S);
-      dor = load_tile(dob + h * 64, (size_t)d, q0 + 64, S);
+      qr.load(base + h * DH, ld, q0 + 64, S);
+      dor.load(dob + h * DH, (size_t)d, q0 + 64, S);
     }
     if (threadIdx.x < 64) {
       int q = q0 + threadIdx.x;
@@ -380,7 +409,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
       f32x16 s, dp;
       zero16(s); zero16(dp);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < NK; ++kk) {
         bf16x8 qa = *reinterpret_cast<const bf16x8*>(&Qs[32 * i + n][16 * kk + 8 * hf]);
         bf16x8 da = *reinterpret_cast<const bf16x8*>(&dOs[32 * i + n][16 * kk + 8 * hf]);
         s = MFMA32(qa, kf[kk], s);
@@ -413,7 +442,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
             int v = 4 * g + j;
             float p = __builtin_amdgcn_exp2f(s[v] * c - l4[j]);
             s[v] = p;
-            dp[v] = p * (dp[v] - d4[j]);          // the factor 1/sqrt(64) of dS is applied once, to the finished dK
+            dp[v] = p * (dp[v] - d4[j]);          // the factor 1/sqrt(DH) of dS is applied once, to the finished dK
           }
         }
       }
@@ -421,7 +450,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
       for (int kk = 0; kk < 2; ++kk) {
         bf16x8 pf = pack8(s, kk), dsf = pack8(dp, kk);
 #pragma unroll
-        for (int dh = 0; dh < 2; ++dh) {
+        for (int dh = 0; dh < ND; ++dh) {
           dva[dh] = MFMA32(frag_tr(dOs, 32 * i + 16 * kk, 32 * dh, lane), pf, dva[dh]);
           dka[dh] = MFMA32(frag_tr(Qs, 32 * i + 16 * kk, 32 * dh, lane), dsf, dka[dh]);
         }
@@ -429,12 +458,12 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
     }
   }
   if (kj < S) {
-    bf16_t* dkp = dqkv + ((size_t)b * S + kj) * ld + d + h * 64;
+    bf16_t* dkp = dqkv + ((size_t)b * S + kj) * ld + d + h * DH;
     bf16_t* dvp = dkp + d;
 #pragma unroll
-    for (int dh = 0; dh < 2; ++dh)
+    for (int dh = 0; dh < ND; ++dh)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NG; ++g) {
         bf16x4 wk, wv;
 #pragma unroll
         for (int j = 0; j < 4; ++j) { wk[j] = (bf16_t)(dka[dh][4 * g + j] * scale); wv[j] = (bf16_t)dva[dh][4 * g + j]; }
@@ -444,21 +473,34 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
   }
 }
 
-hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
-  if (B * S == 0) return hipSuccess;
+template <int DH>
+static hipError_t attn_fwd_t(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
   const int grid = ((S + 127) / 128) * H * B;
-  k_attn_fwd_mfma<<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, H, H * B, causal);
+  k_attn_fwd_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, H, H * B, causal);
   return hipGetLastError();
 }
-hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
-                         void* dqkv, float* delta, int B, int S, int H, int causal) {
-  if (B * S == 0) return hipSuccess;
+template <int DH>
+static hipError_t attn_bwd_t(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
+                             void* dqkv, float* delta, int B, int S, int H, int causal) {
   const int grid = ((S + 127) / 128) * H * B;
-  k_attn_bwd_dq_mfma<<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)dout,
-                                                 (bf16_t*)dqkv, delta, S, H, H * B, causal);
-  k_attn_bwd_dkv_mfma<<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, lse, delta, (const bf16_t*)dout, (bf16_t*)dqkv,
-                                                  S, H, H * B, causal);
+  k_attn_bwd_dq_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)dout,
+                                                     (bf16_t*)dqkv, delta, S, H, H * B, causal);
+  k_attn_bwd_dkv_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, lse, delta, (const bf16_t*)dout, (bf16_t*)dqkv,
+                                                      S, H, H * B, causal);
   return hipGetLastError();
+}
+bool attn_mfma_ok(int dh) { return dh == 16 || dh == 32 || dh == 64; }
+hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal) {
+  if (B * S == 0) return hipSuccess;
+  return dh == 64 ? attn_fwd_t<64>(c, qkv, o, lse, B, S, H, causal)
+                  : (dh == 32 ? attn_fwd_t<32>(c, qkv, o, lse, B, S, H, causal) : attn_fwd_t<16>(c, qkv, o, lse, B, S, H, causal));
+}
+hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
+                         void* dqkv, float* delta, int B, int S, int H, int dh, int causal) {
+  if (B * S == 0) return hipSuccess;
+  return dh == 64 ? attn_bwd_t<64>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal)
+                  : (dh == 32 ? attn_bwd_t<32>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal)
+                              : attn_bwd_t<16>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal));
 }
 
 }  // namespace lp

@@ -138,3 +138,35 @@ def test_resnet_step_off_tile_channels(K):
     x, y = data_for(cfg)
     compare_step(tr, cfg, generic_params(cfg), x, y, label="24, 48", stored=stored_for(cfg))
     tr.close()
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dh", [16, 32])
+@pytest.mark.parametrize("S", [1, 64, 129, 200])
+def test_attention_small_heads(K, S, dh, causal):
+    """Heads of 16 and 32 on the matrix cores, forward and backward; the bounds are those of the 64-wide kernel."""
+    import torch
+    rng = np.random.default_rng(S + dh)
+    B, H = 2, 5
+    d = H * dh
+    qkv, dout = rnd(rng, (B * S, 3 * d), 1, scale=1.5), rnd(rng, (B * S, d), 1)
+    o = torch.zeros(B * S, d, device="cuda", dtype=torch.bfloat16)
+    lse, delta = zeros(B, H, S), zeros(B, H, S)
+    dqkv = torch.zeros(B * S, 3 * d, device="cuda", dtype=torch.bfloat16)
+    K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal)
+    K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal)
+    split = lambda t: t.reshape(B, S, H, dh).transpose(0, 2, 1, 3)
+    merge = lambda t: t.transpose(0, 2, 1, 3).reshape(B * S, d)
+    q64 = qkv.astype(np.float64)
+    q, k, v = split(q64[:, :d]), split(q64[:, d:2 * d]), split(q64[:, 2 * d:])
+    ro, p = ops.attention_fwd(q, k, v, causal=bool(causal))
+    assert relerr(host(o), merge(ro)) <= 6e-3
+    s = (q @ np.swapaxes(k, -1, -2)) / np.sqrt(dh)
+    if causal:
+        s = np.where(np.tril(np.ones((S, S), bool)), s, -np.inf)
+    assert np.abs(host(lse) - (np.log(np.exp(s - s.max(-1, keepdims=True)).sum(-1)) + s.max(-1))).max() <= 2e-3
+    g = host(dqkv)
+    scale = np.linalg.norm(g)
+    for got, ref in zip((g[:, :d], g[:, d:2 * d], g[:, 2 * d:]), ops.attention_bwd(q, k, v, p, split(dout.astype(np.float64)))):
+        # one key per query: dQ and dK vanish and only their size against the whole can be asked for
+        assert np.linalg.norm(got - merge(ref)) <= 1.5e-2 * max(np.linalg.norm(ref), 0.1 * scale)
