@@ -1,7 +1,7 @@
 // Causal multi-head attention on the CDNA4 matrix cores (bf16 operands, fp32 accumulation and
 // softmax), head sizes 16, 32 and 64, flash-style: the S x S score matrix lives only in registers.
 // (Head sizes 16 and 32 at 64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward
-// 149 + 287 us.  Here, DH = 16: 11 us, 12 + 15 us.  The head size only changes the number of 16-deep products of a
+// 149 + 287 us.  Here, DH = 16: 9.4 us, 11.5 + 9.4 us.  The head size only changes the number of 16-deep products of a
 // score tile and of 32-row output tiles; a 16-wide head leaves half of its one output tile unused, which costs
 // nothing that counts, since the exponentials bound the kernels.)
 //
