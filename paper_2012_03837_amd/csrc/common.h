@@ -66,6 +66,8 @@ struct GemmArgs {
   // k-major whose row pitch is padded, so that whole 16-byte chunks can be read past row M.  Fewer than N: the last
   // columns of C are padding, computed from a repeated row.
   int a_rows = 0, b_rows = 0;
+  // rowsum[m] (+)= sum_k A(m,k) (A stored k-major): the bias gradient beside a weight gradient
+  float* rowsum = nullptr;
 };
 static inline int rows_of_a(const GemmArgs& g) { return g.a_rows ? g.a_rows : g.M; }
 static inline int rows_of_b(const GemmArgs& g) { return g.b_rows ? g.b_rows : g.N; }
@@ -164,12 +166,24 @@ hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const flo
 hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows,
                          int n, int write_grad, float inv_rows, int pad_to = 0);
 hipError_t op_mean(const OpCtx& c, const float* v, int n, float* out);
+// A classifier head of at most 32 classes on at most 1024 features in one launch: loss_rows, and if `backward` also dZ
+// [rows, ncls] and dfeat = dZ w [rows, in].
+bool head_ce_ok(int in, int ncls);
+hipError_t op_head_ce(const OpCtx& c, const void* feat, const void* w, const float* bias, const int32_t* y, float* loss_rows,
+                      void* dz, void* dfeat, int rows, int in, int ncls, int backward, float inv_rows);
 
 struct OptArgs {
   int kind; float lr, momentum, beta1, beta2, eps, weight_decay; int t; float grad_scale;
 };
 hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v,
                         void* p_lowp, size_t n);
+// Several ranges [off, off + n) of the same buffers in one launch (offsets and sizes multiples of 4), each with its own
+// gradient scale (OptArgs::grad_scale is ignored); with mean_rows > 0 the launch also writes mean_out[0] = the mean of
+// mean_v[0 .. mean_rows), the same bits as op_mean.
+constexpr int kMaxOptRanges = 8;
+struct OptRanges { size_t off[kMaxOptRanges], n[kMaxOptRanges]; float scale[kMaxOptRanges]; int count = 0; };
+hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
+                               const OptRanges& r, const float* mean_v, int mean_rows, float* mean_out);
 
 hipError_t op_init_normal(const OpCtx& c, float* p, size_t n, float std, uint64_t seed, uint64_t stream_id);
 

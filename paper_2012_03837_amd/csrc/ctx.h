@@ -180,6 +180,11 @@ struct lp_ctx : lp_scratch {
   int g_eager = 0;
   bool ok = false;
   std::string err;
+  std::vector<lp::GemmArgs> waiting;     // products of the chain being issued that go out with its next grouped launch
+  // the mean of the head's row losses, if it is left to the launch that updates the head (mean_with_update)
+  bool mean_with_update = false;
+  int mean_rows = 0;
+  float* mean_out = nullptr;
 
   mutable lp::Profiler prof;
   lp::OpCtx op() const {

@@ -1,6 +1,7 @@
 // Layer and head drivers: the sequence of kernel launches for the forward pass of one atomic layer,
 // its backward pass inside a truncation window, and an auxiliary head's loss and gradient.
 #include "ctx.h"
+#include <vector>
 
 namespace lp {
 
@@ -84,6 +85,8 @@ static int mlp_forward(lp_ctx* c, int li, int batch) {
   return LP_OK;
 }
 
+// Products that only share their inputs share a launch; a bias gradient rides along with its weight gradient.  Products
+// the head left waiting (its weight gradient) go with the first launch.
 static int mlp_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int acc, bool params) {
   LayerState& L = c->layers[li];
   OpCtx o = c->op();
@@ -91,31 +94,35 @@ static int mlp_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx
   bool proj = L.t.count("win") > 0;
   const void* p = proj ? L.mlp_p : x;
   int width = L.s.width, hidden = L.s.hidden;
-  if (params) {
-    DO(op_colsum(o, dout, width, c->G32(L.t["b2"]), batch, width, acc));
-    DO(op_gemm(o, lin_wgrad(c, dout, L.mlp_r, batch, L.t["w2"], acc)));
-  }
+  std::vector<GemmArgs> g;
+  auto wgrad = [&](const void* dy, const void* in, const char* w, const char* b) {
+    GemmArgs a = lin_wgrad(c, dy, in, batch, L.t[w], acc);
+    a.rowsum = c->G32(L.t[b]);
+    return a;
+  };
   // da = (dout W2) * relu'(r)
   GemmArgs gd = lin_dgrad(c, dout, batch, L.t["w2"], c->dF);
   gd.dact = ACT_RELU; gd.dact_src = L.mlp_r; gd.ldd = hidden;
-  DO(op_gemm(o, gd));
-  if (params) {
-    DO(op_colsum(o, c->dF, hidden, c->G32(L.t["b1"]), batch, hidden, acc));
-    DO(op_gemm(o, lin_wgrad(c, c->dF, p, batch, L.t["w1"], acc)));
-  }
-  if (!need_dx && !(proj && params)) return LP_OK;
-  // dp = da W1 + dout
+  g.push_back(gd);
+  g.insert(g.end(), c->waiting.begin(), c->waiting.end());
+  c->waiting.clear();
+  if (params) g.push_back(wgrad(dout, L.mlp_r, "w2", "b2"));
+  DO(op_gemm_grouped(o, g.data(), (int)g.size()));
+  g.clear();
+  if (params) g.push_back(wgrad(c->dF, p, "w1", "b1"));
+  const bool want_dp = need_dx || (proj && params);
   void* dp = proj ? c->dc : dx;
-  GemmArgs g1 = lin_dgrad(c, c->dF, batch, L.t["w1"], dp);
-  g1.res = dout; g1.ldr = width;
-  DO(op_gemm(o, g1));
-  if (proj) {
-    if (params) {
-      DO(op_colsum(o, dp, width, c->G32(L.t["bin"]), batch, width, acc));
-      DO(op_gemm(o, lin_wgrad(c, dp, x, batch, L.t["win"], acc)));
-    }
-    if (need_dx) DO(op_gemm(o, lin_dgrad(c, dp, batch, L.t["win"], dx)));
+  if (want_dp) {       // dp = da W1 + dout
+    GemmArgs g1 = lin_dgrad(c, c->dF, batch, L.t["w1"], dp);
+    g1.res = dout; g1.ldr = width;
+    g.push_back(g1);
   }
+  if (!g.empty()) DO(op_gemm_grouped(o, g.data(), (int)g.size()));
+  if (!want_dp || !proj) return LP_OK;
+  g.clear();
+  if (params) g.push_back(wgrad(dp, x, "win", "bin"));
+  if (need_dx) g.push_back(lin_dgrad(c, dp, batch, L.t["win"], dx));
+  if (!g.empty()) DO(op_gemm_grouped(o, g.data(), (int)g.size()));
   return LP_OK;
 }
 
@@ -354,6 +361,12 @@ static GemmArgs head_dgrad(const lp_ctx* c, const HeadState& Hd, const void* dz,
   return g;
 }
 
+// The mean of the row losses: with the head's update where a step makes one (run), at once otherwise.
+static hipError_t head_mean(lp_ctx* c, int rows, float* loss_out, bool backward) {
+  if (backward && c->mean_with_update) { c->mean_rows = rows; c->mean_out = loss_out; return hipSuccess; }
+  return op_mean(c->op(), c->loss_rows, rows, loss_out);
+}
+
 // The vocabulary head (LayerNorm, projection, cross-entropy) in stages, like the decoder layer: stage 0 ends in the
 // logits product, stage 1 (loss, dZ) in the head's weight gradient, stage 2 in its input gradient, stage 3 is the
 // LayerNorm backward.  Without `backward` only stages 0 and 1 do anything, and stage 1 hands back no product.
@@ -369,7 +382,7 @@ int vocab_head_stage(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss
     out->g[out->n++] = head_fwd(c, Hd, rows, Hd.t["w"], c->logits);
   } else if (stage == 1) {
     DO(op_softmax_ce(o, c->logits, Hd.ldz, y, c->loss_rows, rows, ncls, backward ? 1 : 0, 1.0f / (float)rows, Hd.ldz));
-    DO(op_mean(o, c->loss_rows, rows, loss_out));
+    DO(head_mean(c, rows, loss_out, backward));
     if (backward) out->g[out->n++] = head_wgrad(c, Hd, c->logits, rows, Hd.t["w"]);    // logits now hold dZ
   } else if (stage == 2) {
     if (backward) out->g[out->n++] = head_dgrad(c, Hd, c->logits, rows, Hd.t["w"], c->dfeat);
@@ -423,17 +436,25 @@ int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bo
     rows = batch;
   }
   int tb = Hd.t.count("b") ? Hd.t["b"] : -1;
-  DO(op_gemm(o, lin_fwd(c, feat, rows, Hd.t["w"], tb, c->logits)));
-  DO(op_softmax_ce(o, c->logits, ncls, y, c->loss_rows, rows, ncls, backward ? 1 : 0, 1.0f / (float)rows));
-  DO(op_mean(o, c->loss_rows, rows, loss_out));
+  const float inv_rows = 1.0f / (float)rows;
+  void* dfeat = Hd.s.kind == LP_HEAD_LINEAR_CE ? dh : c->dfeat;
+  if (head_ce_ok(in_dim, ncls)) {
+    DO(op_head_ce(o, feat, c->W(Hd.t["w"]), tb >= 0 ? c->P32(tb) : nullptr, y, c->loss_rows, c->logits, dfeat, rows, in_dim,
+                  ncls, backward ? 1 : 0, inv_rows));
+  } else {
+    DO(op_gemm(o, lin_fwd(c, feat, rows, Hd.t["w"], tb, c->logits)));
+    DO(op_softmax_ce(o, c->logits, ncls, y, c->loss_rows, rows, ncls, backward ? 1 : 0, inv_rows));
+    if (backward) DO(op_gemm(o, lin_dgrad(c, c->logits, rows, Hd.t["w"], dfeat)));
+  }
+  DO(head_mean(c, rows, loss_out, backward));
   if (!backward) return LP_OK;
   // logits now hold dZ
-  if (tb >= 0) DO(op_colsum(o, c->logits, ncls, c->G32(tb), rows, ncls, 0));
-  DO(op_gemm(o, lin_wgrad(c, c->logits, feat, rows, Hd.t["w"], 0)));
+  GemmArgs gw = lin_wgrad(c, c->logits, feat, rows, Hd.t["w"], 0);
+  if (tb >= 0) gw.rowsum = c->G32(tb);
   if (Hd.s.kind == LP_HEAD_LINEAR_CE) {
-    DO(op_gemm(o, lin_dgrad(c, c->logits, rows, Hd.t["w"], dh)));
+    c->waiting.push_back(gw);      // with the first products of the block's backward pass (mlp_backward)
   } else {
-    DO(op_gemm(o, lin_dgrad(c, c->logits, rows, Hd.t["w"], c->dfeat)));
+    DO(op_gemm(o, gw));
     if (Hd.s.kind == LP_HEAD_POOL_LINEAR_CE) {
       DO(op_avgpool_bwd(o, c->dfeat, dh, batch, hw, in_dim));
     } else if (Hd.s.kind == LP_HEAD_BN_POOL_LINEAR_CE) {

@@ -575,13 +575,23 @@ hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, 
   return LP_LAUNCH_CHECK();
 }
 
-// out[0] = mean(v[0..n)) with a fixed summation tree (one block).
-__global__ void k_mean(const float* v, int n, float* out) {
-  __shared__ float sh[4];
-  float a = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) a += v[i];
-  float s = block_sum_256(a, sh);
+// out[0] = mean(v[0..n)) with a fixed summation tree (one block; four loads in flight per thread).
+__device__ __forceinline__ void block_mean_256(const float* v, int n, float* out, float* sh) {
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i = threadIdx.x; i < n; i += 1024) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = i + 256 * u;
+      const float t = v[j < n ? j : i];
+      a[u] += j < n ? t : 0.f;
+    }
+  }
+  float s = block_sum_256((a[0] + a[1]) + (a[2] + a[3]), sh);
   if (threadIdx.x == 0) out[0] = s / (float)n;
+}
+__global__ void __launch_bounds__(256) k_mean(const float* v, int n, float* out) {
+  __shared__ float sh[4];
+  block_mean_256(v, n, out, sh);
 }
 hipError_t op_mean(const OpCtx& c, const float* v, int n, float* out) {
   ProfScope prof_(c, KC_OTHER);
@@ -621,16 +631,23 @@ hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, f
 }
 
 // ------------------------------------------------------------------------------------ optimizer
-// One fused pass over a flat parameter range: reads p, g (and m, v), writes p (and m, v) and the
-// low-precision working copy.  SGD: p -= lr g.  SGD-momentum: m = mu m + g; p -= lr m.
+// One fused pass over up to eight flat parameter ranges (a head's and its window's): reads p, g (and m, v), writes p (and
+// m, v) and the low-precision working copy.  A block more than the ranges need takes the mean of the head's row losses,
+// which otherwise is a launch of its own (8192 rows: 9 us with nothing beside it).  SGD: p -= lr g.  SGD-momentum: m = mu m + g; p -= lr m.
 // Adam: m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr (m/(1-b1^t)) / (sqrt(v/(1-b2^t)) + eps).
 template <int KIND, bool LOWP>
-__global__ void k_optimizer(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, bf16_t* __restrict__ pl, size_t n4, size_t n, float lr,
-                            float mu, float b1, float b2, float eps, float wd, float c1, float c2, float gs) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t st = (size_t)gridDim.x * blockDim.x;
-  for (; i < n4; i += st) {
+__global__ void __launch_bounds__(256) k_optimizer(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
+                            float* __restrict__ v, bf16_t* __restrict__ pl, OptRanges rg, float lr,
+                            float mu, float b1, float b2, float eps, float wd, float c1, float c2,
+                            const float* __restrict__ mean_v, int mean_rows, float* __restrict__ mean_out) {
+  __shared__ float sh[4];
+  const int blocks = gridDim.x - (mean_rows > 0 ? 1 : 0);
+  if ((int)blockIdx.x == blocks) { block_mean_256(mean_v, mean_rows, mean_out, sh); return; }
+  const size_t st = (size_t)blocks * 256;
+  for (int r = 0; r < rg.count; ++r) {
+  const float gs = rg.scale[r];
+  const size_t end = (rg.off[r] + rg.n[r]) >> 2;
+  for (size_t i = (rg.off[r] >> 2) + (size_t)blockIdx.x * 256 + threadIdx.x; i < end; i += st) {
     f32x4 pp = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + i);
     f32x4 gg = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g) + i);
     float pv[4] = {pp.x, pp.y, pp.z, pp.w};
@@ -657,27 +674,38 @@ __global__ void k_optimizer(float* __restrict__ p, const float* __restrict__ g, 
       reinterpret_cast<bf16x4*>(pl)[i] = o;
     }
   }
+  }
 }
-hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v,
-                        void* p_lowp, size_t n) {
+hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
+                               const OptRanges& r, const float* mean_v, int mean_rows, float* mean_out) {
   ProfScope prof_(c, KC_OPTIMIZER);
-  if (n == 0) return hipSuccess;
-  if (n % 4) return hipErrorInvalidValue;   // ranges are padded to 64 elements by the layout
-  size_t n4 = n / 4;
-  size_t want = (n4 + 255) / 256;
-  int blocks = (int)(want < 256 * 16 ? want : 256 * 16);
+  size_t longest = 0;
+  for (int i = 0; i < r.count; ++i) {
+    if (r.n[i] % 4 || r.off[i] % 4) return hipErrorInvalidValue;   // ranges are padded to 64 elements by the layout
+    if (r.n[i] > longest) longest = r.n[i];
+  }
+  if (longest == 0 && mean_rows <= 0) return hipSuccess;
+  const size_t want = (longest / 4 + 255) / 256;
+  const int blocks = (int)(want < 256 * 16 ? want : 256 * 16) + (mean_rows > 0 ? 1 : 0);
   float c1 = 1.f, c2 = 1.f;
   if (o.kind == 2) {
     c1 = (float)(1.0 / (1.0 - pow((double)o.beta1, (double)o.t)));
     c2 = (float)(1.0 / (1.0 - pow((double)o.beta2, (double)o.t)));
   }
   bf16_t* pl = (bf16_t*)p_lowp;
-#define LP_OPT(K, L) k_optimizer<K, L><<<blocks, 256, 0, c.stream>>>(p, g, m, v, pl, n4, n, o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2, o.grad_scale)
+#define LP_OPT(K, L) k_optimizer<K, L><<<blocks, 256, 0, c.stream>>>(p, g, m, v, pl, r, o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2, mean_v, mean_rows, mean_out)
   if (o.kind == 0) { if (pl) LP_OPT(0, true); else LP_OPT(0, false); }
   else if (o.kind == 1) { if (pl) LP_OPT(1, true); else LP_OPT(1, false); }
   else { if (pl) LP_OPT(2, true); else LP_OPT(2, false); }
 #undef LP_OPT
   return LP_LAUNCH_CHECK();
+}
+hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v,
+                        void* p_lowp, size_t n) {
+  if (n == 0) return hipSuccess;
+  OptRanges r;
+  r.off[0] = 0; r.n[0] = n; r.scale[0] = o.grad_scale; r.count = 1;
+  return op_optimizer_ranges(c, o, p, g, m, v, p_lowp, r, nullptr, 0, nullptr);
 }
 
 // ------------------------------------------------------------------------------------ transpose

@@ -1059,7 +1059,7 @@ hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   for (int i = 0; i < n; ++i) {
     const GemmArgs& g = gs[i];
     if (!gemm_dma_ok(g) || g.K != g0.K || g.a_kc != g0.a_kc || g.b_kc != g0.b_kc) return hipErrorInvalidValue;
-    if (g.a_rows || g.b_rows || (!g.a_kc && g.M % 8) || g.N % 8 || ((g.a_kc || g.b_kc) && g.K % 8) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || !al16(g.A) || !al16(g.B) || !al16(g.C) ||
+    if (g.a_rows || g.b_rows || g.rowsum || (!g.a_kc && g.M % 8) || g.N % 8 || ((g.a_kc || g.b_kc) && g.K % 8) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || !al16(g.A) || !al16(g.B) || !al16(g.C) ||
         (g.bias && !al16(g.bias)) || (g.pre && !al16(g.pre)) || (g.dact_src && (!al16(g.dact_src) || g.ldd % 8)) ||
         (g.res && (!al16(g.res) || g.ldr % 8)))
       return hipErrorInvalidValue;

@@ -23,7 +23,7 @@
 
 namespace lp {
 
-hipError_t gemm_plain(const OpCtx& c, const GemmArgs& g);
+hipError_t gemm_f32(const OpCtx& c, const GemmArgs* gs, int n);
 bool gemm_dma_ok(const GemmArgs& g);
 bool gemm_dma_plan(const OpCtx& c, const GemmArgs& g, int kind, int mode, DmaGemmPlan* out);
 hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d);
@@ -212,8 +212,14 @@ hipError_t op_gemm(const OpCtx& c, const GemmArgs& g) {
                        (uint64_t)(g.a_kc != 0) << 60 | (uint64_t)(g.b_kc != 0) << 61 | (uint64_t)(g.c_f32 != 0) << 62;
   ProfScope prof_(c, KC_GEMM, 2.0 * g.M * g.N * g.K, tag);
   if (c.gemm_variant >= 2 && !(c.dt == BF16 && fast_ok(g))) return hipErrorInvalidValue;
-  if (c.dt == BF16 && !use_plain() && fast_ok(g)) return gemm_mfma(c, g);
-  return gemm_plain(c, g);
+  if (c.dt == BF16 && !use_plain() && fast_ok(g)) {
+    if (g.rowsum) {            // the bf16 kernels take no row sums
+      hipError_t e = op_colsum(c, g.A, g.lda, g.rowsum, g.K, g.M, g.accumulate);
+      if (e != hipSuccess) return e;
+    }
+    return gemm_mfma(c, g);
+  }
+  return gemm_f32(c, &g, 1);
 }
 
 static bool grouping_off() {     // LP_NO_GROUP=1: every product in a launch of its own (for measurements)
@@ -223,6 +229,12 @@ static bool grouping_off() {     // LP_NO_GROUP=1: every product in a launch of 
 }
 
 hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
+  if (c.dt == F32 && n >= 2) {
+    double flops = 0.0;
+    for (int i = 0; i < n; ++i) flops += 2.0 * gs[i].M * gs[i].N * gs[i].K;
+    ProfScope prof_(c, KC_GEMM, flops);
+    return gemm_f32(c, gs, n);
+  }
   if (n >= 2 && c.dt == BF16 && !use_plain() && !grouping_off() && c.gemm_variant == 0 && env_choice() == 0) {
     bool ok = true;
     for (int i = 0; i < n; ++i) ok = ok && fast_ok(gs[i]);

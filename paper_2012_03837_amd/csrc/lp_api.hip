@@ -641,14 +641,44 @@ static int check_call(lp_ctx* c, const void* x, const int32_t* y, int batch, flo
   return LP_OK;
 }
 
-static int optimizer_range(lp_ctx* c, size_t b, size_t e, float grad_scale, int t = -1) {
+// One update of head hi and of those layers of its window for which `done` says so (layer, gradient scale), in one launch
+// per eight ranges (neighbouring layers are one range); the head's mean loss rides along if it is waiting.
+template <class F>
+static int update_block(lp_ctx* c, int hi, int t, F done) {
+  HeadState& Hd = c->heads[hi];
+  if (!c->waiting.empty()) {        // no backward pass of this chain has taken them along
+    CK(op_gemm_grouped(c->op(), c->waiting.data(), (int)c->waiting.size()));
+    c->waiting.clear();
+  }
   OptArgs a;
   const lp_opt_spec& s = c->spec.opt;
   a.kind = s.kind; a.lr = s.lr; a.momentum = s.momentum; a.beta1 = s.beta1; a.beta2 = s.beta2; a.eps = s.eps;
-  a.weight_decay = s.weight_decay; a.t = t >= 0 ? t : c->step_t; a.grad_scale = grad_scale;
-  CK(op_optimizer(c->op(), a, c->master + b, c->grads + b, c->mom ? c->mom + b : nullptr,
-                  c->var ? c->var + b : nullptr, c->lowp ? (void*)((bf16_t*)c->lowp + b) : nullptr, e - b));
-  return c->lowp ? refresh_wt(c, b, e - b) : LP_OK;      // behind the update, on the same stream
+  a.weight_decay = s.weight_decay; a.t = t; a.grad_scale = 1.f;
+  OptRanges r;
+  auto flush = [&]() -> int {
+    CK(op_optimizer_ranges(c->op(), a, c->master, c->grads, c->mom, c->var, c->lowp, r, c->loss_rows, c->mean_rows, c->mean_out));
+    c->mean_rows = 0;
+    r.count = 0;
+    return LP_OK;
+  };
+  auto add = [&](size_t b, size_t e, float scale) -> int {
+    if (r.count > 0 && r.scale[r.count - 1] == scale && r.off[r.count - 1] == e) {       // layers come from the top down
+      r.off[r.count - 1] = b; r.n[r.count - 1] += e - b;
+      return LP_OK;
+    }
+    int st = r.count == kMaxOptRanges ? flush() : LP_OK;
+    r.off[r.count] = b; r.n[r.count] = e - b; r.scale[r.count] = scale;
+    ++r.count;
+    return st;
+  };
+  int st = add(Hd.p_begin, Hd.p_end, 1.f);
+  for (int lj = Hd.e; lj > Hd.s_lo && st == LP_OK; --lj) {
+    float scale = 1.f;
+    if (done(lj, &scale)) st = add(c->layers[lj].p_begin, c->layers[lj].p_end, scale);
+  }
+  if (st == LP_OK) st = flush();
+  if (st != LP_OK) return st;
+  return c->lowp ? refresh_wt(c, Hd.p_begin, Hd.p_end - Hd.p_begin) : LP_OK;      // behind the update, on the same stream
 }
 
 // Launches the products collected from one stage of several blocks, at most 16 to a grouped launch.
@@ -735,9 +765,7 @@ static int run_lockstep(lp_ctx* c, const int32_t* ids, float* losses) {
       use_block(j);
       HeadState& Hd = c->heads[j - 1];
       const int t_blk = ++c->blk_updates[j];          // the block's own number of updates
-      if ((st = optimizer_range(c, Hd.p_begin, Hd.p_end, 1.f, t_blk)) != LP_OK) return st;
-      for (int lj = Hd.e; lj > Hd.s_lo; --lj)
-        if ((st = optimizer_range(c, c->layers[lj].p_begin, c->layers[lj].p_end, 1.f, t_blk)) != LP_OK) return st;
+      if ((st = update_block(c, j - 1, t_blk, [](int, float*) { return true; })) != LP_OK) return st;
     }
     if (two_streams) {
       CK(hipEventRecord(c->ev_chain[cur_team], tstream[cur_team]));
@@ -794,9 +822,7 @@ static int run_pipelined(lp_ctx* c, const void* x, const int32_t* y, int batch, 
       void* t = dcur; dcur = dnext; dnext = t;
     }
     const int t_blk = ++c->blk_updates[j];          // the block's own number of updates
-    if ((st = optimizer_range(c, Hd.p_begin, Hd.p_end, 1.f, t_blk)) != LP_OK) return st;
-    for (int lj = Hd.e; lj > Hd.s_lo; --lj)
-      if ((st = optimizer_range(c, c->layers[lj].p_begin, c->layers[lj].p_end, 1.f, t_blk)) != LP_OK) return st;
+    if ((st = update_block(c, j - 1, t_blk, [](int, float*) { return true; })) != LP_OK) return st;
     if (set) CK(hipEventRecord(c->ev_chain[j - 1], c->cur_stream));
     else if (side) CK(hipEventRecord(c->ev_chain[j - 1], c->stream));
   }
@@ -816,6 +842,8 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
   const bool side = train && c->n_side > 0 && !c->prof.on;
   const bool overlap = side && c->overlap_steps && batch > 0 && c->spec.schedule == LP_SCHED_SYNC;
   if (!overlap && (st = join_pending(c)) != LP_OK) return st;
+  c->waiting.clear(); c->mean_rows = 0;      // nothing is left over from a call that failed
+  c->mean_with_update = train && !c->lockstep;
   if (train && batch > 0 && c->spec.schedule != LP_SCHED_SYNC) return run_pipelined(c, x, y, batch, losses);
   for (int li = 1; li <= L; ++li) c->layers[li].in_override = nullptr;
   if (batch == 0) {
@@ -876,15 +904,13 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
         }
         void* t = dcur; dcur = dnext; dnext = t;
       }
-      if ((st = optimizer_range(c, Hd.p_begin, Hd.p_end, 1.f)) != LP_OK) return st;
       // a layer is updated as soon as the last head covering it has contributed
-      for (int lj = Hd.e; lj > Hd.s_lo; --lj) {
-        LayerState& S = c->layers[lj];
-        if (S.seen == S.coverage) {
-          float gs = c->spec.combine == LP_COMBINE_MEAN ? 1.f / (float)S.coverage : 1.f;
-          if ((st = optimizer_range(c, S.p_begin, S.p_end, gs)) != LP_OK) return st;
-        }
-      }
+      st = update_block(c, hj, c->step_t, [&](int lj, float* scale) {
+        const LayerState& S = c->layers[lj];
+        if (c->spec.combine == LP_COMBINE_MEAN) *scale = 1.f / (float)S.coverage;
+        return S.seen == S.coverage;
+      });
+      if (st != LP_OK) return st;
       if (set) CK(hipEventRecord(c->ev_chain[hj], c->cur_stream));
     }
   }

@@ -6,7 +6,7 @@
 #include "common.h"
 
 namespace lp {
-hipError_t gemm_plain(const OpCtx& c, const GemmArgs& g);
+hipError_t gemm_f32(const OpCtx& c, const GemmArgs* gs, int n);
 hipError_t gemm_mfma(const OpCtx& c, const GemmArgs& g);
 hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n);
 hipError_t attn_fwd_plain(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
@@ -41,7 +41,7 @@ extern "C" int lpk_gemm(int dtype, const void* A, int64_t lda, int a_kc, const v
   g.res = res; g.ldr = ldr; g.accumulate = accumulate;
   OpCtx c = mk(dtype, stream);
   c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws_elems;
-  if (variant == 1 || dtype != BF16) return (int)gemm_plain(c, g);
+  if (variant == 1 || dtype != BF16) return (int)gemm_f32(c, &g, 1);
   c.gemm_variant = variant;
   return (int)op_gemm(c, g);
 }

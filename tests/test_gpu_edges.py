@@ -170,3 +170,39 @@ def test_attention_small_heads(K, S, dh, causal):
     for got, ref in zip((g[:, :d], g[:, d:2 * d], g[:, 2 * d:]), ops.attention_bwd(q, k, v, p, split(dout.astype(np.float64)))):
         # one key per query: dQ and dK vanish and only their size against the whole can be asked for
         assert np.linalg.norm(got - merge(ref)) <= 1.5e-2 * max(np.linalg.norm(ref), 0.1 * scale)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("M,N,Kd", [(1, 1, 1), (16, 16, 16), (17, 33, 15), (128, 256, 257), (333, 520, 100), (1030, 1000, 70),
+                                    (10, 256, 128), (300, 7, 1000)])
+def test_fp32_arithmetic_gemm(K, dtype, M, N, Kd):
+    """The fp32 matrix-instruction kernel at its three tile edges, every layout, with odd leading dimensions (no vector
+    loads) and with whole ones: fp32 sums of Kd products, 2e-6."""
+    rng = np.random.default_rng(M + N + Kd)
+    A, B = rnd(rng, (M, Kd), dtype), rnd(rng, (N, Kd), dtype)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    C0 = rng.standard_normal((M, N)).astype(np.float32)
+    for a_kc in (0, 1):
+        for b_kc in (0, 1):
+            Am = A if a_kc else np.ascontiguousarray(A.T)
+            Bm = B if b_kc else np.ascontiguousarray(B.T)
+            C = dev(C0, 0)
+            K.lpk_gemm(dtype, dev(Am, dtype), Am.shape[1], a_kc, dev(Bm, dtype), Bm.shape[1], b_kc, C, N, 1, M, N, Kd, plain=1,
+                       accumulate=1)
+            assert relerr(host(C), ref + C0) <= 2e-6, (a_kc, b_kc)
+
+
+@pytest.mark.parametrize("classes,width,batch", [(2, 64, 6), (32, 256, 33), (33, 96, 19), (10, 1024, 7), (10, 1028, 5)])
+@pytest.mark.parametrize("scheme", ["greedy", "overlap"])
+def test_mlp_heads_and_grouped_gradients(K, classes, width, batch, scheme):
+    """The one-launch classifier head up to its largest sizes and just past them, the grouped weight gradients with their
+    bias sums, and the update of several parameter ranges.  (A loss is a difference of logits: its error is an ulp of
+    those, so the mean over a batch has to stay of order one: several samples, a small learning rate.)"""
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.mlp_config("t", n_layers=3, in_dim=24, width=width, hidden=72, n_classes=classes, batch=batch, scheme=scheme,
+                                combine="mean", opt=LI.configs.OptCfg("sgdm", lr=0.002, momentum=0.9))
+    for ns in (0, 2):
+        tr = lp.LocalTrainer(cfg, n_streams=ns)
+        x, y = data_for(cfg)
+        compare_step(tr, cfg, generic_params(cfg), x, y, n_steps=2, label=scheme)
+        tr.close()
