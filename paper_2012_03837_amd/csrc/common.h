@@ -166,11 +166,13 @@ hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const flo
 hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows,
                          int n, int write_grad, float inv_rows, int pad_to = 0);
 hipError_t op_mean(const OpCtx& c, const float* v, int n, float* out);
-// A classifier head of at most 32 classes on at most 1024 features in one launch: loss_rows, and if `backward` also dZ
-// [rows, ncls] and dfeat = dZ w [rows, in].
+// Classifier heads of at most 32 classes on at most 1024 features, up to eight in one launch over the same rows and
+// labels: loss_rows, and if `backward` also dZ [rows, ncls] and dfeat = dZ w [rows, in] (and a second copy of it).
+struct HeadCe { const void *feat, *w; const float* bias; float* loss_rows; void *dz, *dfeat, *dfeat2; int in, ncls; };
+constexpr int kMaxHeads = 8;
+struct HeadTable { HeadCe h[kMaxHeads]; int n = 0; };
 bool head_ce_ok(int in, int ncls);
-hipError_t op_head_ce(const OpCtx& c, const void* feat, const void* w, const float* bias, const int32_t* y, float* loss_rows,
-                      void* dz, void* dfeat, int rows, int in, int ncls, int backward, float inv_rows);
+hipError_t op_head_ce(const OpCtx& c, const HeadTable& ht, const int32_t* y, int rows, int backward, float inv_rows);
 
 struct OptArgs {
   int kind; float lr, momentum, beta1, beta2, eps, weight_decay; int t; float grad_scale;
@@ -178,12 +180,13 @@ struct OptArgs {
 hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v,
                         void* p_lowp, size_t n);
 // Several ranges [off, off + n) of the same buffers in one launch (offsets and sizes multiples of 4), each with its own
-// gradient scale (OptArgs::grad_scale is ignored); with mean_rows > 0 the launch also writes mean_out[0] = the mean of
-// mean_v[0 .. mean_rows), the same bits as op_mean.
+// gradient scale (OptArgs::grad_scale is ignored); the launch also writes out[i][0] = the mean of v[i][0 .. rows) for
+// the vectors of a MeanTable, the same bits as op_mean.
 constexpr int kMaxOptRanges = 8;
 struct OptRanges { size_t off[kMaxOptRanges], n[kMaxOptRanges]; float scale[kMaxOptRanges]; int count = 0; };
+struct MeanTable { const float* v[kMaxHeads]; float* out[kMaxHeads]; int rows = 0, count = 0; };
 hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
-                               const OptRanges& r, const float* mean_v, int mean_rows, float* mean_out);
+                               const OptRanges& r, const MeanTable& mt);
 
 hipError_t op_init_normal(const OpCtx& c, float* p, size_t n, float std, uint64_t seed, uint64_t stream_id);
 

@@ -164,6 +164,8 @@ struct lp_ctx : lp_scratch {
   size_t label_elems_per_sample = 1;
   hipEvent_t ev_pipe = nullptr;
   bool lockstep = false;                 // pipelined blocks are walked stage by stage (grouped GEMMs across blocks)
+  bool mlp_lockstep = false;             // so are the blocks of a synchronous residual-MLP step (run_mlp)
+  void use_set(int i) { use(i); cur_stream = stream; }      // scratch set i on the caller's stream
   void use(int i) { static_cast<lp_scratch&>(*this) = sets[i]; }
   // steps overlapped across calls: a call does not join its chains into the caller's stream; the next step's
   // forward pass of a layer waits only for the chains that read or update that layer (join_pending otherwise)
@@ -202,6 +204,12 @@ struct lp_ctx : lp_scratch {
 namespace lp {
 // The GEMMs a driver stage hands back for the caller to launch (see drivers.hip).
 struct StageGemms { GemmArgs g[4]; int n = 0; };
+// One layer's backward pass of a residual MLP: gradient in, where its input gradient goes (null: not wanted; dx_acc: added
+// to what is there), whether parameter gradients are taken and whether they are added to.
+struct MlpPass { int li = 0; const void* dout = nullptr; void* dx = nullptr; int dx_acc = 0; bool params = true; int acc = 0; };
+constexpr int kMlpBwdStages = 3;
+void mlp_backward_stage(lp_ctx* c, const MlpPass& p, int batch, int stage, std::vector<GemmArgs>* out);
+int mlp_heads(lp_ctx* c, int batch, const int32_t* y);
 constexpr int kDecFwdStages = 4, kDecBwdStages = 5, kVocabHeadStages = 4;
 int dec_forward_stage(lp_ctx* c, int li, int batch, const int32_t* ids, int stage, StageGemms* out);
 int dec_backward_stage(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int acc,

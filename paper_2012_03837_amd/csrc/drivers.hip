@@ -85,44 +85,53 @@ static int mlp_forward(lp_ctx* c, int li, int batch) {
   return LP_OK;
 }
 
-// Products that only share their inputs share a launch; a bias gradient rides along with its weight gradient.  Products
-// the head left waiting (its weight gradient) go with the first launch.
-static int mlp_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int acc, bool params) {
-  LayerState& L = c->layers[li];
-  OpCtx o = c->op();
-  const void* x = layer_input(c, li);
-  bool proj = L.t.count("win") > 0;
-  const void* p = proj ? L.mlp_p : x;
-  int width = L.s.width, hidden = L.s.hidden;
-  std::vector<GemmArgs> g;
-  auto wgrad = [&](const void* dy, const void* in, const char* w, const char* b) {
-    GemmArgs a = lin_wgrad(c, dy, in, batch, L.t[w], acc);
+// Backward pass of one layer in stages, like the decoder's below: a stage hands back its products, which only share their
+// inputs and so can share a launch with each other and with the same stage of other blocks.  A bias gradient rides along
+// with its weight gradient.  Products of the pass (c->dF, c->dc) live in the scratch set in use.
+void mlp_backward_stage(lp_ctx* c, const MlpPass& p, int batch, int stage, std::vector<GemmArgs>* out) {
+  LayerState& L = c->layers[p.li];
+  const void* x = layer_input(c, p.li);
+  const bool proj = L.t.count("win") > 0;
+  const void* in = proj ? L.mlp_p : x;
+  auto wgrad = [&](const void* dy, const void* xin, const char* w, const char* b) {
+    GemmArgs a = lin_wgrad(c, dy, xin, batch, L.t[w], p.acc);
     a.rowsum = c->G32(L.t[b]);
-    return a;
+    out->push_back(a);
   };
-  // da = (dout W2) * relu'(r)
-  GemmArgs gd = lin_dgrad(c, dout, batch, L.t["w2"], c->dF);
-  gd.dact = ACT_RELU; gd.dact_src = L.mlp_r; gd.ldd = hidden;
-  g.push_back(gd);
-  g.insert(g.end(), c->waiting.begin(), c->waiting.end());
-  c->waiting.clear();
-  if (params) g.push_back(wgrad(dout, L.mlp_r, "w2", "b2"));
-  DO(op_gemm_grouped(o, g.data(), (int)g.size()));
-  g.clear();
-  if (params) g.push_back(wgrad(c->dF, p, "w1", "b1"));
-  const bool want_dp = need_dx || (proj && params);
-  void* dp = proj ? c->dc : dx;
-  if (want_dp) {       // dp = da W1 + dout
-    GemmArgs g1 = lin_dgrad(c, c->dF, batch, L.t["w1"], dp);
-    g1.res = dout; g1.ldr = width;
-    g.push_back(g1);
+  if (stage == 0) {            // da = (dout W2) * relu'(r)
+    GemmArgs gd = lin_dgrad(c, p.dout, batch, L.t["w2"], c->dF);
+    gd.dact = ACT_RELU; gd.dact_src = L.mlp_r; gd.ldd = L.s.hidden;
+    out->push_back(gd);
+    if (p.params) wgrad(p.dout, L.mlp_r, "w2", "b2");
+  } else if (stage == 1) {     // dp = da W1 + dout
+    if (p.params) wgrad(c->dF, in, "w1", "b1");
+    if (p.dx || (proj && p.params)) {
+      GemmArgs g1 = lin_dgrad(c, c->dF, batch, L.t["w1"], proj ? c->dc : p.dx);
+      g1.res = p.dout; g1.ldr = L.s.width;
+      if (!proj) g1.accumulate = p.dx_acc;
+      out->push_back(g1);
+    }
+  } else if (proj) {
+    if (p.params) wgrad(c->dc, x, "win", "bin");
+    if (p.dx) {
+      GemmArgs g = lin_dgrad(c, c->dc, batch, L.t["win"], p.dx);
+      g.accumulate = p.dx_acc;
+      out->push_back(g);
+    }
   }
-  if (!g.empty()) DO(op_gemm_grouped(o, g.data(), (int)g.size()));
-  if (!want_dp || !proj) return LP_OK;
-  g.clear();
-  if (params) g.push_back(wgrad(dp, x, "win", "bin"));
-  if (need_dx) g.push_back(lin_dgrad(c, dp, batch, L.t["win"], dx));
-  if (!g.empty()) DO(op_gemm_grouped(o, g.data(), (int)g.size()));
+}
+
+// One layer alone: products the head left waiting (its weight gradient) go with the first launch.
+static int mlp_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int acc, bool params) {
+  MlpPass p;
+  p.li = li; p.dout = dout; p.dx = need_dx ? dx : nullptr; p.params = params; p.acc = acc;
+  std::vector<GemmArgs> g;
+  g.swap(c->waiting);
+  for (int stage = 0; stage < kMlpBwdStages; ++stage) {
+    mlp_backward_stage(c, p, batch, stage, &g);
+    if (!g.empty()) DO(op_gemm_grouped(c->op(), g.data(), (int)g.size()));
+    g.clear();
+  }
   return LP_OK;
 }
 
@@ -439,8 +448,9 @@ int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bo
   const float inv_rows = 1.0f / (float)rows;
   void* dfeat = Hd.s.kind == LP_HEAD_LINEAR_CE ? dh : c->dfeat;
   if (head_ce_ok(in_dim, ncls)) {
-    DO(op_head_ce(o, feat, c->W(Hd.t["w"]), tb >= 0 ? c->P32(tb) : nullptr, y, c->loss_rows, c->logits, dfeat, rows, in_dim,
-                  ncls, backward ? 1 : 0, inv_rows));
+    HeadTable ht;
+    ht.h[ht.n++] = HeadCe{feat, c->W(Hd.t["w"]), tb >= 0 ? c->P32(tb) : nullptr, c->loss_rows, c->logits, dfeat, nullptr, in_dim, ncls};
+    DO(op_head_ce(o, ht, y, rows, backward ? 1 : 0, inv_rows));
   } else {
     DO(op_gemm(o, lin_fwd(c, feat, rows, Hd.t["w"], tb, c->logits)));
     DO(op_softmax_ce(o, c->logits, ncls, y, c->loss_rows, rows, ncls, backward ? 1 : 0, inv_rows));
@@ -465,6 +475,49 @@ int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bo
       DO(op_layernorm_bwd(o, c->dfeat, h, c->hmean, c->hrstd, c->P32(Hd.t["ln.g"]), nullptr, dh,
                           c->G32(Hd.t["ln.g"]), c->G32(Hd.t["ln.b"]), rows, in_dim, 0));
     }
+  }
+  return LP_OK;
+}
+
+// The loss of every head of an MLP step and its gradient at the head's layer (c->dA of scratch set hi, and the layer's
+// gradient sum where it has one), the heads sharing launches; their weight gradients go to c->waiting.
+int mlp_heads(lp_ctx* c, int batch, const int32_t* y) {
+  const int J = (int)c->heads.size();
+  const float inv_rows = 1.0f / (float)batch;
+  bool fused = true;
+  for (auto& Hd : c->heads) fused = fused && head_ce_ok(Hd.s.in_dim, Hd.s.n_classes);
+  HeadTable ht;
+  std::vector<GemmArgs> g;
+  for (int hi = 0; hi < J; ++hi) {
+    HeadState& Hd = c->heads[hi];
+    LayerState& L = c->layers[Hd.e];
+    c->use_set(hi);
+    const int tb = Hd.t.count("b") ? Hd.t["b"] : -1;
+    if (fused) {
+      ht.h[ht.n++] = HeadCe{L.out, c->W(Hd.t["w"]), tb >= 0 ? c->P32(tb) : nullptr, c->loss_rows, c->logits, c->dA, L.gsum,
+                            Hd.s.in_dim, Hd.s.n_classes};
+      if (ht.n == kMaxHeads || hi == J - 1) { DO(op_head_ce(c->op(), ht, y, batch, 1, inv_rows)); ht.n = 0; }
+    } else {
+      g.push_back(lin_fwd(c, L.out, batch, Hd.t["w"], tb, c->logits));
+    }
+    GemmArgs gw = lin_wgrad(c, c->logits, L.out, batch, Hd.t["w"], 0);
+    if (tb >= 0) gw.rowsum = c->G32(tb);
+    c->waiting.push_back(gw);
+  }
+  if (fused) return LP_OK;
+  DO(op_gemm_grouped(c->op(), g.data(), J));
+  g.clear();
+  for (int hi = 0; hi < J; ++hi) {
+    c->use_set(hi);
+    const int ncls = c->heads[hi].s.n_classes;
+    DO(op_softmax_ce(c->op(), c->logits, ncls, y, c->loss_rows, batch, ncls, 1, inv_rows));
+    g.push_back(lin_dgrad(c, c->logits, batch, c->heads[hi].t["w"], c->dA));
+  }
+  DO(op_gemm_grouped(c->op(), g.data(), J));
+  for (int hi = 0; hi < J; ++hi) {
+    c->use_set(hi);
+    LayerState& L = c->layers[c->heads[hi].e];
+    if (L.gsum) DO(hipMemcpyAsync(L.gsum, c->dA, layer_out_elems(L.s, batch) * dtype_size(c->dt), hipMemcpyDeviceToDevice, c->stream));
   }
   return LP_OK;
 }

@@ -632,17 +632,21 @@ hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, f
 
 // ------------------------------------------------------------------------------------ optimizer
 // One fused pass over up to eight flat parameter ranges (a head's and its window's): reads p, g (and m, v), writes p (and
-// m, v) and the low-precision working copy.  A block more than the ranges need takes the mean of the head's row losses,
-// which otherwise is a launch of its own (8192 rows: 9 us with nothing beside it).  SGD: p -= lr g.  SGD-momentum: m = mu m + g; p -= lr m.
+// m, v) and the low-precision working copy.  A block more per head takes the mean of that head's row losses, which
+// otherwise is a launch of its own (8192 rows: 9 us with nothing beside it).  SGD: p -= lr g.  SGD-momentum: m = mu m + g; p -= lr m.
 // Adam: m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr (m/(1-b1^t)) / (sqrt(v/(1-b2^t)) + eps).
 template <int KIND, bool LOWP>
 __global__ void __launch_bounds__(256) k_optimizer(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
                             float* __restrict__ v, bf16_t* __restrict__ pl, OptRanges rg, float lr,
                             float mu, float b1, float b2, float eps, float wd, float c1, float c2,
-                            const float* __restrict__ mean_v, int mean_rows, float* __restrict__ mean_out) {
+                            MeanTable mt) {
   __shared__ float sh[4];
-  const int blocks = gridDim.x - (mean_rows > 0 ? 1 : 0);
-  if ((int)blockIdx.x == blocks) { block_mean_256(mean_v, mean_rows, mean_out, sh); return; }
+  const int blocks = gridDim.x - mt.count;
+  if ((int)blockIdx.x >= blocks) {
+    const int i = blockIdx.x - blocks;
+    block_mean_256(mt.v[i], mt.rows, mt.out[i], sh);
+    return;
+  }
   const size_t st = (size_t)blocks * 256;
   for (int r = 0; r < rg.count; ++r) {
   const float gs = rg.scale[r];
@@ -677,23 +681,23 @@ __global__ void __launch_bounds__(256) k_optimizer(float* __restrict__ p, const 
   }
 }
 hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
-                               const OptRanges& r, const float* mean_v, int mean_rows, float* mean_out) {
+                               const OptRanges& r, const MeanTable& mt) {
   ProfScope prof_(c, KC_OPTIMIZER);
   size_t longest = 0;
   for (int i = 0; i < r.count; ++i) {
     if (r.n[i] % 4 || r.off[i] % 4) return hipErrorInvalidValue;   // ranges are padded to 64 elements by the layout
     if (r.n[i] > longest) longest = r.n[i];
   }
-  if (longest == 0 && mean_rows <= 0) return hipSuccess;
+  if (longest == 0 && mt.count == 0) return hipSuccess;
   const size_t want = (longest / 4 + 255) / 256;
-  const int blocks = (int)(want < 256 * 16 ? want : 256 * 16) + (mean_rows > 0 ? 1 : 0);
+  const int blocks = (int)(want < 256 * 16 ? want : 256 * 16) + mt.count;
   float c1 = 1.f, c2 = 1.f;
   if (o.kind == 2) {
     c1 = (float)(1.0 / (1.0 - pow((double)o.beta1, (double)o.t)));
     c2 = (float)(1.0 / (1.0 - pow((double)o.beta2, (double)o.t)));
   }
   bf16_t* pl = (bf16_t*)p_lowp;
-#define LP_OPT(K, L) k_optimizer<K, L><<<blocks, 256, 0, c.stream>>>(p, g, m, v, pl, r, o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2, mean_v, mean_rows, mean_out)
+#define LP_OPT(K, L) k_optimizer<K, L><<<blocks, 256, 0, c.stream>>>(p, g, m, v, pl, r, o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2, mt)
   if (o.kind == 0) { if (pl) LP_OPT(0, true); else LP_OPT(0, false); }
   else if (o.kind == 1) { if (pl) LP_OPT(1, true); else LP_OPT(1, false); }
   else { if (pl) LP_OPT(2, true); else LP_OPT(2, false); }
@@ -705,7 +709,7 @@ hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float*
   if (n == 0) return hipSuccess;
   OptRanges r;
   r.off[0] = 0; r.n[0] = n; r.scale[0] = o.grad_scale; r.count = 1;
-  return op_optimizer_ranges(c, o, p, g, m, v, p_lowp, r, nullptr, 0, nullptr);
+  return op_optimizer_ranges(c, o, p, g, m, v, p_lowp, r, MeanTable());
 }
 
 // ------------------------------------------------------------------------------------ transpose

@@ -9,10 +9,10 @@
 // four matrix instructions takes element j of every lane.  Both operands use this order, so any storage layout pairs
 // with any other: k contiguous is one 16-byte (bf16: 8-byte) load per row and chunk, k-major four 4-byte loads.
 //
-// Up to four independent products share a launch (GemmArgs::rowsum adds a bias gradient to a weight gradient: sums of
+// Up to sixteen independent products share a launch (GemmArgs::rowsum adds a bias gradient to a weight gradient: sums of
 // A's rows, taken from the fragments by the blocks of the first tile column).
-//   128 x 256 x 256 fp32 (a layer of the MLP): 12.1 -> 4.5 us; 333 x 1000 x 520: 42 -> 12 us;
-//   1024 x 1024 x 1024: 160 -> 33 us (the 64 x 64 x 32 FMA kernel before).
+//   128 x 256 x 256 fp32 (a layer of the MLP): 12.1 -> 4.2 us; 333 x 1000 x 520: 42 -> 11.6 us;
+//   1024 x 1024 x 1024: 29 us (74 TFLOP/s), 4096 cubed 1.64 ms (84 TFLOP/s, 53 % of the fp32 matrix rate).
 #include <stdio.h>
 #include "common.h"
 #include "gemm_common.h"
@@ -21,13 +21,13 @@ namespace lp {
 
 namespace {
 
-constexpr int kMaxFGroup = 4;
+constexpr int kMaxFGroup = 16;
 
 template <typename T>
 struct FProblem {
   const T* A; const T* B;
   int64_t lda, ldb;
-  int a_kc, b_kc, a_vec, b_vec;      // vec: rows start on whole 4-element loads
+  int a_kc, b_kc, a_vec, b_vec;      // vec: k contiguous in whole 4-element loads
   int M, N, K;
   int first, tiles_n;                // first tile number of this problem, tile columns
   float* rowsum;
@@ -44,32 +44,69 @@ __device__ __forceinline__ f4 load4(const bf16_t* p) {
   return r;
 }
 
-// One lane's four elements of a 16-deep chunk.  `base` points at (row, k = 0) of this lane's row; MASK: some k of the
-// chunk may lie past k_hi (clamped for the load, zeroed after it).
-template <bool MASK, typename T>
-__device__ __forceinline__ f4 fetch4(const T* base, int64_t ld, int kc, int vec, int k, int k_hi) {
+// One lane's four elements of a 16-deep chunk: k .. k + 3 of its row.  VEC (k contiguous, rows on whole 4-element loads
+// and K % 4 == 0): one load.  MASK: the chunk may reach past K (clamped for the load, zeroed after it).
+template <bool VEC, bool MASK, typename T>
+__device__ __forceinline__ f4 fetch4(const T* base, int64_t st, int k, int K) {
   f4 r;
-  if (kc && vec && (!MASK || k + 4 <= k_hi)) {
-    r = load4(base + k);
+  if (VEC) {
+    r = load4(base + (MASK && k >= K ? K - 4 : k));
+    if (MASK && k >= K) r = f4{0.f, 0.f, 0.f, 0.f};
   } else {
-    const int64_t st = kc ? 1 : ld;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int kk = MASK ? (k + j < k_hi ? k + j : k_hi - 1) : k + j;
+      const int kk = MASK ? (k + j < K ? k + j : K - 1) : k + j;
       r[j] = to_f(base[kk * st]);
     }
     if (MASK) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) r[j] = k + j < k_hi ? r[j] : 0.f;
+      for (int j = 0; j < 4; ++j) r[j] = k + j < K ? r[j] : 0.f;
     }
   }
   return r;
 }
 
+// The reduction of one wave: chunks c0 .. c1, DEPTH - 1 of them in flight.
+template <bool AV, bool BV, int TT, int DEPTH, typename T>
+__device__ __forceinline__ void reduce_wave(const T* const (&ap)[TT], const T* const (&bp)[TT], int64_t ast, int64_t bst, int g,
+                                            int c0, int c1, int K, bool sums, f4 (&acc)[TT][TT], float (&rs)[TT]) {
+  f4 a[DEPTH][TT], b[DEPTH][TT];
+  auto fetch = [&](int s, int c) {
+    const int k = 16 * c + 4 * g;
+    if (16 * c + 16 <= K) {
+#pragma unroll
+      for (int t = 0; t < TT; ++t) { a[s][t] = fetch4<AV, false>(ap[t], ast, k, K); b[s][t] = fetch4<BV, false>(bp[t], bst, k, K); }
+    } else {
+#pragma unroll
+      for (int t = 0; t < TT; ++t) { a[s][t] = fetch4<AV, true>(ap[t], ast, k, K); b[s][t] = fetch4<BV, true>(bp[t], bst, k, K); }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < DEPTH - 1; ++s)
+    if (c0 + s < c1) fetch(s, c0 + s);
+  for (int c = c0; c < c1; c += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      if (c + u >= c1) break;
+      if (c + u + DEPTH - 1 < c1) fetch((u + DEPTH - 1) % DEPTH, c + u + DEPTH - 1);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int x = 0; x < TT; ++x)
+#pragma unroll
+          for (int y = 0; y < TT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][x][j], b[u][y][j], acc[x][y], 0, 0, 0);
+      if (sums) {
+#pragma unroll
+        for (int x = 0; x < TT; ++x) rs[x] += (a[u][x][0] + a[u][x][1]) + (a[u][x][2] + a[u][x][3]);
+      }
+    }
+  }
+}
+
 template <typename T, int TT, int NP>
 __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
   constexpr int EDGE = 16 * TT, LDP = EDGE + 4;       // LDS rows of a partial tile
-  constexpr int DEPTH = TT == 4 ? 1 : (TT == 2 ? 2 : 4);       // chunks per register set
+  constexpr int DEPTH = TT == 4 ? 3 : 4;       // chunks in registers
   extern __shared__ __attribute__((aligned(16))) float part[];      // [4][EDGE][LDP], then [4][EDGE] row sums
   int pi = 0;
 #pragma unroll
@@ -79,8 +116,8 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
   const int tile = blockIdx.x - P.first, tm = tile / P.tiles_n, tn = tile - tm * P.tiles_n;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, g = lane >> 4;
-  const int K = P.K, kq = ((K + 3) / 4 + 15) & ~15;     // a wave's share of the reduction: whole chunks
-  const int k_lo = wave * kq, k_hi = k_lo + kq < K ? k_lo + kq : K;
+  const int K = P.K, nch = (K + 15) / 16;               // a wave's share of the reduction: whole chunks
+  const int c0 = nch * wave / 4, c1 = nch * (wave + 1) / 4;
   const T *ap[TT], *bp[TT];
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
@@ -99,52 +136,35 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
 #pragma unroll
     for (int j = 0; j < TT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   }
-  f4 a0[DEPTH][TT], b0[DEPTH][TT], a1[DEPTH][TT], b1[DEPTH][TT];
-  auto fetch = [&](f4 (&a)[DEPTH][TT], f4 (&b)[DEPTH][TT], int k0) {
-    if (k0 + 16 * DEPTH <= k_hi) {
+  const int64_t ast = P.a_kc ? 1 : P.lda, bst = P.b_kc ? 1 : P.ldb;
+  if (P.a_vec) {
+    if (P.b_vec) reduce_wave<true, true, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+    else reduce_wave<true, false, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+  } else {
+    if (P.b_vec) reduce_wave<false, true, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+    else reduce_wave<false, false, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+  }
+  // What the epilogue reads is asked for before the partial tiles are exchanged: element by element behind the reduction,
+  // its loads were a chain of memory latencies longer than the product (16 elements a thread for a 64 x 64 tile: 20 us).
+  // Thread: PER runs of W consecutive columns (64: 4 x 4, 32: 1 x 4, 16: 1 x 1).
+  constexpr int W = TT == 1 ? 1 : 4, RUNS = EDGE * EDGE / W, PER = RUNS / 256, RPR = EDGE / W;     // runs per row
+  const Epilogue& e = P.e;
+  float eb[PER][W], es[PER][W], er[PER][W], ec[PER][W];
 #pragma unroll
-      for (int c = 0; c < DEPTH; ++c)
+  for (int q = 0; q < PER; ++q) {
+    const int run = threadIdx.x + 256 * q;
+    int m = tm * EDGE + run / RPR;
+    m = m < P.M ? m : P.M - 1;
 #pragma unroll
-        for (int t = 0; t < TT; ++t) {
-          a[c][t] = fetch4<false>(ap[t], P.lda, P.a_kc, P.a_vec, k0 + 16 * c + 4 * g, k_hi);
-          b[c][t] = fetch4<false>(bp[t], P.ldb, P.b_kc, P.b_vec, k0 + 16 * c + 4 * g, k_hi);
-        }
-    } else {
-#pragma unroll
-      for (int c = 0; c < DEPTH; ++c)
-#pragma unroll
-        for (int t = 0; t < TT; ++t) {
-          a[c][t] = fetch4<true>(ap[t], P.lda, P.a_kc, P.a_vec, k0 + 16 * c + 4 * g, k_hi);
-          b[c][t] = fetch4<true>(bp[t], P.ldb, P.b_kc, P.b_vec, k0 + 16 * c + 4 * g, k_hi);
-        }
+    for (int w = 0; w < W; ++w) {
+      int n = tn * EDGE + (run % RPR) * W + w;
+      n = n < P.N ? n : P.N - 1;
+      eb[q][w] = e.bias ? e.bias[n] : 0.f;
+      es[q][w] = e.dact != ACT_NONE ? to_f(reinterpret_cast<const T*>(e.dact_src)[(size_t)m * e.ldd + n]) : 0.f;
+      er[q][w] = e.res ? to_f(reinterpret_cast<const T*>(e.res)[(size_t)m * e.ldr + n]) : 0.f;
+      const size_t o = (size_t)m * e.ldc + n;
+      ec[q][w] = e.accumulate ? (e.c_f32 ? reinterpret_cast<const float*>(e.C)[o] : to_f(reinterpret_cast<const T*>(e.C)[o])) : 0.f;
     }
-  };
-  auto mma = [&](const f4 (&a)[DEPTH][TT], const f4 (&b)[DEPTH][TT]) {
-#pragma unroll
-    for (int c = 0; c < DEPTH; ++c) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int x = 0; x < TT; ++x)
-#pragma unroll
-          for (int y = 0; y < TT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][x][j], b[c][y][j], acc[x][y], 0, 0, 0);
-      if (sums) {
-#pragma unroll
-        for (int x = 0; x < TT; ++x) rs[x] += (a[c][x][0] + a[c][x][1]) + (a[c][x][2] + a[c][x][3]);
-      }
-    }
-  };
-  if (k_lo < k_hi) {
-    constexpr int STEP = 16 * DEPTH;
-    fetch(a0, b0, k_lo);
-    int k0 = k_lo;
-    for (; k0 + STEP < k_hi; k0 += 2 * STEP) {       // two register sets, loads one set ahead
-      fetch(a1, b1, k0 + STEP);
-      mma(a0, b0);
-      if (k0 + 2 * STEP < k_hi) fetch(a0, b0, k0 + 2 * STEP);
-      mma(a1, b1);
-    }
-    if (k0 < k_hi) mma(a0, b0);
   }
   // partial tiles: accumulator v of lane (li, g) is row 4 g + v, column li of its 16 x 16 tile
   float* mine = part + (size_t)wave * EDGE * LDP;
@@ -165,12 +185,24 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
   }
   __syncthreads();
   constexpr int PT = EDGE * LDP;
-#pragma unroll 1
-  for (int i = threadIdx.x; i < EDGE * EDGE; i += 256) {
-    const int r = i / EDGE, col = i % EDGE, m = tm * EDGE + r, n = tn * EDGE + col;
-    if (m < P.M && n < P.N) {
-      const float* q = part + r * LDP + col;
-      epilogue_store<T>(P.e, m, n, (q[0] + q[PT]) + (q[2 * PT] + q[3 * PT]));
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int run = threadIdx.x + 256 * q, r = run / RPR, col = (run % RPR) * W, m = tm * EDGE + r;
+    const float* p = part + r * LDP + col;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const int n = tn * EDGE + col + w;
+      float v = ((p[w] + p[PT + w]) + (p[2 * PT + w] + p[3 * PT + w])) + eb[q][w];
+      if (m >= P.M || n >= P.N) continue;
+      const size_t o = (size_t)m * e.ldc + n;
+      if (e.pre) reinterpret_cast<T*>(e.pre)[o] = from_f<T>(v);
+      if (e.act == ACT_RELU) v = fmaxf(v, 0.f);
+      else if (e.act == ACT_GELU) v = gelu_f(v);
+      if (e.dact == ACT_RELU) v = es[q][w] > 0.f ? v : 0.f;
+      else if (e.dact == ACT_GELU) v *= dgelu_f(es[q][w]);
+      v += er[q][w] + ec[q][w];
+      if (e.c_f32) reinterpret_cast<float*>(e.C)[o] = v;
+      else reinterpret_cast<T*>(e.C)[o] = from_f<T>(v);
     }
   }
   if (sums && (int)threadIdx.x < EDGE) {
@@ -178,7 +210,7 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
     if (m < P.M) {
       const float* q = rsum + threadIdx.x;
       const float v = (q[0] + q[EDGE]) + (q[2 * EDGE] + q[3 * EDGE]);
-      P.rowsum[m] = P.e.accumulate ? P.rowsum[m] + v : v;
+      P.rowsum[m] = e.accumulate ? P.rowsum[m] + v : v;
     }
   }
 }
@@ -219,8 +251,8 @@ hipError_t gemm_f_t(const OpCtx& c, const GemmArgs* gs, int n) {
     FProblem<T>& p = grp.p[grp.n++];
     p.A = (const T*)g.A; p.B = (const T*)g.B; p.lda = g.lda; p.ldb = g.ldb;
     p.a_kc = g.a_kc; p.b_kc = g.b_kc;
-    p.a_vec = g.lda % 4 == 0 && ((uintptr_t)g.A & al) == 0;
-    p.b_vec = g.ldb % 4 == 0 && ((uintptr_t)g.B & al) == 0;
+    p.a_vec = g.a_kc && g.K % 4 == 0 && g.lda % 4 == 0 && ((uintptr_t)g.A & al) == 0;
+    p.b_vec = g.b_kc && g.K % 4 == 0 && g.ldb % 4 == 0 && ((uintptr_t)g.B & al) == 0;
     p.M = g.M; p.N = N; p.K = g.K; p.rowsum = g.rowsum;
     p.e = make_epilogue(g);
     t64 += (long)((g.M + 63) / 64) * ((N + 63) / 64);
@@ -235,10 +267,16 @@ hipError_t gemm_f_t(const OpCtx& c, const GemmArgs* gs, int n) {
 }  // namespace
 
 hipError_t gemm_f32(const OpCtx& c, const GemmArgs* gs, int n) {
-  if (n == 1) return c.dt == BF16 ? gemm_f_t<bf16_t, 1>(c, gs, 1) : gemm_f_t<float, 1>(c, gs, 1);
-  for (int i = 0; i < n; i += kMaxFGroup) {
+  if (c.dt == BF16) {
+    for (int i = 0; i < n; ++i) {
+      hipError_t e = gemm_f_t<bf16_t, 1>(c, gs + i, 1);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  for (int i = 0; i < n; i += kMaxFGroup) {          // the table travels as a kernel argument: 1, 4 or 16 entries
     const int k = n - i < kMaxFGroup ? n - i : kMaxFGroup;
-    hipError_t e = c.dt == BF16 ? gemm_f_t<bf16_t, kMaxFGroup>(c, gs + i, k) : gemm_f_t<float, kMaxFGroup>(c, gs + i, k);
+    hipError_t e = k == 1 ? gemm_f_t<float, 1>(c, gs + i, 1) : (k <= 4 ? gemm_f_t<float, 4>(c, gs + i, k) : gemm_f_t<float, kMaxFGroup>(c, gs + i, k));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
