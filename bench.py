@@ -292,9 +292,9 @@ def main():
         ob, npar = optimizer_bytes_per_step(cfg)
         key = "gemm" if "gemm" in phases and cfg.layers[0].kind != "resnet_stage" else "conv"
         # the class's ops: GEMMs run k_gemm_dma / k_mfma_tiles (+ k_splitk_reduce), convolutions the
-        # same tile kernel through gather loaders; the fp32 path runs k_gemm_plain
+        # same tile kernel through gather loaders; fp32 products run k_gemm_f
         kernel_names = {"gemm": "k_gemm_dma+k_mfma_tiles+k_splitk_reduce" if cfg.dtype == "bf16" else "k_gemm_f",
-                        "conv": "k_mfma_tiles<Conv*>+k_gemm_plain(stem)+k_splitk_reduce"}
+                        "conv": "k_mfma_tiles<Conv*>+k_stem_fwd+k_stem_wgrad+k_splitk_reduce"}
         if key in phases:
             p = phases[key]
             peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_F32_TFLOPS

@@ -21,13 +21,13 @@ extern "C" {
  *   v (+= bias[n]); pre[m,n] = v; v = act(v); v *= act'(dact_src[m,n]); v += res[m,n].
  * A(m,k) = a_kc ? A[m*lda+k] : A[k*lda+m]; B(n,k) = b_kc ? B[n*ldb+k] : B[k*ldb+n]  (the forward, dgrad
  * and wgrad forms of a linear layer: paper appendix A, "MLP").  act / dact: 0 none, 1 ReLU, 2 GELU(tanh).
- * variant: 0 lets the library choose the kernel; 1 forces the FMA kernel; for bf16, 2 forces the
+ * variant: 0 lets the library choose the kernel; 1 forces the fp32-arithmetic kernel; for bf16, 2 forces the
  * register-staged MFMA kernel, 3 / 4 the direct-to-LDS kernel with 256 x 128 tiles and the last partial wave
  * of tiles computed whole / cut along k, 5 / 6 the same with 256 x 256 tiles and 8 wavefronts, 7 / 8 with
  * 256 x 256 tiles and 4 wavefronts; 9 / 10 / 11 those three tile shapes in panel mode (outputs 2..8 tiles
  * wide: the tile columns of one tile row walk the same cut of the reduction together, so that the other
- * operand is fetched once per row); 20 / 21 / 22 the 8-wavefront 256 x 256 shape with 64-deep k-tiles (K a
- * multiple of 64), tail whole / cut along k / panel mode; an error if the shape does not qualify (K % 32 != 0, no workspace for
+ * operand is fetched once per row); 20 / 21 / 22 the 8-wavefront 256 x 256 shape with 64-deep k-tiles (any
+ * K from 64 on whose operand rows are whole 16-byte chunks), tail whole / cut along k / panel mode; an error if the shape does not qualify (K % 32 != 0 for 3 .. 11, no workspace for
  * a cut, an output too narrow or too wide or a reduction too short for panel mode).  splitk_ws_dev (may be NULL) is fp32 workspace of
  * splitk_ws_elems floats: with it, reductions over few output tiles are split along k and the partial sums
  * added in a fixed order (at most max(8 * M * N, 2^25) floats are used). */
@@ -37,7 +37,7 @@ int lpk_gemm(int dtype, const void* A, int64_t lda, int a_kc, const void* B, int
              float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
 
 /* n (2..16) independent bf16 products C_i[M_i, N_i] (+)= epilogue(sum_k A_i(m,k) B_i(n,k)) with one reduction length K
- * (a multiple of 32) and one pair of operand layouts, in ONE persistent launch: the weight gradients of the linear
+ * (a multiple of 32, or from 128 on any length whose operand rows are whole 16-byte chunks) and one pair of operand layouts, in ONE persistent launch: the weight gradients of the linear
  * maps of one layer, or the same-shaped products of independent blocks (section 3: blocks are trained in
  * parallel; section 6), each of which alone has too few output tiles for the chip.  Every array is a HOST array of
  * n entries holding DEVICE pointers, leading dimensions and sizes (M_i, N_i multiples of 8).  Outputs are fp32

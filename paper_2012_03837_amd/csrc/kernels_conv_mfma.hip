@@ -5,7 +5,7 @@
 //   forward : out[(n,p,q), o]  = sum_{(r,s,c)} x[n, p*st+r-pad, q*st+s-pad, c] * w[o, r, s, c]
 //   dgrad   : dx[(n,h,w), c]   = sum_{(r,s,o)} dout[n, (h+pad-r)/st, (w+pad-s)/st, o] * w[o, r, s, c]
 //   wgrad   : dw[o, (r,s,c)]   = sum_{(n,p,q)} dout[(n,p,q), o] * x[n, p*st+r-pad, q*st+s-pad, c]   (fp32, split-K)
-// Needs C % 8 == 0 and O % 8 == 0; the 3-channel stem convolution stays on the plain kernel.
+// Needs C % 8 == 0 and O % 8 == 0; the stem convolution on 1 to 3 channels has kernels of its own (kernels_conv_stem.hip).
 #include <stdio.h>
 #include <type_traits>
 #include "common.h"

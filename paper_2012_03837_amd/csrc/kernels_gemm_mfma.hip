@@ -53,8 +53,8 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Shapes the MFMA kernels take: every vector access must be 16-byte aligned and never straddle an edge.  The
 // reduction may have any length where both operands are stored k-major (a weight gradient over any number of rows:
-// a chunk lies along the rows of the tile, so K only counts chunks).  What they do not take falls to the plain FMA
-// kernel: with 2555 rows (K % 8 = 3) and a vocabulary of 10003 a step of six 448-wide layers took 18.1 ms, 16.3 of
+// a chunk lies along the rows of the tile, so K only counts chunks).  What they do not take runs in
+// fp32 arithmetic; on the FMA kernel that it ran on before, with 2555 rows (K % 8 = 3) and a vocabulary of 10003 a step of six 448-wide layers took 18.1 ms, 16.3 of
 // them in 27 plain products (a 1344 x 448 weight gradient 390 .. 660 us); 2.1 ms with them here.
 bool fast_ok(const GemmArgs& g) {
   if (g.M < 1 || g.N < 8 || g.K < 1) return false;
