@@ -503,22 +503,27 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
     };
     constexpr int NDS = (A_KC ? 4 : 8) + (B_KC ? TN : 2 * TN);
     // The reduction's last k-tile, if it is partial, holds the last 64 of k: the first `skip` of them belong to the
-    // k-tile before it and are cleared in the m-side operand (finite values times zero).  Once per output tile, by
-    // all waves, between the barrier that says the k-tile has landed and its first fragment reads.
+    // k-tile before it and are cleared in both operands (an infinity against a cleared one would make a NaN).  Once per
+    // output tile, by all waves, between the barrier that says the k-tile has landed and its first fragment reads.
     const int skip = p.kt * KT - p.K;
-    auto clear_counted = [&](int stage) {
-      char* as = smem + stage * STAGE_BYTES;
+    auto clear_rows = [&](char* sm, auto kc, auto rows) {
+      constexpr int ROWS = decltype(rows)::value;
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-      if (A_KC) {              // K is a multiple of 8: whole 16-byte chunks
+      if (decltype(kc)::value) {              // K is a multiple of 8: whole 16-byte chunks
 #pragma unroll 1
-        for (int i = threadIdx.x; i < BM * 8; i += 64 * NWAVES) {
+        for (int i = threadIdx.x; i < ROWS * 8; i += 64 * NWAVES) {
           const int row = i >> 3, c = i & 7;
-          if (8 * c < skip) *reinterpret_cast<f32x4*>(as + row * 128 + 16 * (c ^ ((row >> 1) & 7))) = zero;
+          if (8 * c < skip) *reinterpret_cast<f32x4*>(sm + row * 128 + 16 * (c ^ ((row >> 1) & 7))) = zero;
         }
       } else {
 #pragma unroll 1
-        for (int i = threadIdx.x; i < skip * (BM * 2 / 16); i += 64 * NWAVES) *reinterpret_cast<f32x4*>(as + 16 * i) = zero;
+        for (int i = threadIdx.x; i < skip * (ROWS * 2 / 16); i += 64 * NWAVES) *reinterpret_cast<f32x4*>(sm + 16 * i) = zero;
       }
+    };
+    auto clear_counted = [&](int stage) {
+      char* as = smem + stage * STAGE_BYTES;
+      clear_rows(as, std::integral_constant<bool, A_KC>{}, std::integral_constant<int, BM>{});
+      clear_rows(as + A_BYTES, std::integral_constant<bool, B_KC>{}, std::integral_constant<int, BN>{});
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
     ItemIter L = first_item(), C = L;

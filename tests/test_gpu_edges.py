@@ -43,6 +43,31 @@ def test_gemm_reduction_of_any_length(K, Kd, a_kc, b_kc):
             assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("a_kc,b_kc", [(1, 1), (1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("Kd", [72, 96, 200])
+def test_gemm_partial_k_tile_infinities(K, Kd, a_kc, b_kc):
+    """An infinity inside a partial last k-tile, on either side of the part that counts, is an infinity of its row or
+    column and nothing else (all operands positive, so that no product of it is NaN)."""
+    import torch
+    rng = np.random.default_rng(Kd)
+    M, N = 264, 256
+    for operand in (0, 1):
+        for k in (Kd - 64, Kd // 64 * 64 - 1, Kd // 64 * 64, Kd - 1):
+            A, B = np.abs(rnd(rng, (M, Kd), 1)) + 1, np.abs(rnd(rng, (N, Kd), 1)) + 1
+            (A, B)[operand][5, k] = np.inf
+            want = np.zeros((M, N), bool)
+            if operand:
+                want[:, 5] = True
+            else:
+                want[5] = True
+            Am = A if a_kc else np.ascontiguousarray(A.T)
+            Bm = B if b_kc else np.ascontiguousarray(B.T)
+            out = zeros(M, N)
+            K.lpk_gemm(1, dev(Am, 1), Am.shape[1], a_kc, dev(Bm, 1), Bm.shape[1], b_kc, out, N, 1, M, N, Kd, variant=20)
+            got = host(out)
+            assert not np.isnan(got).any() and (np.isinf(got) == want).all(), (operand, k)
+
+
 @pytest.mark.parametrize("T", [129, 600, 2555])
 def test_grouped_weight_gradients_any_rows(K, T):
     """One grouped launch over a row count that is no multiple of a k-tile."""
