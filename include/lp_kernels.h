@@ -37,7 +37,7 @@ int lpk_gemm(int dtype, const void* A, int64_t lda, int a_kc, const void* B, int
              float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
 
 /* n (2..16) independent bf16 products C_i[M_i, N_i] (+)= epilogue(sum_k A_i(m,k) B_i(n,k)) with one reduction length K
- * (a multiple of 32, or from 128 on any length whose operand rows are whole 16-byte chunks) and one pair of operand layouts, in ONE persistent launch: the weight gradients of the linear
+ * (a multiple of 32) and one pair of operand layouts, in ONE persistent launch: the weight gradients of the linear
  * maps of one layer, or the same-shaped products of independent blocks (section 3: blocks are trained in
  * parallel; section 6), each of which alone has too few output tiles for the chip.  Every array is a HOST array of
  * n entries holding DEVICE pointers, leading dimensions and sizes (M_i, N_i multiples of 8).  Outputs are fp32

@@ -50,8 +50,10 @@ extern "C" int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda,
                                 int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
                                 float* splitk_ws, size_t splitk_ws_elems, void* stream) {
   if (n < 1 || n > 16 || !A || !lda || !B || !ldb || !C || !ldc || !M || !N) return (int)hipErrorInvalidValue;
+  if (K % 32) return (int)hipErrorInvalidValue;
   GemmArgs g[16];
   for (int i = 0; i < n; ++i) {
+    if (M[i] % 8) return (int)hipErrorInvalidValue;
     g[i].A = A[i]; g[i].lda = lda[i]; g[i].a_kc = a_kc; g[i].B = B[i]; g[i].ldb = ldb[i]; g[i].b_kc = b_kc;
     g[i].C = C[i]; g[i].ldc = ldc[i]; g[i].c_f32 = c_f32; g[i].M = M[i]; g[i].N = N[i]; g[i].K = K;
     g[i].bias = bias ? bias[i] : nullptr; g[i].act = act;

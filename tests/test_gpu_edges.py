@@ -68,20 +68,24 @@ def test_gemm_partial_k_tile_infinities(K, Kd, a_kc, b_kc):
             assert not np.isnan(got).any() and (np.isinf(got) == want).all(), (operand, k)
 
 
-@pytest.mark.parametrize("T", [129, 600, 2555])
-def test_grouped_weight_gradients_any_rows(K, T):
-    """One grouped launch over a row count that is no multiple of a k-tile."""
+@pytest.mark.parametrize("seq,batch", [(43, 3), (200, 3), (365, 7)])
+def test_grouped_weight_gradients_any_rows(K, seq, batch):
+    """A decoder step over a token count that is no multiple of a k-tile: a layer's weight gradients share a launch."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.make_config("cfg3_small", vocab=512, seq_len=seq, batch=batch)
+    tr = lp.LocalTrainer(cfg)
+    x, y = data_for(cfg)
+    compare_step(tr, cfg, generic_params(cfg), x, y, label=f"{seq * batch} tokens")
+    tr.close()
+
+
+@pytest.mark.parametrize("Kd,M", [(129, 64), (72, 64), (64, 63)])
+def test_grouped_products_refused(K, Kd, M):
     import torch
-    rng = np.random.default_rng(T)
-    shapes = [(64, 192), (192, 64), (64, 64), (320, 128)]
-    As = [rnd(rng, (T, m), 1) for m, _ in shapes]
-    Bs = [rnd(rng, (T, n), 1) for _, n in shapes]
-    ws = zeros(2 * 256 * 256 * 256)
-    Cs = [zeros(m, n) for m, n in shapes]
-    K.lpk_gemm_grouped([dev(a, 1) for a in As], [dev(b, 1) for b in Bs], Cs, [m for m, _ in shapes], [n for _, n in shapes],
-                       T, 0, 0, 0, ws)
-    for a, b, c in zip(As, Bs, Cs):
-        assert relerr(host(c), a.astype(np.float64).T @ b.astype(np.float64)) <= 2e-6
+    a = torch.zeros(256, 256, device="cuda", dtype=torch.bfloat16)
+    o = torch.zeros(64, 64, device="cuda", dtype=torch.float32)
+    with pytest.raises(RuntimeError):
+        K.lpk_gemm_grouped([a, a], [a, a], [o, o], [M, M], [64, 64], Kd, 1, 1, 0, zeros(1 << 25))
 
 
 @pytest.mark.parametrize("vocab", [1001, 1024, 1087, 515])
