@@ -14,6 +14,7 @@ hipError_t op_reduce_partials(const OpCtx& c, const float* partial, int nblk, in
 namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 struct StemShape {
   int H, W, C, O;      // image, channels in and out
@@ -41,7 +42,8 @@ __device__ __forceinline__ void load_band(bf16_t* xs, const bf16_t* __restrict__
 
 // Forward.  Block: a band of RB image rows; a wave takes every fourth run of 32 output pixels and 64 output channels
 // at a time (blockIdx.y).  Weights sit in registers (k past the taps is zero), a pixel's 27 taps are read from the
-// band, results leave through a 4 KB patch as whole lines.  STATS (bands of equal size, whole runs, the same number
+// band (its slots past the taps are cleared too: an infinite pixel against a zero weight would be a NaN), results leave
+// through a 4 KB patch as whole lines.  STATS (bands of equal size, whole runs, the same number
 // per wave): the column sums the normalisation needs, per band (see ConvStats).
 template <bool STATS>
 __global__ void __launch_bounds__(256) k_stem_fwd(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
@@ -56,11 +58,13 @@ __global__ void __launch_bounds__(256) k_stem_fwd(const bf16_t* __restrict__ x, 
   const int li = lane & 31, hf = lane >> 5, K = 9 * s.C, n0 = blockIdx.y * 64;
   bf16x8 fw[2][2];
   int off[2][8];
+  u16x8 live[2];             // all ones for the slots that hold a tap
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int k = 16 * ks + 8 * hf + e, kk = k < K ? k : 0;
+      live[ks][e] = k < K ? 0xffff : 0;
       const int r = kk / (3 * s.C);
       off[ks][e] = r * s.LW * s.C + (kk - r * 3 * s.C);
 #pragma unroll
@@ -89,6 +93,7 @@ __global__ void __launch_bounds__(256) k_stem_fwd(const bf16_t* __restrict__ x, 
       bf16x8 fx;
 #pragma unroll
       for (int e = 0; e < 8; ++e) fx[e] = base[off[ks][e]];
+      fx = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u16x8, fx) & live[ks]);
 #pragma unroll
       for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[i][ks], fx, acc[i], 0, 0, 0);
     }
@@ -140,8 +145,8 @@ __global__ void __launch_bounds__(256) k_stem_fwd(const bf16_t* __restrict__ x, 
 }
 
 // Filter gradient: dw[o, j] = sum over pixels of dz[pixel, o] * x[pixel + tap j].  Block: a band of image rows and 64
-// output channels; the reduction index is the pixel, 16 at a time along an image row (a row is rounded up to 16, dz
-// zero there).  A wave takes every fourth run of 64 pixels: dz goes through a wave-private 8 KB LDS tile and is read
+// output channels; the reduction index is the pixel, 16 at a time along an image row (a row is rounded up to 16, a run to
+// four steps: both operands are zero there, because a real pixel's infinity against a zero of dz would be a NaN).  A wave takes every fourth run of 64 pixels: dz goes through a wave-private 8 KB LDS tile and is read
 // transposed (ds_read_b64_tr_b16), the next run's loads in flight meanwhile; the taps of 8 consecutive pixels are
 // eight 2-byte reads of the band.  The four waves' sums are added in order, the blocks' by k_reduce_partials.
 __global__ void __launch_bounds__(256) k_stem_wgrad(const bf16_t* __restrict__ dz, const bf16_t* __restrict__ x,
@@ -193,6 +198,12 @@ __global__ void __launch_bounds__(256) k_stem_wgrad(const bf16_t* __restrict__ d
       bf16x8 fx;
 #pragma unroll
       for (int e = 0; e < 8; ++e) fx[e] = xb[e * s.C];
+      const int left = t0 + u < steps ? s.W - (q - 8 * hf) : 0;      // pixels of the step inside the row (wave-uniform)
+      if (left < 16) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (8 * hf + e >= left) fx[e] = (bf16_t)0.f;
+      }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         // chunk c of pixel row k sits in slot c ^ ((k & 3) << 1): the four rows of a read fall on different banks

@@ -132,6 +132,36 @@ def test_stem_convolution(K, N, H, C, O):
     assert relerr(host(dw), 2 * rdw) <= 5e-6         # fp32 sums of exact products
 
 
+@pytest.mark.parametrize("N,H,C,O", [(2, 32, 3, 64), (3, 28, 1, 24), (5, 5, 3, 8), (2, 37, 2, 72), (1, 1, 1, 8)])
+def test_stem_convolution_infinities(K, N, H, C, O):
+    """An infinite pixel, in each corner and inside, is an infinity of the outputs and of the taps that it reaches and of
+    nothing else (weights and gradients positive, so that no product of it is NaN; the products that the border makes
+    are zeros times finite values)."""
+    import torch
+    rng = np.random.default_rng(N * H + C)
+    ws = zeros(1 << 22)
+    w, dout = np.abs(rnd(rng, (O, 3, 3, C), 1)) + 1, np.abs(rnd(rng, (N, H, H, O), 1)) + 1
+    for (h, q) in sorted({(0, 0), (0, H - 1), (H - 1, 0), (H - 1, H - 1), (H // 2, H // 2)}):
+        for c in range(C):
+            x = np.abs(rnd(rng, (N, H, H, C), 1)) + 1
+            x[N - 1, h, q, c] = np.inf
+            z = torch.zeros(N, H, H, O, device="cuda", dtype=torch.bfloat16)
+            K.lpk_conv_fwd(1, dev(x, 1), dev(w, 1), z, N, H, H, C, O, 3, 1, 1)
+            want = np.zeros((N, H, H, O), bool)
+            want[N - 1, max(h - 1, 0):h + 2, max(q - 1, 0):q + 2] = True
+            got = host(z)
+            assert not np.isnan(got).any() and (np.isinf(got) == want).all(), ("forward", h, q, c)
+            dw = zeros(O, 3, 3, C)
+            K.lpk_conv_bwd_weight_ws(1, dev(dout, 1), dev(x, 1), dw, N, H, H, C, O, 3, 1, 1, ws)
+            # tap (r, s) meets the pixel at output pixel (h + 1 - r, q + 1 - s)
+            want = np.zeros((O, 3, 3, C), bool)
+            for r in range(3):
+                for s in range(3):
+                    want[:, r, s, c] = 0 <= h + 1 - r < H and 0 <= q + 1 - s < H
+            got = host(dw)
+            assert not np.isnan(got).any() and (np.isinf(got) == want).all(), ("filter gradient", h, q, c)
+
+
 @pytest.mark.parametrize("rows,C", [(7, 8), (39200, 24), (1000, 48), (777, 96), (129, 1032), (300, 2048), (64, 200)])
 def test_batchnorm_any_channel_chunks(K, rows, C):
     """Channel counts whose 8-wide chunks do not divide a block, forward and backward."""
