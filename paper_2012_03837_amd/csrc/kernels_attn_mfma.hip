@@ -1,7 +1,7 @@
 // Causal multi-head attention on the CDNA4 matrix cores (bf16 operands, fp32 accumulation and
 // softmax), head sizes 16, 32 and 64, flash-style: the S x S score matrix lives only in registers.
-// (Head sizes 16 and 32 at 64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward
-// 149 + 287 us.  Here, DH = 16: 9.4 us, 11.5 + 9.4 us.  The head size only changes the number of 16-deep products of a
+// (64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward 149 + 287 us.  Here 7.3 us and
+// 19.5 us for both backward kernels.  The head size only changes the number of 16-deep products of a
 // score tile and of 32-row output tiles; a 16-wide head leaves half of its one output tile unused, which costs
 // nothing that counts, since the exponentials bound the kernels.)
 //
@@ -28,6 +28,7 @@ template <int DH> constexpr float kScale = DH == 64 ? 0.125f : (DH == 32 ? 0.176
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 
 __device__ __forceinline__ bf16x8 zero8() {
@@ -46,6 +47,14 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int kk) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16_t)a[8 * kk + e];
   return r;
+}
+// Is any of eight bf16 values infinite or NaN?
+__device__ __forceinline__ bool any_non_finite(const bf16x8& v) {
+  const u32x4 w = __builtin_bit_cast(u32x4, v);
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) bad = bad || (w[e] & 0x7f80u) == 0x7f80u || (w[e] & 0x7f800000u) == 0x7f800000u;
+  return bad;
 }
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
@@ -86,6 +95,12 @@ struct TileRegs {
       for (int i = 0; i < NCH; ++i) v[i] = *reinterpret_cast<const bf16x8*>(p + 8 * i);
     }
   }
+  // Narrow heads: tiles that hold an infinity or a NaN are marked in `bad` (see the tile loops).
+  __device__ __forceinline__ void mark(int* bad, int tile) const {
+    if constexpr (DH < 64) {
+      if (any_non_finite(v[0])) *bad = tile;
+    }
+  }
   template <int ALD>
   __device__ __forceinline__ void store(bf16_t (*dst)[ALD]) const {
     const int r = threadIdx.x / TPR, ch = (threadIdx.x % TPR) * 8 * NCH;
@@ -95,6 +110,27 @@ struct TileRegs {
     }
   }
 };
+
+// Narrow heads, tiles with an infinity or a NaN among the rows that P or dS multiplies (or in dS): the sums are then taken
+// row by row in fp32, masked rows left out.  In a matrix product a masked row's 0 times infinity would be a NaN in outputs
+// that such a row does not reach.
+// Score of tile row `row` with this lane column's vector: each half of the wave has eight of every sixteen elements.
+template <int NK>
+__device__ __forceinline__ float row_dot(const bf16x8 (&f)[NK], const bf16_t* row, int hf) {
+  float s = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = __builtin_fmaf((float)f[kk][e], (float)row[16 * kk + 8 * hf + e], s);
+  return s + __shfl_xor(s, 32, 64);
+}
+template <int ND>
+__device__ __forceinline__ void add_row(f32x16 (&acc)[ND], const bf16_t* row, float w, int hf) {
+#pragma unroll
+  for (int dh = 0; dh < ND; ++dh)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[dh][v] = __builtin_fmaf(w, (float)row[32 * dh + 8 * (v / 4) + 4 * hf + (v % 4)], acc[dh][v]);
+}
 
 // Work order.  The grid is one-dimensional: block L takes sequence block L / (B*H) (counted from the heavy end)
 // of head-and-batch index L % (B*H).  With causal masking the work of a 128-row block grows with its position
@@ -118,6 +154,7 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
                                                        float* __restrict__ lse, int S, int H, int BH, int causal) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
+  __shared__ int bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
@@ -141,12 +178,15 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
   TileRegs<DH> kr, vr;
   kr.load(base + d + h * DH, ld, 0, S);
   vr.load(base + 2 * d + h * DH, ld, 0, S);
+  if (DH < 64 && threadIdx.x == 0) bad = -1;
   for (int jt = 0; jt < n_tiles; ++jt) {
     const int k0 = jt * 64;
     __syncthreads();
     kr.store(Ks);
     vr.store(Vs);
+    vr.mark(&bad, jt);
     __syncthreads();
+    const bool slow = DH < 64 && bad == jt;
     if (jt + 1 < n_tiles) {      // the next key tile's loads fly during this tile's MFMAs
       kr.load(base + d + h * DH, ld, k0 + 64, S);
       vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
@@ -207,6 +247,15 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[dh][v] *= alpha;
     }
+    if (DH < 64 && slow) {        // key by key
+#pragma unroll 1
+      for (int r = 0; r < 64 && k0 + r < S; ++r) {
+        const float s = row_dot<NK>(qf, Ks[r], hf);
+        if (qi >= S || (causal && k0 + r > qi)) continue;
+        add_row(oacc, Vs[r], __builtin_amdgcn_exp2f(__builtin_fmaf(s, c, -mref)), hf);
+      }
+      continue;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -235,12 +284,13 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
 
 // ================================================================================= backward: dQ
 template <int DH>
-__global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+__global__ void __launch_bounds__(256, DH == 64 ? 2 : 3) k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                           const float* __restrict__ lse,
                                                           const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv,
                                                           float* __restrict__ delta, int S, int H, int BH, int causal) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
+  __shared__ int bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
@@ -280,12 +330,15 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
   TileRegs<DH> kr, vr;
   kr.load(base + d + h * DH, ld, 0, S);
   vr.load(base + 2 * d + h * DH, ld, 0, S);
+  if (DH < 64 && threadIdx.x == 0) bad = -1;
   for (int jt = 0; jt < n_tiles; ++jt) {
     const int k0 = jt * 64;
     __syncthreads();
     kr.store(Ks);
     vr.store(Vs);
+    kr.mark(&bad, jt);
     __syncthreads();
+    bool slow = DH < 64 && bad == jt;
     if (jt + 1 < n_tiles) {
       kr.load(base + d + h * DH, ld, k0 + 64, S);
       vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
@@ -324,6 +377,23 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
           st[i][v] = p * (dp[i][v] - D);        // the factor 1/sqrt(DH) of dS is applied once, to the finished dQ
         }
     }
+    if constexpr (DH < 64) {
+      float t = 0.f;             // NaN if any dS is not finite
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t = __builtin_fmaf(st[i][v], 0.f, t);
+      slow = slow || __builtin_amdgcn_ballot_w64(t != t) != 0;
+      if (slow) {                // key by key
+#pragma unroll 1
+        for (int r = 0; r < 64 && k0 + r < S; ++r) {
+          const float s = row_dot<NK>(qf, Ks[r], hf), dpr = row_dot<NK>(dof, Vs[r], hf);
+          if (qi >= S || (causal && k0 + r > qi)) continue;
+          add_row(dqa, Ks[r], __builtin_amdgcn_exp2f(s * c - lse2) * (dpr - D), hf);
+        }
+        continue;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -349,7 +419,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq_mfma(const bf16_t* __res
 
 // ================================================================================= backward: dK, dV
 template <int DH>
-__global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv,
+__global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv,
                                                            const float* __restrict__ lse,
                                                            const float* __restrict__ delta,
                                                            const bf16_t* __restrict__ dout,
@@ -358,6 +428,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
   __shared__ __attribute__((aligned(16))) bf16_t dOs[64][kAld<DH>];
   __shared__ __attribute__((aligned(16))) float lse2s[64];
   __shared__ __attribute__((aligned(16))) float deltas[64];
+  __shared__ int bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, false);
   const int bx = ab.x;
@@ -387,11 +458,14 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
   TileRegs<DH> qr, dor;
   qr.load(base + h * DH, ld, t_begin * 64, S);
   dor.load(dob + h * DH, (size_t)d, t_begin * 64, S);
+  if (DH < 64 && threadIdx.x == 0) bad = -1;
   for (int it = t_begin; it < t_end; ++it) {
     const int q0 = it * 64;
     __syncthreads();
     qr.store(Qs);
     dor.store(dOs);
+    qr.mark(&bad, it);
+    dor.mark(&bad, it);
     if (it + 1 < t_end) {
       qr.load(base + h * DH, ld, q0 + 64, S);
       dor.load(dob + h * DH, (size_t)d, q0 + 64, S);
@@ -433,6 +507,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
             p = masked ? 0.f : p;
             s[v] = p;
             dp[v] = p * (dp[v] - d4[j]);
+            if constexpr (DH < 64) dp[v] = masked ? 0.f : dp[v];      // also where dO or V is infinite
           }
         }
       } else {
@@ -447,6 +522,22 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv_mfma(const bf16_t* __re
             s[v] = p;
             dp[v] = p * (dp[v] - d4[j]);          // the factor 1/sqrt(DH) of dS is applied once, to the finished dK
           }
+        }
+      }
+      if constexpr (DH < 64) {
+        float t = 0.f;           // NaN if any P or dS is not finite (an infinite P makes its dS infinite or NaN)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t = __builtin_fmaf(dp[v], 0.f, t);
+        if (bad == it || __builtin_amdgcn_ballot_w64(t != t) != 0) {      // query by query
+#pragma unroll 1
+          for (int r = 32 * i; r < 32 * i + 32 && q0 + r < S; ++r) {
+            const float sr = row_dot<NK>(kf, Qs[r], hf), dpr = row_dot<NK>(vf, dOs[r], hf);
+            if (kj >= S || (causal && kj > q0 + r)) continue;
+            const float p = __builtin_amdgcn_exp2f(sr * c - lse2s[r]);
+            add_row(dva, dOs[r], p, hf);
+            add_row(dka, Qs[r], p * (dpr - deltas[r]), hf);
+          }
+          continue;
         }
       }
 #pragma unroll

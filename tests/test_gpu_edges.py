@@ -231,6 +231,37 @@ def test_attention_small_heads(K, S, dh, causal):
         assert np.linalg.norm(got - merge(ref)) <= 1.5e-2 * max(np.linalg.norm(ref), 0.1 * scale)
 
 
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dh", [16, 32])
+def test_attention_small_heads_non_finite(K, dh, causal):
+    """An infinity or a NaN in q, k, v or the output's gradient reaches the rows of the results that it reaches in the
+    row-by-row kernels and no others (a masked row's weight is left out, not multiplied by zero)."""
+    import torch
+    rng = np.random.default_rng(dh)
+    B, S, H = 1, 150, 2
+    d = H * dh
+    for what in (np.inf, -np.inf, np.nan):
+        for part in range(4):                   # q, k, v, dout
+            # (not key 0: a first score of -inf makes a NaN of the row-by-row kernel's running maximum)
+            for row in (5, 70, 149):
+                qkv, dout = rnd(rng, (S, 3 * d), 1), rnd(rng, (S, d), 1)
+                (dout if part == 3 else qkv)[row, (0 if part == 3 else part * d) + dh + 3] = what
+                seen = []
+                for plain in (0, 1):
+                    o = torch.zeros(S, d, device="cuda", dtype=torch.bfloat16)
+                    lse, delta = zeros(B, H, S), zeros(B, H, S)
+                    dqkv = torch.zeros(S, 3 * d, device="cuda", dtype=torch.bfloat16)
+                    K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal, plain=plain)
+                    K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal, plain=plain)
+                    seen.append([host(t) for t in (o, lse, dqkv)])
+                for name, a, b in zip(("o", "lse", "dqkv"), *seen):
+                    case = (what, "q k v dout".split()[part], row, name)
+                    assert (np.isfinite(a) == np.isfinite(b)).all(), case
+                    assert (np.isposinf(a) == np.isposinf(b)).all() and (np.isneginf(a) == np.isneginf(b)).all(), case
+                    ok = np.isfinite(b)
+                    assert np.abs(a[ok] - b[ok]).max(initial=0) <= 2.0 ** -6 * max(1.0, np.abs(b[ok]).max(initial=0)), case
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 @pytest.mark.parametrize("M,N,Kd", [(1, 1, 1), (16, 16, 16), (17, 33, 15), (128, 256, 257), (333, 520, 100), (1030, 1000, 70),
                                     (10, 256, 128), (300, 7, 1000)])
