@@ -1,7 +1,7 @@
 // Causal multi-head attention on the CDNA4 matrix cores (bf16 operands, fp32 accumulation and
 // softmax), head sizes 16, 32 and 64, flash-style: the S x S score matrix lives only in registers.
-// (64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward 149 + 287 us.  Here 7.3 us and
-// 19.5 us for both backward kernels.  The head size only changes the number of 16-deep products of a
+// (64 sequences of 128, 8 heads of 16, on the plain kernels: forward 112 us, backward 149 + 287 us.  Here 7.9 us and
+// 22.8 us for both backward kernels.  The head size only changes the number of 16-deep products of a
 // score tile and of 32-row output tiles; a 16-wide head leaves half of its one output tile unused, which costs
 // nothing that counts, since the exponentials bound the kernels.)
 //
@@ -11,6 +11,9 @@
 //   dQ      : S^T, dP^T[key, q] = V dO^T -> dS^T -> dQ^T[dh, q] += K^T dS^T
 //   dK, dV  : S[q, key] = Q K^T, dP[q, key] = dO V^T -> P, dS -> dV^T[dh, key] += dO^T P,
 //             dK^T[dh, key] += Q^T dS
+// P and dS of heads of 64 are rounded to bf16 for the second products; those of narrower heads stay in fp32 (split8).
+// Three matrix instructions instead of one there, measured over the rounded form: 64 sequences of 128, 8 heads of 16,
+// forward 7.1 -> 7.9 us, backward 18.7 -> 22.8 us; 4 of 2048, 8 heads of 32, 29.2 -> 46.2 us and 77 -> 122 us.
 // The accumulator layout of v_mfma_f32_32x32x16_bf16 (value v of lane l: row 8*(v/4) + 4*(l/32) + v%4,
 // column l%32) is exactly the B-operand layout of the next MFMA over the row index, so P and dS
 // never pass through LDS.  Operands whose reduction index is the slow one in memory (V for the
@@ -47,6 +50,36 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int kk) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16_t)a[8 * kk + e];
   return r;
+}
+// B-operand fragments of the same eight values.  Heads of 64 take one, rounded to bf16.  Narrower heads keep P and dS in
+// fp32: the three fragments are the value's top, middle and last eight bits (cut, not rounded), whose sum is the value, and
+// their products with the bf16 operand are exact, so that the sums are fp32 sums of exact products.
+template <int DH> constexpr int kParts = DH == 64 ? 1 : 3;
+template <int NP>
+__device__ __forceinline__ void split8(const f32x16& a, int kk, bf16x8 (&f)[NP]) {
+  if constexpr (NP == 1) {
+    f[0] = pack8(a, kk);
+  } else {
+    float r[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = a[8 * kk + e];
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)        // the upper halves of two values
+        w[e] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, r[2 * e + 1]), __builtin_bit_cast(unsigned, r[2 * e]), 0x07060302u);
+      f[s] = __builtin_bit_cast(bf16x8, w);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r[e] -= __builtin_bit_cast(float, __builtin_bit_cast(unsigned, r[e]) & 0xffff0000u);
+    }
+  }
+}
+template <int NP>
+__device__ __forceinline__ f32x16 mma_parts(const bf16x8& a, const bf16x8 (&f)[NP], f32x16 acc) {
+#pragma unroll
+  for (int s = NP - 1; s >= 0; --s) acc = MFMA32(a, f[s], acc);      // smallest first
+  return acc;
 }
 // Is any of eight bf16 values infinite or NaN?
 __device__ __forceinline__ bool any_non_finite(const bf16x8& v) {
@@ -112,8 +145,8 @@ struct TileRegs {
 };
 
 // Narrow heads, tiles with an infinity or a NaN among the rows that P or dS multiplies (or in dS): the sums are then taken
-// row by row in fp32, masked rows left out.  In a matrix product a masked row's 0 times infinity would be a NaN in outputs
-// that such a row does not reach.
+// row by row in fp32, masked rows left out.  In a matrix product a masked row's 0 times infinity, and a zero part of a split
+// value times infinity, would be a NaN in outputs that such a row does not reach.
 // Score of tile row `row` with this lane column's vector: each half of the wave has eight of every sixteen elements.
 template <int NK>
 __device__ __forceinline__ float row_dot(const bf16x8 (&f)[NK], const bf16_t* row, int hf) {
@@ -260,9 +293,10 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 pf = pack8(st[i], kk);
+        bf16x8 pf[kParts<DH>];
+        split8(st[i], kk, pf);
 #pragma unroll
-        for (int dh = 0; dh < ND; ++dh) oacc[dh] = MFMA32(frag_tr(Vs, 32 * i + 16 * kk, 32 * dh, lane), pf, oacc[dh]);
+        for (int dh = 0; dh < ND; ++dh) oacc[dh] = mma_parts(frag_tr(Vs, 32 * i + 16 * kk, 32 * dh, lane), pf, oacc[dh]);
       }
   }
   float lt = l + __shfl_xor(l, 32, 64);
@@ -398,9 +432,10 @@ __global__ void __launch_bounds__(256, DH == 64 ? 2 : 3) k_attn_bwd_dq_mfma(cons
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 dsf = pack8(st[i], kk);
+        bf16x8 dsf[kParts<DH>];
+        split8(st[i], kk, dsf);
 #pragma unroll
-        for (int dh = 0; dh < ND; ++dh) dqa[dh] = MFMA32(frag_tr(Ks, 32 * i + 16 * kk, 32 * dh, lane), dsf, dqa[dh]);
+        for (int dh = 0; dh < ND; ++dh) dqa[dh] = mma_parts(frag_tr(Ks, 32 * i + 16 * kk, 32 * dh, lane), dsf, dqa[dh]);
       }
   }
   if (qi < S) {
@@ -542,11 +577,13 @@ __global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(con
       }
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 pf = pack8(s, kk), dsf = pack8(dp, kk);
+        bf16x8 pf[kParts<DH>], dsf[kParts<DH>];
+        split8(s, kk, pf);
+        split8(dp, kk, dsf);
 #pragma unroll
         for (int dh = 0; dh < ND; ++dh) {
-          dva[dh] = MFMA32(frag_tr(dOs, 32 * i + 16 * kk, 32 * dh, lane), pf, dva[dh]);
-          dka[dh] = MFMA32(frag_tr(Qs, 32 * i + 16 * kk, 32 * dh, lane), dsf, dka[dh]);
+          dva[dh] = mma_parts(frag_tr(dOs, 32 * i + 16 * kk, 32 * dh, lane), pf, dva[dh]);
+          dka[dh] = mma_parts(frag_tr(Qs, 32 * i + 16 * kk, 32 * dh, lane), dsf, dka[dh]);
         }
       }
     }

@@ -233,6 +233,38 @@ def test_attention_small_heads(K, S, dh, causal):
 
 @pytest.mark.parametrize("causal", [1, 0])
 @pytest.mark.parametrize("dh", [16, 32])
+@pytest.mark.parametrize("S", [64, 200])
+def test_attention_small_heads_fp32_probabilities(K, S, dh, causal):
+    """P and dS of heads of 16 and 32 stay in fp32: what is left against float64 is one rounding of the result to bf16
+    (a P or dS rounded to bf16 adds as much again, a factor of 1.4; the 5 % are for fp32 sums next to a rounding edge)."""
+    import torch
+    rng = np.random.default_rng(S + dh)
+    B, H = 2, 5
+    d = H * dh
+    qkv, dout = rnd(rng, (B * S, 3 * d), 1), rnd(rng, (B * S, d), 1)
+    o = torch.zeros(B * S, d, device="cuda", dtype=torch.bfloat16)
+    lse, delta = zeros(B, H, S), zeros(B, H, S)
+    dqkv = torch.zeros(B * S, 3 * d, device="cuda", dtype=torch.bfloat16)
+    K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal)
+    K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal)
+    split = lambda t: t.reshape(B, S, H, dh).transpose(0, 2, 1, 3)
+    merge = lambda t: t.transpose(0, 2, 1, 3).reshape(B * S, d)
+    q64 = qkv.astype(np.float64)
+    q, k, v, g = split(q64[:, :d]), split(q64[:, d:2 * d]), split(q64[:, 2 * d:]), split(dout.astype(np.float64))
+    ro, p = ops.attention_fwd(q, k, v, causal=bool(causal))
+    # the backward pass takes the stored output, rounded as it is
+    D = (g * split(host(o))).sum(-1, keepdims=True)
+    ds = p * (g @ np.swapaxes(v, -1, -2) - D) / np.sqrt(dh)
+    got = host(dqkv)
+    for name, a, ref in (("o", host(o), ro), ("dq", got[:, :d], ds @ k), ("dk", got[:, d:2 * d], np.swapaxes(ds, -1, -2) @ q),
+                         ("dv", got[:, 2 * d:], np.swapaxes(p, -1, -2) @ g)):
+        ref = merge(ref)
+        rounding = relerr(ops.bf16_round(ref.astype(np.float32)), ref)
+        assert relerr(a, ref) <= 1.05 * rounding, (name, relerr(a, ref), rounding)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dh", [16, 32])
 def test_attention_small_heads_non_finite(K, dh, causal):
     """An infinity or a NaN in q, k, v or the output's gradient reaches the rows of the results that it reaches in the
     row-by-row kernels and no others (a masked row's weight is left out, not multiplied by zero)."""
