@@ -130,7 +130,10 @@ int lpk_conv_bn_fwd(int dtype, const void* x, const void* w, void* z, const floa
                     void* y, float* mean, float* rstd, int N, int H, int W, int C, int O, int R, int stride, int pad,
                     int relu, float* scratch_dev, size_t scratch_elems, void* stream);
 
-/* BatchNorm with batch statistics over rows = N*H*W, fused residual add and ReLU. */
+/* BatchNorm with batch statistics over rows = N*H*W, fused residual add and ReLU.  scratch_dev: S * C floats forward
+ * (2 * S * C where C / 8 is whole and divides 256, bf16), (2 * S + 2) * C backward, S = ceil(rows / 1024); in the bf16
+ * case just named S = ceil(rows / max(ceil(rows / 1024), 8 * (256 / (C / 8)))).  (2*1024 + 2) * C floats always do
+ * for at most 2^20 rows; more than needed lets more of the chip work. */
 int lpk_batchnorm_fwd(int dtype, const void* z, const float* g, const float* b, const void* res, void* y,
                       float* mean, float* rstd, int rows, int C, int relu, float* scratch_dev, size_t scratch_elems,
                       void* stream);

@@ -207,6 +207,8 @@ hipError_t op_conv_bwd_data(const OpCtx& c, const ConvArgs& a, const void* dout,
                             const void* add = nullptr);
 hipError_t op_conv_bwd_weight(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
                               int accumulate);
+// bf16 batch normalisation: do the channel count's 8-wide chunks fill whole 256-thread rows (C % 8 == 0)?
+static inline bool bn_shifted(int C) { return C >= 8 && 256 % (C / 8) == 0; }
 // Running statistics of one batch normalisation (the evaluation form of the method appendix B.3 cites).
 // use == 0: the forward pass normalises with the batch's statistics and folds them in,
 //   mean <- (1 - momentum) mean + momentum mean_B,  var <- (1 - momentum) var + momentum var_B rows / (rows - 1);

@@ -538,12 +538,24 @@ __global__ void __launch_bounds__(256) k_bn_bwd_apply_v(const bf16_t* __restrict
   }
 }
 
-int bn_slab(int rows, int C) {
+// Rows per slab, given how many slabs the workspace holds.
+int bn_slab(int rows, int C, size_t room) {
   int RL = 256 / (C / 8);
   int slab = (rows + 1023) / 1024;         // aim at about a thousand blocks
   int min_slab = RL * 4;                   // four rows in flight per thread
   if (slab < min_slab) slab = min_slab;
+  if (room < (size_t)(rows + slab - 1) / slab) slab = (int)((rows + room - 1) / room);
   return slab;
+}
+// Slabs whose sums a caller's workspace has to hold, however the rows are cut here: slabs of eight rows per thread, or of the
+// generic kernels' 1024 rows for the channel counts that are not bn_shifted.
+size_t bn_least_slabs(int rows, int C) {
+  int slab = 1024;
+  if (bn_shifted(C)) {
+    slab = (rows + 1023) / 1024;
+    if (slab < 256 / (C / 8) * 8) slab = 256 / (C / 8) * 8;
+  }
+  return ((size_t)rows + slab - 1) / slab;
 }
 int blocks_for(size_t n) { size_t b = (n + 255) / 256; return (int)(b < 16384 ? b : 16384); }
 
@@ -553,11 +565,8 @@ bool bn_fast_ok(const OpCtx& c, int rows, int C, const void* a, const void* b, c
   if (c.dt != BF16 || C % 8 || C < 8 || C > 2048 || rows < 1) return false;
   return al16(a) && al16(b) && (!cc || al16(cc)) && (!d || al16(d));
 }
-size_t bn_fast_scratch(int rows, int C) {
-  int slab = bn_slab(rows, C);
-  size_t nslab = (rows + slab - 1) / slab;
-  return (2 * nslab + 2) * (size_t)C;
-}
+// Does the workspace hold a slab's forward sums?  Where the generic kernels need less (one sum per slab at a time), they run.
+bool bn_fwd_room(const OpCtx& c, int C) { return bn_shifted(C) || c.partial_elems >= (size_t)2 * C; }
 hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const float* b, const void* res, void* y,
                        float* mean, float* rstd, int rows, int C, int relu, const BnRunning* run, const ConvStats* pre) {
   const bool given = run && run->use;   // mean / rstd already hold the statistics to normalise with
@@ -567,8 +576,8 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
         pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, run ? run->mean : nullptr, run ? run->var : nullptr,
         run ? run->momentum : 0.f);
   } else if (!given) {
-    const int slab = bn_slab(rows, C), nslab = (rows + slab - 1) / slab;
-    if ((size_t)2 * nslab * C > c.partial_elems) return hipErrorInvalidValue;
+    if ((bn_shifted(C) ? 2 : 1) * bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
+    const int slab = bn_slab(rows, C, c.partial_elems / ((size_t)2 * C)), nslab = (rows + slab - 1) / slab;
     const int RL = 256 / (C / 8);
     const size_t shm = (size_t)2 * RL * C * sizeof(float);
     k_bn_partial_v<0><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, (const bf16_t*)z, nullptr, nullptr,
@@ -585,8 +594,8 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
 hipError_t bn_bwd_fast(const OpCtx& c, const void* dy, const void* y, const void* z, const float* mean,
                        const float* rstd, const float* g, void* dz, void* dres, float* dg, float* db, int rows, int C,
                        int relu, int accumulate) {
-  const int slab = bn_slab(rows, C), nslab = (rows + slab - 1) / slab;
-  if ((size_t)(2 * nslab + 2) * C > c.partial_elems) return hipErrorInvalidValue;
+  if ((2 * bn_least_slabs(rows, C) + 2) * C > c.partial_elems) return hipErrorInvalidValue;
+  const int slab = bn_slab(rows, C, c.partial_elems / ((size_t)2 * C) - 1), nslab = (rows + slab - 1) / slab;
   float* sums = c.partial + (size_t)2 * nslab * C;
   const int RL = 256 / (C / 8);
   const size_t shm = (size_t)2 * RL * C * sizeof(float);

@@ -188,6 +188,32 @@ def test_batchnorm_any_channel_chunks(K, rows, C):
     assert relerr(host(dz), rdz) <= 4e-3 and relerr(host(dres), d) == 0
 
 
+@pytest.mark.parametrize("rows,C", [(39200, 24), (1000, 48), (5000, 1032), (4096, 64), (300, 2048), (3, 8), (70000, 8)])
+def test_batchnorm_least_workspace(K, rows, C):
+    """The smallest workspace that the interface names gives the results of an ample one; a float less is refused."""
+    import torch
+    rng = np.random.default_rng(rows + C)
+    z, dy = dev(rnd(rng, (rows, C), 1), 1), dev(rnd(rng, (rows, C), 1), 1)
+    g, b = dev(rng.standard_normal(C).astype(np.float32), 0), zeros(C)
+    shifted = 256 % (C // 8) == 0
+    slab = max(-(-rows // 1024), 8 * (256 // (C // 8))) if shifted else 1024
+    S = -(-rows // slab)
+    fwd, bwd = (2 if shifted else 1) * S * C, (2 * S + 2) * C
+    seen = []
+    for n_fwd, n_bwd in ((fwd, bwd), ((2 * 1024 + 2) * C, (2 * 1024 + 2) * C)):
+        y = torch.zeros(rows, C, device="cuda", dtype=torch.bfloat16)
+        mean, rstd, dz, dg, db = zeros(C), zeros(C), torch.zeros_like(y), zeros(C), zeros(C)
+        K.lpk_batchnorm_fwd(1, z, g, b, None, y, mean, rstd, rows, C, 1, zeros(n_fwd))
+        K.lpk_batchnorm_bwd(1, dy, y, z, mean, rstd, g, dz, None, dg, db, rows, C, 1, 0, zeros(n_bwd))
+        seen.append([host(t) for t in (mean, rstd, dg, db)])
+    for a, ref in zip(*seen):                  # fp32 sums cut differently
+        assert np.abs(a - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+    with pytest.raises(RuntimeError):
+        K.lpk_batchnorm_fwd(1, z, g, b, None, y, mean, rstd, rows, C, 1, zeros(fwd - 1))
+    with pytest.raises(RuntimeError):
+        K.lpk_batchnorm_bwd(1, dy, y, z, mean, rstd, g, dz, None, dg, db, rows, C, 1, 0, zeros(bwd - 1))
+
+
 def test_resnet_step_off_tile_channels(K):
     """A step of a two-stage network whose channel counts fit no tile (pooling, normalisation, stem, convolutions)."""
     import paper_2012_03837_amd as lp
