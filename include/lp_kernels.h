@@ -123,7 +123,7 @@ int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x, float* dw
 
 /* One convolution + normalisation unit of a ResNet stage, forward (appendix B.3): z = conv(x, w) as lpk_conv_fwd,
  * then y = [relu](bn(z) (+ res)) as lpk_batchnorm_fwd, with z, y, mean, rstd all written.  Where the convolution's
- * output is whole tiles of the matrix-core kernel, the convolution itself leaves the per-channel sums of its rounded
+ * output is whole tiles of the matrix-core kernel and O / 8 divides 256, the convolution itself leaves the per-channel sums of its rounded
  * outputs in scratch_dev and the normalisation does not read z for its statistics; otherwise the two run as the
  * separate calls would.  scratch_dev: at least max(3 * (N*P*Q/32 + O), (2*1024 + 2) * O) floats. */
 int lpk_conv_bn_fwd(int dtype, const void* x, const void* w, void* z, const float* g, const float* b, const void* res,

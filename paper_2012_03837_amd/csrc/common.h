@@ -195,6 +195,9 @@ hipError_t op_init_normal(const OpCtx& c, float* p, size_t n, float std, uint64_
 // behind it: for slab t of slab_rows consecutive rows and column j, p = the slab's first row, s0 = sum (z - p),
 // s1 = sum (z - p)^2 over the rounded outputs, stored as buf[(0 * nslab + t) * C + j], [(1 * nslab + t) ...] and
 // [(2 * nslab + t) ...].  The caller sets buf / cap (floats); nslab stays 0 if the launch did not produce them.
+// Used where the normalisation's own statistics are shifted sums as well (bn_shifted: whole 256-thread rows of 8-channel
+// chunks, C % 8 == 0); for other channel counts it takes fp64 sums over z, and the convolution leaves none.
+static inline bool bn_shifted(int C) { return C >= 8 && 256 % (C / 8) == 0; }
 struct ConvStats {
   float* buf = nullptr;
   size_t cap = 0;
@@ -207,8 +210,6 @@ hipError_t op_conv_bwd_data(const OpCtx& c, const ConvArgs& a, const void* dout,
                             const void* add = nullptr);
 hipError_t op_conv_bwd_weight(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
                               int accumulate);
-// bf16 batch normalisation: do the channel count's 8-wide chunks fill whole 256-thread rows (C % 8 == 0)?
-static inline bool bn_shifted(int C) { return C >= 8 && 256 % (C / 8) == 0; }
 // Running statistics of one batch normalisation (the evaluation form of the method appendix B.3 cites).
 // use == 0: the forward pass normalises with the batch's statistics and folds them in,
 //   mean <- (1 - momentum) mean + momentum mean_B,  var <- (1 - momentum) var + momentum var_B rows / (rows - 1);

@@ -54,6 +54,7 @@ hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const flo
 hipError_t op_conv_fwd(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* stats) {
   ProfScope prof_(c, KC_CONV, 2.0 * a.N * a.P * a.Q * a.O * a.R * a.S * a.C);
   if (stats) { stats->nslab = 0; stats->slab_rows = 0; }
+  if (!bn_shifted(a.O)) stats = nullptr;
   if (!plain_conv() && conv_mfma_ok(c, a, x, w, out)) return conv_fwd_mfma(c, a, x, w, out, stats);
   if (!plain_conv() && conv_stem_ok(c, a, out, out)) return conv_stem_fwd(c, a, x, w, out, stats);
   return conv_fwd_plain(c, a, x, w, out);

@@ -3,6 +3,7 @@
 //   LayerNorm forward / backward : rows of up to 1024 elements, one wavefront per row
 //   softmax cross-entropy        : rows of up to 32768 logits, one 256-thread block per row
 // Shapes outside these limits (or unaligned) use the generic kernels.
+#include <type_traits>
 #include "common.h"
 
 namespace lp {
@@ -296,36 +297,44 @@ hipError_t ce_fast(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float*
 // BatchNorm over [rows, C] bf16 with C % 8 == 0: 16 bytes (8 channels) per lane.
 //   statistics : one pass; per-channel sums of (x - p) and (x - p)^2 with the pivot p = the channel's
 //                value in row 0 (a sample of the distribution, so the shifted variance formula
-//                S2/n - (S1/n)^2 does not cancel), per-slab partials, ordered reduction
+//                S2/n - (S1/n)^2 does not cancel), per-slab partials, ordered reduction.  Channel counts whose
+//                chunks do not divide 256 (see bn_shifted): sums of x and x^2 in fp64 instead
 //   apply      : y = [relu]((z - mean) * rstd * g + b (+ res))
 //   backward   : per-slab partial sums of dy_eff and dy_eff * xhat, then
 //                dz = g * rstd * (dy_eff - mean(dy_eff) - xhat * mean(dy_eff * xhat)), dres = dy_eff
 // Block = (C/8) channel chunks x floor(256 / (C/8)) row lanes (the threads left over idle: 1 of 256 at 24 channels,
 // at worst 127 at 1032); any C % 8 == 0 up to 2048.  Channel counts whose chunks do not divide 256 (24, 48, 96, ...)
-// ran on the generic two-pass kernels before: 39200 x 24, statistics of the backward pass 156 us with two bytes per
-// lane and 39 blocks, 5.2 us here.
+// ran on the generic two-pass kernels before, whose variance is a sum of squares around the mean: with row 0 far from
+// the mean the shifted formula would lose bits against that (row 0 at 300 standard deviations of 39200 rows: 1e-3 of
+// the variance), sums in fp64 lose none (the square of a bf16 value is exact, 2^-53 times mean^2 / variance is below
+// fp32's rounding for any bf16 column).  39200 x 24, statistics of the backward pass 156 us with two bytes per lane and
+// 39 blocks, 5.2 us here.
 namespace lp {
 namespace {
 
 constexpr float kBnEpsV = 1e-5f;
 
 // MODE 0: s0 = sum (z - p), s1 = sum (z - p)^2.   MODE 1: s0 = sum dy_eff, s1 = sum dy_eff * xhat.
+// MODE 2: s0 = sum z, s1 = sum z^2 in fp64, left as two floats each ([4][nslab][C]: s0, s1, what they lack).
 template <int MODE>
 __global__ void __launch_bounds__(256) k_bn_partial_v(const bf16_t* __restrict__ a, const bf16_t* __restrict__ yrelu,
                                                       const bf16_t* __restrict__ z, const float* __restrict__ mean,
                                                       const float* __restrict__ rstd, float* __restrict__ partial,
                                                       int rows, int C, int slab, int relu) {
-  extern __shared__ float sh[];        // [2][RL][C]
+  typedef typename std::conditional<MODE == 2, double, float>::type acc_t;
+  extern __shared__ __attribute__((aligned(16))) char sh_bytes[];
+  acc_t* sh = reinterpret_cast<acc_t*>(sh_bytes);        // [2][RL][C]
   const int cpr = C >> 3, RL = 256 / cpr;
   const int cc = threadIdx.x % cpr, rl = threadIdx.x / cpr;
   const int r0 = blockIdx.x * slab;
   const int r1 = r0 + slab < rows ? r0 + slab : rows;
-  float s0[8], s1[8], p[8], q[8];
+  acc_t s0[8], s1[8];
+  float p[8], q[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { s0[e] = 0.f; s1[e] = 0.f; }
+  for (int e = 0; e < 8; ++e) { s0[e] = 0; s1[e] = 0; }
   if (rl < RL) {
     if (MODE == 0) load8(z + 8 * cc, p);                      // pivot: row 0
-    else { loadf8(mean + 8 * cc, p); loadf8(rstd + 8 * cc, q); }
+    else if (MODE == 1) { loadf8(mean + 8 * cc, p); loadf8(rstd + 8 * cc, q); }
     // four rows' loads in flight per thread (twelve 16-byte loads in the backward pass)
     for (int r = r0 + rl; r < r1; r += 4 * RL) {
       bf16x8 av[4], zv[4], yv[4];
@@ -346,6 +355,7 @@ __global__ void __launch_bounds__(256) k_bn_partial_v(const bf16_t* __restrict__
         for (int e = 0; e < 8; ++e) {
           float v = (float)av[u][e];
           if (MODE == 0) { const float t = v - p[e]; s0[e] += t; s1[e] += t * t; }
+          else if (MODE == 2) { const acc_t t = v; s0[e] += t; s1[e] += t * t; }
           else {
             if (relu) v = (float)yv[u][e] > 0.f ? v : 0.f;
             s0[e] += v; s1[e] += v * ((float)zv[u][e] - p[e]) * q[e];
@@ -362,10 +372,15 @@ __global__ void __launch_bounds__(256) k_bn_partial_v(const bf16_t* __restrict__
   __syncthreads();
   const int nslab = gridDim.x;
   for (int j = threadIdx.x; j < C; j += 256) {
-    float t0 = 0.f, t1 = 0.f;
+    acc_t t0 = 0, t1 = 0;
     for (int r = 0; r < RL; ++r) { t0 += sh[(size_t)r * C + j]; t1 += sh[(size_t)(RL + r) * C + j]; }
-    partial[(size_t)blockIdx.x * C + j] = t0;
-    partial[(size_t)(nslab + blockIdx.x) * C + j] = t1;
+    partial[(size_t)blockIdx.x * C + j] = (float)t0;
+    partial[(size_t)(nslab + blockIdx.x) * C + j] = (float)t1;
+    if (MODE == 2) {          // nothing where the float is infinite already
+      const acc_t l0 = t0 - (acc_t)(float)t0, l1 = t1 - (acc_t)(float)t1;
+      partial[(size_t)(2 * nslab + blockIdx.x) * C + j] = __builtin_isfinite((float)t0) ? (float)l0 : 0.f;
+      partial[(size_t)(3 * nslab + blockIdx.x) * C + j] = __builtin_isfinite((float)t1) ? (float)l1 : 0.f;
+    }
   }
 }
 // Adds the slab partials in order (64 channels x 16 slab groups per block: group q adds slabs q, q+16, ...
@@ -425,6 +440,49 @@ k_bn_finish_v(const float* __restrict__ partial, int nslab, int C, int rows, con
       aux0[j] = auxf != 0.f ? aux0[j] + a : a;
       aux1[j] = auxf != 0.f ? aux1[j] + b : b;
     }
+  }
+}
+// Forward statistics from the fp64 sums of k_bn_partial_v<2>, in the same order.  A variance of NaN (an infinity in the
+// column) stays one.
+__global__ void __launch_bounds__(64 * kBnFinishGroups)
+k_bn_finish_wide(const float* __restrict__ partial, int nslab, int C, int rows, float* __restrict__ mean,
+                 float* __restrict__ rstd, float* __restrict__ run_mean, float* __restrict__ run_var, float mom) {
+  __shared__ double sh[2][kBnFinishGroups][64];
+  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + lc;
+  double a = 0, b = 0;
+  if (j < C) {
+    const size_t part = (size_t)nslab * C;
+    for (int s = q; s < nslab; s += 4 * kBnFinishGroups) {      // sixteen loads in flight
+      float v[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int su = s + u * kBnFinishGroups < nslab ? s + u * kBnFinishGroups : s;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[u][k] = partial[k * part + (size_t)su * C + j];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (s + u * kBnFinishGroups >= nslab) break;
+        a += (double)v[u][0] + (double)v[u][2];
+        b += (double)v[u][1] + (double)v[u][3];
+      }
+    }
+  }
+  sh[0][q][lc] = a; sh[1][q][lc] = b;
+  __syncthreads();
+  if (q != 0 || j >= C) return;
+  a = 0; b = 0;
+#pragma unroll
+  for (int g = 0; g < kBnFinishGroups; ++g) { a += sh[0][g][lc]; b += sh[1][g][lc]; }
+  const double m1 = a / rows, v1 = b / rows - m1 * m1;
+  const float mu = (float)m1, var = v1 < 0 ? 0.f : (float)v1;
+  mean[j] = mu;
+  rstd[j] = rsqrtf(var + kBnEpsV);
+  if (run_mean) {   // running statistics take the unbiased batch variance
+    const float unb = rows > 1 ? var * ((float)rows / (float)(rows - 1)) : var;
+    run_mean[j] = (1.f - mom) * run_mean[j] + mom * mu;
+    run_var[j] = (1.f - mom) * run_var[j] + mom * unb;
   }
 }
 // Forward statistics from the per-slab sums the convolution kernel left (ConvStats: slab t has its own pivot p_t, the
@@ -566,25 +624,35 @@ bool bn_fast_ok(const OpCtx& c, int rows, int C, const void* a, const void* b, c
   return al16(a) && al16(b) && (!cc || al16(cc)) && (!d || al16(d));
 }
 // Does the workspace hold a slab's forward sums?  Where the generic kernels need less (one sum per slab at a time), they run.
-bool bn_fwd_room(const OpCtx& c, int C) { return bn_shifted(C) || c.partial_elems >= (size_t)2 * C; }
+bool bn_fwd_room(const OpCtx& c, int C) { return bn_shifted(C) || c.partial_elems >= (size_t)4 * C; }
 hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const float* b, const void* res, void* y,
                        float* mean, float* rstd, int rows, int C, int relu, const BnRunning* run, const ConvStats* pre) {
   const bool given = run && run->use;   // mean / rstd already hold the statistics to normalise with
+  float* rm = run ? run->mean : nullptr;
+  float* rv = run ? run->var : nullptr;
+  const float mom = run ? run->momentum : 0.f;
   if (!given && pre && pre->nslab > 0 && (size_t)pre->nslab * pre->slab_rows == (size_t)rows) {
     // the convolution in front left the per-slab sums: no pass over z for the statistics
     k_bn_finish_slabs<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(
-        pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, run ? run->mean : nullptr, run ? run->var : nullptr,
-        run ? run->momentum : 0.f);
+        pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, rm, rv, mom);
+  } else if (!given && !bn_shifted(C)) {
+    if (bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
+    // at most a slab per compute unit: two blocks add up all of 65536 x 96's sums, 13.7 us with 512 slabs, 7.3 us with 256
+    const size_t room = c.partial_elems / ((size_t)4 * C);
+    const int slab = bn_slab(rows, C, room < 256 ? room : 256), nslab = (rows + slab - 1) / slab;
+    const size_t shm = (size_t)2 * (256 / (C / 8)) * C * sizeof(double);
+    k_bn_partial_v<2><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, nullptr, nullptr, nullptr, c.partial, rows, C,
+                                                     slab, 0);
+    k_bn_finish_wide<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(c.partial, nslab, C, rows, mean, rstd, rm, rv, mom);
   } else if (!given) {
-    if ((bn_shifted(C) ? 2 : 1) * bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
+    if (2 * bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
     const int slab = bn_slab(rows, C, c.partial_elems / ((size_t)2 * C)), nslab = (rows + slab - 1) / slab;
     const int RL = 256 / (C / 8);
     const size_t shm = (size_t)2 * RL * C * sizeof(float);
     k_bn_partial_v<0><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, (const bf16_t*)z, nullptr, nullptr,
                                                      c.partial, rows, C, slab, 0);
     k_bn_finish_v<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(
-        c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, run ? run->mean : nullptr,
-        run ? run->var : nullptr, run ? run->momentum : 0.f);
+        c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
   }
   const size_t nch = (size_t)rows * C / 8;
   k_bn_apply_v<<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)z, g, b, (const bf16_t*)res, (bf16_t*)y, mean, rstd,

@@ -188,6 +188,57 @@ def test_batchnorm_any_channel_chunks(K, rows, C):
     assert relerr(host(dz), rdz) <= 4e-3 and relerr(host(dres), d) == 0
 
 
+@pytest.mark.parametrize("rows,C", [(39200, 24), (12000, 96), (3000, 1032)])
+@pytest.mark.parametrize("far", ["row 0", "mean"])
+def test_batchnorm_variance_keeps_its_bits(K, rows, C, far):
+    """Channel counts whose chunks do not divide a block: a first row far from the mean, or a mean far from zero, costs the
+    variance nothing (fp64 sums, then fp32 roundings of the variance, of the added epsilon and of the root: 2e-7 each)."""
+    import torch
+    rng = np.random.default_rng(rows + C)
+    z = rnd(rng, (rows, C), 1)
+    if far == "row 0":
+        z[0] = 300.0
+    else:
+        z = ops.bf16_round(z + 100).astype(np.float32)
+    y, mean, rstd = torch.zeros(rows, C, device="cuda", dtype=torch.bfloat16), zeros(C), zeros(C)
+    K.lpk_batchnorm_fwd(1, dev(z, 1), dev(np.ones(C, np.float32), 0), zeros(C), None, y, mean, rstd, rows, C, 0,
+                        zeros((2 * 1024 + 2) * C))
+    z64 = z.astype(np.float64)
+    want = 1 / np.sqrt(z64.var(0) + 1e-5)
+    assert np.abs(host(rstd) / want - 1).max() <= 6e-7
+    assert np.abs(host(mean) - z64.mean(0)).max() <= 2e-7 * np.abs(z64.mean(0)).max()
+
+
+@pytest.mark.parametrize("C,O,H", [(3, 24, 32), (1, 96, 32), (64, 384, 16)])
+def test_conv_bn_variance_keeps_its_bits(K, C, O, H):
+    """The same behind a convolution, with an image whose left column is far from the rest."""
+    import torch
+    rng = np.random.default_rng(C + O)
+    N = 4
+    x, w = rnd(rng, (N, H, H, C), 1), rnd(rng, (O, 3, 3, C), 1, 0.3)
+    x[:, :, 0] = 256.0
+    z = torch.zeros(N, H, H, O, device="cuda", dtype=torch.bfloat16)
+    y, mean, rstd = torch.zeros_like(z), zeros(O), zeros(O)
+    K.lpk_conv_bn_fwd(1, dev(x, 1), dev(w, 1), z, dev(np.ones(O, np.float32), 0), zeros(O), None, y, mean, rstd, N, H, H, C, O, 3, 1,
+                      1, 0, zeros((2 * 1024 + 2) * O + 3 * N * H * H))
+    want = 1 / np.sqrt(host(z).reshape(-1, O).var(0) + 1e-5)
+    assert np.abs(host(rstd) / want - 1).max() <= 6e-7
+
+
+@pytest.mark.parametrize("rows,C", [(7, 24), (513, 96)])
+def test_batchnorm_infinity(K, rows, C):
+    """An infinity makes its own channel's statistics infinite and NaN, and no other's."""
+    import torch
+    z = rnd(np.random.default_rng(C), (rows, C), 1)
+    z[3, 5] = np.inf
+    y, mean, rstd = torch.zeros(rows, C, device="cuda", dtype=torch.bfloat16), zeros(C), zeros(C)
+    K.lpk_batchnorm_fwd(1, dev(z, 1), dev(np.ones(C, np.float32), 0), zeros(C), None, y, mean, rstd, rows, C, 0,
+                        zeros((2 * 1024 + 2) * C))
+    other = np.arange(C) != 5
+    assert np.isposinf(host(mean)[5]) and np.isnan(host(rstd)[5]) and np.isnan(host(y)[:, 5]).all()
+    assert np.isfinite(host(mean)[other]).all() and np.isfinite(host(rstd)[other]).all() and np.isfinite(host(y)[:, other]).all()
+
+
 @pytest.mark.parametrize("rows,C", [(39200, 24), (1000, 48), (5000, 1032), (4096, 64), (300, 2048), (3, 8), (70000, 8)])
 def test_batchnorm_least_workspace(K, rows, C):
     """The smallest workspace that the interface names gives the results of an ample one; a float less is refused."""
