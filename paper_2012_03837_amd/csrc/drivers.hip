@@ -347,20 +347,21 @@ int drv_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool 
 }
 
 // ===================================================================================== heads
-// The three products of a vocabulary head, whose logits have a padded pitch (HeadState::ldz): the forward product
-// fills whole 8-column chunks (columns past the vocabulary come from a repeated weight row and are never used), the
-// weight gradient reads whole chunks of dZ's rows, and the input gradient runs over the padding too where the
+// The three products of a vocabulary head, whose logits have a padded pitch (HeadState::ldz).  Only where the vocabulary
+// is no multiple of 8 (a grouped launch takes no such product): the forward product fills whole 8-column chunks
+// (columns past the vocabulary come from a repeated weight row and are never used), the weight gradient reads whole
+// chunks of dZ's rows, and the input gradient runs over the padding too where the
 // transposed weight copy has the same one (zeros in both).
 static GemmArgs head_fwd(const lp_ctx* c, const HeadState& Hd, int rows, int ti_w, void* z) {
   GemmArgs g = lin_fwd(c, c->feat, rows, ti_w, -1, z);
   g.ldc = Hd.ldz;
-  if (Hd.ldz > g.N && g.K % 8 == 0) { g.b_rows = g.N; g.N = (g.N + 7) & ~7; }
+  if (g.N % 8 && Hd.ldz > g.N && g.K % 8 == 0) { g.b_rows = g.N; g.N = (g.N + 7) & ~7; }
   return g;
 }
 static GemmArgs head_wgrad(const lp_ctx* c, const HeadState& Hd, const void* dz, int rows, int ti_w) {
   GemmArgs g = lin_wgrad(c, dz, c->feat, rows, ti_w, 0);
   g.lda = Hd.ldz;
-  if (Hd.ldz > g.M) g.a_rows = (g.M + 7) & ~7;
+  if (g.M % 8 && Hd.ldz > g.M) g.a_rows = (g.M + 7) & ~7;
   return g;
 }
 static GemmArgs head_dgrad(const lp_ctx* c, const HeadState& Hd, const void* dz, int rows, int ti_w, void* dx) {

@@ -405,3 +405,19 @@ def test_mlp_heads_and_grouped_gradients(K, classes, width, batch, scheme):
         x, y = data_for(cfg)
         compare_step(tr, cfg, generic_params(cfg), x, y, n_steps=2, label=scheme)
         tr.close()
+
+
+def test_grouped_vocabulary_of_whole_chunks(K):
+    """A vocabulary that is a multiple of 8 and not of 64: the blocks' head products share grouped launches."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.make_config("cfg3_small", n_layers=4, vocab=520, seq_len=64, batch=4)
+    tr = lp.LocalTrainer(cfg, schedule="pipelined_grouped")
+    tr.set_params(generic_params(cfg))
+    xd, yd = tr.stage(*data_for(cfg))
+    for _ in range(5):
+        tr.step(xd, yd)
+    lp.lp_profile_enable(tr.ctx, True)
+    tr.step(xd, yd)
+    alone = [r for r in lp.lp_profile_gemm_shapes(tr.ctx) if 520 in (r["M"], r["N"])]
+    tr.close()
+    assert not alone, alone
