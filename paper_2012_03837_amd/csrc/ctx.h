@@ -209,6 +209,7 @@ struct StageGemms { GemmArgs g[4]; int n = 0; };
 struct MlpPass { int li = 0; const void* dout = nullptr; void* dx = nullptr; int dx_acc = 0; bool params = true; int acc = 0; };
 constexpr int kMlpBwdStages = 3;
 void mlp_backward_stage(lp_ctx* c, const MlpPass& p, int batch, int stage, std::vector<GemmArgs>* out);
+int mlp_products(lp_ctx* c, const std::vector<GemmArgs>& g);
 int mlp_heads(lp_ctx* c, int batch, const int32_t* y);
 constexpr int kDecFwdStages = 4, kDecBwdStages = 5, kVocabHeadStages = 4;
 int dec_forward_stage(lp_ctx* c, int li, int batch, const int32_t* ids, int stage, StageGemms* out);

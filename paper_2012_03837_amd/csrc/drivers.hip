@@ -480,6 +480,14 @@ int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bo
   return LP_OK;
 }
 
+// Products of several blocks of an MLP step: fp32 ones share launches.
+int mlp_products(lp_ctx* c, const std::vector<GemmArgs>& g) {
+  if (c->dt == F32 && !g.empty()) DO(op_gemm_grouped(c->op(), g.data(), (int)g.size()));
+  if (c->dt != F32)
+    for (const GemmArgs& a : g) DO(op_gemm(c->op(), a));
+  return LP_OK;
+}
+
 // The loss of every head of an MLP step and its gradient at the head's layer (c->dA of scratch set hi, and the layer's
 // gradient sum where it has one), the heads sharing launches; their weight gradients go to c->waiting.
 int mlp_heads(lp_ctx* c, int batch, const int32_t* y) {
@@ -506,7 +514,8 @@ int mlp_heads(lp_ctx* c, int batch, const int32_t* y) {
     c->waiting.push_back(gw);
   }
   if (fused) return LP_OK;
-  DO(op_gemm_grouped(c->op(), g.data(), J));
+  int st;
+  if ((st = mlp_products(c, g)) != LP_OK) return st;
   g.clear();
   for (int hi = 0; hi < J; ++hi) {
     c->use_set(hi);
@@ -514,7 +523,7 @@ int mlp_heads(lp_ctx* c, int batch, const int32_t* y) {
     DO(op_softmax_ce(c->op(), c->logits, ncls, y, c->loss_rows, batch, ncls, 1, inv_rows));
     g.push_back(lin_dgrad(c, c->logits, batch, c->heads[hi].t["w"], c->dA));
   }
-  DO(op_gemm_grouped(c->op(), g.data(), J));
+  if ((st = mlp_products(c, g)) != LP_OK) return st;
   for (int hi = 0; hi < J; ++hi) {
     c->use_set(hi);
     LayerState& L = c->layers[c->heads[hi].e];

@@ -114,3 +114,18 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode != 0
     assert "--gpus must be 1" in r.stderr
     assert not r.stdout.strip()
+
+
+def test_scratch_sets_of_a_residual_mlp():
+    """bf16 with two streams or more: chains, a whole scratch set per stream, however many heads there are.  fp32: the blocks
+    run in lockstep, a set per head, whatever the streams."""
+    def work(dtype, ns):
+        cfg = dataclasses.replace(LI.configs.mlp_config("t", n_layers=4), dtype=dtype)
+        spec, keep = lp.make_spec(cfg, n_streams=ns)
+        return lp.lp_query_sizes(spec).work_bytes
+
+    def step(dtype, ns):
+        return work(dtype, ns + 1) - work(dtype, ns)
+
+    assert step("bf16", 2) == step("bf16", 7)
+    assert step("f32", 2) < step("f32", 7)

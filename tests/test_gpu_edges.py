@@ -421,3 +421,37 @@ def test_grouped_vocabulary_of_whole_chunks(K):
     alone = [r for r in lp.lp_profile_gemm_shapes(tr.ctx) if 520 in (r["M"], r["N"])]
     tr.close()
     assert not alone, alone
+
+
+def with_heads(cfg, heads):
+    """The network with heads of its own kind behind the given layers, as (layer, window) pairs."""
+    h = cfg.heads[0]
+    return dataclasses.replace(cfg, heads=tuple(dataclasses.replace(h, after_layer=e, window=w) for e, w in heads))
+
+
+@pytest.mark.parametrize("layers,heads", [(5, [(2, 2), (4, 3), (5, 3)]), (6, [(k, k) for k in range(1, 7)]),
+                                          (6, [(k, 3) for k in range(1, 7)]), (18, [(k, 1) for k in range(1, 19)]),
+                                          (18, [(k, 2) for k in range(1, 19)]), (4, [(2, 2), (2, 1), (4, 3)])])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_mlp_windows(K, layers, heads, dtype):
+    """Windows of several layers that overlap, more heads than one launch takes, more products than one, two heads behind
+    a layer; blocks in lockstep and (bf16 with streams, two heads behind a layer) as chains.  bf16: the same bits."""
+    import paper_2012_03837_amd as lp
+    from gpu_util import stored_for
+    cfg = LI.configs.mlp_config("t", n_layers=layers, in_dim=24, width=40, hidden=56, batch=19, combine="mean",
+                                opt=LI.configs.OptCfg("sgdm", lr=0.002, momentum=0.9))
+    cfg = dataclasses.replace(with_heads(cfg, heads), dtype=dtype)
+    x, y = data_for(cfg)
+    P = generic_params(cfg)
+    if dtype == "bf16":      # weights that bf16 holds, one step: both sides then decide every ReLU on the same sums
+        P = {k: ops.bf16_round(v).astype(np.float32) for k, v in P.items()}
+    seen = []
+    for ns in (0, 2):
+        tr = lp.LocalTrainer(cfg, n_streams=ns)
+        compare_step(tr, cfg, P, x, y, n_steps=2 if dtype == "f32" else 1, label=f"{heads} {dtype}", stored=stored_for(cfg))
+        seen.append([tr.get_params(), tr.losses.cpu().numpy().copy()])
+        tr.close()
+    if dtype == "bf16":
+        np.testing.assert_array_equal(seen[0][1], seen[1][1])
+        for k in P:
+            np.testing.assert_array_equal(seen[0][0][k], seen[1][0][k])
