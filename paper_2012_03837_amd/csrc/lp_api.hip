@@ -1026,7 +1026,11 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
         }
         void* t = dcur; dcur = dnext; dnext = t;
       }
-      // a layer is updated as soon as the last head covering it has contributed
+      // a layer is updated as soon as the last head covering it has contributed; the earlier heads' passes through it, which
+      // read its weights, may still run on their streams (ev_contrib says only that their gradients have been added)
+      if (set)
+        for (int k = 0; k < hj; ++k)
+          if (c->heads[k].e > Hd.s_lo) CK(hipStreamWaitEvent(c->cur_stream, c->ev_chain[k], 0));
       st = update_block(c, hj, c->step_t, [&](int lj, float* scale) {
         const LayerState& S = c->layers[lj];
         if (c->spec.combine == LP_COMBINE_MEAN) *scale = 1.f / (float)S.coverage;

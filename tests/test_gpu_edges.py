@@ -455,3 +455,26 @@ def test_mlp_windows(K, layers, heads, dtype):
         np.testing.assert_array_equal(seen[0][1], seen[1][1])
         for k in P:
             np.testing.assert_array_equal(seen[0][0][k], seen[1][0][k])
+
+
+@pytest.mark.parametrize("window", [2, 3])
+def test_overlapping_windows_side_streams(K, window):
+    """Overlapping windows of a decoder on side streams: the bits of the single stream over three steps."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.make_config("cfg4_small", n_layers=5)
+    cfg = with_heads(cfg, [(k, window) for k in range(1, 6)])
+    seen = []
+    for ns in (0, 2, 5):
+        tr = lp.LocalTrainer(cfg, n_streams=ns)
+        tr.set_params(generic_params(cfg))
+        losses = []
+        for i in range(3):
+            xd, yd = tr.stage(*data_for(cfg, i))
+            losses.append(tr.step(xd, yd).cpu().numpy().copy())
+        seen.append((losses, tr.get_params()))
+        tr.close()
+    for losses, params in seen[1:]:
+        for a, b in zip(losses, seen[0][0]):
+            np.testing.assert_array_equal(a, b)
+        for k in params:
+            np.testing.assert_array_equal(params[k], seen[0][1][k])
