@@ -569,7 +569,7 @@ hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, 
   if (rows == 0) return hipSuccess;
   if (pad_to > ld) return hipErrorInvalidValue;
   // a row that does not end on a 16-byte chunk needs its padding: the last chunk is read and written whole
-  if (ce_fast_ok(c, z, ld, n) && (n % 8 == 0 || pad_to >= n)) return ce_fast(c, z, ld, y, loss_rows, rows, n, write_grad, inv_rows, pad_to);
+  if (ce_fast_ok(c, z, ld, n) && (n % 8 == 0 || pad_to >= ((n + 7) & ~7))) return ce_fast(c, z, ld, y, loss_rows, rows, n, write_grad, inv_rows, pad_to);
   if (c.dt == BF16) k_softmax_ce<bf16_t><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
   else k_softmax_ce<float><<<rows, 256, 0, c.stream>>>((float*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
   return LP_LAUNCH_CHECK();
