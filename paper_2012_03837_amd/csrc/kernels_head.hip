@@ -100,7 +100,8 @@ __global__ void __launch_bounds__(256) k_head_ce(HeadTable ht, const int32_t* __
         wv[u][i] = row4<VEC>(w + (size_t)(c0 + u < ncls ? c0 + u : ncls - 1) * in, 4 * lane + 256 * i, in);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float dc = __shfl(dv, c0 + u, 64);      // zero past the last class
+      if (c0 + u >= ncls) break;                    // a zero would do, but not against an infinite weight
+      const float dc = __shfl(dv, c0 + u, 64);
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll

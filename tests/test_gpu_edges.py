@@ -478,3 +478,25 @@ def test_overlapping_windows_side_streams(K, window):
             np.testing.assert_array_equal(a, b)
         for k in params:
             np.testing.assert_array_equal(params[k], seen[0][1][k])
+
+
+@pytest.mark.parametrize("width", [64, 300])
+def test_mlp_head_infinite_weight(K, width):
+    """An infinite weight of the last class makes its own feature's gradient infinite, not NaN."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.mlp_config("t", n_layers=1, in_dim=24, width=width, hidden=56, batch=1)
+    P = generic_params(cfg)
+    tr = lp.LocalTrainer(cfg)
+    x, y = data_for(cfg)
+    y[:] = 9
+    tr.set_params(P)
+    xd, yd = tr.stage(x, y)
+    tr.eval(xd, yd)
+    k = int(np.argmin(tr.get("L1.out").ravel()))
+    assert tr.get("L1.out").ravel()[k] < 0
+    P["H1.w"][9, k] = np.inf               # the logit is -inf, the class's gradient -1
+    tr.set_params(P)
+    tr.step(xd, yd)
+    g = tr.get("L1.b2.grad").ravel()       # one sample: the gradient of the head's features
+    assert np.isneginf(g[k]) and np.isfinite(np.delete(g, k)).all()
+    tr.close()
