@@ -34,7 +34,12 @@ static bool plain_conv() {
   return v != 0;
 }
 
-static bool use_mfma_attn(const OpCtx& c, int dh) {
+// Heads of 16 and 32 come here from the row-by-row kernels, which read and write element by element: buffers that are not
+// on 16-byte boundaries stay there.
+static bool use_mfma_attn(const OpCtx& c, int dh, std::initializer_list<const void*> bufs) {
+  uintptr_t low = 0;
+  for (const void* p : bufs) low |= (uintptr_t)p;
+  if (dh < 64 && (low & 15)) return false;
   static int plain = -1;
   if (plain < 0) { const char* s = getenv("LP_PLAIN_ATTN"); plain = (s && s[0] == '1') ? 1 : 0; }
   return c.dt == BF16 && attn_mfma_ok(dh) && !plain;
@@ -42,13 +47,13 @@ static bool use_mfma_attn(const OpCtx& c, int dh) {
 
 hipError_t op_attn_fwd(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal) {
   ProfScope prof_(c, KC_ATTN_FWD);
-  if (use_mfma_attn(c, dh)) return attn_fwd_mfma(c, qkv, o, lse, B, S, H, dh, causal);
+  if (use_mfma_attn(c, dh, {qkv, o})) return attn_fwd_mfma(c, qkv, o, lse, B, S, H, dh, causal);
   return attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
 }
 hipError_t op_attn_bwd(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv,
                        float* delta, int B, int S, int H, int dh, int causal) {
   ProfScope prof_(c, KC_ATTN_BWD);
-  if (use_mfma_attn(c, dh)) return attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
+  if (use_mfma_attn(c, dh, {qkv, o, dout, dqkv})) return attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
   return attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
 }
 hipError_t op_conv_fwd(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* stats) {

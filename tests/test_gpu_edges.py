@@ -500,3 +500,23 @@ def test_mlp_head_infinite_weight(K, width):
     g = tr.get("L1.b2.grad").ravel()       # one sample: the gradient of the head's features
     assert np.isneginf(g[k]) and np.isfinite(np.delete(g, k)).all()
     tr.close()
+
+
+@pytest.mark.parametrize("dh", [16, 32])
+def test_attention_small_heads_any_alignment(K, dh):
+    """Buffers that start between 16-byte boundaries."""
+    import torch
+    rng = np.random.default_rng(dh)
+    B, S, H = 2, 70, 3
+    d = H * dh
+    at = lambda a: torch.cat([torch.zeros(1, device="cuda", dtype=torch.bfloat16), dev(a, 1).ravel()])[1:].view(a.shape)
+    qkv, dout = rnd(rng, (B * S, 3 * d), 1), rnd(rng, (B * S, d), 1)
+    seen = []
+    for put in (lambda a: dev(a, 1), at):
+        o, dqkv = put(np.zeros((B * S, d), np.float32)), put(np.zeros((B * S, 3 * d), np.float32))
+        lse, delta = zeros(B, H, S), zeros(B, H, S)
+        K.lpk_attention_fwd(1, put(qkv), o, lse, B, S, H, dh, 1)
+        K.lpk_attention_bwd(1, put(qkv), o, lse, put(dout), dqkv, delta, B, S, H, dh, 1)
+        seen.append([host(t) for t in (o, lse, dqkv)])
+    for a, b in zip(*seen):
+        assert relerr(a, b) <= 4e-3            # both round exact results to bf16
