@@ -520,3 +520,15 @@ def test_attention_small_heads_any_alignment(K, dh):
         seen.append([host(t) for t in (o, lse, dqkv)])
     for a, b in zip(*seen):
         assert relerr(a, b) <= 4e-3            # both round exact results to bf16
+
+
+@pytest.mark.parametrize("width", [65, 391, 500, 768, 770])
+def test_mlp_head_widths(K, width):
+    """The one-launch classifier head with one to four loads per lane, in whole loads and element by element."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.mlp_config("t", n_layers=2, in_dim=24, width=width, hidden=72, n_classes=11, batch=9,
+                                opt=LI.configs.OptCfg("sgdm", lr=0.002, momentum=0.9))
+    tr = lp.LocalTrainer(cfg)
+    x, y = data_for(cfg)
+    compare_step(tr, cfg, generic_params(cfg), x, y, label=str(width))
+    tr.close()
