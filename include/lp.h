@@ -115,7 +115,11 @@ typedef struct {
                                them, default priority) as soon as the head's activation exists, while the
                                forward pass continues on the caller's stream; all of them are joined back
                                into the caller's stream before lp_local_step returns.  Results do not depend
-                               on n (every per-parameter accumulation keeps its order).  At most 8.        */
+                               on n (every per-parameter accumulation keeps its order).  At most 8.  The
+                               synchronous step of a residual MLP whose heads sit behind different layers does
+                               not use them in fp32 (nor in bf16 with n = 1): its blocks walk their backward
+                               passes together on the caller's stream, the products of all of them in shared
+                               launches.                                                                   */
   int schedule;             /* lp_schedule: how lp_local_step feeds the blocks (see there)                 */
   int debug;                /* != 0: keep, for every convolution + normalisation unit of a ResNet stage, a copy of
                                the upstream gradient its backward pass was given and of the input gradient it
@@ -214,8 +218,8 @@ int lp_step_graph(lp_ctx* ctx, int on);
  * (bit for bit).  The price is a weaker contract: x_dev, y_dev and losses_dev of a call must stay untouched
  * (and losses_dev unread) until lp_join, or any entry point that takes the context other than lp_local_step,
  * lp_last_error, lp_num_params, lp_param_name and lp_destroy (which drains the side streams itself), has been
- * called on the context and the caller's stream has reached that point.  Needs side streams (n_streams > 0; otherwise it
- * has no effect); LP_EINVAL with the pipelined schedule or while graph replay is on. */
+ * called on the context and the caller's stream has reached that point.  Needs chains on side streams (otherwise it has no
+ * effect: n_streams = 0, or a residual MLP whose step does not use them, see n_streams); LP_EINVAL with the pipelined schedule or while graph replay is on. */
 int lp_overlap_steps(lp_ctx* ctx, int on);
 /* Makes the caller's stream wait for everything earlier calls left running (stream-ordered, does not block
  * the host).  A no-op unless steps are overlapped. */

@@ -291,8 +291,9 @@ def lp_destroy(ctx: int) -> None:
 
 def default_side_streams(cfg) -> int:
     """Side streams for the heads' chains that the benchmark times each workload with (the fastest measured on
-    one MI355X): two for the decoders, three for the residual MLP, one per stage (at most four) for the ResNets,
-    whose chains are short enough to run side by side."""
+    one MI355X): two for the decoders, three for the residual MLP (its bf16 and pipelined steps; the synchronous fp32
+    step runs on the caller's stream), one per stage (at most four) for the ResNets, whose chains are short enough to
+    run side by side."""
     kind0 = cfg.layers[0].kind
     if kind0 == "resnet_stage":
         return min(4, len(cfg.heads))

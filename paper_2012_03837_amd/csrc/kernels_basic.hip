@@ -635,7 +635,7 @@ hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, f
 // m, v) and the low-precision working copy.  A block more per head takes the mean of that head's row losses, which
 // otherwise is a launch of its own (8192 rows: 9 us with nothing beside it).  SGD: p -= lr g.  SGD-momentum: m = mu m + g; p -= lr m.
 // Adam: m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr (m/(1-b1^t)) / (sqrt(v/(1-b2^t)) + eps).
-// Bound by memory (28 bytes an element with Adam and bf16 copies, 5.5 TB/s).  A block takes two vectors per thread and ends:
+// Bound by memory (30 bytes an element with Adam and bf16 copies, 5.5 TB/s).  A block takes two vectors per thread and ends:
 // the update runs beside the next block's products on another stream, and blocks that stay for the whole range keep every
 // wave slot of the chip until the update is over (24 layers of 1024 in six chunks of four, ranges of 63 M elements in one
 // launch of 4096 looping blocks: a LayerNorm beside it 18 -> 37 us, the step 40.1 ms instead of 39.3).

@@ -305,8 +305,8 @@ hipError_t ce_fast(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float*
 // Block = (C/8) channel chunks x floor(256 / (C/8)) row lanes (the threads left over idle: 1 of 256 at 24 channels,
 // at worst 127 at 1032); any C % 8 == 0 up to 2048.  Channel counts whose chunks do not divide 256 (24, 48, 96, ...)
 // ran on the generic two-pass kernels before, whose variance is a sum of squares around the mean: with row 0 far from
-// the mean the shifted formula would lose bits against that (row 0 at 300 standard deviations of 39200 rows: 1e-3 of
-// the variance), sums in fp64 lose none (the square of a bf16 value is exact, 2^-53 times mean^2 / variance is below
+// the mean the shifted formula would lose bits against that (row 0 at 300 standard deviations of 39200 rows: rstd off by
+// 6e-3), sums in fp64 lose none (the square of a bf16 value is exact, 2^-53 times mean^2 / variance is below
 // fp32's rounding for any bf16 column).  39200 x 24, statistics of the backward pass 156 us with two bytes per lane and
 // 39 blocks, 5.2 us here.
 namespace lp {

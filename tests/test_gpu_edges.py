@@ -79,8 +79,9 @@ def test_grouped_weight_gradients_any_rows(K, seq, batch):
     tr.close()
 
 
-@pytest.mark.parametrize("Kd,M", [(129, 64), (72, 64), (64, 63)])
+@pytest.mark.parametrize("Kd,M", [(129, 64), (72, 64), (64, 63), (136, 64)])
 def test_grouped_products_refused(K, Kd, M):
+    """What the entry point refuses; 136 only there (the grouped kernel takes a partial last k-tile)."""
     import torch
     a = torch.zeros(256, 256, device="cuda", dtype=torch.bfloat16)
     o = torch.zeros(64, 64, device="cuda", dtype=torch.float32)
@@ -532,3 +533,27 @@ def test_mlp_head_widths(K, width):
     x, y = data_for(cfg)
     compare_step(tr, cfg, generic_params(cfg), x, y, label=str(width))
     tr.close()
+
+
+def test_overlapped_steps_bf16_mlp(K):
+    """A residual MLP whose chains run on side streams: overlapped steps leave the bits of ordinary ones."""
+    import torch
+    import paper_2012_03837_amd as lp
+    cfg = dataclasses.replace(LI.make_config("cfg1_small", scheme="overlap"), dtype="bf16")
+    seen = []
+    for overlap in (False, True):
+        tr = lp.LocalTrainer(cfg, n_streams=2)
+        tr.set_params(generic_params(cfg))
+        tr.overlap_steps(overlap)
+        bufs = [tr.stage(*data_for(cfg, i)) for i in range(4)]
+        loss = [torch.zeros(len(cfg.heads), device="cuda") for _ in bufs]
+        for (xd, yd), l in zip(bufs, loss):
+            lp.lp_local_step(tr.ctx, xd.data_ptr(), yd.data_ptr(), cfg.batch, l.data_ptr())
+        tr.eval(*bufs[0])                   # joins first
+        torch.cuda.synchronize()
+        seen.append(([host(l) for l in loss], tr.get_params()))
+        tr.close()
+    for a, b in zip(seen[0][0], seen[1][0]):
+        np.testing.assert_array_equal(a, b)
+    for k in seen[0][1]:
+        np.testing.assert_array_equal(seen[0][1][k], seen[1][1][k])
