@@ -1,7 +1,8 @@
 // Small classifier heads on [rows, in] features (at most 32 classes, 1024 features): logits, cross-entropy, dZ and the
 // gradient of the features in one kernel, one wave per row, up to eight heads (blocks of the network) per launch.  As
 // separate launches (product, softmax, product) each is a memory latency and a launch gap long and nothing else:
-// 128 x 10 x 256 fp32 took 6 + 3.4 + 12 us and their gaps, 256 x 10 x 512 bf16 9.3 + 4.7 + 6 us; 4.5 and 5.5 us here.
+// 128 x 10 x 256 fp32 took 6 + 3.4 + 12 us and their gaps, 256 x 10 x 512 bf16 9.3 + 4.7 + 6 us; 4.5 and 5.5 us here
+// (four of the former in one launch: 7.3 us).
 // A lane owns four consecutive features (16-byte loads), several classes' loads are in flight at a time, and the weights
 // (at most 128 KB) come from L2 for every wave, which is why the class count is limited.
 // Logits are rounded to the compute dtype before the softmax, and dZ is stored in it for the weight gradient.
