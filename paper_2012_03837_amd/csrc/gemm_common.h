@@ -1,8 +1,25 @@
 // Epilogue shared by the GEMM kernels, and operand accessors for the plain (FMA) GEMM.
 #pragma once
+#include <atomic>
 #include "common.h"
 
 namespace lp {
+
+// Raises a kernel's limit of dynamic LDS, which belongs to the function on one device: once per device, one object per
+// kernel (two threads may both set it, to the same value).
+struct LdsLimit {
+  std::atomic<uint64_t> done{0};
+  hipError_t raise(const void* fn, int bytes) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+  }
+};
 
 struct Epilogue {
   const float* bias;

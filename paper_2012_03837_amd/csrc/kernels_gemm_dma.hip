@@ -928,13 +928,10 @@ hipError_t launch(const OpCtx& c, const GemmArgs& g, const SkPlan& p, bool parti
                   double flops = 0.0) {
   constexpr int BN = 32 * TN * WNW;
   constexpr int smem = NSTAGE * (BM + BN) * KT * 2 + (xpose_shape(WNW, TN, PIPE) ? 2 * WNW * XPOSE_BYTES_PER_WAVE : 0);
-  static bool configured = false;
   auto kern = k_gemm_dma<A_KC, B_KC, WNW, TN, NSTAGE, PIPE, KT>;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  static LdsLimit limit;
+  hipError_t le = limit.raise(reinterpret_cast<const void*>(kern), smem);
+  if (le != hipSuccess) return le;
   Operand A{(const bf16_t*)g.A, g.lda, rows_of_a(g)}, B{(const bf16_t*)g.B, g.ldb, rows_of_b(g)};
   Epilogue e = make_epilogue(g);
   static char kname[64];

@@ -226,11 +226,10 @@ hipError_t launch_f(const OpCtx& c, FGroup<T, NP>& grp) {
   }
   constexpr int EDGE = 16 * TT;
   constexpr size_t shm = (size_t)(4 * EDGE * (EDGE + 4) + 4 * EDGE) * sizeof(float);
-  static bool configured = false;
-  if (shm > 64 * 1024 && !configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f<T, TT, NP>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+  if (shm > 64 * 1024) {
+    static LdsLimit limit;
+    hipError_t e = limit.raise(reinterpret_cast<const void*>(k_gemm_f<T, TT, NP>), (int)shm);
     if (e != hipSuccess) return e;
-    configured = true;
   }
   k_gemm_f<T, TT, NP><<<tiles, 256, shm, c.stream>>>(grp);
   return hipGetLastError();

@@ -432,11 +432,11 @@ def with_heads(cfg, heads):
 
 @pytest.mark.parametrize("layers,heads", [(5, [(2, 2), (4, 3), (5, 3)]), (6, [(k, k) for k in range(1, 7)]),
                                           (6, [(k, 3) for k in range(1, 7)]), (18, [(k, 1) for k in range(1, 19)]),
-                                          (18, [(k, 2) for k in range(1, 19)]), (4, [(2, 2), (2, 1), (4, 3)])])
+                                          (18, [(k, 2) for k in range(1, 19)]), (18, [(k, 1) for k in range(2, 19, 2)]), (4, [(2, 2), (2, 1), (4, 3)])])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_mlp_windows(K, layers, heads, dtype):
-    """Windows of several layers that overlap, more heads than one launch takes, more products than one, two heads behind
-    a layer; blocks in lockstep and (bf16 with streams, two heads behind a layer) as chains.  bf16: the same bits."""
+    """Windows of several layers that overlap, more heads than one launch takes, more products than one, more disjoint
+    parameter ranges than one update takes (every other layer), two heads behind a layer; blocks in lockstep and (bf16 with streams, two heads behind a layer) as chains.  bf16: the same bits."""
     import paper_2012_03837_amd as lp
     from gpu_util import stored_for
     cfg = LI.configs.mlp_config("t", n_layers=layers, in_dim=24, width=40, hidden=56, batch=19, combine="mean",
@@ -557,3 +557,21 @@ def test_overlapped_steps_bf16_mlp(K):
         np.testing.assert_array_equal(a, b)
     for k in seen[0][1]:
         np.testing.assert_array_equal(seen[0][1][k], seen[1][1][k])
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_products_on_a_second_device(K, dtype):
+    """Kernels with more than 64 KB of LDS on each device of one process (the limit is raised per device)."""
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("one device")
+    rng = np.random.default_rng(0)
+    M, N, Kd = 1024, 1024, 512
+    A, B = rnd(rng, (M, Kd), dtype), rnd(rng, (N, Kd), dtype)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    for d in (0, 1):
+        with torch.cuda.device(d):
+            C = zeros(M, N)
+            K.lpk_gemm(dtype, dev(A, dtype), Kd, 1, dev(B, dtype), Kd, 1, C, N, 1, M, N, Kd, variant=20 if dtype else 0)
+            torch.cuda.synchronize()
+            assert relerr(host(C), ref) <= 2e-6, d
