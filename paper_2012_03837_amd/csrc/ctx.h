@@ -164,6 +164,7 @@ struct lp_ctx : lp_scratch {
   size_t label_elems_per_sample = 1;
   hipEvent_t ev_pipe = nullptr;
   bool lockstep = false;                 // pipelined blocks are walked stage by stage (grouped GEMMs across blocks)
+  bool one_stream = false;               // a step that is being captured and whose windows overlap (run_graph)
   bool mlp_lockstep = false;             // so are the blocks of a synchronous residual-MLP step (run_mlp)
   void use_set(int i) { use(i); cur_stream = stream; }      // scratch set i on the caller's stream
   void use(int i) { static_cast<lp_scratch&>(*this) = sets[i]; }
