@@ -43,8 +43,6 @@ constexpr int BM = 256, BK = 32;
 constexpr int XPOSE_BYTES_PER_WAVE = 32 * 128;
 constexpr bool xpose_shape(int WNW, int TN, bool PIPE) { return PIPE && WNW == 4 && TN == 2; }
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void glb_void;
 
 struct Operand { const bf16_t* p; int64_t ld; int rows; };
 
@@ -52,12 +50,21 @@ __device__ __forceinline__ int nmap(int i) {
   int g = i >> 3, h = (i >> 2) & 1, j = i & 3;
   return 16 * (g >> 1) + 8 * h + 4 * (g & 1) + j;
 }
-// Wait until at most VM of this wave's vector-memory loads are outstanding, then the workgroup barrier.
+// 16 bytes per lane, global -> LDS, lane l's at dst + 16 l.  In assembly because of what the compiler does around the builtin:
+// it knows that the load writes LDS, not where, and puts an s_waitcnt vmcnt(0) in front of the next ds_read_b64_tr_b16, so
+// that the loops with a k-major operand had no load in flight behind their matrix instructions (alone, both operands k-major:
+// 32000 x 768 x 8192 449 -> 401 us, 8192 cubed 964 -> 851 us; a layer's four weight gradients 159 -> 140 us at width 768,
+// 256 -> 240 us at 1024).  Nothing is returned in registers; who reads the LDS waits with wait_loads_and_barrier.
+__device__ __forceinline__ void to_lds(const bf16_t* src, char* dst) {
+  const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0");
+}
+// Wait until at most VM of this wave's vector-memory loads are outstanding and its LDS reads have been done, then the barrier.
 // One asm statement with a memory clobber: the compiler neither moves LDS accesses across it nor turns
 // it into a full fence (a fence would wait for *all* loads, i.e. drain the pipeline every k-tile).
 template <int VM>
 __device__ __forceinline__ void wait_loads_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(VM) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
 }
 
 // Same fused epilogue as the register-staged kernel (8 consecutive columns of one row).
@@ -161,13 +168,12 @@ struct DmaPlan {
     }
     kmul = KC ? 1 : o.ld;
   }
+  __device__ __forceinline__ int64_t offset(int tile) const { return (int64_t)(tile * KT < klim ? tile * KT : klim) * kmul; }
+  __device__ __forceinline__ void issue1(int i, char* stage_base, int64_t off) const { to_lds(g[i] + off, stage_base + lds_off[i]); }
   __device__ __forceinline__ void issue(char* stage_base, int tile) const {
-    const int64_t off = (int64_t)(tile * KT < klim ? tile * KT : klim) * kmul;
+    const int64_t off = offset(tile);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const bf16_t* src = g[i] + off;
-      __builtin_amdgcn_global_load_lds((glb_void*)src, (lds_void*)(stage_base + lds_off[i]), 16, 0, 0);
-    }
+    for (int i = 0; i < NI; ++i) issue1(i, stage_base, off);
   }
 };
 
@@ -491,17 +497,19 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
     // have a whole k-tile of MFMA time to land.  As in the 32-deep loop the k-tiles of all of a block's items form
     // one stream through the two stages.
     static_assert(NSTAGE == 2, "the 64-deep loop has two stages");
+    // fragment r of substep kk, n side first
+    auto read1 = [&](const char* as, const char* bs, int kk, int r, bf16x8* fn, bf16x8* fm) {
+      if (r < TN)
+        fn[r] = B_KC ? frag_kc64(bs, wn + 32 * r + n_row, 2 * kk + hf)
+                     : frag_t<BN>(bs, wn + 32 * r + n_rowbase_t, 16 * kk + 8 * hf + kq);
+      else
+        fm[r - TN] = A_KC ? frag_kc64(as, wm + 32 * (r - TN) + li, 2 * kk + hf)
+                          : frag_t<BM>(as, wm + 32 * (r - TN) + m_rowbase_t, 16 * kk + 8 * hf + kq);
+    };
     auto read = [&](const char* as, const char* bs, int kk, bf16x8* fn, bf16x8* fm) {
 #pragma unroll
-      for (int i = 0; i < TN; ++i)
-        fn[i] = B_KC ? frag_kc64(bs, wn + 32 * i + n_row, 2 * kk + hf)
-                     : frag_t<BN>(bs, wn + 32 * i + n_rowbase_t, 16 * kk + 8 * hf + kq);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        fm[j] = A_KC ? frag_kc64(as, wm + 32 * j + li, 2 * kk + hf)
-                     : frag_t<BM>(as, wm + 32 * j + m_rowbase_t, 16 * kk + 8 * hf + kq);
+      for (int r = 0; r < TN + 4; ++r) read1(as, bs, kk, r, fn, fm);
     };
-    constexpr int NDS = (A_KC ? 4 : 8) + (B_KC ? TN : 2 * TN);
     // The reduction's last k-tile, if it is partial, holds the last 64 of k: the first `skip` of them belong to the
     // k-tile before it and are cleared in both operands (an infinity against a cleared one would make a NaN).  Once per
     // output tile, by all waves, between the barrier that says the k-tile has landed and its first fragment reads.
@@ -568,13 +576,30 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int x = 0; x < 16; ++x) acc[i][j][x] = 0.f;
-      auto mma = [&](const bf16x8* fn, const bf16x8* fm) {
+      // One 16-deep substep: its matrix instructions, the next substep's fragment reads (READS) between the first half of
+      // them and NL direct-to-LDS loads between the second.  The order is fixed here: a wave issues in order, a burst of
+      // loads that fills the memory pipeline's queue holds back the matrix instructions behind it, and so do reads that
+      // come too late to have landed.
+      auto sub = [&](auto reads, const bf16x8* fn, const bf16x8* fm, const char* as, const char* bs, int kk, bf16x8* gn, bf16x8* gm,
+                     auto nload, auto load_at) {
+        constexpr int NMF = 4 * TN, NR = TN + 4, RD = NMF / 2, NL = decltype(nload)::value;
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+        for (int g = 0; g < NMF; ++g) {
+          acc[g / 4][g % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fn[g / 4], fm[g % 4], acc[g / 4][g % 4], 0, 0, 0);
+          if (decltype(reads)::value && g < RD) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fn[i], fm[j], acc[i][j], 0, 0, 0);
+            for (int r = g * NR / RD; r < (g + 1) * NR / RD; ++r) read1(as, bs, kk, r, gn, gm);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (NL > 0 && g >= RD) {
+#pragma unroll
+            for (int l = (g - RD) * NL / RD; l < (g - RD + 1) * NL / RD; ++l) load_at(l);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       };
+      typedef std::integral_constant<int, 0> None;
+      auto no_load = [](int) {};
       // One 64-deep k-tile.  STEADY (1: first of a run, 2: later ones): the loader is two k-tiles ahead inside this
       // item, so everything is unconditional: the A half of k-tile t + 2 goes out in t's last substep (behind the
       // barrier), its B half in the first substep of t + 1, so that a wave's eight loads do not reach the memory
@@ -583,34 +608,26 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         constexpr int ST = decltype(steady)::value;
         const char* as = smem + cstage * STAGE_BYTES;
         const char* bs = as + A_BYTES;
-        read(as, bs, 1, fn1, fm1);
         if (ST == 2) {
-          pb.issue(smem + (lstage ^ 1) * STAGE_BYTES + A_BYTES, lt - 1);
-          mma(fn0, fm0);
-          interleave_hint_loads<4 * TN, NDS, BI>();
+          char* dst = smem + (lstage ^ 1) * STAGE_BYTES + A_BYTES;
+          const int64_t off = pb.offset(lt - 1);
+          sub(std::true_type{}, fn0, fm0, as, bs, 1, fn1, fm1, std::integral_constant<int, BI>{}, [&](int l) { pb.issue1(l, dst, off); });
         } else {
-          mma(fn0, fm0);
-          interleave_hint<4 * TN, NDS, 0>();
+          sub(std::true_type{}, fn0, fm0, as, bs, 1, fn1, fm1, None{}, no_load);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        read(as, bs, 2, fn0, fm0);
-        mma(fn1, fm1);
-        interleave_hint<4 * TN, NDS, 0>();
-        __builtin_amdgcn_sched_barrier(0);
-        read(as, bs, 3, fn1, fm1);
-        mma(fn0, fm0);
-        interleave_hint<4 * TN, NDS, 0>();
-        __builtin_amdgcn_sched_barrier(0);
+        sub(std::true_type{}, fn1, fm1, as, bs, 2, fn0, fm0, None{}, no_load);
+        sub(std::true_type{}, fn0, fm0, as, bs, 3, fn1, fm1, None{}, no_load);
         // last substep: behind the barrier every wave has read all of this stage and the next k-tile has landed
         if (ST != 0) {
           wait_loads_and_barrier<0>();
           cstage ^= 1;
-          read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
-          pa.issue(smem + lstage * STAGE_BYTES, lt);
+          const char* an = smem + cstage * STAGE_BYTES;
+          char* dst = smem + lstage * STAGE_BYTES;
+          const int64_t off = pa.offset(lt);
+          sub(std::true_type{}, fn1, fm1, an, an + A_BYTES, 0, fn0, fm0, std::integral_constant<int, AI>{},
+              [&](int l) { pa.issue1(l, dst, off); });
           ++lt; --l_left;
           lstage ^= 1;
-          mma(fn1, fm1);
-          interleave_hint_loads<4 * TN, NDS, AI>();
         } else {
           const bool more = inflight > 0;
           bool load = false;
@@ -624,10 +641,8 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
             if (tail_next) clear_counted(cstage);
             if (!last) read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
           }
-          mma(fn1, fm1);
-          interleave_hint<4 * TN, NDS, 0>();
+          sub(std::false_type{}, fn1, fm1, nullptr, nullptr, 0, fn0, fm0, None{}, no_load);
         }
-        __builtin_amdgcn_sched_barrier(0);
       };
       const int nt = C.ke - C.ks;
       int t = 0;
