@@ -22,7 +22,7 @@ extern "C" {
  * A(m,k) = a_kc ? A[m*lda+k] : A[k*lda+m]; B(n,k) = b_kc ? B[n*ldb+k] : B[k*ldb+n]  (the forward, dgrad
  * and wgrad forms of a linear layer: paper appendix A, "MLP").  act / dact: 0 none, 1 ReLU, 2 GELU(tanh).
  * variant: 0 lets the library choose the kernel; 1 forces the fp32-arithmetic kernel; for bf16, 2 forces the
- * register-staged MFMA kernel, 3 / 4 the direct-to-LDS kernel with 256 x 128 tiles and the last partial wave
+ * one-tile-per-block MFMA kernel, 3 / 4 the direct-to-LDS kernel with 256 x 128 tiles and the last partial wave
  * of tiles computed whole / cut along k, 5 / 6 the same with 256 x 256 tiles and 8 wavefronts, 7 / 8 with
  * 256 x 256 tiles and 4 wavefronts; 9 / 10 / 11 those three tile shapes in panel mode (outputs 2..8 tiles
  * wide: the tile columns of one tile row walk the same cut of the reduction together, so that the other

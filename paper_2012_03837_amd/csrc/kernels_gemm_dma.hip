@@ -16,7 +16,7 @@
 // *global* address of each lane undoes:
 //   kc tile   [row][4 chunks of 8 k]   : chunk c of row r sits in slot c ^ ((r>>2)&3)
 //   k-major   [k][32.. chunks of 8 rows]: chunk j of k-row k sits in slot j ^ ((k&3)<<2)   (read with
-//                                         ds_read_b64_tr_b16, as in the register-staged kernel)
+//                                         ds_read_b64_tr_b16)
 // The grid is persistent (one block per resident slot): a block computes several whole tiles, and the last
 // partial wave of tiles is cut along k so that every CU gets the same number of k-steps (see SkPlan).
 // Plain main loop, one barrier per k-tile: wait until this thread's loads of tile t have landed (s_waitcnt
@@ -67,7 +67,7 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
 }
 
-// Same fused epilogue as the register-staged kernel (8 consecutive columns of one row).
+// The fused epilogue on 8 consecutive columns of one row.
 __device__ __forceinline__ void epilogue8(const Epilogue& e, int m, int n, float* v) {
   if (e.bias) {
     f32x4 b0 = *reinterpret_cast<const f32x4*>(e.bias + n), b1 = *reinterpret_cast<const f32x4*>(e.bias + n + 4);

@@ -1,4 +1,4 @@
-// Shared pieces of the register-staged MFMA tile kernel: LDS staging, fragment reads (straight and
+// The register-staged MFMA tile kernel of the convolutions, and pieces shared with the other product kernels: LDS staging, fragment reads (straight and
 // transposing), the fused epilogue, and the kernel template itself, generic over operand loaders.
 // A loader turns (tile row, k) into 16-byte global loads; the plain loaders read dense matrices, the
 // convolution loaders gather NHWC pixels (implicit GEMM) and report zero padding as invalid chunks.

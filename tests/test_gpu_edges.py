@@ -601,3 +601,73 @@ def test_step_graph_with_overlapping_windows(K, family):
     np.testing.assert_array_equal(seen[0][0], seen[1][0])
     for k in seen[0][1]:
         np.testing.assert_array_equal(seen[0][1][k], seen[1][1][k])
+
+
+# sizes that reach each tile shape of the one-tile-per-block kernel, with remainders in every direction; (333, 264, 2048),
+# (1000, 136, 4104) are cut along k
+TILE_SHAPES = [(1, 8, 8), (67, 72, 40), (600, 392, 136), (333, 264, 2048), (1000, 136, 4104), (6149, 144, 136), (2555, 448, 1208),
+               (6714, 2384, 216), (642, 3184, 136), (6999, 528, 136), (8331, 904, 136)]
+
+
+@pytest.mark.parametrize("a_kc,b_kc", [(1, 1), (1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,Kd", TILE_SHAPES)
+def test_gemm_tile_shapes(K, M, N, Kd, a_kc, b_kc):
+    """fp32 outputs against float64 (sums of at most 4104 products: 2e-6), bits equal when repeated, and the fused forms
+    (bias, stored pre-activation, ReLU, residual; activation derivative) to the rounding of a bf16 result (2^-9 relative per
+    element: 4e-3 with room for what the fp32 sums add)."""
+    import torch
+    if not a_kc and M % 8:
+        M = (M + 7) // 8 * 8
+    rng = np.random.default_rng(M + N + Kd)
+    A, B = rnd(rng, (M, Kd), 1), rnd(rng, (N, Kd), 1)
+    Am, Bm = A if a_kc else np.ascontiguousarray(A.T), B if b_kc else np.ascontiguousarray(B.T)
+    dA, dB = dev(Am, 1), dev(Bm, 1)
+    ref = (torch.from_numpy(A).cuda().double() @ torch.from_numpy(B).cuda().double().T).cpu().numpy()
+    ws = zeros(1 << 24)
+    outs = []
+    for _ in range(2):
+        out = torch.full((M + 1, N), 3.0, device="cuda")
+        K.lpk_gemm(1, dA, Am.shape[1], a_kc, dB, Bm.shape[1], b_kc, out, N, 1, M, N, Kd, variant=2, splitk_ws=ws)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+    assert relerr(host(outs[0][:M]), ref) <= 2e-6
+    assert bool((outs[0][M] == 3.0).all())
+    K.lpk_gemm(1, dA, Am.shape[1], a_kc, dB, Bm.shape[1], b_kc, outs[1], N, 1, M, N, Kd, variant=2, accumulate=1, splitk_ws=ws)
+    assert relerr(host(outs[1][:M]), 2 * ref) <= 2e-6
+    bias = rng.standard_normal(N).astype(np.float32)
+    ldr, ldd = N + 8, N + 16
+    res, dsrc = rnd(rng, (M, ldr), 1), rnd(rng, (M, ldd), 1)
+    dres, dds, dbias = dev(res, 1), dev(dsrc, 1), dev(bias, 0)
+    out = torch.full((M + 1, N), 3.0, device="cuda", dtype=torch.bfloat16)
+    pre = torch.full((M + 1, N), 3.0, device="cuda", dtype=torch.bfloat16)
+    K.lpk_gemm(1, dA, Am.shape[1], a_kc, dB, Bm.shape[1], b_kc, out, N, 0, M, N, Kd, bias=dbias, act=1, pre=pre, res=dres, ldr=ldr,
+               variant=2, splitk_ws=ws)
+    v = ref + bias
+    assert relerr(host(pre[:M]), v) <= 4e-3
+    assert relerr(host(out[:M]), np.maximum(v, 0.0) + res[:, :N]) <= 4e-3
+    assert bool((out[M] == 3.0).all()) and bool((pre[M] == 3.0).all())
+    K.lpk_gemm(1, dA, Am.shape[1], a_kc, dB, Bm.shape[1], b_kc, out, N, 0, M, N, Kd, dact_src=dds, dact=2, ldd=ldd, variant=2,
+               splitk_ws=ws)
+    assert relerr(host(out[:M]), ops.gelu_bwd(dsrc[:, :N].astype(np.float64), ref)) <= 4e-3
+
+
+@pytest.mark.parametrize("a_kc,b_kc", [(1, 1), (1, 0), (0, 1), (0, 0)])
+def test_gemm_tile_infinities(K, a_kc, b_kc):
+    """Rows and columns past the end are read from the last ones, k past the end from zeros: an infinity in the last row, the
+    last column or the last k is an infinity of its row or column and nothing else (operands positive: no NaN)."""
+    import torch
+    rng = np.random.default_rng(5)
+    M, N, Kd = 72, 136, 136
+    for operand, at in ((0, (M - 1, Kd - 1)), (0, (3, 127)), (1, (N - 1, Kd - 1)), (1, (0, 128))):
+        A, B = np.abs(rnd(rng, (M, Kd), 1)) + 1, np.abs(rnd(rng, (N, Kd), 1)) + 1
+        (A, B)[operand][at] = np.inf
+        want = np.zeros((M, N), bool)
+        if operand:
+            want[:, at[0]] = True
+        else:
+            want[at[0], :] = True
+        Am, Bm = A if a_kc else np.ascontiguousarray(A.T), B if b_kc else np.ascontiguousarray(B.T)
+        out = zeros(M, N)
+        K.lpk_gemm(1, dev(Am, 1), Am.shape[1], a_kc, dev(Bm, 1), Bm.shape[1], b_kc, out, N, 1, M, N, Kd, variant=2)
+        got = host(out)
+        assert np.array_equal(np.isinf(got), want) and not np.isnan(got).any()
