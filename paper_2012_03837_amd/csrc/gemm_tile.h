@@ -1,4 +1,4 @@
-// bf16 product tile on the matrix cores, one output tile per block: operand tiles stream global -> LDS with the 16-byte
+// bf16 product tile on the matrix cores, one output tile per block (and pieces that the persistent kernel shares): operand tiles stream global -> LDS with the 16-byte
 // direct-to-LDS load through a ring of NST stages of 64 k, so that a short reduction is in flight as a whole and a long
 // one NST - 1 k-tiles ahead.  Generic over the operands' loaders (dense matrices here, pixels in the convolutions).
 //
@@ -6,34 +6,43 @@
 // LDS tiles are unpadded (a direct-to-LDS load fills 1 KB of contiguous LDS per wave) with an XOR swizzle that each lane's
 // global address undoes:
 //   k contiguous: [row][8 chunks of 8 k], 128-byte rows, chunk c of row r in slot c ^ ((r >> 1) & 7)
-//   k-major     : [64 k][ROWS / 8 chunks of 8 rows], chunk j of k-row k in slot j ^ swz(k), read with ds_read_b64_tr_b16
+//   k-major     : [64 k][ROWS / 8 chunks of 8 rows], chunk j of k-row k in slot j ^ kswz(k), read with ds_read_b64_tr_b16
 // A chunk that does not exist (past the reduction's end, a convolution's padding) is loaded from a zero page.
 #pragma once
 #include "common.h"
 #include "gemm_common.h"
-#include "mfma_tile.h"
 
 namespace lp {
 namespace tile {
 
-using mfma::Operand;
-using mfma::nmap;
-
 constexpr int KT = 64;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void glb_void;
+
+struct Operand { const bf16_t* p; int64_t ld; int rows; };
+
+// MFMA row i of the n-side fragment holds tile column 16*(g/2) + 8*h + 4*(g%2) + j, i = 8g + 4h + j, so
+// that accumulator values 0..7 / 8..15 of lane-half h are columns 8h..8h+7 / 16+8h..16+8h+7.
+__device__ __forceinline__ int nmap(int i) {
+  int g = i >> 3, h = (i >> 2) & 1, j = i & 3;
+  return 16 * (g >> 1) + 8 * h + 4 * (g & 1) + j;
+}
 
 static __device__ const __attribute__((aligned(16))) unsigned kZeroPage[4] = {0, 0, 0, 0};
 
 // 16 bytes per lane, global -> LDS, lane l's at dst + 16 l.  In assembly because of what the compiler does around the
 // builtin: it knows that the load writes LDS, not where, and puts an s_waitcnt vmcnt(0) in front of the next
-// ds_read_b64_tr_b16, so that a loop with a k-major operand never had a load in flight behind its matrix instructions.
-// Nothing is returned in registers; who reads the LDS waits with wait_barrier (which clobbers memory).
+// ds_read_b64_tr_b16, so that a loop with a k-major operand never had a load in flight behind its matrix instructions
+// (persistent kernel, both operands k-major, alone: 32000 x 768 x 8192 449 -> 401 us, 8192 cubed 964 -> 851 us; a layer's
+// four weight gradients 159 -> 140 us at width 768, 256 -> 240 us at 1024).  Nothing is returned in registers; who reads the
+// LDS waits with a barrier that clobbers memory.
 __device__ __forceinline__ void to_lds(const bf16_t* src, char* dst) {
   const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0");
 }
+
+// k-major tiles: four neighbouring k-rows, which a transposing read takes together, in different quarters of the banks.
+template <int ROWS>
+__device__ __forceinline__ int kswz(int k) { return ROWS == 32 ? 0 : (ROWS == 64 ? ((k >> 1) & 1) << 2 : (k & 3) << 2); }
 
 // Which chunk of a tile lane `lane` carries in the q-th 1 KB of it: (row, k) of its first element.
 template <bool KC, int ROWS>
@@ -44,8 +53,7 @@ __device__ __forceinline__ void chunk_of(int q, int lane, int& row, int& k) {
   } else {
     constexpr int CPR = ROWS / 8, KPI = 64 / CPR;      // chunks per k-row, k-rows per 1 KB
     k = q * KPI + lane / CPR;
-    const int swz = ROWS == 64 ? ((k >> 1) & 1) << 2 : (k & 3) << 2;
-    row = 8 * ((lane % CPR) ^ swz);
+    row = 8 * ((lane % CPR) ^ kswz<ROWS>(k));
   }
 }
 
@@ -96,8 +104,7 @@ __device__ __forceinline__ bf16x8 frag_kc(const char* sm, int row, int chunk) {
 }
 template <int ROWS>
 __device__ __forceinline__ bf16x8 frag_t(const char* sm, int rowbase, int k) {
-  const int swz = ROWS == 64 ? ((k >> 1) & 1) << 2 : (k & 3) << 2;
-  const char* p = sm + k * (ROWS * 2) + 16 * ((rowbase >> 3) ^ swz) + (rowbase & 7) * 2;
+  const char* p = sm + k * (ROWS * 2) + 16 * ((rowbase >> 3) ^ kswz<ROWS>(k)) + (rowbase & 7) * 2;
   bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p));
   bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 4 * ROWS * 2));
   bf16x8 r;
@@ -218,8 +225,8 @@ __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n
   wait(pre - 1);
 #pragma unroll
   for (int r = 0; r < TM + TN; ++r) read1(smem, 0, r, fn0, fm0);
-  int st = 0;
-  // substeps 0 .. 2 of the k-tile in stage st, with parts 1 .. of the k-tile that goes to stage `pend`
+  int st = 0, t = 0;
+  // substeps 0 .. 2 of the k-tile in stage st, with parts 1 .. of k-tile t - 1 + NST, which goes to stage `pend`
   auto head = [&](auto pending, int pend) {
     constexpr bool L = decltype(pending)::value;
     const char* sm = smem + st * STAGE;
@@ -227,13 +234,13 @@ __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n
     constexpr int P1 = L ? part_of(LPT, PARTS, 1) : 0, P2 = L && PARTS == 4 ? part_of(LPT, PARTS, 2) : 0,
                   P3 = L && PARTS == 4 ? part_of(LPT, PARTS, 3) : 0;
     substep(std::true_type{}, fn0, fm0, sm, 1, fn1, fm1, std::integral_constant<int, P1>{},
-            [&](int l) { load(std::false_type{}, LPT / PARTS + l, dst, 0); });
+            [&](int l) { load(std::false_type{}, LPT / PARTS + l, dst, t - 1 + NST); });
     substep(std::true_type{}, fn1, fm1, sm, 2, fn0, fm0, std::integral_constant<int, P2>{},
-            [&](int l) { load(std::false_type{}, 2 * LPT / PARTS + l, dst, 0); });
+            [&](int l) { load(std::false_type{}, 2 * LPT / PARTS + l, dst, t - 1 + NST); });
     substep(std::true_type{}, fn0, fm0, sm, 3, fn1, fm1, std::integral_constant<int, P3>{},
-            [&](int l) { load(std::false_type{}, 3 * LPT / PARTS + l, dst, 0); });
+            [&](int l) { load(std::false_type{}, 3 * LPT / PARTS + l, dst, t - 1 + NST); });
   };
-  int t = 0, pend = 0;
+  int pend = 0;
   const int steady = nt < full ? nt : full;
   auto step = [&](auto pending) {          // the k-tile that is asked for exists and is whole
     head(pending, pend);
@@ -241,14 +248,14 @@ __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n
     pend = st;
     st = st + 1 == NST ? 0 : st + 1;
     substep(std::true_type{}, fn1, fm1, smem + st * STAGE, 0, fn0, fm0, std::integral_constant<int, part_of(LPT, PARTS, 0)>{},
-            [&](int l) { load(std::false_type{}, l, smem + pend * STAGE, 0); });
+            [&](int l) { load(std::false_type{}, l, smem + pend * STAGE, t + NST); });
     ++t;
   };
   if (NST < steady) {
     step(std::false_type{});
     while (t + NST < steady) step(std::true_type{});
 #pragma unroll
-    for (int i = LPT / PARTS; i < LPT; ++i) load(std::false_type{}, i, smem + pend * STAGE, 0);
+    for (int i = LPT / PARTS; i < LPT; ++i) load(std::false_type{}, i, smem + pend * STAGE, t - 1 + NST);
   }
   for (; t + 1 < nt; ++t) {
     head(std::false_type{}, 0);
@@ -263,6 +270,88 @@ __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n
   head(std::false_type{}, 0);
   substep(std::false_type{}, fn1, fm1, nullptr, 0, fn0, fm0, None{}, no_load);
 }
+
+// The fused epilogue on 8 consecutive columns n..n+7 of row m.
+__device__ __forceinline__ void epilogue8(const Epilogue& e, int m, int n, float* v) {
+  if (e.bias) {
+    f32x4 b0 = *reinterpret_cast<const f32x4*>(e.bias + n), b1 = *reinterpret_cast<const f32x4*>(e.bias + n + 4);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) { v[x] += b0[x]; v[4 + x] += b1[x]; }
+  }
+  if (e.pre) {
+    bf16x8 w;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) w[x] = (bf16_t)v[x];
+    *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16_t*>(e.pre) + (size_t)m * e.ldc + n) = w;
+  }
+  if (e.act == ACT_RELU) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = fmaxf(v[x], 0.f);
+  } else if (e.act == ACT_GELU) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = gelu_f(v[x]);
+  }
+  if (e.dact != ACT_NONE) {
+    bf16x8 s = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(e.dact_src) + (size_t)m * e.ldd + n);
+    if (e.dact == ACT_RELU) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] = (float)s[x] > 0.f ? v[x] : 0.f;
+    } else {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] *= dgelu_f((float)s[x]);
+    }
+  }
+  if (e.res) {
+    bf16x8 r = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(e.res) + (size_t)m * e.ldr + n);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] += (float)r[x];
+  }
+  if (e.c_f32) {
+    float* cp = reinterpret_cast<float*>(e.C) + (size_t)m * e.ldc + n;
+    if (e.accumulate) {
+      f32x4 c0 = *reinterpret_cast<const f32x4*>(cp), c1 = *reinterpret_cast<const f32x4*>(cp + 4);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) { v[x] += c0[x]; v[4 + x] += c1[x]; }
+    }
+    f32x4 o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
+    *reinterpret_cast<f32x4*>(cp) = o0;
+    *reinterpret_cast<f32x4*>(cp + 4) = o1;
+  } else {
+    bf16_t* cp = reinterpret_cast<bf16_t*>(e.C) + (size_t)m * e.ldc + n;
+    if (e.accumulate) {
+      bf16x8 c0 = *reinterpret_cast<const bf16x8*>(cp);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] += (float)c0[x];
+    }
+    bf16x8 w;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) w[x] = (bf16_t)v[x];
+    *reinterpret_cast<bf16x8*>(cp) = w;
+  }
+}
+
+// Per-column sums of a wave's rows around the first row's value (lane: 8 columns, every RPI-th row; the same in all lanes of
+// a column after reduce).
+template <int TN>
+struct ColumnSums {
+  float s0[8], s1[8], p[8];
+  __device__ __forceinline__ void add(const bf16x8& w, bool first, int lane) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const float v = (float)w[x];
+      if (first) { p[x] = __shfl(v, lane % (4 * TN), 64); s0[x] = 0.f; s1[x] = 0.f; }
+      const float t = v - p[x];
+      s0[x] += t;
+      s1[x] += t * t;
+    }
+  }
+  __device__ __forceinline__ void reduce(int) {
+#pragma unroll
+    for (int o = 4 * TN; o < 64; o <<= 1)
+#pragma unroll
+      for (int x = 0; x < 8; ++x) { s0[x] += __shfl_xor(s0[x], o, 64); s1[x] += __shfl_xor(s1[x], o, 64); }
+  }
+};
 
 // The epilogue's inputs and outputs in rows: each wave turns its sub-tile around in its own patch of the (now idle) LDS, so
 // that a lane holds 8 consecutive columns and every global access of 8 lanes is one whole 128-byte line (TN = 2).  In the
@@ -296,9 +385,10 @@ struct RowStore {
       for (int x = 0; x < 4; ++x) { bias[x] = b0[x]; bias[4 + x] = b1[x]; }
     }
   }
-  // `raw`: partial sums, stored as fp32 at raw[m * N + n]
+  // `raw`: partial sums, stored as fp32 at raw[m * N + n].  STATS: also the column sums of the stored bf16 values (whole tiles).
+  template <bool STATS>
   __device__ __forceinline__ void store(const Epilogue& e, const f32x16 (&acc)[TN][TM], char* patch, int mb, int nb, int M,
-                                        int N, int lane, float* raw) {
+                                        int N, int lane, float* raw, ColumnSums<TN>& cs) {
     const int li = lane & 31, hf = lane >> 5;
     const int rc = lane % LPR, n = nb + 8 * rc;
     const bool d = e.dact != ACT_NONE;
@@ -322,8 +412,8 @@ struct RowStore {
       const int row = (I % (IPJ * PJ)) * RPI + lane / LPR, m = mb + I * RPI + lane / LPR;
       const f32x4 a = *reinterpret_cast<const f32x4*>(patch + row * PITCH + 16 * slot(row, 2 * rc));
       const f32x4 b = *reinterpret_cast<const f32x4*>(patch + row * PITCH + 16 * slot(row, 2 * rc + 1));
-      if (m >= M || n >= N) continue;
-      if (raw) {
+      if (!STATS && (m >= M || n >= N)) continue;
+      if (!STATS && raw) {
         float* p = raw + (size_t)m * N + n;
         *reinterpret_cast<f32x4*>(p) = a;
         *reinterpret_cast<f32x4*>(p + 4) = b;
@@ -379,10 +469,36 @@ struct RowStore {
 #pragma unroll
         for (int x = 0; x < 8; ++x) w[x] = (bf16_t)v[x];
         *reinterpret_cast<bf16x8*>(cp) = w;
+        if (STATS) cs.add(w, I == 0, lane);
       }
     }
   }
 };
+
+// Sums `pieces` partial sums of 8 columns in order, eight loads in flight, and hands them to f.
+template <class F>
+__device__ __forceinline__ void add_pieces(const float* src, size_t slab, int pieces, F f) {
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  int s = 0;
+  for (; s + 4 <= pieces; s += 4) {
+    f32x4 a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a[u] = *reinterpret_cast<const f32x4*>(src + (s + u) * slab);
+      b[u] = *reinterpret_cast<const f32x4*>(src + (s + u) * slab + 4);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) { v[x] += a[u][x]; v[4 + x] += b[u][x]; }
+  }
+  for (; s < pieces; ++s) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(src + s * slab), b = *reinterpret_cast<const f32x4*>(src + s * slab + 4);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) { v[x] += a[x]; v[4 + x] += b[x]; }
+  }
+  f(v);
+}
 
 // Tile number -> coordinates: column-major groups of 8 tile rows, so that blocks that run together share operands.
 __device__ __forceinline__ void tile_coords(int q, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -398,4 +514,8 @@ __device__ __forceinline__ int xcd_range(int bid, int total) {
 }
 
 }  // namespace tile
+
+// The cheapest of the shapes in `mask` (bits: rows of the shape table) and cut for n products of one reduction length.
+TilePlan tile_plan(const OpCtx& c, int n, const int* M, const int* N, int K, unsigned mask, int max_pieces);
+
 }  // namespace lp

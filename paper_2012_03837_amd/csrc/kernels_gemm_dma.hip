@@ -30,10 +30,15 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <type_traits>
-#include "common.h"
-#include "gemm_common.h"
+#include "gemm_tile.h"
 
 namespace lp {
+
+using tile::Operand;
+using tile::nmap;
+using tile::to_lds;
+using tile::epilogue8;
+using tile::lds_bf16x4;
 
 namespace {
 
@@ -42,88 +47,12 @@ constexpr int BM = 256, BK = 32;
 // sub-tile around, so that each store instruction writes whole 128-byte lines (see store_subtile).
 constexpr int XPOSE_BYTES_PER_WAVE = 32 * 128;
 constexpr bool xpose_shape(int WNW, int TN, bool PIPE) { return PIPE && WNW == 4 && TN == 2; }
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
-struct Operand { const bf16_t* p; int64_t ld; int rows; };
-
-__device__ __forceinline__ int nmap(int i) {
-  int g = i >> 3, h = (i >> 2) & 1, j = i & 3;
-  return 16 * (g >> 1) + 8 * h + 4 * (g & 1) + j;
-}
-// 16 bytes per lane, global -> LDS, lane l's at dst + 16 l.  In assembly because of what the compiler does around the builtin:
-// it knows that the load writes LDS, not where, and puts an s_waitcnt vmcnt(0) in front of the next ds_read_b64_tr_b16, so
-// that the loops with a k-major operand had no load in flight behind their matrix instructions (alone, both operands k-major:
-// 32000 x 768 x 8192 449 -> 401 us, 8192 cubed 964 -> 851 us; a layer's four weight gradients 159 -> 140 us at width 768,
-// 256 -> 240 us at 1024).  Nothing is returned in registers; who reads the LDS waits with wait_loads_and_barrier.
-__device__ __forceinline__ void to_lds(const bf16_t* src, char* dst) {
-  const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0");
-}
 // Wait until at most VM of this wave's vector-memory loads are outstanding and its LDS reads have been done, then the barrier.
 // One asm statement with a memory clobber: the compiler neither moves LDS accesses across it nor turns
 // it into a full fence (a fence would wait for *all* loads, i.e. drain the pipeline every k-tile).
 template <int VM>
 __device__ __forceinline__ void wait_loads_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
-}
-
-// The fused epilogue on 8 consecutive columns of one row.
-__device__ __forceinline__ void epilogue8(const Epilogue& e, int m, int n, float* v) {
-  if (e.bias) {
-    f32x4 b0 = *reinterpret_cast<const f32x4*>(e.bias + n), b1 = *reinterpret_cast<const f32x4*>(e.bias + n + 4);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) { v[x] += b0[x]; v[4 + x] += b1[x]; }
-  }
-  if (e.pre) {
-    bf16x8 w;
-#pragma unroll
-    for (int x = 0; x < 8; ++x) w[x] = (bf16_t)v[x];
-    *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16_t*>(e.pre) + (size_t)m * e.ldc + n) = w;
-  }
-  if (e.act == ACT_RELU) {
-#pragma unroll
-    for (int x = 0; x < 8; ++x) v[x] = fmaxf(v[x], 0.f);
-  } else if (e.act == ACT_GELU) {
-#pragma unroll
-    for (int x = 0; x < 8; ++x) v[x] = gelu_f(v[x]);
-  }
-  if (e.dact != ACT_NONE) {
-    bf16x8 s = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(e.dact_src) + (size_t)m * e.ldd + n);
-    if (e.dact == ACT_RELU) {
-#pragma unroll
-      for (int x = 0; x < 8; ++x) v[x] = (float)s[x] > 0.f ? v[x] : 0.f;
-    } else {
-#pragma unroll
-      for (int x = 0; x < 8; ++x) v[x] *= dgelu_f((float)s[x]);
-    }
-  }
-  if (e.res) {
-    bf16x8 r = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(e.res) + (size_t)m * e.ldr + n);
-#pragma unroll
-    for (int x = 0; x < 8; ++x) v[x] += (float)r[x];
-  }
-  if (e.c_f32) {
-    float* cp = reinterpret_cast<float*>(e.C) + (size_t)m * e.ldc + n;
-    if (e.accumulate) {
-      f32x4 c0 = *reinterpret_cast<const f32x4*>(cp), c1 = *reinterpret_cast<const f32x4*>(cp + 4);
-#pragma unroll
-      for (int x = 0; x < 4; ++x) { v[x] += c0[x]; v[4 + x] += c1[x]; }
-    }
-    f32x4 o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
-    *reinterpret_cast<f32x4*>(cp) = o0;
-    *reinterpret_cast<f32x4*>(cp + 4) = o1;
-  } else {
-    bf16_t* cp = reinterpret_cast<bf16_t*>(e.C) + (size_t)m * e.ldc + n;
-    if (e.accumulate) {
-      bf16x8 c0 = *reinterpret_cast<const bf16x8*>(cp);
-#pragma unroll
-      for (int x = 0; x < 8; ++x) v[x] += (float)c0[x];
-    }
-    bf16x8 w;
-#pragma unroll
-    for (int x = 0; x < 8; ++x) w[x] = (bf16_t)v[x];
-    *reinterpret_cast<bf16x8*>(cp) = w;
-  }
 }
 
 // Per-lane global pointers of the direct-to-LDS loads of one operand: NI loads per thread per k-tile.

@@ -63,7 +63,9 @@ k_gemm_tile(TileGroup<NP> g) {
   multiply<SH, WGN, TM, TN, NST>(la, lb, tm * SH::BM, tn * SH::BN, t0, t1, g.K, smem, acc,
                                  [&] { if (!raw) out.prefetch(e, mb, nb, M, N, lane); });
   __syncthreads();                     // the stages become the waves' patches
-  out.store(e, acc, smem + wave * SH::PATCH, mb, nb, M, N, lane, raw ? g.ws + P.ws + (size_t)piece * M * N : nullptr);
+  ColumnSums<TN> none;
+  out.template store<false>(e, acc, smem + wave * SH::PATCH, mb, nb, M, N, lane, raw ? g.ws + P.ws + (size_t)piece * M * N : nullptr,
+                            none);
 }
 
 // Adds the pieces' partial sums in order and applies the epilogue; one thread per 8 columns, the problems one after the
@@ -83,26 +85,7 @@ __global__ void __launch_bounds__(256) k_tile_reduce(TileGroup<NP> g) {
   const int m = (int)(idx / n8), n = (int)(idx % n8) * 8;
   const size_t slab = (size_t)P.M * P.N;
   const float* src = g.ws + P.ws + (size_t)m * P.N + n;
-  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int s = 0;
-  for (; s + 4 <= g.splits; s += 4) {          // eight loads in flight
-    f32x4 a[4], b[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = *reinterpret_cast<const f32x4*>(src + (s + u) * slab);
-      b[u] = *reinterpret_cast<const f32x4*>(src + (s + u) * slab + 4);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int x = 0; x < 4; ++x) { v[x] += a[u][x]; v[4 + x] += b[u][x]; }
-  }
-  for (; s < g.splits; ++s) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(src + s * slab), b = *reinterpret_cast<const f32x4*>(src + s * slab + 4);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) { v[x] += a[x]; v[4 + x] += b[x]; }
-  }
-  mfma::epilogue8(P.e, m, n, v);
+  add_pieces(src, slab, g.splits, [&](float* v) { epilogue8(P.e, m, n, v); });
 }
 
 // Cost of a launch in microseconds: `fixed` (launch, first loads, epilogue), then per 64 of k `alone` where a compute unit has
@@ -111,6 +94,8 @@ struct TileShape { int bm, bn, per_cu; double fixed, alone, full, round; };
 const TileShape kShapes[kTileShapes] = {
     {64, 64, 2, 3.3, 0.27, 0.40, 1.8},   {128, 64, 2, 4.0, 0.30, 0.64, 3.1},  {128, 128, 2, 5.5, 0.52, 1.05, 5.7},
     {128, 128, 1, 5.8, 0.38, 0.70, 3.9}, {256, 128, 1, 6.0, 0.80, 0.95, 5.4}, {256, 256, 1, 8.0, 1.50, 1.62, 8.3},
+    {64, 128, 2, 4.0, 0.30, 0.64, 3.1},  {256, 64, 2, 9.0, 0.60, 1.10, 5.0},       // convolutions only
+    {128, 32, 4, 3.5, 0.25, 0.80, 2.0},
 };
 
 template <bool A_KC, bool B_KC, int WGM, int WGN, int TM, int TN, int NST, int NP>
@@ -182,25 +167,26 @@ hipError_t launch_group(const OpCtx& c, const GemmArgs* gs, int n, const TilePla
 // The cheapest tile shape and number of pieces for n products that share a launch.  Long reductions over few tiles are cut
 // into pieces of at least eight k-tiles, whose fp32 partial sums a second launch adds in order (4.5 TB/s and 4.6 us: what the
 // smallest launch costs behind another one).
-TilePlan gemm_tile_plan(const OpCtx& c, const GemmArgs* gs, int n) {
+TilePlan tile_plan(const OpCtx& c, int n, const int* M, const int* N, int K, unsigned mask, int max_pieces) {
   TilePlan best;
-  const int nt = (gs[0].K + KT - 1) / KT;
+  const int nt = (K + KT - 1) / KT;
   for (int s = 0; s < kTileShapes; ++s) {
+    if (!(mask >> s & 1)) continue;
     const TileShape& h = kShapes[s];
     long tiles = 0;
     double elems = 0.0;
     for (int i = 0; i < n; ++i) {
-      tiles += (long)((gs[i].M + h.bm - 1) / h.bm) * ((gs[i].N + h.bn - 1) / h.bn);
-      elems += (double)gs[i].M * gs[i].N;
+      tiles += (long)((M[i] + h.bm - 1) / h.bm) * ((N[i] + h.bn - 1) / h.bn);
+      elems += (double)M[i] * N[i];
     }
     if (tiles > (1L << 28)) continue;
-    int last = 0;
-    for (int sp = 1; sp <= 32; ++sp) {
+    int last = -1;
+    for (int sp = 1; sp <= max_pieces; ++sp) {
       if (sp > 1 && (!c.splitk_ws || nt < 8 * sp || sp * elems > (double)c.splitk_elems)) break;
       const int per = (nt + sp - 1) / sp;
       if (per == last) continue;
       last = per;
-      const int pieces = (nt + per - 1) / per;          // no piece is empty
+      const int pieces = per > 0 ? (nt + per - 1) / per : 1;          // no piece is empty
       const long blocks = tiles * pieces, slots = 256L * h.per_cu;
       double us = h.fixed;
       if (blocks <= 256) {
@@ -216,6 +202,11 @@ TilePlan gemm_tile_plan(const OpCtx& c, const GemmArgs* gs, int n) {
     }
   }
   return best;
+}
+TilePlan gemm_tile_plan(const OpCtx& c, const GemmArgs* gs, int n) {
+  int M[kTileGroup], N[kTileGroup];
+  for (int i = 0; i < n; ++i) { M[i] = gs[i].M; N[i] = gs[i].N; }
+  return tile_plan(c, n, M, N, gs[0].K, 0x3f, 32);
 }
 
 // n products (one, or up to kTileGroupMax of one reduction length and the same operand layouts), all of shapes that the

@@ -671,3 +671,38 @@ def test_gemm_tile_infinities(K, a_kc, b_kc):
         K.lpk_gemm(1, dev(Am, 1), Am.shape[1], a_kc, dev(Bm, 1), Bm.shape[1], b_kc, out, N, 1, M, N, Kd, variant=2)
         got = host(out)
         assert np.array_equal(np.isinf(got), want) and not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("N,H,W,C,O,R,stride", [
+    (3, 9, 7, 8, 16, 3, 1), (2, 5, 11, 64, 8, 3, 2), (5, 12, 12, 24, 72, 3, 2), (1, 33, 18, 40, 24, 5, 3), (4, 16, 16, 64, 64, 3, 1),
+    (2, 8, 8, 128, 200, 1, 2), (3, 4, 4, 192, 320, 3, 1), (37, 14, 14, 32, 32, 3, 1), (130, 16, 16, 64, 128, 3, 2)])
+def test_convolution_tiles(K, N, H, W, C, O, R, stride):
+    """Forward, data gradient and filter gradient (one piece, and cut along the pixels) at odd image sizes, channel counts on
+    both sides of a 64-deep k-tile, strides and filter sizes, against float64.  bf16 results: 4e-3; fp32 sums over at most
+    N H W pixels: 2e-6."""
+    import torch
+    import torch.nn.functional as F
+    rng = np.random.default_rng(H * W + C)
+    pad = R // 2
+    x, w = rnd(rng, (N, H, W, C), 1), rnd(rng, (O, R, R, C), 1, 0.2)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    dy = rnd(rng, (N, P, Q, O), 1)
+    tx = torch.from_numpy(x).double().permute(0, 3, 1, 2).requires_grad_()
+    tw = torch.from_numpy(w).double().permute(0, 3, 1, 2).requires_grad_()
+    ty = F.conv2d(tx, tw, stride=stride, padding=pad)
+    ty.backward(torch.from_numpy(dy).double().permute(0, 3, 1, 2))
+    dx_, dw_, dd = dev(x, 1), dev(w, 1), dev(dy, 1)
+    out = torch.full((N * P * Q + 1, O), 3.0, device="cuda", dtype=torch.bfloat16)
+    K.lpk_conv_fwd(1, dx_, dw_, out, N, H, W, C, O, R, stride, pad)
+    assert relerr(host(out[:-1]).reshape(N, P, Q, O), ty.detach().permute(0, 2, 3, 1).numpy()) <= 4e-3
+    assert bool((out[-1] == 3.0).all())
+    gx = torch.full((N * H * W + 1, C), 3.0, device="cuda", dtype=torch.bfloat16)
+    K.lpk_conv_bwd_data(1, dd, dw_, gx, N, H, W, C, O, R, stride, pad)
+    assert relerr(host(gx[:-1]).reshape(N, H, W, C), tx.grad.permute(0, 2, 3, 1).numpy()) <= 4e-3
+    assert bool((gx[-1] == 3.0).all())
+    want = tw.grad.permute(0, 2, 3, 1).numpy()
+    gw = zeros(O, R, R, C)
+    K.lpk_conv_bwd_weight(1, dd, dx_, gw, N, H, W, C, O, R, stride, pad)
+    assert relerr(host(gw), want) <= 2e-6
+    K.lpk_conv_bwd_weight_ws(1, dd, dx_, gw, N, H, W, C, O, R, stride, pad, zeros(1 << 22), accumulate=1)
+    assert relerr(host(gw), 2 * want) <= 2e-6
