@@ -13,7 +13,7 @@
 //             dK^T[dh, key] += Q^T dS
 // P and dS of heads of 64 are rounded to bf16 for the second products; those of narrower heads stay in fp32 (split8).
 // Three matrix instructions instead of one there, measured over the rounded form: 64 sequences of 128, 8 heads of 16,
-// forward 7.1 -> 7.9 us, backward 18.7 -> 22.8 us; 4 of 2048, 8 heads of 32, 29.2 -> 46.2 us and 77 -> 122 us.
+// forward 7.1 -> 7.9 us, backward 18.7 -> 22.8 us; 4 of 2048, 8 heads of 32, 29.2 -> 46.2 us and 77 -> 122 us (backward: both launches).
 // The accumulator layout of v_mfma_f32_32x32x16_bf16 (value v of lane l: row 8*(v/4) + 4*(l/32) + v%4,
 // column l%32) is exactly the B-operand layout of the next MFMA over the row index, so P and dS
 // never pass through LDS.  Operands whose reduction index is the slow one in memory (V for the
@@ -128,6 +128,18 @@ struct TileRegs {
       for (int i = 0; i < NCH; ++i) v[i] = *reinterpret_cast<const bf16x8*>(p + 8 * i);
     }
   }
+  // out[r] = the dot product of this tile's row r with the other tile's (fp32; a row's threads are neighbours)
+  __device__ __forceinline__ void row_dots(const TileRegs& other, float* out) const {
+    const int r = threadIdx.x / TPR;
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += (float)v[i][e] * (float)other.v[i][e];
+#pragma unroll
+    for (int x = 1; x < TPR; x <<= 1) s += __shfl_xor(s, x, 64);
+    if ((ALL || r < 64) && threadIdx.x % TPR == 0) out[r] = s;
+  }
   // Narrow heads: tiles that hold an infinity or a NaN are marked in `bad` (see the tile loops).
   __device__ __forceinline__ void mark(int* bad, int tile) const {
     if constexpr (DH < 64) {
@@ -172,8 +184,8 @@ __device__ __forceinline__ void add_row(f32x16 (&acc)[ND], const bf16_t* row, fl
 // gaps, every XCD gets the same mix when B*H is a multiple of 8, and all blocks of one head and batch entry
 // run on one XCD, whose L2 then serves their shared K and V (or Q and dO) tiles.
 struct AttnBlock { int x, h, b; };
-__device__ __forceinline__ AttnBlock attn_block(int H, int BH, int nblk, bool heavy_last) {
-  const int cls = blockIdx.x / BH, bh = blockIdx.x % BH;
+__device__ __forceinline__ AttnBlock attn_block(int index, int H, int BH, int nblk, bool heavy_last) {
+  const int cls = index / BH, bh = index % BH;
   AttnBlock a;
   a.x = heavy_last ? nblk - 1 - cls : cls;
   a.h = bh % H;
@@ -189,7 +201,7 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
   __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
   __shared__ int bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
-  const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
+  const AttnBlock ab = attn_block(blockIdx.x, H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
   constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
@@ -316,17 +328,24 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
   }
 }
 
-// ================================================================================= backward: dQ
+// ================================================================================= backward
+// LDS of a backward block: its two streamed tiles (K and V, or Q and dO) and, for dK/dV, the rows' statistics.
 template <int DH>
-__global__ void __launch_bounds__(256, DH == 64 ? 2 : 3) k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
-                                                          const float* __restrict__ lse,
-                                                          const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv,
-                                                          float* __restrict__ delta, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
-  __shared__ int bad;
+struct BwdLds {
+  __attribute__((aligned(16))) bf16_t t0[64][kAld<DH>], t1[64][kAld<DH>];
+  __attribute__((aligned(16))) float lse2s[64], deltas[64];
+  int bad;
+};
+
+// ---------------------------------------------------------------------------------- dQ (and delta = rowsum(dO * O))
+template <int DH>
+__device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                            const float* __restrict__ lse, const bf16_t* __restrict__ dout,
+                                            bf16_t* __restrict__ dqkv, float* __restrict__ delta, int S, int H, int causal) {
+  auto& Ks = sm.t0;
+  auto& Vs = sm.t1;
+  int& bad = sm.bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
-  const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, causal != 0);
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
   constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
@@ -452,26 +471,27 @@ __global__ void __launch_bounds__(256, DH == 64 ? 2 : 3) k_attn_bwd_dq_mfma(cons
   }
 }
 
-// ================================================================================= backward: dK, dV
-template <int DH>
-__global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv,
-                                                           const float* __restrict__ lse,
-                                                           const float* __restrict__ delta,
-                                                           const bf16_t* __restrict__ dout,
-                                                           bf16_t* __restrict__ dqkv, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[64][kAld<DH>];
-  __shared__ __attribute__((aligned(16))) bf16_t dOs[64][kAld<DH>];
-  __shared__ __attribute__((aligned(16))) float lse2s[64];
-  __shared__ __attribute__((aligned(16))) float deltas[64];
-  __shared__ int bad;
+// ---------------------------------------------------------------------------------- dK, dV
+// OWN_DELTA: a query tile's deltas are taken from its dO and O rows as they come by (a read of O more per key block), so that
+// these blocks do not wait for the dQ blocks and both kinds can share a launch.
+template <int DH, bool OWN_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                             const float* __restrict__ lse, const float* __restrict__ delta,
+                                             const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv, int S, int H,
+                                             int causal) {
+  auto& Qs = sm.t0;
+  auto& dOs = sm.t1;
+  auto& lse2s = sm.lse2s;
+  auto& deltas = sm.deltas;
+  int& bad = sm.bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
-  const AttnBlock ab = attn_block(H, BH, (S + 127) / 128, false);
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
   constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
   const bf16_t* dob = dout + (size_t)b * S * d;
+  const bf16_t* ob = o + (size_t)b * S * d;
   const int k0w = bx * 128 + wave * 32, kj = k0w + n;
   bf16x8 kf[NK], vf[NK];
 #pragma unroll
@@ -490,9 +510,10 @@ __global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(con
   const float scale = kScale<DH>, c = scale * kLog2e;
   const int t_begin = causal ? (bx * 128) / 64 : 0;
   const int t_end = (S + 63) / 64;
-  TileRegs<DH> qr, dor;
+  TileRegs<DH> qr, dor, orow;
   qr.load(base + h * DH, ld, t_begin * 64, S);
   dor.load(dob + h * DH, (size_t)d, t_begin * 64, S);
+  if (OWN_DELTA) orow.load(ob + h * DH, (size_t)d, t_begin * 64, S);
   if (DH < 64 && threadIdx.x == 0) bad = -1;
   for (int it = t_begin; it < t_end; ++it) {
     const int q0 = it * 64;
@@ -501,15 +522,17 @@ __global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(con
     dor.store(dOs);
     qr.mark(&bad, it);
     dor.mark(&bad, it);
+    if (OWN_DELTA) dor.row_dots(orow, deltas);
     if (it + 1 < t_end) {
       qr.load(base + h * DH, ld, q0 + 64, S);
       dor.load(dob + h * DH, (size_t)d, q0 + 64, S);
+      if (OWN_DELTA) orow.load(ob + h * DH, (size_t)d, q0 + 64, S);
     }
     if (threadIdx.x < 64) {
       int q = q0 + threadIdx.x;
-      size_t si = ((size_t)b * H + h) * S + q;
+      const size_t si = ((size_t)b * H + h) * S + q;
       lse2s[threadIdx.x] = q < S ? lse[si] * kLog2e : 0.f;
-      deltas[threadIdx.x] = q < S ? delta[si] : 0.f;
+      if (!OWN_DELTA) deltas[threadIdx.x] = q < S ? delta[si] : 0.f;
     }
     __syncthreads();
     const bool active = k0w < S && (!causal || q0 + 63 >= k0w);
@@ -604,6 +627,37 @@ __global__ void __launch_bounds__(256, DH == 16 ? 3 : 2) k_attn_bwd_dkv_mfma(con
   }
 }
 
+// Both kinds of blocks in one launch, eight of one kind and eight of the other in turn (an XCD gets both, and the heaviest of
+// both start first).  Apart, few blocks leave the chip half empty twice: 5 x 511, 7 heads of 64 (140 blocks of a kind)
+// 37.2 -> 23.3 us, 2 x 1100, 5 heads 66.4 -> 38.8, 3 x 200, 2 heads 22.1 -> 12.8.  With 512 blocks of a kind, two to a compute
+// unit, they are level (64 x 128, 8 heads of 16: 23.0 and 23.4; 4 x 2048, 8 heads of 32: 128 and 120), with more the launches apart win
+// (4 x 2048, 16 heads of 64: 163 against 184): one kind's blocks share their tiles in L2.
+constexpr int kBwdTogether = 512;
+enum BwdKind { BWD_BOTH, BWD_DQ, BWD_DKV };
+template <int DH, BwdKind KIND>
+__global__ void __launch_bounds__(256, KIND == BWD_DQ ? (DH == 64 ? 2 : 3) : (DH == 16 ? 3 : 2))
+k_attn_bwd_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
+                const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv, float* __restrict__ delta, int S, int H, int BH, int causal) {
+  __shared__ BwdLds<DH> sm;
+  const int nblk = (S + 127) / 128, n = nblk * BH, n8 = n & ~7, L = blockIdx.x;
+  bool dq = KIND == BWD_DQ;
+  int index = L;
+  if (KIND == BWD_BOTH) {
+    if (L < 2 * n8) {
+      dq = (L >> 3) & 1;
+      index = (L >> 4) * 8 + (L & 7);
+    } else {
+      const int r = L - 2 * n8;
+      dq = r >= n - n8;
+      index = n8 + (dq ? r - (n - n8) : r);
+    }
+  }
+  if (KIND != BWD_DKV && dq)
+    attn_bwd_dq<DH>(attn_block(index, H, BH, nblk, causal != 0), sm, qkv, o, lse, dout, dqkv, delta, S, H, causal);
+  else if (KIND != BWD_DQ)
+    attn_bwd_dkv<DH, KIND == BWD_BOTH>(attn_block(index, H, BH, nblk, false), sm, qkv, o, lse, delta, dout, dqkv, S, H, causal);
+}
+
 template <int DH>
 static hipError_t attn_fwd_t(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
   const int grid = ((S + 127) / 128) * H * B;
@@ -613,11 +667,14 @@ static hipError_t attn_fwd_t(const OpCtx& c, const void* qkv, void* o, float* ls
 template <int DH>
 static hipError_t attn_bwd_t(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                              void* dqkv, float* delta, int B, int S, int H, int causal) {
-  const int grid = ((S + 127) / 128) * H * B;
-  k_attn_bwd_dq_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)dout,
-                                                     (bf16_t*)dqkv, delta, S, H, H * B, causal);
-  k_attn_bwd_dkv_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, lse, delta, (const bf16_t*)dout, (bf16_t*)dqkv,
-                                                      S, H, H * B, causal);
+  const int n = ((S + 127) / 128) * H * B;
+  const bf16_t *q = (const bf16_t*)qkv, *out = (const bf16_t*)o, *dy = (const bf16_t*)dout;
+  if (n <= kBwdTogether) {
+    k_attn_bwd_mfma<DH, BWD_BOTH><<<2 * n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
+  } else {
+    k_attn_bwd_mfma<DH, BWD_DQ><<<n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
+    k_attn_bwd_mfma<DH, BWD_DKV><<<n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
+  }
   return hipGetLastError();
 }
 bool attn_mfma_ok(int dh) { return dh == 16 || dh == 32 || dh == 64; }
