@@ -97,6 +97,25 @@ struct Profiler {
   std::map<std::string, KernelTotal> by_kernel;
 };
 
+// Partial sums that a chain of work has left and that one launch adds later (op_add_pending): the parameter gradients of a
+// layer's normalisations and its bias gradients, which nothing before the update reads.  A launch behind another one costs
+// 4.6 us however little it does.
+constexpr int kMaxPending = 12;
+struct PendingSums {
+  float* buf = nullptr;
+  size_t cap = 0, used = 0;
+  int count = 0;
+  struct Sum { const float* part; float* out; int nblk, n, accumulate; } s[kMaxPending];
+  // room for `sums` more of `floats` partial sums in all
+  float* take(size_t floats, int sums) {
+    if (!buf || used + floats > cap || count + sums > kMaxPending) return nullptr;
+    float* p = buf + used;
+    used += floats;
+    return p;
+  }
+  void add(const float* part, float* out, int nblk, int n, int accumulate) { s[count++] = Sum{part, out, nblk, n, accumulate}; }
+};
+
 struct OpCtx {
   hipStream_t stream;
   int dt;              // compute dtype
@@ -106,6 +125,7 @@ struct OpCtx {
   int gemm_variant = 0;         // 0: chosen by the cost model; otherwise a forced GEMM kernel (see lpk_gemm)
   float* splitk_ws = nullptr;   // fp32 workspace for split-K partial sums (may be null: no split-K)
   size_t splitk_elems = 0;
+  PendingSums* pending = nullptr;   // where op_layernorm_bwd and op_colsum_batched may leave their sums (null: nowhere)
 };
 
 // RAII bracket: records an event pair around the launches of one op when profiling is on.
@@ -150,10 +170,14 @@ hipError_t op_layernorm_fwd(const OpCtx& c, const void* x, const float* g, const
 hipError_t op_layernorm_bwd(const OpCtx& c, const void* dy, const void* x, const float* mean, const float* rstd,
                             const float* g, const void* add, void* dx, float* dg, float* db, int rows, int d,
                             int accumulate);
+constexpr int kLnFastRows = 16;      // rows per block, and per partial sum of dg and db, of the vectorised backward kernel
 hipError_t op_colsum(const OpCtx& c, const void* dy, int64_t ld, float* out, int rows, int n, int accumulate);
 // count (<= 4 for the single pair of launches) column sums over the same rows; the same bits as op_colsum one by one
 hipError_t op_colsum_batched(const OpCtx& c, int count, const void* const* dy, const int64_t* ld, float* const* out,
                              int rows, const int* n, int accumulate);
+
+// Adds what is pending, in one launch (the same bits as at once).
+hipError_t op_add_pending(const OpCtx& c);
 
 hipError_t op_attn_fwd(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh,
                        int causal);

@@ -91,6 +91,7 @@ struct lp_scratch {
   float* partial = nullptr; size_t partial_elems = 0;
   float* splitk_ws = nullptr; size_t splitk_elems = 0;
   float* loss_rows = nullptr;
+  float* pend_buf = nullptr; size_t pend_elems = 0;     // decoder: partial sums left for one launch (PendingSums)
   // backward scratch
   void *dA = nullptr, *dB = nullptr, *dF = nullptr, *dc = nullptr, *du = nullptr, *dO = nullptr, *dqkv = nullptr,
        *da = nullptr;
@@ -189,10 +190,19 @@ struct lp_ctx : lp_scratch {
   int mean_rows = 0;
   float* mean_out = nullptr;
 
+  // Sums left by the chain being issued (one scratch set, one stream from its head to its update).  Not in the grouped
+  // schedule, which walks several chains at once.
+  mutable lp::PendingSums pend;
+
   mutable lp::Profiler prof;
   lp::OpCtx op() const {
     lp::OpCtx c; c.stream = cur_stream; c.dt = dt; c.partial = partial; c.partial_elems = partial_elems;
-    c.prof = &prof; c.splitk_ws = splitk_ws; c.splitk_elems = splitk_elems; return c;
+    c.prof = &prof; c.splitk_ws = splitk_ws; c.splitk_elems = splitk_elems;
+    if (!lockstep) {
+      if (pend.count == 0) { pend.buf = pend_buf; pend.cap = pend_elems; pend.used = 0; }
+      c.pending = &pend;
+    }
+    return c;
   }
   float* P32(int ti) const { return master + tensors[ti].off; }
   float* G32(int ti) const { return grads + tensors[ti].off; }

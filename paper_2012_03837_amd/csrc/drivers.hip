@@ -223,6 +223,7 @@ int dec_backward_stage(lp_ctx* c, int li, int batch, const void* dout, void* dx,
       float* outs[4] = {c->G32(L.t["b2"]), c->G32(L.t["b1"]), c->G32(L.t["bo"]), c->G32(L.t["bqkv"])};
       const int ns[4] = {d, F, d, 3 * d};
       DO(op_colsum_batched(o, 4, dys, lds, outs, T, ns, acc));
+      DO(op_add_pending(o));         // these, both normalisations' gradients and, behind a head, its normalisation's
       for (int i = 0; i < 4; ++i) out->g[out->n++] = L.wg[i];
     }
   }

@@ -291,6 +291,17 @@ __global__ void k_ln_bwd(const T* dy, const T* x, const float* mean, const float
 // order (four independent loads in flight at a time) and the sixteen group sums are then added in order:
 // a fixed tree, so the result does not depend on the launch.
 constexpr int kReduceGroups = 16;
+__device__ __forceinline__ float group_sum(const float* __restrict__ partial, int nblk, int n, int j, int q) {
+  float a = 0.f;
+  int b = q;
+  for (; b + 3 * kReduceGroups < nblk; b += 4 * kReduceGroups) {
+    float v0 = partial[(size_t)b * n + j], v1 = partial[(size_t)(b + kReduceGroups) * n + j];
+    float v2 = partial[(size_t)(b + 2 * kReduceGroups) * n + j], v3 = partial[(size_t)(b + 3 * kReduceGroups) * n + j];
+    a += v0; a += v1; a += v2; a += v3;
+  }
+  for (; b < nblk; b += kReduceGroups) a += partial[(size_t)b * n + j];
+  return a;
+}
 __global__ void __launch_bounds__(64 * kReduceGroups)
 k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out, int accumulate,
                   float* out_y1 = nullptr) {
@@ -299,17 +310,7 @@ k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out
   __shared__ float sh[kReduceGroups][64];
   int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
   int j = blockIdx.x * 64 + lc;
-  float a = 0.f;
-  if (j < n) {
-    int b = q;
-    for (; b + 3 * kReduceGroups < nblk; b += 4 * kReduceGroups) {
-      float v0 = partial[(size_t)b * n + j], v1 = partial[(size_t)(b + kReduceGroups) * n + j];
-      float v2 = partial[(size_t)(b + 2 * kReduceGroups) * n + j], v3 = partial[(size_t)(b + 3 * kReduceGroups) * n + j];
-      a += v0; a += v1; a += v2; a += v3;
-    }
-    for (; b < nblk; b += kReduceGroups) a += partial[(size_t)b * n + j];
-  }
-  sh[q][lc] = a;
+  sh[q][lc] = j < n ? group_sum(partial, nblk, n, j, q) : 0.f;
   __syncthreads();
   if (q == 0 && j < n) {
     float t = 0.f;
@@ -317,6 +318,42 @@ k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out
     for (int g = 0; g < kReduceGroups; ++g) t += sh[g][lc];
     out[j] = accumulate ? out[j] + t : t;
   }
+}
+struct PendingTable { PendingSums::Sum s[kMaxPending]; int first[kMaxPending]; int count; };
+__global__ void __launch_bounds__(64 * kReduceGroups) k_add_pending(PendingTable t) {
+  __shared__ float sh[kReduceGroups][64];
+  int p = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxPending; ++i)
+    if (i < t.count && (int)blockIdx.x >= t.first[i]) p = i;
+  const float* part = t.s[p].part;
+  const int n = t.s[p].n, nblk = t.s[p].nblk;
+  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6, j = (blockIdx.x - t.first[p]) * 64 + lc;
+  sh[q][lc] = j < n ? group_sum(part, nblk, n, j, q) : 0.f;
+  __syncthreads();
+  if (q == 0 && j < n) {
+    float v = 0.f;
+#pragma unroll
+    for (int g = 0; g < kReduceGroups; ++g) v += sh[g][lc];
+    float* out = t.s[p].out;
+    out[j] = t.s[p].accumulate ? out[j] + v : v;
+  }
+}
+hipError_t op_add_pending(const OpCtx& c) {
+  PendingSums* ps = c.pending;
+  if (!ps || ps->count == 0) return hipSuccess;
+  ProfScope prof_(c, KC_COLSUM);
+  PendingTable t = {};
+  int blocks = 0;
+  for (int i = 0; i < ps->count; ++i) {
+    t.s[i] = ps->s[i];
+    t.first[i] = blocks;
+    blocks += (ps->s[i].n + 63) / 64;
+  }
+  t.count = ps->count;
+  ps->count = 0; ps->used = 0;
+  k_add_pending<<<blocks, 64 * kReduceGroups, 0, c.stream>>>(t);
+  return LP_LAUNCH_CHECK();
 }
 hipError_t op_reduce_partials(const OpCtx& c, const float* partial, int nblk, int n, float* out, int accumulate) {
   k_reduce_partials<<<(n + 63) / 64, 64 * kReduceGroups, 0, c.stream>>>(partial, nblk, n, out, accumulate);
@@ -329,6 +366,16 @@ hipError_t op_layernorm_bwd(const OpCtx& c, const void* dy, const void* x, const
   if (rows == 0) return hipSuccess;
   if (ln_fast_ok(c, dy, x, add, dx, d)) {
     int nb = 0;
+    const size_t need = (size_t)((rows + kLnFastRows - 1) / kLnFastRows) * d * 2;
+    if (float* later = c.pending && dg ? c.pending->take(need, 2) : nullptr) {
+      OpCtx cc = c;
+      cc.partial = later; cc.partial_elems = need;
+      hipError_t e = ln_bwd_fast(cc, dy, x, mean, rstd, g, add, dx, rows, d, &nb);
+      if (e != hipSuccess) return e;
+      c.pending->add(later, dg, nb, d, accumulate);
+      c.pending->add(later + (size_t)nb * d, db, nb, d, accumulate);
+      return hipSuccess;
+    }
     hipError_t e = ln_bwd_fast(c, dy, x, mean, rstd, g, add, dx, rows, d, &nb);
     if (e != hipSuccess || !dg) return e;          // no dg: the caller wants the input gradient only
     k_reduce_partials<<<dim3((d + 63) / 64, 2), 64 * kReduceGroups, 0, c.stream>>>(c.partial, nb, d, dg, accumulate, db);
@@ -479,17 +526,7 @@ k_reduce_partials_batched(ColsumBatch b, const float* __restrict__ partial, int 
   float* out = b.out[p];
   int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
   int j = (blockIdx.x - b.first64[p]) * 64 + lc;
-  float a = 0.f;
-  if (j < n) {
-    int r = q;
-    for (; r + 3 * kReduceGroups < nblk; r += 4 * kReduceGroups) {
-      float v0 = part[(size_t)r * n + j], v1 = part[(size_t)(r + kReduceGroups) * n + j];
-      float v2 = part[(size_t)(r + 2 * kReduceGroups) * n + j], v3 = part[(size_t)(r + 3 * kReduceGroups) * n + j];
-      a += v0; a += v1; a += v2; a += v3;
-    }
-    for (; r < nblk; r += kReduceGroups) a += part[(size_t)r * n + j];
-  }
-  sh[q][lc] = a;
+  sh[q][lc] = j < n ? group_sum(part, nblk, n, j, q) : 0.f;
   __syncthreads();
   if (q == 0 && j < n) {
     float t = 0.f;
@@ -508,7 +545,8 @@ hipError_t op_colsum_batched(const OpCtx& c, int count, const void* const* dy, c
     fast = fast && n[p] > 0 && n[p] % 8 == 0 && ld[p] % 8 == 0 && ((uintptr_t)dy[p] & 15) == 0;
     total += (size_t)nslab * n[p];
   }
-  if (!fast || total > c.partial_elems) {         // one by one: any type, any alignment
+  float* later = fast && c.pending ? c.pending->take(total, count) : nullptr;
+  if (!later && (!fast || total > c.partial_elems)) {         // one by one: any type, any alignment
     for (int p = 0; p < count; ++p) {
       hipError_t e = op_colsum(c, dy[p], ld[p], out[p], rows, n[p], accumulate);
       if (e != hipSuccess) return e;
@@ -526,6 +564,11 @@ hipError_t op_colsum_batched(const OpCtx& c, int count, const void* const* dy, c
     f128 += (n[p] + 127) / 128; f64 += (n[p] + 63) / 64; off += (size_t)nslab * n[p];
   }
   for (int p = count; p <= kMaxColsumBatch; ++p) { b.first128[p] = f128; b.first64[p] = f64; }
+  if (later) {
+    k_colsum_partial_batched<<<dim3(f128, nslab), 256, 0, c.stream>>>(b, later, rows);
+    for (int p = 0; p < count; ++p) c.pending->add(later + b.part_off[p], out[p], nslab, n[p], accumulate);
+    return LP_LAUNCH_CHECK();
+  }
   k_colsum_partial_batched<<<dim3(f128, nslab), 256, 0, c.stream>>>(b, c.partial, rows);
   k_reduce_partials_batched<<<f64, 64 * kReduceGroups, 0, c.stream>>>(b, c.partial, nslab, accumulate);
   return LP_LAUNCH_CHECK();

@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) k_ln_fwd_v(const bf16_t* __restrict__ x, 
   if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
 }
 
-constexpr int kRowsPerBlock = 16;
+constexpr int kRowsPerBlock = kLnFastRows;
 // Backward; block partials of dg and db go to partial[blk][d] and partial[nblk + blk][d].  A wave owns four
 // rows of its block's sixteen and keeps the next row's loads (x, dy and the addend, 16 bytes per lane each) in
 // flight while it reduces and writes the current one: with one row at a time the kernel is a chain of memory

@@ -386,6 +386,9 @@ static void plan(lp_ctx* c, const lp_buffers* buf, lp_sizes* sizes) {
       S.dF = wa.take(T * F * es); S.dc = wa.take(T * d * es); S.du = wa.take(T * d * es);
       S.dO = wa.take(T * d * es); S.dqkv = wa.take(T * 3 * d * es); S.da = wa.take(T * d * es);
       S.delta = (float*)wa.take(T * l.n_heads * 4);
+      // gain and shift gradients of a head's and a layer's two normalisations, and the layer's four bias gradients
+      S.pend_elems = 3 * 2 * ((T + kLnFastRows - 1) / kLnFastRows) * d + ((T + 127) / 128) * (F + 5 * d);
+      S.pend_buf = (float*)wa.take(S.pend_elems * 4);
     } else if (kind0 == LP_LAYER_RESMLP) {
       S.dA = wa.take(max_act * es); S.dB = wa.take(max_act * es);
       S.dF = wa.take(max_act * es); S.dc = wa.take(max_act * es);
@@ -698,6 +701,7 @@ static int update_block(lp_ctx* c, int hi, int t, F done) {
     CK(op_gemm_grouped(c->op(), c->waiting.data(), (int)c->waiting.size()));
     c->waiting.clear();
   }
+  CK(op_add_pending(c->op()));      // nor these sums
   Updater u(c, t);
   int st = LP_OK;
   if (c->mean_rows > 0) st = u.mean(c->loss_rows, c->mean_rows, c->mean_out);
@@ -963,7 +967,7 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
   const bool side = train && c->n_side > 0 && !c->prof.on && !c->one_stream;
   const bool overlap = side && c->overlap_steps && batch > 0 && c->spec.schedule == LP_SCHED_SYNC;
   if (!overlap && (st = join_pending(c)) != LP_OK) return st;
-  c->waiting.clear(); c->mean_rows = 0;      // nothing is left over from a call that failed
+  c->waiting.clear(); c->mean_rows = 0; c->pend.count = 0;      // nothing is left over from a call that failed
   c->mean_with_update = train && !c->lockstep;
   if (train && batch > 0 && c->spec.schedule != LP_SCHED_SYNC) return run_pipelined(c, x, y, batch, losses);
   for (int li = 1; li <= L; ++li) c->layers[li].in_override = nullptr;
