@@ -183,10 +183,146 @@ __global__ void k_embed_bwd(const int32_t* ids, const int* __restrict__ counts, 
     if (n_hits != 0 || !accumulate) demb[o] = accumulate ? demb[o] + acc : acc;
   }
 }
+// The same sums from a sorted list of positions.  A block per table row that scans all ids and then adds its rows one after
+// another is a chain of memory latencies: the most frequent of 8192 Zipf-distributed ids has 1150 rows, and the launch took
+// 141 us at width 128, behind 24 us of counting.  Here the positions are sorted by (id, position) first: a
+// position's place is the number of smaller keys, counted by comparing it with all others (T^2 / 64 wave compares, about
+// 8 us for 8192 positions on half the compute units; the other blocks of the launch clear the table meanwhile).  Then rows of
+// up to 32 positions are added by a wave each, in position order, longer ones by a block of 1024 threads whose row lanes add
+// every RL-th row, eight loads in flight, and are added in order.  Alone, both launches: 8192 positions, 8000 ids of width 128
+// 70 -> 21 us; 32000 of 768 172 -> 41; 2048 positions, 16000 of 512 36 -> 16.
+constexpr int kEmbedShort = 32, kEmbedKeys = 8192;
+__global__ void __launch_bounds__(1024) k_embed_order(const int32_t* __restrict__ ids, int T_, int V, int* __restrict__ order,
+                                                      int* __restrict__ sorted, float* __restrict__ demb, size_t clear4, int sort_blocks) {
+  if ((int)blockIdx.x >= sort_blocks) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    for (size_t i = (size_t)(blockIdx.x - sort_blocks) * 1024 + threadIdx.x; i < clear4; i += (size_t)(gridDim.x - sort_blocks) * 1024)
+      reinterpret_cast<f32x4*>(demb)[i] = zero;
+    return;
+  }
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  __shared__ int sh[16][64];
+  __shared__ __attribute__((aligned(16))) int keys[kEmbedKeys];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = blockIdx.x * 64 + lane;
+  const int id = t < T_ ? clamp_id(ids[t], V) : V;
+  const int key = t < T_ ? id * T_ + t : 0x7fffffff;      // V * T fits in 31 bits
+  int n = 0;
+  for (int base = 0; base < T_; base += kEmbedKeys) {     // a tile of keys in LDS, a sixteenth of it for each wave
+    const int len = T_ - base < kEmbedKeys ? T_ - base : kEmbedKeys, per = ((len + 63) / 64) * 4;
+    __syncthreads();
+    for (int j = threadIdx.x; j < 16 * per; j += 1024) keys[j] = j < len ? clamp_id(ids[base + j], V) * T_ + base + j : 0x7fffffff;
+    __syncthreads();
+#pragma unroll 4
+    for (int j = w * per; j < (w + 1) * per; j += 4) {
+      const i32x4 k = *reinterpret_cast<const i32x4*>(keys + j);
+      n += (k[0] < key ? 1 : 0) + (k[1] < key ? 1 : 0) + (k[2] < key ? 1 : 0) + (k[3] < key ? 1 : 0);
+    }
+  }
+  sh[w][lane] = n;
+  __syncthreads();
+  if (w == 0 && t < T_) {
+    int at = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) at += sh[i][lane];
+    order[at] = t;
+    sorted[at] = id;
+  }
+}
+__device__ __forceinline__ void add8(const bf16_t* p, float* a) {
+  const bf16x8 v = *reinterpret_cast<const bf16x8*>(p);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] += (float)v[e];
+}
+__device__ __forceinline__ void add8(const float* p, float* a) {
+  const f32x4 v = *reinterpret_cast<const f32x4*>(p), u = *reinterpret_cast<const f32x4*>(p + 4);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { a[e] += v[e]; a[4 + e] += u[e]; }
+}
+template <typename T>
+__global__ void __launch_bounds__(1024) k_embed_rows(const int* __restrict__ order, const int* __restrict__ sorted,
+                                                     const T* __restrict__ dh, float* __restrict__ demb, int T_, int d, int accumulate,
+                                                     int short_blocks) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), CH = d >> 3;
+  if ((int)blockIdx.x < short_blocks) {          // a wave per position that starts a row
+    const int p = blockIdx.x * 16 + w;
+    if (p >= T_) return;
+    const int v = sorted[p];
+    if (p > 0 && sorted[p - 1] == v) return;
+    const bool mine = lane <= kEmbedShort && p + lane < T_ && sorted[p + lane] == v;
+    const int n = __popcll(__ballot(mine));
+    if (n > kEmbedShort) return;
+    const int at = mine ? order[p + lane] : 0;
+    for (int c = lane; c < CH; c += 64) {
+      float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int r = 0; r < n; ++r) add8(dh + (size_t)__builtin_amdgcn_readlane(at, r) * d + 8 * c, a);
+      float* o = demb + (size_t)v * d + 8 * c;
+      if (accumulate) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] += o[e];
+      }
+      *reinterpret_cast<f32x4*>(o) = f32x4{a[0], a[1], a[2], a[3]};
+      *reinterpret_cast<f32x4*>(o + 4) = f32x4{a[4], a[5], a[6], a[7]};
+    }
+    return;
+  }
+  // Long rows: every one holds a position that is a multiple of kEmbedShort; the block of the first such position takes it.
+  __shared__ int pos[1024];
+  __shared__ float red[1024 * 8];
+  const int p0 = (blockIdx.x - short_blocks) * kEmbedShort, v = sorted[p0];
+  if (p0 >= kEmbedShort && sorted[p0 - kEmbedShort] == v) return;
+  const int before = p0 - 1 - lane;
+  const int start = p0 - __popcll(__ballot(lane < kEmbedShort && before >= 0 && sorted[before >= 0 ? before : 0] == v));
+  if (start + kEmbedShort >= T_ || sorted[start + kEmbedShort] != v) return;
+  const int RL = 1024 / CH, rl = threadIdx.x / CH, c = threadIdx.x - rl * CH;
+  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int base = start;; base += 1024) {
+    const int i = base + threadIdx.x;
+    const bool mine = i < T_ && sorted[i] == v;
+    pos[threadIdx.x] = mine ? order[i] : 0;
+    const int n = __syncthreads_count(mine);
+    if (rl < RL) {
+#pragma unroll 8
+      for (int r = rl; r < n; r += RL) add8(dh + (size_t)pos[r] * d + 8 * c, a);
+    }
+    if (n < 1024) break;
+    __syncthreads();
+  }
+  if (rl < RL) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[rl * d + 8 * c + e] = a[e];
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < d; j += 1024) {
+    float t = 0.f;
+    for (int r = 0; r < RL; ++r) t += red[r * d + j];
+    const size_t o = (size_t)v * d + j;
+    demb[o] = accumulate ? demb[o] + t : t;
+  }
+}
 hipError_t op_embed_bwd(const OpCtx& c, const int32_t* ids, const void* dh, float* demb, int T_, int V, int d,
                         int accumulate) {
   ProfScope prof_(c, KC_EMBED);
   if (V <= 0 || d <= 0) return hipSuccess;
+  // The sorted list needs two words per position in the reduction scratch and keys of 31 bits; its rows are read and written
+  // 16 bytes at a time.  Beyond 65536 positions the comparisons would cost more than the scans.
+  if (c.partial && T_ > 0 && T_ <= 65536 && (size_t)2 * T_ <= c.partial_elems && (int64_t)V * T_ < 0x7fffffff && d % 8 == 0 && d <= 8192 &&
+      (((uintptr_t)dh | (uintptr_t)demb) & 15) == 0) {
+    int* order = reinterpret_cast<int*>(c.partial);
+    int* sorted = order + T_;
+    const int sort_blocks = (T_ + 63) / 64, short_blocks = (T_ + 15) / 16, long_blocks = (T_ + kEmbedShort - 1) / kEmbedShort;
+    const size_t clear4 = accumulate ? 0 : (size_t)V * d / 4;
+    const size_t want = (clear4 + 4095) / 4096;
+    const int clear_blocks = (int)(want < 512 ? want : 512);
+    k_embed_order<<<sort_blocks + clear_blocks, 1024, 0, c.stream>>>(ids, T_, V, order, sorted, demb, clear4, sort_blocks);
+    hipError_t e = LP_LAUNCH_CHECK();
+    if (e != hipSuccess) return e;
+    if (c.dt == BF16)
+      k_embed_rows<bf16_t><<<short_blocks + long_blocks, 1024, 0, c.stream>>>(order, sorted, (const bf16_t*)dh, demb, T_, d, accumulate, short_blocks);
+    else
+      k_embed_rows<float><<<short_blocks + long_blocks, 1024, 0, c.stream>>>(order, sorted, (const float*)dh, demb, T_, d, accumulate, short_blocks);
+    return LP_LAUNCH_CHECK();
+  }
   // per-id counts in the reduction scratch (integers; 0.0f is the zero word)
   int* counts = nullptr;
   if (c.partial && (size_t)V <= c.partial_elems && T_ > 0) {

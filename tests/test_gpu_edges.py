@@ -706,3 +706,57 @@ def test_convolution_tiles(K, N, H, W, C, O, R, stride):
     assert relerr(host(gw), want) <= 2e-6
     K.lpk_conv_bwd_weight_ws(1, dd, dx_, gw, N, H, W, C, O, R, stride, pad, zeros(1 << 22), accumulate=1)
     assert relerr(host(gw), 2 * want) <= 2e-6
+
+
+@pytest.mark.parametrize("T,V,d", [(1, 1, 8), (33, 1, 16), (32, 3, 128), (65, 70, 24), (600, 40, 128), (2555, 1003, 448), (1100, 2, 1040),
+                                   (4096, 5000, 768), (70, 9, 8192)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_embedding_gradient_sorted(K, T, V, d, accumulate):
+    """Rows of one to all positions (a wave's and a block's kind, and the length between them), rows that do not occur, ids
+    out of range, both types, twice.  fp32 sums of at most 2555 terms: 1e-6 relative."""
+    import torch
+    rng = np.random.default_rng(T + V)
+    ids = (rng.zipf(1.3, T) - 1).clip(-1, V).astype(np.int32)
+    ids[:: 5] = rng.integers(0, V, len(ids[:: 5]))
+    if T > 40 and V > 2:
+        ids[:33] = V - 1                   # one more than the short kind takes
+    for dtype in (0, 1):
+        dh = rnd(rng, (T, d), dtype)
+        scratch = zeros(max(2 * T, V))
+        outs = []
+        for _ in range(2):
+            demb = torch.full((V, d), 1.0, device="cuda")
+            K.lpk_embed_bwd(dtype, dev(ids, 0), dev(dh, dtype), demb, T, V, d, accumulate, scratch=scratch)
+            outs.append(demb)
+        ref = ops.embed_bwd(np.clip(ids, 0, V - 1), V, dh.astype(np.float64)) + accumulate
+        assert relerr(host(outs[0]), ref) <= 1e-6
+        assert torch.equal(outs[0], outs[1])
+        never = np.setdiff1d(np.arange(V), np.clip(ids, 0, V - 1))
+        assert bool((outs[0][torch.from_numpy(never).cuda().long()] == float(accumulate)).all())
+
+
+@pytest.mark.parametrize("B,S,H,dh", [(1, 1, 1, 64), (3, 129, 3, 64), (2, 200, 5, 32), (1, 500, 9, 16), (5, 511, 7, 64), (64, 128, 8, 16), (65, 128, 8, 64)])
+@pytest.mark.parametrize("causal", [0, 1])
+def test_attention_backward_launches(K, B, S, H, dh, causal):
+    """Both kinds of backward blocks in one launch (up to 512 of a kind, also where their number is no multiple of 8) and
+    apart (520), against float64; results are bf16 and P is rounded to bf16 on the way for heads of 64: 1e-2."""
+    import torch
+    rng = np.random.default_rng(S + H)
+    d = H * dh
+    qkv, do = rnd(rng, (B * S, 3 * d), 1), rnd(rng, (B * S, d), 1)
+    dq = dev(qkv, 1)
+    o, lse, delta = zeros(B * S, d).bfloat16(), zeros(B * H * S), zeros(B * H * S)
+    K.lpk_attention_fwd(1, dq, o, lse, B, S, H, dh, causal)
+    g = torch.full((B * S, 3 * d), 3.0, device="cuda", dtype=torch.bfloat16)
+    K.lpk_attention_bwd(1, dq, o, lse, dev(do, 1), g, delta, B, S, H, dh, causal)
+    q, k, v = (torch.from_numpy(qkv).double().reshape(B, S, 3, H, dh).permute(2, 0, 3, 1, 4)[i].contiguous().requires_grad_() for i in range(3))
+    s = torch.matmul(q, k.transpose(-1, -2).contiguous()) / dh ** 0.5
+    if causal:
+        s = s.masked_fill(torch.ones(S, S, dtype=torch.bool).triu(1), float("-inf"))
+    ref = torch.matmul(s.softmax(-1), v)
+    ref.backward(torch.from_numpy(do).double().reshape(B, S, H, dh).permute(0, 2, 1, 3).contiguous())
+    want = torch.stack([q.grad, k.grad, v.grad]).permute(1, 3, 0, 2, 4).reshape(B * S, 3 * d).numpy()
+    # S = 1 and the first causal row: dQ and dK are exactly zero in theory and rounding of P (dP - delta) here
+    assert np.linalg.norm(host(g).astype(np.float64) - want) <= 1e-2 * np.linalg.norm(want)
+    dd = (torch.from_numpy(do).cuda().double() * o.double()).reshape(B, S, H, dh).sum(-1).permute(0, 2, 1).reshape(-1)
+    assert float((delta.double() - dd).abs().max()) <= 1e-4 * float(dd.abs().max())
