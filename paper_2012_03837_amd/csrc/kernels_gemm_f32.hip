@@ -7,13 +7,19 @@
 //
 // A chunk is 16 k: lane (i = lane % 16, g = lane / 16) holds k = 4 g .. 4 g + 3 of row i, and the j-th of the chunk's
 // four matrix instructions takes element j of every lane.  Both operands use this order, so any storage layout pairs
-// with any other: k contiguous is one 16-byte (bf16: 8-byte) load per row and chunk, k-major four 4-byte loads.
+// with any other: k contiguous is one 16-byte (bf16: 8-byte) load per row and chunk; k-major is one load of the T neighbouring
+// rows that a lane then owns, T i .. T i + T - 1 instead of i, 16 + i, ... (rows in whole T-element loads), or four
+// one-element loads per row.  The former only in 64-wide tiles, where a weight gradient otherwise issues 32 loads of 4 bytes per
+// chunk, each with 64-bit address arithmetic (a step of six layers of 520 and 1000 with a batch of 333: 478 -> 443 us);
+// in the smaller ones, which are latencies and not loads, more code paths cost what they save (61.5 -> 63.8 us, four
+// layers of 256).
 //
 // Up to sixteen independent products share a launch (GemmArgs::rowsum adds a bias gradient to a weight gradient: sums of
 // A's rows, taken from the fragments by the blocks of the first tile column).
 //   128 x 256 x 256 fp32 (a layer of the MLP): 12.1 -> 4.2 us; 333 x 1000 x 520: 42 -> 11.6 us;
 //   1024 x 1024 x 1024: 29 us (74 TFLOP/s), 4096 cubed 1.64 ms (84 TFLOP/s, 53 % of the fp32 matrix rate).
 #include <stdio.h>
+#include <type_traits>
 #include "common.h"
 #include "gemm_common.h"
 
@@ -23,11 +29,14 @@ namespace {
 
 constexpr int kMaxFGroup = 16;
 
+// How an operand is read: element by element; k contiguous in whole 4-element loads; k-major in whole loads of T rows.
+enum FMode { F_ANY, F_K4, F_ROWS };
+
 template <typename T>
 struct FProblem {
   const T* A; const T* B;
   int64_t lda, ldb;
-  int a_kc, b_kc, a_vec, b_vec;      // vec: k contiguous in whole 4-element loads
+  int a_kc, b_kc, a_mode, b_mode;    // see FMode
   int M, N, K;
   int first, tiles_n;                // first tile number of this problem, tile columns
   float* rowsum;
@@ -44,41 +53,64 @@ __device__ __forceinline__ f4 load4(const bf16_t* p) {
   return r;
 }
 
-// One lane's four elements of a 16-deep chunk: k .. k + 3 of its row.  VEC (k contiguous, rows on whole 4-element loads
-// and K % 4 == 0): one load.  MASK: the chunk may reach past K (clamped for the load, zeroed after it).
-template <bool VEC, bool MASK, typename T>
-__device__ __forceinline__ f4 fetch4(const T* base, int64_t st, int k, int K) {
-  f4 r;
-  if (VEC) {
-    r = load4(base + (MASK && k >= K ? K - 4 : k));
-    if (MASK && k >= K) r = f4{0.f, 0.f, 0.f, 0.f};
-  } else {
+template <int N> __device__ __forceinline__ void load_rows(const float* p, float (&v)[N]) {
+  if constexpr (N == 4) { const f4 t = *reinterpret_cast<const f4*>(p); for (int e = 0; e < 4; ++e) v[e] = t[e]; }
+  else if constexpr (N == 2) { const float2 t = *reinterpret_cast<const float2*>(p); v[0] = t.x; v[1] = t.y; }
+  else v[0] = *p;
+}
+template <int N> __device__ __forceinline__ void load_rows(const bf16_t* p, float (&v)[N]) {
+  if constexpr (N == 4) { const f4 t = load4(p); for (int e = 0; e < 4; ++e) v[e] = t[e]; }
+  else if constexpr (N == 2) { const bf16x2 t = *reinterpret_cast<const bf16x2*>(p); v[0] = (float)t[0]; v[1] = (float)t[1]; }
+  else v[0] = (float)*p;
+}
+// Tile row that lane i's element of the t-th 16-row group is.
+template <int MODE, int TT> __device__ __forceinline__ int tile_row(int t, int i) { return MODE == F_ROWS ? TT * i + t : 16 * t + i; }
+
+// One lane's elements of a 16-deep chunk, k .. k + 3 of its TT rows.  p[t]: row t (F_ROWS: p[0], the first of TT neighbours).
+// MASK: the chunk may reach past K (clamped for the load, zeroed after it).
+template <int MODE, bool MASK, int TT, typename T>
+__device__ __forceinline__ void fetch_chunk(const T* const (&p)[TT], int64_t st, int k, int K, f4 (&r)[TT]) {
+  if constexpr (MODE == F_K4) {
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      r[t] = load4(p[t] + (MASK && k >= K ? K - 4 : k));
+      if (MASK && k >= K) r[t] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+  } else if constexpr (MODE == F_ROWS) {
+    const T* q = p[0] + (int64_t)(MASK && k >= K ? K - 1 : k) * st;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int kk = MASK ? (k + j < K ? k + j : K - 1) : k + j;
-      r[j] = to_f(base[kk * st]);
-    }
-    if (MASK) {
+      float v[TT];
+      load_rows<TT>(q, v);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) r[j] = k + j < K ? r[j] : 0.f;
+      for (int t = 0; t < TT; ++t) r[t][j] = !MASK || k + j < K ? v[t] : 0.f;
+      if (!MASK || k + j + 1 < K) q += st;
     }
+  } else {
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int kk = MASK ? (k + j < K ? k + j : K - 1) : k + j;
+        const float v = to_f(p[t][kk * st]);
+        r[t][j] = !MASK || k + j < K ? v : 0.f;
+      }
   }
-  return r;
 }
 
 // The reduction of one wave: chunks c0 .. c1, DEPTH - 1 of them in flight.
-template <bool AV, bool BV, int TT, int DEPTH, typename T>
+template <int AM, int BM, int TT, int DEPTH, typename T>
 __device__ __forceinline__ void reduce_wave(const T* const (&ap)[TT], const T* const (&bp)[TT], int64_t ast, int64_t bst, int g,
                                             int c0, int c1, int K, bool sums, f4 (&acc)[TT][TT], float (&rs)[TT]) {
   f4 a[DEPTH][TT], b[DEPTH][TT];
   auto fetch = [&](int s, int c) {
     const int k = 16 * c + 4 * g;
     if (16 * c + 16 <= K) {
-#pragma unroll
-      for (int t = 0; t < TT; ++t) { a[s][t] = fetch4<AV, false>(ap[t], ast, k, K); b[s][t] = fetch4<BV, false>(bp[t], bst, k, K); }
+      fetch_chunk<AM, false, TT>(ap, ast, k, K, a[s]);
+      fetch_chunk<BM, false, TT>(bp, bst, k, K, b[s]);
     } else {
-#pragma unroll
-      for (int t = 0; t < TT; ++t) { a[s][t] = fetch4<AV, true>(ap[t], ast, k, K); b[s][t] = fetch4<BV, true>(bp[t], bst, k, K); }
+      fetch_chunk<AM, true, TT>(ap, ast, k, K, a[s]);
+      fetch_chunk<BM, true, TT>(bp, bst, k, K, b[s]);
     }
   };
 #pragma unroll
@@ -103,8 +135,35 @@ __device__ __forceinline__ void reduce_wave(const T* const (&ap)[TT], const T* c
   }
 }
 
+// A wave's partial tile and row sums into its part of LDS.  Accumulator v of lane (li, g) is row 4 g + v, column li of its
+// 16 x 16 tile.
+template <int AM, int BM, int TT>
+__device__ __forceinline__ void leave_partial(const f4 (&acc)[TT][TT], float (&rs)[TT], bool sums, float* mine, float* rsum, int li, int g) {
+  constexpr int EDGE = 16 * TT, LDP = EDGE + 4;
+#pragma unroll
+  for (int x = 0; x < TT; ++x)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float* row = mine + tile_row<AM, TT>(x, 4 * g + v) * LDP;
+      if constexpr (BM == F_ROWS && TT == 4) {
+        *reinterpret_cast<f4*>(row + 4 * li) = f4{acc[x][0][v], acc[x][1][v], acc[x][2][v], acc[x][3][v]};
+      } else {
+#pragma unroll
+        for (int y = 0; y < TT; ++y) row[tile_row<BM, TT>(y, li)] = acc[x][y][v];
+      }
+    }
+  if (sums) {
+#pragma unroll
+    for (int x = 0; x < TT; ++x) {
+      rs[x] += __shfl_xor(rs[x], 16, 64);
+      rs[x] += __shfl_xor(rs[x], 32, 64);
+      if (g == 0) rsum[tile_row<AM, TT>(x, li)] = rs[x];
+    }
+  }
+}
+
 template <typename T, int TT, int NP>
-__global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
+__global__ void __launch_bounds__(256, TT == 4 ? 2 : 1) k_gemm_f(FGroup<T, NP> grp) {
   constexpr int EDGE = 16 * TT, LDP = EDGE + 4;       // LDS rows of a partial tile
   constexpr int DEPTH = TT == 4 ? 3 : 4;       // chunks in registers
   extern __shared__ __attribute__((aligned(16))) float part[];      // [4][EDGE][LDP], then [4][EDGE] row sums
@@ -118,15 +177,6 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
   const int li = lane & 15, g = lane >> 4;
   const int K = P.K, nch = (K + 15) / 16;               // a wave's share of the reduction: whole chunks
   const int c0 = nch * wave / 4, c1 = nch * (wave + 1) / 4;
-  const T *ap[TT], *bp[TT];
-#pragma unroll
-  for (int t = 0; t < TT; ++t) {
-    int m = tm * EDGE + 16 * t + li, n = tn * EDGE + 16 * t + li;
-    m = m < P.M ? m : P.M - 1;
-    n = n < P.N ? n : P.N - 1;
-    ap[t] = P.A + (P.a_kc ? (int64_t)m * P.lda : (int64_t)m);
-    bp[t] = P.B + (P.b_kc ? (int64_t)n * P.ldb : (int64_t)n);
-  }
   const bool sums = P.rowsum && tn == 0;
   f4 acc[TT][TT];
   float rs[TT];
@@ -137,52 +187,62 @@ __global__ void __launch_bounds__(256) k_gemm_f(FGroup<T, NP> grp) {
     for (int j = 0; j < TT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   }
   const int64_t ast = P.a_kc ? 1 : P.lda, bst = P.b_kc ? 1 : P.ldb;
-  if (P.a_vec) {
-    if (P.b_vec) reduce_wave<true, true, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
-    else reduce_wave<true, false, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
-  } else {
-    if (P.b_vec) reduce_wave<false, true, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
-    else reduce_wave<false, false, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
-  }
+  auto rows = [&](auto mode, const T* base, bool kc, int64_t ld, int first, int n, const T* (&p)[TT]) {
+    constexpr int MODE = decltype(mode)::value;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      int r = first + tile_row<MODE, TT>(t, li);
+      const int last = MODE == F_ROWS ? n - TT + t : n - 1;       // whole loads of TT rows
+      r = r < last ? r : last;
+      p[t] = base + (kc ? (int64_t)r * ld : (int64_t)r);
+    }
+  };
+  float* mine = part + (size_t)wave * EDGE * LDP;
+  float* rsum = part + (size_t)4 * EDGE * LDP;
   // What the epilogue reads is asked for before the partial tiles are exchanged: element by element behind the reduction,
   // its loads were a chain of memory latencies longer than the product (16 elements a thread for a 64 x 64 tile: 20 us).
   // Thread: PER runs of W consecutive columns (64: 4 x 4, 32: 1 x 4, 16: 1 x 1).
   constexpr int W = TT == 1 ? 1 : 4, RUNS = EDGE * EDGE / W, PER = RUNS / 256, RPR = EDGE / W;     // runs per row
   const Epilogue& e = P.e;
   float eb[PER][W], es[PER][W], er[PER][W], ec[PER][W];
+  auto ask = [&] {
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int run = threadIdx.x + 256 * q;
-    int m = tm * EDGE + run / RPR;
-    m = m < P.M ? m : P.M - 1;
+    for (int q = 0; q < PER; ++q) {
+      const int run = threadIdx.x + 256 * q;
+      int m = tm * EDGE + run / RPR;
+      m = m < P.M ? m : P.M - 1;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-      int n = tn * EDGE + (run % RPR) * W + w;
-      n = n < P.N ? n : P.N - 1;
-      eb[q][w] = e.bias ? e.bias[n] : 0.f;
-      es[q][w] = e.dact != ACT_NONE ? to_f(reinterpret_cast<const T*>(e.dact_src)[(size_t)m * e.ldd + n]) : 0.f;
-      er[q][w] = e.res ? to_f(reinterpret_cast<const T*>(e.res)[(size_t)m * e.ldr + n]) : 0.f;
-      const size_t o = (size_t)m * e.ldc + n;
-      ec[q][w] = e.accumulate ? (e.c_f32 ? reinterpret_cast<const float*>(e.C)[o] : to_f(reinterpret_cast<const T*>(e.C)[o])) : 0.f;
+      for (int w = 0; w < W; ++w) {
+        int n = tn * EDGE + (run % RPR) * W + w;
+        n = n < P.N ? n : P.N - 1;
+        eb[q][w] = e.bias ? e.bias[n] : 0.f;
+        es[q][w] = e.dact != ACT_NONE ? to_f(reinterpret_cast<const T*>(e.dact_src)[(size_t)m * e.ldd + n]) : 0.f;
+        er[q][w] = e.res ? to_f(reinterpret_cast<const T*>(e.res)[(size_t)m * e.ldr + n]) : 0.f;
+        const size_t o = (size_t)m * e.ldc + n;
+        ec[q][w] = e.accumulate ? (e.c_f32 ? reinterpret_cast<const float*>(e.C)[o] : to_f(reinterpret_cast<const T*>(e.C)[o])) : 0.f;
+      }
     }
-  }
-  // partial tiles: accumulator v of lane (li, g) is row 4 g + v, column li of its 16 x 16 tile
-  float* mine = part + (size_t)wave * EDGE * LDP;
-#pragma unroll
-  for (int x = 0; x < TT; ++x)
-#pragma unroll
-    for (int y = 0; y < TT; ++y)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) mine[(16 * x + 4 * g + v) * LDP + 16 * y + li] = acc[x][y][v];
-  float* rsum = part + (size_t)4 * EDGE * LDP;
-  if (sums) {
-#pragma unroll
-    for (int x = 0; x < TT; ++x) {
-      rs[x] += __shfl_xor(rs[x], 16, 64);
-      rs[x] += __shfl_xor(rs[x], 32, 64);
-      if (g == 0) rsum[wave * EDGE + 16 * x + li] = rs[x];
-    }
-  }
+  };
+  auto product = [&](auto am, auto bm) {
+    constexpr int AM = decltype(am)::value, BM = decltype(bm)::value;
+    const T *ap[TT], *bp[TT];
+    rows(am, P.A, P.a_kc, P.lda, tm * EDGE, P.M, ap);
+    rows(bm, P.B, P.b_kc, P.ldb, tn * EDGE, P.N, bp);
+    reduce_wave<AM, BM, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+    ask();
+    leave_partial<AM, BM, TT>(acc, rs, sums, mine, rsum + wave * EDGE, li, g);
+  };
+  typedef std::integral_constant<int, F_ANY> Any;
+  typedef std::integral_constant<int, F_K4> K4;
+  typedef std::integral_constant<int, TT == 4 ? F_ROWS : F_ANY> Rows;
+  auto by_b = [&](auto am) {
+    if (P.b_mode == F_K4) product(am, K4{});
+    else if (TT == 4 && P.b_mode == F_ROWS) product(am, Rows{});
+    else product(am, Any{});
+  };
+  if (P.a_mode == F_K4) by_b(K4{});
+  else if (TT == 4 && P.a_mode == F_ROWS) by_b(Rows{});
+  else by_b(Any{});
   __syncthreads();
   constexpr int PT = EDGE * LDP;
 #pragma unroll
@@ -250,8 +310,12 @@ hipError_t gemm_f_t(const OpCtx& c, const GemmArgs* gs, int n) {
     FProblem<T>& p = grp.p[grp.n++];
     p.A = (const T*)g.A; p.B = (const T*)g.B; p.lda = g.lda; p.ldb = g.ldb;
     p.a_kc = g.a_kc; p.b_kc = g.b_kc;
-    p.a_vec = g.a_kc && g.K % 4 == 0 && g.lda % 4 == 0 && ((uintptr_t)g.A & al) == 0;
-    p.b_vec = g.b_kc && g.K % 4 == 0 && g.ldb % 4 == 0 && ((uintptr_t)g.B & al) == 0;
+    auto mode = [&](const void* base, int64_t ld, int kc, int n) {      // rows: whole loads of four, so of fewer too
+      if (ld % 4 || ((uintptr_t)base & al)) return F_ANY;
+      return kc ? (g.K % 4 == 0 ? F_K4 : F_ANY) : (n % 4 == 0 ? F_ROWS : F_ANY);
+    };
+    p.a_mode = mode(g.A, g.lda, g.a_kc, g.M);
+    p.b_mode = mode(g.B, g.ldb, g.b_kc, N);
     p.M = g.M; p.N = N; p.K = g.K; p.rowsum = g.rowsum;
     p.e = make_epilogue(g);
     t64 += (long)((g.M + 63) / 64) * ((N + 63) / 64);

@@ -760,3 +760,19 @@ def test_attention_backward_launches(K, B, S, H, dh, causal):
     assert np.linalg.norm(host(g).astype(np.float64) - want) <= 1e-2 * np.linalg.norm(want)
     dd = (torch.from_numpy(do).cuda().double() * o.double()).reshape(B, S, H, dh).sum(-1).permute(0, 2, 1).reshape(-1)
     assert float((delta.double() - dd).abs().max()) <= 1e-4 * float(dd.abs().max())
+
+
+@pytest.mark.parametrize("a_kc,b_kc", [(1, 1), (1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,Kd", [(1004, 1100, 16), (1004, 1100, 37), (1003, 1101, 333), (1028, 1096, 68), (960, 1152, 64)])
+def test_gemm_fp32_wide_tiles(K, M, N, Kd, a_kc, b_kc):
+    """64-wide fp32 tiles with k-major operands read four rows at a time (row counts in fours, a last tile cut short) and
+    element by element (odd counts), reductions with a partial chunk, against float64: sums of at most 333 products, 1e-6."""
+    rng = np.random.default_rng(M + Kd)
+    A, B = rng.standard_normal((M, Kd)).astype(np.float32), rng.standard_normal((N, Kd)).astype(np.float32)
+    Am, Bm = A if a_kc else np.ascontiguousarray(A.T), B if b_kc else np.ascontiguousarray(B.T)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    out = zeros(M + 1, N)
+    out += 3.0
+    K.lpk_gemm(0, dev(Am, 0), Am.shape[1], a_kc, dev(Bm, 0), Bm.shape[1], b_kc, out, N, 1, M, N, Kd)
+    assert relerr(host(out[:M]), ref) <= 1e-6
+    assert bool((out[M] == 3.0).all())
