@@ -383,19 +383,41 @@ __global__ void __launch_bounds__(256) k_bn_partial_v(const bf16_t* __restrict__
     }
   }
 }
-// Adds the slab partials in order (64 channels x 16 slab groups per block: group q adds slabs q, q+16, ...
+// Adds the slab partials in order (CW channels x 1024 / CW slab groups per block: group q adds slabs q, q + groups, ...
 // with two independent pairs of loads in flight, then the group sums are added in order) and finishes.
+// 64 channels a block, or 16 where the slabs are many: with 1024 slabs of 64 channels one block of 16 groups was a chain of
+// sixteen memory latencies (9 us, with nothing beside it on the way from one convolution to the next).
 // mode 0: forward statistics (needs the pivots from row 0 of z); with aux0 / aux1 the batch mean and unbiased
 // variance are also folded into those running statistics with weight auxf.  mode 1: plain sums into out0, out1;
 // with aux0 / aux1 they are also written (auxf == 0) or added (auxf != 0) there: the shift and gain gradients.
-constexpr int kBnFinishGroups = 16;
-__global__ void __launch_bounds__(64 * kBnFinishGroups)
+constexpr int kBnFinishThreads = 1024, kBnManySlabs = 128;
+// The groups' sums added in order: sixteen one after the other, or 64 as eight times eight.
+template <int CW, typename A>
+__device__ __forceinline__ void bn_group_sums(A (&sh)[2][kBnFinishThreads / CW][CW], int q, int lc, A& a, A& b) {
+  constexpr int G = kBnFinishThreads / CW;
+  if constexpr (G == 64) {
+    if (q < 8) {
+      a = 0; b = 0;
+#pragma unroll
+      for (int g = 0; g < 8; ++g) { a += sh[0][8 * q + g][lc]; b += sh[1][8 * q + g][lc]; }
+    }
+    __syncthreads();
+    if (q < 8) { sh[0][q][lc] = a; sh[1][q][lc] = b; }
+    __syncthreads();
+  }
+  a = 0; b = 0;
+#pragma unroll
+  for (int g = 0; g < (G == 64 ? 8 : G); ++g) { a += sh[0][g][lc]; b += sh[1][g][lc]; }
+}
+template <int CW>
+__global__ void __launch_bounds__(kBnFinishThreads)
 k_bn_finish_v(const float* __restrict__ partial, int nslab, int C, int rows, const bf16_t* __restrict__ z,
               float* __restrict__ out0, float* __restrict__ out1, int mode, float* __restrict__ aux0 = nullptr,
               float* __restrict__ aux1 = nullptr, float auxf = 0.f) {
-  __shared__ float sh[2][kBnFinishGroups][64];
-  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lc;
+  constexpr int kBnFinishGroups = kBnFinishThreads / CW;
+  __shared__ float sh[2][kBnFinishGroups][CW];
+  const int lc = threadIdx.x % CW, q = threadIdx.x / CW;
+  const int j = blockIdx.x * CW + lc;
   float a = 0.f, b = 0.f;
   if (j < C) {
     int s = q;
@@ -418,10 +440,8 @@ k_bn_finish_v(const float* __restrict__ partial, int nslab, int C, int rows, con
   }
   sh[0][q][lc] = a; sh[1][q][lc] = b;
   __syncthreads();
+  bn_group_sums<CW>(sh, q, lc, a, b);
   if (q != 0 || j >= C) return;
-  a = 0.f; b = 0.f;
-#pragma unroll
-  for (int g = 0; g < kBnFinishGroups; ++g) { a += sh[0][g][lc]; b += sh[1][g][lc]; }
   if (mode == 0) {
     const float inv = 1.f / (float)rows, m1 = a * inv;
     float var = b * inv - m1 * m1;
@@ -444,12 +464,14 @@ k_bn_finish_v(const float* __restrict__ partial, int nslab, int C, int rows, con
 }
 // Forward statistics from the fp64 sums of k_bn_partial_v<2>, in the same order.  A variance of NaN (an infinity in the
 // column) stays one.
-__global__ void __launch_bounds__(64 * kBnFinishGroups)
+template <int CW>
+__global__ void __launch_bounds__(kBnFinishThreads)
 k_bn_finish_wide(const float* __restrict__ partial, int nslab, int C, int rows, float* __restrict__ mean,
                  float* __restrict__ rstd, float* __restrict__ run_mean, float* __restrict__ run_var, float mom) {
-  __shared__ double sh[2][kBnFinishGroups][64];
-  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lc;
+  constexpr int kBnFinishGroups = kBnFinishThreads / CW;
+  __shared__ double sh[2][kBnFinishGroups][CW];
+  const int lc = threadIdx.x % CW, q = threadIdx.x / CW;
+  const int j = blockIdx.x * CW + lc;
   double a = 0, b = 0;
   if (j < C) {
     const size_t part = (size_t)nslab * C;
@@ -471,10 +493,8 @@ k_bn_finish_wide(const float* __restrict__ partial, int nslab, int C, int rows, 
   }
   sh[0][q][lc] = a; sh[1][q][lc] = b;
   __syncthreads();
+  bn_group_sums<CW>(sh, q, lc, a, b);
   if (q != 0 || j >= C) return;
-  a = 0; b = 0;
-#pragma unroll
-  for (int g = 0; g < kBnFinishGroups; ++g) { a += sh[0][g][lc]; b += sh[1][g][lc]; }
   const double m1 = a / rows, v1 = b / rows - m1 * m1;
   const float mu = (float)m1, var = v1 < 0 ? 0.f : (float)v1;
   mean[j] = mu;
@@ -490,12 +510,14 @@ k_bn_finish_wide(const float* __restrict__ partial, int nslab, int C, int rows, 
 //   sum (z - P) = s0_t + n d,   sum (z - P)^2 = s1_t + 2 d s0_t + n d^2,
 // the slabs are added in the order of k_bn_finish_v (16 groups of every 16th slab, then the groups in order), and the
 // batch mean, 1 / sqrt(var + eps) and the running pair follow as there.
-__global__ void __launch_bounds__(64 * kBnFinishGroups)
+template <int CW>
+__global__ void __launch_bounds__(kBnFinishThreads)
 k_bn_finish_slabs(const float* __restrict__ st, int nslab, int slab_rows, int C, int rows, float* __restrict__ mean,
                   float* __restrict__ rstd, float* __restrict__ run_mean, float* __restrict__ run_var, float mom) {
-  __shared__ float sh[2][kBnFinishGroups][64];
-  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lc;
+  constexpr int kBnFinishGroups = kBnFinishThreads / CW;
+  __shared__ float sh[2][kBnFinishGroups][CW];
+  const int lc = threadIdx.x % CW, q = threadIdx.x / CW;
+  const int j = blockIdx.x * CW + lc;
   float a = 0.f, b = 0.f, P = 0.f;
   if (j < C) {
     const float* s0p = st + j;
@@ -527,10 +549,8 @@ k_bn_finish_slabs(const float* __restrict__ st, int nslab, int slab_rows, int C,
   }
   sh[0][q][lc] = a; sh[1][q][lc] = b;
   __syncthreads();
+  bn_group_sums<CW>(sh, q, lc, a, b);
   if (q != 0 || j >= C) return;
-  a = 0.f; b = 0.f;
-#pragma unroll
-  for (int g = 0; g < kBnFinishGroups; ++g) { a += sh[0][g][lc]; b += sh[1][g][lc]; }
   const float inv = 1.f / (float)rows, m1 = a * inv;
   float var = b * inv - m1 * m1;
   var = var > 0.f ? var : 0.f;
@@ -633,8 +653,10 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
   const float mom = run ? run->momentum : 0.f;
   if (!given && pre && pre->nslab > 0 && (size_t)pre->nslab * pre->slab_rows == (size_t)rows) {
     // the convolution in front left the per-slab sums: no pass over z for the statistics
-    k_bn_finish_slabs<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(
-        pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, rm, rv, mom);
+    if (pre->nslab >= kBnManySlabs)
+      k_bn_finish_slabs<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, rm, rv, mom);
+    else
+      k_bn_finish_slabs<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, rm, rv, mom);
   } else if (!given && !bn_shifted(C)) {
     if (bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
     // at most a slab per compute unit: two blocks add up all of 65536 x 96's sums, 13.7 us with 512 slabs, 7.3 us with 256
@@ -643,7 +665,10 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
     const size_t shm = (size_t)2 * (256 / (C / 8)) * C * sizeof(double);
     k_bn_partial_v<2><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, nullptr, nullptr, nullptr, c.partial, rows, C,
                                                      slab, 0);
-    k_bn_finish_wide<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(c.partial, nslab, C, rows, mean, rstd, rm, rv, mom);
+    if (nslab >= kBnManySlabs)
+      k_bn_finish_wide<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, mean, rstd, rm, rv, mom);
+    else
+      k_bn_finish_wide<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, mean, rstd, rm, rv, mom);
   } else if (!given) {
     if (2 * bn_least_slabs(rows, C) * C > c.partial_elems) return hipErrorInvalidValue;
     const int slab = bn_slab(rows, C, c.partial_elems / ((size_t)2 * C)), nslab = (rows + slab - 1) / slab;
@@ -651,8 +676,10 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
     const size_t shm = (size_t)2 * RL * C * sizeof(float);
     k_bn_partial_v<0><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, (const bf16_t*)z, nullptr, nullptr,
                                                      c.partial, rows, C, slab, 0);
-    k_bn_finish_v<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(
-        c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
+    if (nslab >= kBnManySlabs)
+      k_bn_finish_v<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
+    else
+      k_bn_finish_v<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
   }
   const size_t nch = (size_t)rows * C / 8;
   k_bn_apply_v<<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)z, g, b, (const bf16_t*)res, (bf16_t*)y, mean, rstd,
@@ -669,8 +696,10 @@ hipError_t bn_bwd_fast(const OpCtx& c, const void* dy, const void* y, const void
   const size_t shm = (size_t)2 * RL * C * sizeof(float);
   k_bn_partial_v<1><<<nslab, 256, shm, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean, rstd,
                                                    c.partial, rows, C, slab, relu);
-  k_bn_finish_v<<<(C + 63) / 64, 64 * kBnFinishGroups, 0, c.stream>>>(c.partial, nslab, C, rows, nullptr, sums, sums + C, 1,
-                                                                      db, dg, accumulate ? 1.f : 0.f);
+  if (nslab >= kBnManySlabs)
+    k_bn_finish_v<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, nullptr, sums, sums + C, 1, db, dg, accumulate ? 1.f : 0.f);
+  else
+    k_bn_finish_v<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, nullptr, sums, sums + C, 1, db, dg, accumulate ? 1.f : 0.f);
   const size_t nch = (size_t)rows * C / 8;
   k_bn_bwd_apply_v<<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean,
                                                          rstd, g, sums, (bf16_t*)dz, (bf16_t*)dres, nch, C, rows, relu);
