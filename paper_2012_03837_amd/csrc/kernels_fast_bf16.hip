@@ -563,10 +563,94 @@ k_bn_finish_slabs(const float* __restrict__ st, int nslab, int slab_rows, int C,
     run_var[j] = (1.f - mom) * run_var[j] + mom * unb;
   }
 }
+// Few slabs: every block of the kernel that applies the statistics adds them up for itself, at the price of a read of all sums
+// per block (at most 4096 per plane, from L2) and without the launch in between, which costs 4.4 us and a unit of a small
+// network three of its fifteen launches.  Thread (channel j, group q): slabs q, q + G, ..., the groups' sums in order.
+constexpr int kBnSmallC = 128, kBnSmallSums = 4096, kBnSmallBlocks = 512;
+inline bool bn_small(int nslab, int C) { return C <= kBnSmallC && nslab * C <= kBnSmallSums; }
+enum BnFinish { BN_GIVEN, BN_SHIFTED, BN_WIDE, BN_CONV };
+struct BnSums {            // what the statistics come from, and where they go (block 0)
+  const float* partial; int nslab, slab_rows, rows;
+  float *mean, *rstd, *run_mean, *run_var; float mom;
+};
+template <typename A, class F>
+__device__ __forceinline__ void bn_small_sums(int nslab, int C, A* sh, F add, A& a, A& b) {
+  const int G = 256 / C, q = threadIdx.x / C, j = threadIdx.x - q * C;
+  a = 0; b = 0;
+  if (q < G) {
+#pragma unroll 4
+    for (int s = q; s < nslab; s += G) add(s, j, a, b);
+    sh[q * C + j] = a;
+    sh[256 + q * C + j] = b;
+  }
+  __syncthreads();
+  if (q == 0) {
+    a = 0; b = 0;
+    for (int g = 0; g < G; ++g) { a += sh[g * C + j]; b += sh[256 + g * C + j]; }
+  }
+}
+// Batch mean and 1 / sqrt(var + eps) of every channel into LDS; block 0 also leaves them in memory with the running pair.
+template <BnFinish FIN>
+__device__ __forceinline__ void bn_small_stats(const BnSums& t, const bf16_t* __restrict__ z, int C, float* mu_s, float* rs_s) {
+  typedef typename std::conditional<FIN == BN_WIDE, double, float>::type A;
+  __shared__ A sh[512];
+  const size_t plane = (size_t)t.nslab * C;
+  A a, b;
+  float P = 0.f;
+  if (FIN == BN_CONV && (int)threadIdx.x < 256 / C * C) P = t.partial[2 * plane + threadIdx.x % C];
+  const float n = (float)t.slab_rows;
+  bn_small_sums(t.nslab, C, sh, [&](int s, int j, A& x, A& y) {
+    const float* p = t.partial + (size_t)s * C + j;
+    if (FIN == BN_WIDE) {
+      x += (A)p[0] + (A)p[2 * plane];
+      y += (A)p[plane] + (A)p[3 * plane];
+    } else if (FIN == BN_CONV) {
+      const float d = p[2 * plane] - P, s0 = p[0];
+      x += s0 + n * d;
+      y += p[plane] + 2.f * d * s0 + n * d * d;
+    } else {
+      x += p[0];
+      y += p[plane];
+    }
+  }, a, b);
+  const int j = threadIdx.x;
+  if (j < C) {
+    float mu, var;
+    if (FIN == BN_WIDE) {
+      const A m1 = a / t.rows, v1 = b / t.rows - m1 * m1;
+      mu = (float)m1;
+      var = v1 < 0 ? 0.f : (float)v1;
+    } else {
+      const float inv = 1.f / (float)t.rows, m1 = (float)a * inv;
+      var = (float)b * inv - m1 * m1;
+      var = var > 0.f ? var : 0.f;
+      mu = (FIN == BN_CONV ? P : (float)z[j]) + m1;
+    }
+    const float rs = rsqrtf(var + kBnEpsV);
+    mu_s[j] = mu;
+    rs_s[j] = rs;
+    if (blockIdx.x == 0) {
+      t.mean[j] = mu;
+      t.rstd[j] = rs;
+      if (t.run_mean) {   // running statistics take the unbiased batch variance
+        const float unb = t.rows > 1 ? var * ((float)t.rows / (float)(t.rows - 1)) : var;
+        t.run_mean[j] = (1.f - t.mom) * t.run_mean[j] + t.mom * mu;
+        t.run_var[j] = (1.f - t.mom) * t.run_var[j] + t.mom * unb;
+      }
+    }
+  }
+  __syncthreads();
+}
+template <BnFinish FIN>
 __global__ void __launch_bounds__(256) k_bn_apply_v(const bf16_t* __restrict__ z, const float* __restrict__ g,
                                                     const float* __restrict__ b, const bf16_t* __restrict__ res,
                                                     bf16_t* __restrict__ y, const float* __restrict__ mean,
-                                                    const float* __restrict__ rstd, size_t nchunks, int C, int relu) {
+                                                    const float* __restrict__ rstd, size_t nchunks, int C, int relu, BnSums t) {
+  __shared__ __attribute__((aligned(16))) float mu_s[FIN ? kBnSmallC : 4], rs_s[FIN ? kBnSmallC : 4];
+  if constexpr (FIN != BN_GIVEN) {
+    bn_small_stats<FIN>(t, z, C, mu_s, rs_s);
+    mean = mu_s; rstd = rs_s;
+  }
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, st = (size_t)gridDim.x * 256;
   for (; i < nchunks; i += st) {
     const int c = (int)((i * 8) % C);
@@ -587,12 +671,35 @@ __global__ void __launch_bounds__(256) k_bn_apply_v(const bf16_t* __restrict__ z
     store8(y + i * 8, v);
   }
 }
+// SMALL: `sums` are the slabs' [2][nslab][C], added up here; block 0 leaves the shift and gain gradients in db and dg.
+template <bool SMALL>
 __global__ void __launch_bounds__(256) k_bn_bwd_apply_v(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ yrelu,
                                                         const bf16_t* __restrict__ z, const float* __restrict__ mean,
                                                         const float* __restrict__ rstd, const float* __restrict__ g,
                                                         const float* __restrict__ sums, bf16_t* __restrict__ dz,
                                                         bf16_t* __restrict__ dres, size_t nchunks, int C, int rows,
-                                                        int relu) {
+                                                        int relu, int nslab, float* __restrict__ db, float* __restrict__ dg, int accumulate) {
+  __shared__ __attribute__((aligned(16))) float tot[SMALL ? 2 * kBnSmallC : 4];
+  __shared__ float sh[SMALL ? 512 : 4];
+  if constexpr (SMALL) {
+    const size_t plane = (size_t)nslab * C;
+    float a, b;
+    bn_small_sums(nslab, C, sh, [&](int s, int j, float& x, float& y) {
+      x += sums[(size_t)s * C + j];
+      y += sums[plane + (size_t)s * C + j];
+    }, a, b);
+    const int j = threadIdx.x;
+    if (j < C) {
+      tot[j] = a;
+      tot[C + j] = b;
+      if (blockIdx.x == 0) {
+        db[j] = accumulate ? db[j] + a : a;
+        dg[j] = accumulate ? dg[j] + b : b;
+      }
+    }
+    __syncthreads();
+    sums = tot;
+  }
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, st = (size_t)gridDim.x * 256;
   const float inv = 1.f / (float)rows;
   for (; i < nchunks; i += st) {
@@ -651,8 +758,22 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
   float* rm = run ? run->mean : nullptr;
   float* rv = run ? run->var : nullptr;
   const float mom = run ? run->momentum : 0.f;
+  const size_t nch = (size_t)rows * C / 8;
+  BnSums t = {c.partial, 0, 0, rows, mean, rstd, rm, rv, mom};
+  auto apply = [&](auto fin) {
+    constexpr BnFinish FIN = decltype(fin)::value;
+    int blocks = blocks_for(nch);
+    if (FIN != BN_GIVEN && blocks > kBnSmallBlocks) blocks = kBnSmallBlocks;
+    k_bn_apply_v<FIN><<<blocks, 256, 0, c.stream>>>((const bf16_t*)z, g, b, (const bf16_t*)res, (bf16_t*)y, mean, rstd, nch, C, relu, t);
+    return hipGetLastError();
+  };
+  typedef std::integral_constant<BnFinish, BN_SHIFTED> Shifted;
+  typedef std::integral_constant<BnFinish, BN_WIDE> Wide;
+  typedef std::integral_constant<BnFinish, BN_CONV> Conv;
   if (!given && pre && pre->nslab > 0 && (size_t)pre->nslab * pre->slab_rows == (size_t)rows) {
     // the convolution in front left the per-slab sums: no pass over z for the statistics
+    t.partial = pre->buf; t.nslab = pre->nslab; t.slab_rows = pre->slab_rows;
+    if (bn_small(t.nslab, C)) return apply(Conv{});
     if (pre->nslab >= kBnManySlabs)
       k_bn_finish_slabs<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(pre->buf, pre->nslab, pre->slab_rows, C, rows, mean, rstd, rm, rv, mom);
     else
@@ -665,6 +786,8 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
     const size_t shm = (size_t)2 * (256 / (C / 8)) * C * sizeof(double);
     k_bn_partial_v<2><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, nullptr, nullptr, nullptr, c.partial, rows, C,
                                                      slab, 0);
+    t.nslab = nslab;
+    if (bn_small(nslab, C)) return apply(Wide{});
     if (nslab >= kBnManySlabs)
       k_bn_finish_wide<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, mean, rstd, rm, rv, mom);
     else
@@ -676,15 +799,14 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
     const size_t shm = (size_t)2 * RL * C * sizeof(float);
     k_bn_partial_v<0><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, (const bf16_t*)z, nullptr, nullptr,
                                                      c.partial, rows, C, slab, 0);
+    t.nslab = nslab;
+    if (bn_small(nslab, C)) return apply(Shifted{});
     if (nslab >= kBnManySlabs)
       k_bn_finish_v<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
     else
       k_bn_finish_v<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
   }
-  const size_t nch = (size_t)rows * C / 8;
-  k_bn_apply_v<<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)z, g, b, (const bf16_t*)res, (bf16_t*)y, mean, rstd,
-                                                     nch, C, relu);
-  return hipGetLastError();
+  return apply(std::integral_constant<BnFinish, BN_GIVEN>{});
 }
 hipError_t bn_bwd_fast(const OpCtx& c, const void* dy, const void* y, const void* z, const float* mean,
                        const float* rstd, const float* g, void* dz, void* dres, float* dg, float* db, int rows, int C,
@@ -696,13 +818,19 @@ hipError_t bn_bwd_fast(const OpCtx& c, const void* dy, const void* y, const void
   const size_t shm = (size_t)2 * RL * C * sizeof(float);
   k_bn_partial_v<1><<<nslab, 256, shm, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean, rstd,
                                                    c.partial, rows, C, slab, relu);
+  const size_t nch = (size_t)rows * C / 8;
+  if (bn_small(nslab, C)) {
+    const int blocks = blocks_for(nch) < kBnSmallBlocks ? blocks_for(nch) : kBnSmallBlocks;
+    k_bn_bwd_apply_v<true><<<blocks, 256, 0, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean, rstd, g, c.partial,
+                                                         (bf16_t*)dz, (bf16_t*)dres, nch, C, rows, relu, nslab, db, dg, accumulate);
+    return hipGetLastError();
+  }
   if (nslab >= kBnManySlabs)
     k_bn_finish_v<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, nullptr, sums, sums + C, 1, db, dg, accumulate ? 1.f : 0.f);
   else
     k_bn_finish_v<64><<<(C + 63) / 64, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, nullptr, sums, sums + C, 1, db, dg, accumulate ? 1.f : 0.f);
-  const size_t nch = (size_t)rows * C / 8;
-  k_bn_bwd_apply_v<<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean,
-                                                         rstd, g, sums, (bf16_t*)dz, (bf16_t*)dres, nch, C, rows, relu);
+  k_bn_bwd_apply_v<false><<<blocks_for(nch), 256, 0, c.stream>>>((const bf16_t*)dy, (const bf16_t*)y, (const bf16_t*)z, mean, rstd, g, sums,
+                                                                (bf16_t*)dz, (bf16_t*)dres, nch, C, rows, relu, 0, nullptr, nullptr, 0);
   return hipGetLastError();
 }
 
