@@ -11,8 +11,8 @@
 // rows that a lane then owns, T i .. T i + T - 1 instead of i, 16 + i, ... (rows in whole T-element loads), or four
 // one-element loads per row.  The former only in 64-wide tiles, where a weight gradient otherwise issues 32 loads of 4 bytes per
 // chunk, each with 64-bit address arithmetic (a step of six layers of 520 and 1000 with a batch of 333: 478 -> 443 us);
-// in the smaller ones, which are latencies and not loads, more code paths cost what they save (61.5 -> 63.8 us, four
-// layers of 256).
+// in the smaller ones, which are latencies and not loads, more forms of the code cost what they save (61.5 -> 63.8 us,
+// four layers of 256).
 //
 // Up to sixteen independent products share a launch (GemmArgs::rowsum adds a bias gradient to a weight gradient: sums of
 // A's rows, taken from the fragments by the blocks of the first tile column).
@@ -223,26 +223,40 @@ __global__ void __launch_bounds__(256, TT == 4 ? 2 : 1) k_gemm_f(FGroup<T, NP> g
       }
     }
   };
-  auto product = [&](auto am, auto bm) {
-    constexpr int AM = decltype(am)::value, BM = decltype(bm)::value;
-    const T *ap[TT], *bp[TT];
-    rows(am, P.A, P.a_kc, P.lda, tm * EDGE, P.M, ap);
-    rows(bm, P.B, P.b_kc, P.ldb, tn * EDGE, P.N, bp);
-    reduce_wave<AM, BM, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
-    ask();
-    leave_partial<AM, BM, TT>(acc, rs, sums, mine, rsum + wave * EDGE, li, g);
-  };
   typedef std::integral_constant<int, F_ANY> Any;
   typedef std::integral_constant<int, F_K4> K4;
   typedef std::integral_constant<int, TT == 4 ? F_ROWS : F_ANY> Rows;
-  auto by_b = [&](auto am) {
-    if (P.b_mode == F_K4) product(am, K4{});
-    else if (TT == 4 && P.b_mode == F_ROWS) product(am, Rows{});
-    else product(am, Any{});
-  };
-  if (P.a_mode == F_K4) by_b(K4{});
-  else if (TT == 4 && P.a_mode == F_ROWS) by_b(Rows{});
-  else by_b(Any{});
+  const T *ap[TT], *bp[TT];
+  if constexpr (TT != 2) {
+    auto product = [&](auto am, auto bm) {
+      constexpr int AM = decltype(am)::value, BM = decltype(bm)::value;
+      rows(am, P.A, P.a_kc, P.lda, tm * EDGE, P.M, ap);
+      rows(bm, P.B, P.b_kc, P.ldb, tn * EDGE, P.N, bp);
+      reduce_wave<AM, BM, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+      ask();
+      leave_partial<AM, BM, TT>(acc, rs, sums, mine, rsum + wave * EDGE, li, g);
+    };
+    auto by_b = [&](auto am) {
+      if (P.b_mode == F_K4) product(am, K4{});
+      else if (TT == 4 && P.b_mode == F_ROWS) product(am, Rows{});
+      else product(am, Any{});
+    };
+    if (P.a_mode == F_K4) by_b(K4{});
+    else if (TT == 4 && P.a_mode == F_ROWS) by_b(Rows{});
+    else by_b(Any{});
+  } else {                 // 32-wide tiles: only the reduction's code is there in several forms (56.6 -> 55.4 us, two layers of 324)
+    rows(Any{}, P.A, P.a_kc, P.lda, tm * EDGE, P.M, ap);
+    rows(Any{}, P.B, P.b_kc, P.ldb, tn * EDGE, P.N, bp);
+    if (P.a_mode == F_K4) {
+      if (P.b_mode == F_K4) reduce_wave<F_K4, F_K4, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+      else reduce_wave<F_K4, F_ANY, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+    } else {
+      if (P.b_mode == F_K4) reduce_wave<F_ANY, F_K4, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+      else reduce_wave<F_ANY, F_ANY, TT, DEPTH>(ap, bp, ast, bst, g, c0, c1, K, sums, acc, rs);
+    }
+    ask();
+    leave_partial<F_ANY, F_ANY, TT>(acc, rs, sums, mine, rsum + wave * EDGE, li, g);
+  }
   __syncthreads();
   constexpr int PT = EDGE * LDP;
 #pragma unroll
