@@ -189,6 +189,42 @@ def test_batchnorm_any_channel_chunks(K, rows, C):
     assert relerr(host(dz), rdz) <= 4e-3 and relerr(host(dres), d) == 0
 
 
+@pytest.mark.parametrize("rows,C", [(1, 8), (2049, 8), (4096, 128), (4097, 128), (34816, 120), (34817, 120), (4096, 136)])
+def test_batchnorm_few_slabs(K, rows, C):
+    """The slabs' sums added by the kernel that applies them (at most 128 channels and 4096 sums a plane: pairs of sizes on
+    both sides of each edge), against float64: fp32 sums of at most 2048 terms a slab, then sums of the slabs, 1e-5 of the
+    terms' magnitude; stored results to bf16's half step (4e-3). Gradients are added to what is there; twice: same bits."""
+    import torch
+    rng = np.random.default_rng(rows * 7 + C)
+    z, res, dy = rnd(rng, (rows, C), 1), rnd(rng, (rows, C), 1), rnd(rng, (rows, C), 1)
+    g, b = rng.standard_normal(C).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    seen = []
+    for _ in range(2):
+        scratch = zeros((2 * 1024 + 2) * C + 64)
+        y = torch.zeros(rows, C, device="cuda", dtype=torch.bfloat16)
+        mean, rstd = zeros(C), zeros(C)
+        K.lpk_batchnorm_fwd(1, dev(z, 1), dev(g, 0), dev(b, 0), dev(res, 1), y, mean, rstd, rows, C, 1, scratch)
+        dz, dres = torch.zeros_like(y), torch.zeros_like(y)
+        dg, db = zeros(C) + 2, zeros(C) - 3
+        K.lpk_batchnorm_bwd(1, dev(dy, 1), y, dev(z, 1), mean, rstd, dev(g, 0), dz, dres, dg, db, rows, C, 1, 1, scratch)
+        seen.append([host(t) for t in (y, mean, rstd, dz, dres, dg, db)])
+    for a, ref in zip(*seen):
+        assert np.array_equal(a, ref)
+    y, mean, rstd, dz, dres, dg, db = seen[0]
+    z64 = z.astype(np.float64)
+    mu, rs = z64.mean(0), 1 / np.sqrt(z64.var(0) + 1e-5)
+    assert np.abs(mean - mu).max() <= 1e-5 * max(1.0, np.abs(mu).max()) and relerr(rstd, rs) <= 1e-5
+    xh = (z64 - mu) * rs
+    assert relerr(y, np.maximum(xh * g + b + res, 0)) <= 4e-3
+    d = dy.astype(np.float64) * (y > 0)
+    rdb, rdg = d.sum(0), (d * xh).sum(0)
+    assert np.abs(db + 3 - rdb).max() <= 1e-5 * np.abs(d).sum(0).max() + 1e-6
+    assert np.abs(dg - 2 - rdg).max() <= 1e-5 * np.abs(d * xh).sum(0).max() + 1e-6
+    assert relerr(dres, d) == 0
+    want = g * rs * (d - rdb / rows - xh * rdg / rows)
+    assert np.abs(dz - want).max() <= 4e-3 * np.abs(g * rs * d).max()
+
+
 @pytest.mark.parametrize("rows,C", [(39200, 24), (12000, 96), (3000, 1032)])
 @pytest.mark.parametrize("far", ["row 0", "mean"])
 def test_batchnorm_variance_keeps_its_bits(K, rows, C, far):
