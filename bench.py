@@ -291,10 +291,10 @@ def main():
         af, ab = attention_flops_per_step(cfg)
         ob, npar = optimizer_bytes_per_step(cfg)
         key = "gemm" if "gemm" in phases and cfg.layers[0].kind != "resnet_stage" else "conv"
-        # the class's ops: GEMMs run k_gemm_dma / k_mfma_tiles (+ k_splitk_reduce), convolutions the
-        # same tile kernel through gather loaders; fp32 products run k_gemm_f
-        kernel_names = {"gemm": "k_gemm_dma+k_mfma_tiles+k_splitk_reduce" if cfg.dtype == "bf16" else "k_gemm_f",
-                        "conv": "k_mfma_tiles<Conv*>+k_stem_fwd+k_stem_wgrad+k_splitk_reduce"}
+        # the class's ops: GEMMs run k_gemm_dma / k_gemm_tile (+ their reductions), convolutions the
+        # same tile through gather loaders; fp32 products run k_gemm_f
+        kernel_names = {"gemm": "k_gemm_dma+k_sk_fixup+k_gemm_tile+k_tile_reduce" if cfg.dtype == "bf16" else "k_gemm_f",
+                        "conv": "k_conv_tile+k_conv_reduce+k_stem_fwd+k_stem_wgrad"}
         if key in phases:
             p = phases[key]
             peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_F32_TFLOPS

@@ -1,5 +1,5 @@
-// bf16 product tile on the matrix cores, one output tile per block (and pieces that the persistent kernel shares): operand tiles stream global -> LDS with the 16-byte
-// direct-to-LDS load through a ring of NST stages of 64 k, so that a short reduction is in flight as a whole and a long
+// bf16 product tile on the matrix cores, one output tile per block (and pieces that the persistent kernel shares): operand
+// tiles stream global -> LDS with the 16-byte direct-to-LDS load through a ring of NST stages of 64 k, so that a short reduction is in flight as a whole and a long
 // one NST - 1 k-tiles ahead.  Generic over the operands' loaders (dense matrices here, pixels in the convolutions).
 //
 // Block: WGM x WGN waves of (32 TM) x (32 TN), v_mfma_f32_32x32x16_bf16, the n-side fragment as the first operand.

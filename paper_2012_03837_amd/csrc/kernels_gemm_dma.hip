@@ -1043,9 +1043,9 @@ hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
     // equal pieces (s = 1: whole tiles, no partial sums and no fix-up launch at all); blocks of one tile row or
     // column then walk the same k-steps together and share their operand panels.  Measured on a layer's four
     // weight gradients: width 768 (108 tiles: two pieces each, 128 k-steps against 108) 182 -> 172 us alone and the
-    // same step time; width 1024 (192 tiles: whole, 256 k-steps against 192) 279 -> 309 us: the k-step of this
-    // kernel with both operands k-major costs 1.05 .. 1.2 us however the operands are shared, so idle CUs are not
-    // paid back.  The uniform cut is taken when it leaves the longest block at most 1.25 times the balanced work.
+    // same step time; width 1024 (192 tiles: whole, 256 k-steps against 192) 279 -> 309 us (with a loop that waited
+    // for each k-tile's loads; 140 and 240 us as they are taken now): idle CUs are not paid back.  The uniform cut
+    // is taken when it leaves the longest block at most 1.25 times the balanced work.
     const long U = (long)p.tail_tiles * p.kt;
     long upb = (U + p.G - 1) / p.G;
     if (upb < min_len) upb = min_len;

@@ -13,8 +13,8 @@
 //   128 x 128, 4 stages        6.4              10.6                 19.4               62.7               145
 //   256 x 128, 3 stages        7.2              12.2                 25.8               51.4               103
 //   256 x 256, 2 stages       10.9              18.0                 45.7               76.2                91
-// (the last with GELU and a stored pre-activation; 69 us without, where the register-staged kernel that took these products
-// before had 81, and 58.9, 16.3 + 5.3, 13 to 15 and 8.8 us on the others from the right).
+// (the last with GELU and a stored pre-activation; 69 us without, where a kernel that staged its tiles through registers had 81,
+// and 58.9, 16.3 + 5.3, 13 to 15 and 8.8 us on the others from the right).
 #include <stdio.h>
 #include "gemm_tile.h"
 
