@@ -800,7 +800,8 @@ hipError_t bn_fwd_fast(const OpCtx& c, const void* z, const float* g, const floa
     k_bn_partial_v<0><<<nslab, 256, shm, c.stream>>>((const bf16_t*)z, nullptr, (const bf16_t*)z, nullptr, nullptr,
                                                      c.partial, rows, C, slab, 0);
     t.nslab = nslab;
-    if (bn_small(nslab, C)) return apply(Shifted{});
+    // not in place: the blocks take their pivots from row 0 of z, which block 0 has written by then
+    if (bn_small(nslab, C) && y != z) return apply(Shifted{});
     if (nslab >= kBnManySlabs)
       k_bn_finish_v<16><<<(C + 15) / 16, kBnFinishThreads, 0, c.stream>>>(c.partial, nslab, C, rows, (const bf16_t*)z, mean, rstd, 0, rm, rv, mom);
     else

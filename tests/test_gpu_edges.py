@@ -225,6 +225,28 @@ def test_batchnorm_few_slabs(K, rows, C):
     assert np.abs(dz - want).max() <= 4e-3 * np.abs(g * rs * d).max()
 
 
+@pytest.mark.parametrize("rows,C", [(2049, 8), (2048, 128), (2049, 128), (4000, 24), (4096, 136)])
+def test_batchnorm_in_place(K, rows, C):
+    """The normalised rows over the pre-activations themselves, few slabs and many, shifted sums and fp64 ones, against
+    float64, with a first row away from the mean so that a pivot read after row 0 is written shows.  fp32 sums of the shifted
+    terms: 1e-5 of their magnitude (168 roundings of 2^-24; a lane adds at most 16 rows of a slab, then lanes and slabs), so the
+    mean to 1e-5 E|z - p| and rstd to 1e-5 E(z - p)^2 / var (half of it from each sum); stored results bf16's half step, 4e-3."""
+    rng = np.random.default_rng(rows + C)
+    z = rnd(rng, (rows, C), 1)
+    z[0] = ops.bf16_round(z[0] + 8)
+    g, b = rng.standard_normal(C).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    buf = dev(z, 1)
+    mean, rstd = zeros(C), zeros(C)
+    K.lpk_batchnorm_fwd(1, buf, dev(g, 0), dev(b, 0), None, buf, mean, rstd, rows, C, 0, zeros((2 * 1024 + 2) * C + 64))
+    z64 = z.astype(np.float64)
+    mu, rs = z64.mean(0), 1 / np.sqrt(z64.var(0) + 1e-5)
+    far = np.abs(z64 - z64[0])
+    assert (np.abs(host(mean) - mu) <= 1e-5 * far.mean(0)).all()
+    assert (np.abs(host(rstd) / rs - 1) <= 1e-5 * (far ** 2).mean(0) / z64.var(0)).all()
+    want = (z64 - mu) * rs * g + b
+    assert np.abs(host(buf) - want).max() <= 4e-3 * np.abs(want).max()
+
+
 @pytest.mark.parametrize("rows,C", [(39200, 24), (12000, 96), (3000, 1032)])
 @pytest.mark.parametrize("far", ["row 0", "mean"])
 def test_batchnorm_variance_keeps_its_bits(K, rows, C, far):
