@@ -692,7 +692,7 @@ __global__ void __launch_bounds__(256) k_bn_bwd_apply_v(const bf16_t* __restrict
     if (j < C) {
       tot[j] = a;
       tot[C + j] = b;
-      if (blockIdx.x == 0) {
+      if (blockIdx.x == 0 && db) {      // none: the caller wants the input gradient only
         db[j] = accumulate ? db[j] + a : a;
         dg[j] = accumulate ? dg[j] + b : b;
       }

@@ -247,6 +247,26 @@ def test_batchnorm_in_place(K, rows, C):
     assert np.abs(host(buf) - want).max() <= 4e-3 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("rows,C", [(300, 16), (2048, 128), (2049, 128), (2000, 24)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_batchnorm_input_gradient_only(K, rows, C, accumulate):
+    """No shift and gain gradients wanted, few slabs and many: the input gradients are the same bits as with them."""
+    import torch
+    rng = np.random.default_rng(rows + C)
+    z, dy = dev(rnd(rng, (rows, C), 1), 1), dev(rnd(rng, (rows, C), 1), 1)
+    g, b = dev(rng.standard_normal(C).astype(np.float32), 0), zeros(C)
+    scratch = zeros((2 * 1024 + 2) * C + 64)
+    y, mean, rstd = torch.zeros_like(z), zeros(C), zeros(C)
+    K.lpk_batchnorm_fwd(1, z, g, b, None, y, mean, rstd, rows, C, 1, scratch)
+    seen = []
+    for dg, db in ((zeros(C), zeros(C)), (None, None)):
+        dz, dres = torch.zeros_like(z), torch.zeros_like(z)
+        K.lpk_batchnorm_bwd(1, dy, y, z, mean, rstd, g, dz, dres, dg, db, rows, C, 1, accumulate, scratch)
+        seen.append((dz, dres))
+    assert torch.equal(seen[0][0], seen[1][0]) and torch.equal(seen[0][1], seen[1][1])
+    assert bool((seen[0][0] != 0).any())
+
+
 @pytest.mark.parametrize("rows,C", [(39200, 24), (12000, 96), (3000, 1032)])
 @pytest.mark.parametrize("far", ["row 0", "mean"])
 def test_batchnorm_variance_keeps_its_bits(K, rows, C, far):
