@@ -390,9 +390,11 @@ hipError_t conv_bwd_data_mfma(const OpCtx& c, const ConvArgs& a, const void* dou
   return a.O % KT == 0 ? go(std::true_type{}, "ConvGather<true>, ConvFilterT<true>")
                        : go(std::false_type{}, "ConvGather<false>, ConvFilterT<false>");
 }
-hipError_t conv_bwd_weight_mfma(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
+hipError_t conv_bwd_weight_mfma(const OpCtx& c, const ConvArgs& conv, const void* dout, const void* x, float* dw,
                                 int accumulate) {
+  ConvArgs a = conv;
   const int K = a.N * a.P * a.Q, J = a.R * a.S * a.C;
+  if (K <= 0) a.P = a.Q = 1;      // no output pixels (a filter larger than the image): a sum of none, with divisors above zero
   const DenseLoader<false> A{Operand{(const bf16_t*)dout, a.O, a.O}};
   const Epilogue e = plain_epilogue(dw, J, 1, accumulate);
   auto go = [&](auto same, const char* name) {

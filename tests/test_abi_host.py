@@ -129,3 +129,15 @@ def test_scratch_sets_of_a_residual_mlp():
 
     assert step("bf16", 2) == step("bf16", 7)
     assert step("f32", 2) < step("f32", 7)
+
+
+def test_filter_gradient_without_output_pixels_returns_on_the_host():
+    """A 3 x 3 filter on a 2 x 2 image without padding has no output: the call's host part divides by no output size.  In a
+    process of its own without a device, where the launch behind it is an error code."""
+    import subprocess
+    import sys
+    code = ("import ctypes as C\nfrom paper_2012_03837_amd.binding import lib\n"
+            "print(lib().lpk_conv_bwd_weight(1, C.c_void_p(4096), C.c_void_p(8192), C.c_void_p(16384), 2, 2, 2, 8, 8, 3, 1, 0, 0, C.c_void_p(0)))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"), capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0 and int(r.stdout.split()[-1]) != 0, (r.returncode, r.stderr)

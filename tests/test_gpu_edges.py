@@ -786,6 +786,18 @@ def test_convolution_tiles(K, N, H, W, C, O, R, stride):
     assert relerr(host(gw), 2 * want) <= 2e-6
 
 
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_convolution_without_output_pixels(K, accumulate):
+    """A filter one larger than its image: the gradients of an empty sum (a stored one, and one added to what is there)."""
+    import torch
+    x, w, none = zeros(2, 2, 2, 16).bfloat16() + 1, zeros(8, 3, 3, 16).bfloat16() + 1, zeros(8).bfloat16()
+    dw, dx = zeros(8, 3, 3, 16) + 5, x.clone()
+    K.lpk_conv_bwd_weight(1, none, x, dw, 2, 2, 2, 16, 8, 3, 1, 0, accumulate=accumulate)
+    assert torch.equal(dw, torch.full_like(dw, 5.0 * accumulate))
+    K.lpk_conv_bwd_data(1, none, w, dx, 2, 2, 2, 16, 8, 3, 1, 0)
+    assert not bool(dx.any())
+
+
 @pytest.mark.parametrize("T,V,d", [(1, 1, 8), (33, 1, 16), (32, 3, 128), (65, 70, 24), (600, 40, 128), (2555, 1003, 448), (1100, 2, 1040),
                                    (4096, 5000, 768), (70, 9, 8192)])
 @pytest.mark.parametrize("accumulate", [0, 1])
