@@ -100,8 +100,9 @@ int lpk_transpose_bf16(const void* src_dev, void* dst_dev, int R, int C, void* s
 
 /* Embedding-table gradient: demb[v,:] (+)= sum of dh[t,:] over positions with ids[t] == v, in order of t
  * (ids outside [0, V) count as the nearest valid id, as in the forward lookup).  scratch_dev (may be NULL)
- * is device scratch of scratch_elems 4-byte words; with at least V words the kernel first counts every
- * id's positions there and skips the rows that do not occur. */
+ * is device scratch of scratch_elems 4-byte words.  With at least 2 T of them (T up to 65536, V T below 2^31 - 1, d a
+ * multiple of 8 up to 8192, dh and demb on 16-byte boundaries) the positions are sorted there first; otherwise, with
+ * at least V, every id's positions are counted there and the rows that do not occur are skipped.  Same bits each way. */
 int lpk_embed_bwd(int dtype, const int32_t* ids, const void* dh, float* demb, int T, int V, int d, int accumulate,
                   float* scratch_dev, size_t scratch_elems, void* stream);
 

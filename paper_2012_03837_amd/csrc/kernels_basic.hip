@@ -2,6 +2,7 @@
 // the fused optimizer update, and the weight initialiser.  64-wide wavefront reductions; every
 // reduction has a fixed order, so repeated runs are bit-identical.
 #include "common.h"
+#include "gemm_common.h"
 
 namespace lp {
 
@@ -183,14 +184,16 @@ __global__ void k_embed_bwd(const int32_t* ids, const int* __restrict__ counts, 
     if (n_hits != 0 || !accumulate) demb[o] = accumulate ? demb[o] + acc : acc;
   }
 }
-// The same sums from a sorted list of positions.  A block per table row that scans all ids and then adds its rows one after
-// another is a chain of memory latencies: the most frequent of 8192 Zipf-distributed ids has 1150 rows, and the launch took
-// 141 us at width 128, behind 24 us of counting.  Here the positions are sorted by (id, position) first: a
+// The same sums, in the same order, from a sorted list of positions.  A block per table row that scans all ids and then adds its
+// rows one after another is a chain of memory latencies: the most frequent of 8192 Zipf-distributed ids has 1250 rows, and the
+// launch took 141 us at width 128, behind 24 us of counting.  Here the positions are sorted by (id, position) first: a
 // position's place is the number of smaller keys, counted by comparing it with all others (T^2 / 64 wave compares, about
 // 8 us for 8192 positions on half the compute units; the other blocks of the launch clear the table meanwhile).  Then rows of
-// up to 32 positions are added by a wave each, in position order, longer ones by a block of 1024 threads whose row lanes add
-// every RL-th row, eight loads in flight, and are added in order.  Alone, both launches: 8192 positions, 8000 ids of width 128
-// 70 -> 21 us; 32000 of 768 172 -> 41; 2048 positions, 16000 of 512 36 -> 16.
+// up to 32 positions are added by a wave each, longer ones by a block per 256 columns: 1024 threads bring tiles of 32
+// positions through LDS, four of them in flight, and a thread per column adds them in position order.
+// All launches of a call: 8192 positions, 8000 ids of width 128 96 -> 35 us (22 us where row lanes added every 64th position:
+// 1250 additions in order are 4 us at best, a tile's way through LDS twice that); 32000 of 768 196 -> 43; 2048 positions, 16000
+// of 512 46 -> 18; 65536 positions, 32000 of 64 735 -> 408.
 constexpr int kEmbedShort = 32, kEmbedKeys = 8192;
 __global__ void __launch_bounds__(1024) k_embed_order(const int32_t* __restrict__ ids, int T_, int V, int* __restrict__ order,
                                                       int* __restrict__ sorted, float* __restrict__ demb, size_t clear4, int sort_blocks) {
@@ -228,20 +231,38 @@ __global__ void __launch_bounds__(1024) k_embed_order(const int32_t* __restrict_
     sorted[at] = id;
   }
 }
-__device__ __forceinline__ void add8(const bf16_t* p, float* a) {
-  const bf16x8 v = *reinterpret_cast<const bf16x8*>(p);
+template <typename T> struct EightOf;
+template <> struct EightOf<bf16_t> { bf16x8 v; };
+template <> struct EightOf<float> { f32x4 v, u; };
+__device__ __forceinline__ void fetch8(const bf16_t* p, EightOf<bf16_t>& r) { r.v = *reinterpret_cast<const bf16x8*>(p); }
+__device__ __forceinline__ void fetch8(const float* p, EightOf<float>& r) { r.v = *reinterpret_cast<const f32x4*>(p); r.u = *reinterpret_cast<const f32x4*>(p + 4); }
+__device__ __forceinline__ void widen8(const EightOf<bf16_t>& r, float* a) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] += (float)v[e];
+  for (int e = 0; e < 8; ++e) a[e] = (float)r.v[e];
 }
-__device__ __forceinline__ void add8(const float* p, float* a) {
-  const f32x4 v = *reinterpret_cast<const f32x4*>(p), u = *reinterpret_cast<const f32x4*>(p + 4);
+__device__ __forceinline__ void widen8(const EightOf<float>& r, float* a) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) { a[e] += v[e]; a[4 + e] += u[e]; }
+  for (int e = 0; e < 4; ++e) { a[e] = r.v[e]; a[4 + e] = r.u[e]; }
 }
+template <typename T>
+__device__ __forceinline__ void add8(const T* p, float* a) {
+  EightOf<T> r;
+  float v[8];
+  fetch8(p, r);
+  widen8(r, v);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] += v[e];
+}
+// A barrier behind this wave's LDS accesses alone (__syncthreads would wait for the loads in flight too).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// A long row's tile in LDS: 32 positions of 256 columns, fp32, the lower four of every eight columns in the first half (whole
+// 16-byte writes of neighbouring lanes; constants, so that all reads of a column are offsets from one address).
+constexpr int kEmbedTileRows = 32, kEmbedTileCols = 256, kEmbedTile = kEmbedTileRows * kEmbedTileCols;
+constexpr int kEmbedTilesAhead = 4, kEmbedAhead = (kEmbedTilesAhead + 1) * kEmbedTileRows;      // tiles in flight; positions asked for past a batch's end
 template <typename T>
 __global__ void __launch_bounds__(1024) k_embed_rows(const int* __restrict__ order, const int* __restrict__ sorted,
                                                      const T* __restrict__ dh, float* __restrict__ demb, int T_, int d, int accumulate,
-                                                     int short_blocks) {
+                                                     int short_blocks, int groups) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), CH = d >> 3;
   if ((int)blockIdx.x < short_blocks) {          // a wave per position that starts a row
     const int p = blockIdx.x * 16 + w;
@@ -266,38 +287,75 @@ __global__ void __launch_bounds__(1024) k_embed_rows(const int* __restrict__ ord
     }
     return;
   }
-  // Long rows: every one holds a position that is a multiple of kEmbedShort; the block of the first such position takes it.
-  __shared__ int pos[1024];
-  __shared__ float red[1024 * 8];
-  const int p0 = (blockIdx.x - short_blocks) * kEmbedShort, v = sorted[p0];
+  // Long rows: every one holds a position that is a multiple of kEmbedShort; the blocks of the first such position take it.
+  constexpr int AHEAD = kEmbedTilesAhead;
+  extern __shared__ __attribute__((aligned(16))) float tiles[];      // two of them, and where 1024 positions' rows start
+  unsigned* at = reinterpret_cast<unsigned*>(tiles + 2 * kEmbedTile);       // (in elements: at most 65536 of 8192), then the first row's
+  const int lb = blockIdx.x - short_blocks, p0 = (lb / groups) * kEmbedShort, v = sorted[p0];
   if (p0 >= kEmbedShort && sorted[p0 - kEmbedShort] == v) return;
   const int before = p0 - 1 - lane;
   const int start = p0 - __popcll(__ballot(lane < kEmbedShort && before >= 0 && sorted[before >= 0 ? before : 0] == v));
   if (start + kEmbedShort >= T_ || sorted[start + kEmbedShort] != v) return;
-  const int RL = 1024 / CH, rl = threadIdx.x / CH, c = threadIdx.x - rl * CH;
-  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const int first = lb % groups * kEmbedTileCols, cols = d - first < kEmbedTileCols ? d - first : kEmbedTileCols;
+  const int rl = threadIdx.x >> 5, c = threadIdx.x & 31;
+  const bool has = 8 * c < cols;
+  const T* src = dh + first + (has ? 8 * c : 0);
+  const int column = 8 * (lane >> 2) + 128 * (w & 1) + 4 * (w >> 1) + (lane & 3);       // of this thread, if it adds
+  const bool adds = w < 4 && 128 * (w & 1) < cols;
+  float sum = 0.f;
+  if (threadIdx.x < kEmbedAhead) at[1024 + threadIdx.x] = 0;
   for (int base = start;; base += 1024) {
     const int i = base + threadIdx.x;
     const bool mine = i < T_ && sorted[i] == v;
-    pos[threadIdx.x] = mine ? order[i] : 0;
+    at[threadIdx.x] = mine ? (unsigned)order[i] * (unsigned)d : 0;
     const int n = __syncthreads_count(mine);
-    if (rl < RL) {
-#pragma unroll 8
-      for (int r = rl; r < n; r += RL) add8(dh + (size_t)pos[r] * d + 8 * c, a);
-    }
-    if (n < 1024) break;
-    __syncthreads();
-  }
-  if (rl < RL) {
+    if (n == 0) break;
+    // every load is issued (past the end the first row's): with some skipped, a wait for the oldest would wait for all
+    auto fetch = [&](int r, EightOf<T>& e) { fetch8(src + at[r], e); };
+    auto leave = [&](const EightOf<T>& e, float* to) {
+      float a[8];
+      widen8(e, a);
+      f32x4* o = reinterpret_cast<f32x4*>(to + rl * kEmbedTileCols + 4 * c);
+      if (has) {
+        o[0] = f32x4{a[0], a[1], a[2], a[3]};
+        o[32] = f32x4{a[4], a[5], a[6], a[7]};
+      }
+    };
+    EightOf<T> row[AHEAD];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[rl * d + 8 * c + e] = a[e];
+    for (int s = 0; s < AHEAD; ++s) fetch(s * kEmbedTileRows + rl, row[s]);
+    leave(row[0], tiles);
+    fetch(AHEAD * kEmbedTileRows + rl, row[0]);
+    for (int r0 = 0; r0 < n; r0 += AHEAD * kEmbedTileRows) {
+#pragma unroll
+      for (int s = 0; s < AHEAD; ++s) {         // the next tile is left in one half while this one is added from the other
+        constexpr int N = AHEAD;
+        const int t0 = r0 + s * kEmbedTileRows;
+        float x[kEmbedTileRows];
+        if (t0 >= n) break;
+        lds_barrier();
+        if (adds) {
+#pragma unroll
+          for (int u = 0; u < kEmbedTileRows; ++u) x[u] = tiles[s % 2 * kEmbedTile + u * kEmbedTileCols + threadIdx.x];
+        }
+        leave(row[(s + 1) % N], tiles + (s + 1) % 2 * kEmbedTile);
+        fetch(t0 + (N + 1) * kEmbedTileRows + rl, row[(s + 1) % N]);
+        if (adds) {
+          if (t0 + kEmbedTileRows > n) {
+#pragma unroll
+            for (int u = 0; u < kEmbedTileRows; ++u) x[u] = t0 + u < n ? x[u] : 0.f;      // no change: the sum is never -0
+          }
+#pragma unroll
+          for (int u = 0; u < kEmbedTileRows; ++u) sum += x[u];
+        }
+      }
+    }
+    lds_barrier();
+    if (n < 1024) break;
   }
-  __syncthreads();
-  for (int j = threadIdx.x; j < d; j += 1024) {
-    float t = 0.f;
-    for (int r = 0; r < RL; ++r) t += red[r * d + j];
-    const size_t o = (size_t)v * d + j;
-    demb[o] = accumulate ? demb[o] + t : t;
+  if (adds && column < cols) {
+    float* o = demb + (size_t)v * d + first + column;
+    *o = accumulate ? *o + sum : sum;
   }
 }
 hipError_t op_embed_bwd(const OpCtx& c, const int32_t* ids, const void* dh, float* demb, int T_, int V, int d,
@@ -310,18 +368,24 @@ hipError_t op_embed_bwd(const OpCtx& c, const int32_t* ids, const void* dh, floa
       (((uintptr_t)dh | (uintptr_t)demb) & 15) == 0) {
     int* order = reinterpret_cast<int*>(c.partial);
     int* sorted = order + T_;
-    const int sort_blocks = (T_ + 63) / 64, short_blocks = (T_ + 15) / 16, long_blocks = (T_ + kEmbedShort - 1) / kEmbedShort;
+    const int sort_blocks = (T_ + 63) / 64, short_blocks = (T_ + 15) / 16;
+    const int groups = (d + kEmbedTileCols - 1) / kEmbedTileCols, long_blocks = (T_ + kEmbedShort - 1) / kEmbedShort * groups;
     const size_t clear4 = accumulate ? 0 : (size_t)V * d / 4;
     const size_t want = (clear4 + 4095) / 4096;
     const int clear_blocks = (int)(want < 512 ? want : 512);
     k_embed_order<<<sort_blocks + clear_blocks, 1024, 0, c.stream>>>(ids, T_, V, order, sorted, demb, clear4, sort_blocks);
     hipError_t e = LP_LAUNCH_CHECK();
     if (e != hipSuccess) return e;
-    if (c.dt == BF16)
-      k_embed_rows<bf16_t><<<short_blocks + long_blocks, 1024, 0, c.stream>>>(order, sorted, (const bf16_t*)dh, demb, T_, d, accumulate, short_blocks);
-    else
-      k_embed_rows<float><<<short_blocks + long_blocks, 1024, 0, c.stream>>>(order, sorted, (const float*)dh, demb, T_, d, accumulate, short_blocks);
-    return LP_LAUNCH_CHECK();
+    auto rows = [&](auto zero) {
+      typedef decltype(zero) T;
+      constexpr int lds = (2 * kEmbedTile + 1024 + kEmbedAhead) * 4;
+      static LdsLimit limit;
+      const hipError_t le = limit.raise(reinterpret_cast<const void*>(k_embed_rows<T>), lds);
+      if (le != hipSuccess) return le;
+      k_embed_rows<T><<<short_blocks + long_blocks, 1024, lds, c.stream>>>(order, sorted, (const T*)dh, demb, T_, d, accumulate, short_blocks, groups);
+      return LP_LAUNCH_CHECK();
+    };
+    return c.dt == BF16 ? rows(bf16_t()) : rows(0.f);
   }
   // per-id counts in the reduction scratch (integers; 0.0f is the zero word)
   int* counts = nullptr;

@@ -825,6 +825,24 @@ def test_embedding_gradient_sorted(K, T, V, d, accumulate):
         assert bool((outs[0][torch.from_numpy(never).cuda().long()] == float(accumulate)).all())
 
 
+@pytest.mark.parametrize("T,V,d", [(33, 1, 16), (600, 40, 136), (3000, 3, 8), (3000, 5, 264), (2048, 1, 768), (1100, 2, 2056), (70, 9, 8192)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_embedding_gradient_order(K, T, V, d, accumulate):
+    """A table row is the fp32 sum of its positions' rows in order of t, bit for bit, whichever kernels add it: from the sorted
+    list (rows below and above 32 positions, above 1024, several column groups), counted, and without scratch."""
+    rng = np.random.default_rng(T + V + d)
+    ids = (rng.zipf(1.5, T) - 1).clip(0, V - 1).astype(np.int32)
+    for dtype in (0, 1):
+        dh = rnd(rng, (T, d), dtype)
+        ref = np.zeros((V, d), np.float32)
+        np.add.at(ref, ids, dh.astype(np.float32))            # one position after the other
+        ref += np.float32(accumulate)
+        for words in (2 * T, V, 0):
+            demb = zeros(V, d) + 1
+            K.lpk_embed_bwd(dtype, dev(ids, 0), dev(dh, dtype), demb, T, V, d, accumulate, scratch=zeros(words) if words else None)
+            np.testing.assert_array_equal(host(demb).astype(np.float32), ref)
+
+
 @pytest.mark.parametrize("B,S,H,dh", [(1, 1, 1, 64), (3, 129, 3, 64), (2, 200, 5, 32), (1, 500, 9, 16), (5, 511, 7, 64), (64, 128, 8, 16), (65, 128, 8, 64)])
 @pytest.mark.parametrize("causal", [0, 1])
 def test_attention_backward_launches(K, B, S, H, dh, causal):
