@@ -50,6 +50,16 @@ int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda, const void
                      int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
                      float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
 
+/* The same products on a chosen kernel (for tests and measurements): shape -1 is the persistent kernel of lpk_gemm_grouped, with
+ * any K that its operands' 16-byte accesses allow (at least 128 if not a multiple of 32); shape 0 .. 5 is one tile per block, n
+ * up to 4, tiles of 64 x 64, 128 x 64, 128 x 128 (two stages), 128 x 128 (four), 256 x 128 or 256 x 256, the reduction in
+ * `pieces` equal runs of whole 64-deep k-tiles (the last may be shorter; hipErrorInvalidValue if there is no such cut) that a
+ * second launch adds in order from splitk_ws_dev (pieces * sum M_i N_i floats). */
+int lpk_gemm_grouped_tiles(int shape, int pieces, int n, const void* const* A, const int64_t* lda, const void* const* B,
+                           const int64_t* ldb, void* const* C, const int64_t* ldc, int c_f32, const int* M, const int* N, int K,
+                           int a_kc, int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
+                           float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
+
 /* Causal (or full) multi-head attention of a decoder layer (appendix B.2).  qkv [B*S, 3*H*dh]
  * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch. */
 int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal,
@@ -121,6 +131,21 @@ int lpk_conv_bwd_weight(int dtype, const void* dout, const void* x, float* dw, i
 int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x, float* dw, int N, int H, int W, int C, int O,
                            int R, int stride, int pad, int accumulate, float* splitk_ws_dev, size_t splitk_ws_elems,
                            void* stream);
+
+/* A bf16 convolution on chosen tiles of the matrix-core kernel (for tests and measurements).  dir 0: out = conv(a = x, b = w);
+ * 1: out = data gradient of (a = dout, b = w), plus `add` if given; 2: out (fp32) = filter gradient of (a = dout, b = x), added to
+ * what is there if `accumulate`.  shape: rows x columns 0: 64 x 64, 1: 128 x 64, 2: 128 x 128 (two stages), 3: 128 x 128 (four),
+ * 4: 256 x 128, 6: 64 x 128, 7: 256 x 64, 8: 128 x 32 (outputs of at most 32 columns); pieces as in lpk_gemm_grouped_tiles.
+ * dir 0 with stats_dev: where the output is whole tiles in one piece, the normalisation's sums per tile and column
+ * ([3][tiles][O] floats: sum (z - p), sum (z - p)^2 and p, the tile's first row) are left there and *stats_rows is a
+ * tile's rows, otherwise 0.  hipErrorInvalidValue if the kernel does not take the convolution that way. */
+int lpk_conv_tile(int dir, const void* a, const void* b, void* out, const void* add, int accumulate, int N, int H, int W, int C,
+                  int O, int R, int stride, int pad, int shape, int pieces, float* stats_dev, size_t stats_elems, int* stats_rows,
+                  float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
+/* The shape and number of pieces the library takes for such a convolution by itself, with splitk_ws_elems floats of workspace
+ * (host only). */
+int lpk_conv_plan(int dir, int N, int H, int W, int C, int O, int R, int stride, int pad, size_t splitk_ws_elems, int* shape,
+                  int* pieces);
 
 /* One convolution + normalisation unit of a ResNet stage, forward (appendix B.3): z = conv(x, w) as lpk_conv_fwd,
  * then y = [relu](bn(z) (+ res)) as lpk_batchnorm_fwd, with z, y, mean, rstd all written.  Where the convolution's

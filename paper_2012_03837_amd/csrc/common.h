@@ -123,6 +123,7 @@ struct OpCtx {
   size_t partial_elems;
   Profiler* prof = nullptr;
   int gemm_variant = 0;         // 0: chosen by the cost model; otherwise a forced GEMM kernel (see lpk_gemm)
+  int tile_shape = -1, tile_pieces = 1;   // one-tile-per-block products: a forced tile shape and cut (-1: by the cost model)
   float* splitk_ws = nullptr;   // fp32 workspace for split-K partial sums (may be null: no split-K)
   size_t splitk_elems = 0;
   PendingSums* pending = nullptr;   // where op_layernorm_bwd and op_colsum_batched may leave their sums (null: nowhere)

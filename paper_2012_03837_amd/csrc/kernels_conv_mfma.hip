@@ -318,11 +318,14 @@ hipError_t launch_shape(const OpCtx& c, const LA& A, const LB& B, const Epilogue
 // Tile shapes beside those of the dense products: 256 x 64 and 64 x 128 for 64-channel convolutions and their filter gradients;
 // 128 x 32 where the output has at most 32 columns (65536 pixels x 16 channels: 12.0 us with 64 columns, 8.8 with 32; with
 // more columns than that it loses to 64 x 64: 2450 x 96 16.9 against 9.9 us).
+TilePlan conv_plan(const OpCtx& c, int M, int N, int K) {
+  const unsigned mask = 0x1f | 1u << 6 | 1u << 7 | (N <= 32 ? 1u << 8 : 0u);
+  return tile_plan(c, 1, &M, &N, K, mask, 64);
+}
 template <class LA, class LB>
 hipError_t conv_product(const OpCtx& c, const LA& A, const LB& B, const Epilogue& e, int M, int N, int K, const char* loaders,
                         ConvStats* st = nullptr) {
-  const unsigned mask = 0x1f | 1u << 6 | 1u << 7 | (N <= 32 ? 1u << 8 : 0u);
-  const TilePlan plan = tile_plan(c, 1, &M, &N, K, mask, 64);
+  const TilePlan plan = conv_plan(c, M, N, K);
   hipError_t err = hipErrorInvalidValue;
   switch (plan.shape) {
     case 0: err = launch_shape<LA, LB, 2, 2, 1, 1, 4>(c, A, B, e, M, N, K, plan, loaders, st); break;
@@ -360,6 +363,13 @@ bool conv_mfma_ok(const OpCtx& c, const ConvArgs& a, const void* p0, const void*
   return c.dt == BF16 && a.C % 8 == 0 && a.O % 8 == 0 && a.C >= 8 && a.O >= 8 && small && al16(p0) && al16(p1) && al16(p2);
 }
 
+// The tiles that a convolution's forward (0), data-gradient (1) or filter-gradient (2) product takes.
+TilePlan conv_mfma_plan(const OpCtx& c, const ConvArgs& a, int dir) {
+  const int pixels = a.N * a.P * a.Q, taps = a.R * a.S;
+  if (dir == 0) return conv_plan(c, pixels, a.O, taps * a.C);
+  if (dir == 1) return conv_plan(c, a.N * a.H * a.W, a.C, taps * a.O);
+  return conv_plan(c, a.O, taps * a.C, pixels);
+}
 hipError_t conv_fwd_mfma(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out, ConvStats* st) {
   const int M = a.N * a.P * a.Q, K = a.R * a.S * a.C;
   if (M <= 0) return hipSuccess;

@@ -161,6 +161,14 @@ hipError_t op_gemm(const OpCtx& c, const GemmArgs& g) {
   return gemm_f32(c, &g, 1);
 }
 
+// n <= kTileGroupMax products in one launch of the one-tile-per-block kernel, whatever the other grouped kernel would cost.
+hipError_t gemm_tile_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
+  if (n < 1 || n > kTileGroupMax || c.dt != BF16) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (!fast_ok(gs[i]) || gs[i].K != gs[0].K || gs[i].a_kc != gs[0].a_kc || gs[i].b_kc != gs[0].b_kc || gs[i].rowsum) return hipErrorInvalidValue;
+  return gemm_tile(c, gs, n, gemm_tile_plan(c, gs, n));
+}
+
 static bool grouping_off() {     // LP_NO_GROUP=1: every product in a launch of its own (for measurements)
   static int v = -1;
   if (v < 0) { const char* s = getenv("LP_NO_GROUP"); v = (s && s[0] == '1') ? 1 : 0; }

@@ -165,11 +165,21 @@ hipError_t launch_group(const OpCtx& c, const GemmArgs* gs, int n, const TilePla
 }  // namespace
 
 // The cheapest tile shape and number of pieces for n products that share a launch.  Long reductions over few tiles are cut
-// into pieces of at least eight k-tiles, whose fp32 partial sums a second launch adds in order (4.5 TB/s and 4.6 us: what the
+// into pieces of about eight k-tiles or more (the last may be shorter: 25 in three are 9, 9 and 7), whose fp32 partial sums a second launch adds in order (4.5 TB/s and 4.6 us: what the
 // smallest launch costs behind another one).
 TilePlan tile_plan(const OpCtx& c, int n, const int* M, const int* N, int K, unsigned mask, int max_pieces) {
   TilePlan best;
   const int nt = (K + KT - 1) / KT;
+  if (c.tile_shape >= 0) {              // forced (nothing that the workspace does not hold)
+    double elems = 0.0;
+    for (int i = 0; i < n; ++i) elems += (double)M[i] * N[i];
+    const int sp = c.tile_pieces < 1 ? 1 : c.tile_pieces, per = (nt + sp - 1) / sp, pieces = per > 0 ? (nt + per - 1) / per : 1;
+    if (c.tile_shape >= kTileShapes || !(mask >> c.tile_shape & 1) || pieces != sp ||
+        (pieces > 1 && (!c.splitk_ws || pieces * elems > (double)c.splitk_elems)))
+      return best;
+    best.shape = c.tile_shape; best.splits = pieces; best.per = per; best.us = 0.0;
+    return best;
+  }
   for (int s = 0; s < kTileShapes; ++s) {
     if (!(mask >> s & 1)) continue;
     const TileShape& h = kShapes[s];

@@ -4,11 +4,15 @@
 
 #include "../../include/lp_kernels.h"
 #include "common.h"
+#include "gemm_common.h"
 
 namespace lp {
 hipError_t gemm_f32(const OpCtx& c, const GemmArgs* gs, int n);
 hipError_t gemm_mfma(const OpCtx& c, const GemmArgs& g);
 hipError_t gemm_dma_grouped(const OpCtx& c, const GemmArgs* gs, int n);
+hipError_t gemm_tile_grouped(const OpCtx& c, const GemmArgs* gs, int n);
+bool conv_mfma_ok(const OpCtx& c, const ConvArgs& a, const void* p0, const void* p1, const void* p2);
+TilePlan conv_mfma_plan(const OpCtx& c, const ConvArgs& a, int dir);
 hipError_t attn_fwd_plain(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
 hipError_t attn_bwd_plain(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                           void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
@@ -45,12 +49,11 @@ extern "C" int lpk_gemm(int dtype, const void* A, int64_t lda, int a_kc, const v
   c.gemm_variant = variant;
   return (int)op_gemm(c, g);
 }
-extern "C" int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda, const void* const* B, const int64_t* ldb,
-                                void* const* C, const int64_t* ldc, int c_f32, const int* M, const int* N, int K, int a_kc,
-                                int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
-                                float* splitk_ws, size_t splitk_ws_elems, void* stream) {
+extern "C" int lpk_gemm_grouped_tiles(int shape, int pieces, int n, const void* const* A, const int64_t* lda, const void* const* B,
+                                      const int64_t* ldb, void* const* C, const int64_t* ldc, int c_f32, const int* M, const int* N,
+                                      int K, int a_kc, int b_kc, const float* const* bias, int act, const void* const* res,
+                                      int accumulate, float* splitk_ws, size_t splitk_ws_elems, void* stream) {
   if (n < 1 || n > 16 || !A || !lda || !B || !ldb || !C || !ldc || !M || !N) return (int)hipErrorInvalidValue;
-  if (K % 32) return (int)hipErrorInvalidValue;
   GemmArgs g[16];
   for (int i = 0; i < n; ++i) {
     if (M[i] % 8) return (int)hipErrorInvalidValue;
@@ -62,7 +65,17 @@ extern "C" int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda,
   }
   OpCtx c = mk(BF16, stream);
   c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws_elems;
-  return (int)gemm_dma_grouped(c, g, n);
+  if (shape < 0) return (int)gemm_dma_grouped(c, g, n);
+  c.tile_shape = shape; c.tile_pieces = pieces;
+  return (int)gemm_tile_grouped(c, g, n);
+}
+extern "C" int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda, const void* const* B, const int64_t* ldb,
+                                void* const* C, const int64_t* ldc, int c_f32, const int* M, const int* N, int K, int a_kc,
+                                int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
+                                float* splitk_ws, size_t splitk_ws_elems, void* stream) {
+  if (K % 32) return (int)hipErrorInvalidValue;
+  return lpk_gemm_grouped_tiles(-1, 1, n, A, lda, B, ldb, C, ldc, c_f32, M, N, K, a_kc, b_kc, bias, act, res, accumulate, splitk_ws,
+                                splitk_ws_elems, stream);
 }
 extern "C" int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh,
                                  int causal, int plain, void* stream) {
@@ -165,6 +178,34 @@ extern "C" int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x
   OpCtx c = mk(dtype, stream);
   c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws ? splitk_ws_elems : 0;
   return (int)op_conv_bwd_weight(c, mkconv(N, H, W, C, O, R, stride, pad), dout, x, dw, accumulate);
+}
+extern "C" int lpk_conv_plan(int dir, int N, int H, int W, int C, int O, int R, int stride, int pad, size_t splitk_ws_elems,
+                             int* shape, int* pieces) {
+  if (dir < 0 || dir > 2 || !shape || !pieces) return (int)hipErrorInvalidValue;
+  static float ws;                       // only whether there is a workspace matters
+  OpCtx c = mk(BF16, nullptr);
+  c.splitk_ws = splitk_ws_elems ? &ws : nullptr; c.splitk_elems = splitk_ws_elems;
+  const ConvArgs a = mkconv(N, H, W, C, O, R, stride, pad);
+  if (!conv_mfma_ok(c, a, nullptr, nullptr, nullptr)) return (int)hipErrorInvalidValue;
+  const TilePlan p = conv_mfma_plan(c, a, dir);
+  *shape = p.shape; *pieces = p.splits;
+  return 0;
+}
+extern "C" int lpk_conv_tile(int dir, const void* a, const void* b, void* out, const void* add, int accumulate, int N, int H, int W,
+                             int C, int O, int R, int stride, int pad, int shape, int pieces, float* stats, size_t stats_elems,
+                             int* stats_rows, float* splitk_ws, size_t splitk_ws_elems, void* stream) {
+  OpCtx c = mk(BF16, stream);
+  c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws ? splitk_ws_elems : 0;
+  c.tile_shape = shape; c.tile_pieces = pieces;
+  const ConvArgs g = mkconv(N, H, W, C, O, R, stride, pad);
+  if (dir < 0 || dir > 2 || !conv_mfma_ok(c, g, a, b, out) || ((uintptr_t)add & 15)) return (int)hipErrorInvalidValue;
+  if (dir == 1) return (int)op_conv_bwd_data(c, g, a, b, out, add);
+  if (dir == 2) return (int)op_conv_bwd_weight(c, g, a, b, (float*)out, accumulate);
+  ConvStats st;
+  st.buf = stats; st.cap = stats ? stats_elems : 0;
+  const hipError_t e = op_conv_fwd(c, g, a, b, out, &st);
+  if (stats_rows) *stats_rows = st.nslab > 0 ? st.slab_rows : 0;
+  return (int)e;
 }
 extern "C" int lpk_conv_bn_fwd(int dtype, const void* x, const void* w, void* z, const float* g, const float* b,
                                const void* res, void* y, float* mean, float* rstd, int N, int H, int W, int C, int O,

@@ -37,9 +37,9 @@ def lpk_gemm(dtype, A, lda, a_kc, B, ldb, b_kc, Cout, ldc, c_f32, M, N, K, bias=
                        _sz(0 if splitk_ws is None else splitk_ws.numel()), _stream()), "lpk_gemm")
 
 
-def lpk_gemm_grouped(As, Bs, Cs, Ms, Ns, K, a_kc, b_kc, accumulate, splitk_ws, biases=None, act=0, ress=None):
+def lpk_gemm_grouped(As, Bs, Cs, Ms, Ns, K, a_kc, b_kc, accumulate, splitk_ws, biases=None, act=0, ress=None, tiles=None):
     """As, Bs, Cs: lists of torch CUDA tensors (bf16 operands as stored; outputs [M_i, N_i], all fp32 or all bf16);
-    biases / ress: optional lists of fp32 [N_i] / bf16 [M_i, N_i] tensors."""
+    biases / ress: optional lists of fp32 [N_i] / bf16 [M_i, N_i] tensors; tiles: (shape, pieces) of lpk_gemm_grouped_tiles."""
     import torch
     n = len(As)
     vp = (C.c_void_p * n)
@@ -48,12 +48,14 @@ def lpk_gemm_grouped(As, Bs, Cs, Ms, Ns, K, a_kc, b_kc, accumulate, splitk_ws, b
     c_f32 = 1 if Cs[0].dtype == torch.float32 else 0
     bias = vp(*[b.data_ptr() for b in biases]) if biases is not None else None
     res = vp(*[r.data_ptr() for r in ress]) if ress is not None else None
-    _ck(lib().lpk_gemm_grouped(_i(n), vp(*[a.data_ptr() for a in As]), i64(*[a.shape[1] for a in As]),
-                               vp(*[b.data_ptr() for b in Bs]), i64(*[b.shape[1] for b in Bs]),
-                               vp(*[c.data_ptr() for c in Cs]), i64(*[c.shape[1] for c in Cs]), _i(c_f32), ia(*Ms), ia(*Ns),
-                               _i(K), _i(a_kc), _i(b_kc), bias, _i(act), res, _i(accumulate), _p(splitk_ws),
-                               _sz(splitk_ws.numel()), _stream()),
-        "lpk_gemm_grouped")
+    args = [_i(n), vp(*[a.data_ptr() for a in As]), i64(*[a.shape[1] for a in As]), vp(*[b.data_ptr() for b in Bs]),
+            i64(*[b.shape[1] for b in Bs]), vp(*[c.data_ptr() for c in Cs]), i64(*[c.shape[1] for c in Cs]), _i(c_f32),
+            ia(*Ms), ia(*Ns), _i(K), _i(a_kc), _i(b_kc), bias, _i(act), res, _i(accumulate), _p(splitk_ws),
+            _sz(splitk_ws.numel()), _stream()]
+    if tiles is None:
+        _ck(lib().lpk_gemm_grouped(*args), "lpk_gemm_grouped")
+    else:
+        _ck(lib().lpk_gemm_grouped_tiles(_i(tiles[0]), _i(tiles[1]), *args), "lpk_gemm_grouped_tiles")
 
 
 def lpk_attention_fwd(dtype, qkv, o, lse, B, S, H, dh, causal=1, plain=0):
@@ -129,6 +131,25 @@ def lpk_conv_bwd_weight_ws(dtype, dout, x, dw, N, H, W, Cin, O, R, stride, pad, 
     _ck(lib().lpk_conv_bwd_weight_ws(_i(dtype), _p(dout), _p(x), _p(dw), _i(N), _i(H), _i(W), _i(Cin), _i(O), _i(R),
                                      _i(stride), _i(pad), _i(accumulate), _p(splitk_ws), _sz(splitk_ws.numel()),
                                      _stream()), "lpk_conv_bwd_weight_ws")
+
+
+def lpk_conv_tile(direction, a, b, out, N, H, W, Cin, O, R, stride, pad, shape, pieces=1, add=None, accumulate=0, stats=None,
+                  splitk_ws=None):
+    """Returns the rows of a tile whose column sums were left in `stats` (0: none)."""
+    rows = C.c_int(0)
+    _ck(lib().lpk_conv_tile(_i(direction), _p(a), _p(b), _p(out), _p(add), _i(accumulate), _i(N), _i(H), _i(W), _i(Cin), _i(O),
+                            _i(R), _i(stride), _i(pad), _i(shape), _i(pieces), _p(stats),
+                            _sz(0 if stats is None else stats.numel()), C.byref(rows), _p(splitk_ws),
+                            _sz(0 if splitk_ws is None else splitk_ws.numel()), _stream()), "lpk_conv_tile")
+    return rows.value
+
+
+def lpk_conv_plan(direction, N, H, W, Cin, O, R, stride, pad, splitk_ws_elems):
+    """(tile shape, pieces); needs no device."""
+    shape, pieces = C.c_int(-1), C.c_int(0)
+    _ck(lib().lpk_conv_plan(_i(direction), _i(N), _i(H), _i(W), _i(Cin), _i(O), _i(R), _i(stride), _i(pad), _sz(splitk_ws_elems),
+                            C.byref(shape), C.byref(pieces)), "lpk_conv_plan")
+    return shape.value, pieces.value
 
 
 def lpk_conv_bn_fwd(dtype, x, w, z, g, b, res, y, mean, rstd, N, H, W, Cin, O, R, stride, pad, relu, scratch):

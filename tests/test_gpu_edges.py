@@ -70,7 +70,8 @@ def test_gemm_partial_k_tile_infinities(K, Kd, a_kc, b_kc):
 
 @pytest.mark.parametrize("seq,batch", [(43, 3), (200, 3), (365, 7)])
 def test_grouped_weight_gradients_any_rows(K, seq, batch):
-    """A decoder step over a token count that is no multiple of a k-tile: a layer's weight gradients share a launch."""
+    """A decoder step over a token count that is no multiple of a k-tile: a layer's weight gradients share a launch (of 64 x 64
+    tiles at these sizes; every tile and the persistent kernel: test_grouped_products_every_tile)."""
     import paper_2012_03837_amd as lp
     cfg = LI.make_config("cfg3_small", vocab=512, seq_len=seq, batch=batch)
     tr = lp.LocalTrainer(cfg)
@@ -784,6 +785,84 @@ def test_convolution_tiles(K, N, H, W, C, O, R, stride):
     assert relerr(host(gw), want) <= 2e-6
     K.lpk_conv_bwd_weight_ws(1, dd, dx_, gw, N, H, W, C, O, R, stride, pad, zeros(1 << 22), accumulate=1)
     assert relerr(host(gw), 2 * want) <= 2e-6
+
+
+TILES = {0: (64, 64), 1: (128, 64), 2: (128, 128), 3: (128, 128), 4: (256, 128), 6: (64, 128), 7: (256, 64), 8: (128, 32)}
+
+
+@pytest.mark.parametrize("pieces", [1, 2])
+@pytest.mark.parametrize("N,H,W,C,O,R,stride", [(5, 13, 11, 72, 136, 3, 1), (3, 11, 9, 64, 128, 3, 2), (11, 13, 11, 24, 32, 1, 1)])
+@pytest.mark.parametrize("shape", sorted(TILES))
+def test_convolution_every_tile(K, shape, N, H, W, C, O, R, stride, pieces):
+    """Every tile shape, forward, data gradient (with an addend) and filter gradient (added to what is there), whole and cut
+    along the reduction, with a remainder in every direction, against float64.  bf16 results: 4e-3; fp32 sums over at most
+    1573 pixels: 2e-6."""
+    import torch
+    import torch.nn.functional as F
+    rng = np.random.default_rng(H * W + C)
+    pad = R // 2
+    x, w = rnd(rng, (N, H, W, C), 1), rnd(rng, (O, R, R, C), 1, 0.2)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    dy, add = rnd(rng, (N, P, Q, O), 1), rnd(rng, (N, H, W, C), 1)
+    tx = torch.from_numpy(x).double().permute(0, 3, 1, 2).requires_grad_()
+    tw = torch.from_numpy(w).double().permute(0, 3, 1, 2).requires_grad_()
+    ty = F.conv2d(tx, tw, stride=stride, padding=pad)
+    ty.backward(torch.from_numpy(dy).double().permute(0, 3, 1, 2))
+    dx_, dw_, dd, ws = dev(x, 1), dev(w, 1), dev(dy, 1), zeros(1 << 22)
+    sizes = (N, H, W, C, O, R, stride, pad)
+
+    def fits(columns, reduction):
+        return (shape != 8 or columns <= 32) and (reduction + 63) // 64 >= pieces
+
+    ran = 0
+    if fits(O, R * R * C):
+        out = torch.full((N * P * Q + 1, O), 3.0, device="cuda", dtype=torch.bfloat16)
+        K.lpk_conv_tile(0, dx_, dw_, out, *sizes, shape, pieces, splitk_ws=ws)
+        assert relerr(host(out[:-1]).reshape(N, P, Q, O), ty.detach().permute(0, 2, 3, 1).numpy()) <= 4e-3
+        assert bool((out[-1] == 3.0).all())
+        ran += 1
+    if fits(C, R * R * O):
+        gx = torch.full((N * H * W + 1, C), 3.0, device="cuda", dtype=torch.bfloat16)
+        K.lpk_conv_tile(1, dd, dw_, gx, *sizes, shape, pieces, add=dev(add, 1), splitk_ws=ws)
+        assert relerr(host(gx[:-1]).reshape(N, H, W, C), tx.grad.permute(0, 2, 3, 1).numpy() + add) <= 4e-3
+        assert bool((gx[-1] == 3.0).all())
+        ran += 1
+    if fits(R * R * C, N * P * Q):
+        want = tw.grad.permute(0, 2, 3, 1).numpy()
+        gw = zeros(O * R * R * C + 1) + 3
+        for times in (1, 2):
+            K.lpk_conv_tile(2, dd, dx_, gw, *sizes, shape, pieces, accumulate=times - 1, splitk_ws=ws)
+            assert relerr(host(gw[:-1]).reshape(want.shape), times * want) <= 2e-6
+            assert float(gw[-1]) == 3.0
+        ran += 1
+    if not ran:
+        pytest.skip("no direction of this convolution takes the shape")
+
+
+@pytest.mark.parametrize("shape", sorted(TILES))
+def test_convolution_statistics_every_tile(K, shape):
+    """The normalisation's sums that a forward convolution leaves, for every tile shape: the pivot is the tile's first row as
+    it is stored, the sums are those of the stored values (fp32 sums of at most 256 terms: 1e-5 of the terms' magnitude)."""
+    import torch
+    BM, BN = TILES[shape]
+    N, H, C = 4, 16, 24
+    O = BN * (1 if shape == 8 else 2)
+    rng = np.random.default_rng(shape)
+    x, w = rnd(rng, (N, H, H, C), 1), rnd(rng, (O, 3, 3, C), 1, 0.2)
+    x[0, :2] += 4                          # the first rows of the first tile away from the others
+    x = ops.bf16_round(x)
+    z = torch.zeros(N * H * H, O, device="cuda", dtype=torch.bfloat16)
+    tiles = N * H * H // BM
+    st = zeros(3 * tiles * O + 1) + 7
+    assert K.lpk_conv_tile(0, dev(x, 1), dev(w, 1), z, N, H, H, C, O, 3, 1, 1, shape, stats=st) == BM
+    assert relerr(host(z).reshape(N, H, H, O), ops.conv2d_fwd(x.astype(np.float64), w.astype(np.float64), 1, 1)) <= 4e-3
+    assert float(st[-1]) == 7.0
+    s0, s1, p = host(st[:-1]).reshape(3, tiles, O)
+    zt = host(z).astype(np.float64).reshape(tiles, BM, O)
+    np.testing.assert_array_equal(p, zt[:, 0])
+    t = zt - zt[:, :1]
+    assert (np.abs(s0 - t.sum(1)) <= 1e-5 * np.abs(t).sum(1)).all()
+    assert (np.abs(s1 - (t * t).sum(1)) <= 1e-5 * (t * t).sum(1)).all()
 
 
 @pytest.mark.parametrize("accumulate", [0, 1])

@@ -416,9 +416,12 @@ def test_bn_running_statistics_and_evaluation(lpmod, dtype, sched):
 
 
 def test_convolutions_cut_along_k_match_oracle(lpmod):
-    """Few output tiles and a long reduction (4 x 4 images, 128 channels, K = 1152): the forward and data-gradient
+    """Few output tiles and a long reduction (4 x 4 images, 256 channels, K = 2304): the forward and data-gradient
     convolutions run cut along k with fp32 partial sums added in a fixed order; same bar as every bf16 step."""
-    cfg = LI.configs.resnet_config("t_cut", channels=(128,), in_hw=4, in_ch=3, n_classes=5, batch=8,
+    from paper_2012_03837_amd import kernels
+    for direction in (0, 1):
+        assert kernels.lpk_conv_plan(direction, 8, 4, 4, 256, 256, 3, 1, 1, 1 << 22)[1] > 1
+    cfg = LI.configs.resnet_config("t_cut", channels=(256,), in_hw=4, in_ch=3, n_classes=5, batch=8,
                                    n_basic_blocks=1, dtype="bf16")
     tr = lpmod.LocalTrainer(cfg, n_streams=1)
     x, y = data_for(cfg)
