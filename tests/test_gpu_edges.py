@@ -949,6 +949,44 @@ def test_attention_backward_launches(K, B, S, H, dh, causal):
     assert float((delta.double() - dd).abs().max()) <= 1e-4 * float(dd.abs().max())
 
 
+@pytest.mark.parametrize("a_kc,b_kc", [(0, 0), (1, 1), (1, 0)])
+@pytest.mark.parametrize("shape,pieces", [(s, p) for s in range(6) for p in (1, 3)] + [(-1, 1)])
+def test_grouped_products_every_tile(K, shape, pieces, a_kc, b_kc):
+    """Four products of different ragged sizes over one odd reduction in a launch: on every tile shape, whole and cut, and on
+    the persistent kernel, whose last k-tile is then partial.  fp32 sums of 1000 products, stored and added to what is there:
+    2e-6; nothing behind the last row."""
+    import torch
+    Kd = 1000 if a_kc or b_kc else 999
+    sizes = [(264, 520), (520, 136), (8, 8), (1000, 264)]
+    rng = np.random.default_rng(Kd)
+    A, B = [rnd(rng, (m, Kd), 1, 0.5) for m, _ in sizes], [rnd(rng, (n, Kd), 1, 0.5) for _, n in sizes]
+    dA = [dev(a if a_kc else np.ascontiguousarray(a.T), 1) for a in A]
+    dB = [dev(b if b_kc else np.ascontiguousarray(b.T), 1) for b in B]
+    outs = [torch.full((m + 1, n), 3.0, device="cuda") for m, n in sizes]
+    ws = zeros(1 << 25)
+    for times in (1, 2):
+        K.lpk_gemm_grouped(dA, dB, outs, [m for m, _ in sizes], [n for _, n in sizes], Kd, a_kc, b_kc, times - 1, ws, tiles=(shape, pieces))
+        for a, b, o in zip(A, B, outs):
+            assert relerr(host(o[:-1]), times * (a.astype(np.float64) @ b.astype(np.float64).T)) <= 2e-6
+            assert bool((o[-1] == 3.0).all())
+
+
+@pytest.mark.parametrize("shape,pieces", [(0, 1), (2, 2), (4, 1), (5, 3)])
+def test_grouped_tiles_with_epilogues(K, shape, pieces):
+    """Forward products of independent blocks in one launch of the tile kernel: each its own bias, ReLU and residual, bf16."""
+    import torch
+    rng = np.random.default_rng(shape)
+    Kd, N, Ms = 384, 520, [1304, 776, 8]
+    W, X = [rnd(rng, (N, Kd), 1, 0.5) for _ in Ms], [rnd(rng, (m, Kd), 1, 0.5) for m in Ms]
+    bias, res = [rng.standard_normal(N).astype(np.float32) for _ in Ms], [rnd(rng, (m, N), 1) for m in Ms]
+    outs = [torch.zeros(m, N, device="cuda", dtype=torch.bfloat16) for m in Ms]
+    K.lpk_gemm_grouped([dev(x, 1) for x in X], [dev(w, 1) for w in W], outs, Ms, [N] * len(Ms), Kd, 1, 1, 0, zeros(1 << 25),
+                       biases=[dev(b, 0) for b in bias], act=1, ress=[dev(r, 1) for r in res], tiles=(shape, pieces))
+    for i in range(len(Ms)):
+        ref = np.maximum(ops.linear_fwd(X[i].astype(np.float64), W[i].astype(np.float64), bias[i].astype(np.float64)), 0.0) + res[i]
+        assert relerr(host(outs[i]), ref) <= 4e-3, i
+
+
 @pytest.mark.parametrize("a_kc,b_kc", [(1, 1), (1, 0), (0, 1), (0, 0)])
 @pytest.mark.parametrize("M,N,Kd", [(1004, 1100, 16), (1004, 1100, 37), (1003, 1101, 333), (1028, 1096, 68), (960, 1152, 64)])
 def test_gemm_fp32_wide_tiles(K, M, N, Kd, a_kc, b_kc):

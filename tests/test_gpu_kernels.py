@@ -415,7 +415,7 @@ GROUPS = [
     (8192, [(768, 3072), (3072, 768), (768, 768), (2304, 768)]),
     (2048, [(264, 520), (520, 136), (8, 8), (1000, 264), (136, 776)]),
     (512, [(4096, 4104), (2056, 1032)]),
-    (1056, [(520, 264), (264, 776), (2056, 520)]),       # K not a multiple of 64: the 32-deep k-tiles
+    (1056, [(520, 264), (264, 776), (2056, 520)]),       # K not a multiple of 64: the last 64-deep k-tile is partial
 ]
 
 
@@ -562,8 +562,8 @@ def test_gemm_persistent_fused_epilogues(K, variant, a_kc, b_kc):
                                                   (3, 10, 16, 64, 3, 1, 1), (5, 12, 24, 72, 3, 1, 1)])
 def test_conv_bn_unit_forward(K, N, H, C, O, R, stride, pad):
     """A convolution + normalisation unit in one call (the convolution leaves the normalisation's column sums where its
-    output is whole tiles, 128- and 256-row tiles, 64 and 128 columns wide: the first five shapes; the others fall back
-    to the separate statistics pass): z, the batch
+    output is whole tiles, here 64 and 128 rows of 64 columns; every tile: test_convolution_statistics_every_tile; the
+    others fall back to the separate statistics pass): z, the batch
     mean and 1 / sqrt(var + eps), and y against the CPU oracle's convolution and batch normalisation, and the same
     bits as the two separate calls for z; twice: bit-repeatable."""
     import torch
