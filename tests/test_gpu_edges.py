@@ -949,6 +949,60 @@ def test_attention_backward_launches(K, B, S, H, dh, causal):
     assert float((delta.double() - dd).abs().max()) <= 1e-4 * float(dd.abs().max())
 
 
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dh", [16, 32])
+def test_attention_small_heads_launches_apart(K, dh, causal):
+    """Heads of 16 and 32 with 520 blocks of a kind, so that dQ and dK / dV run in launches of their own: one rounding of the
+    result to bf16 away from float64, as in test_attention_small_heads_fp32_probabilities."""
+    rng = np.random.default_rng(dh)
+    B, S, H = 26, 200, 10
+    d = H * dh
+    qkv, dout = rnd(rng, (B * S, 3 * d), 1), rnd(rng, (B * S, d), 1)
+    o, lse, delta = zeros(B * S, d).bfloat16(), zeros(B, H, S), zeros(B, H, S)
+    dqkv = zeros(B * S, 3 * d).bfloat16()
+    K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal)
+    K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal)
+    split = lambda t: t.astype(np.float64).reshape(B, S, H, dh).transpose(0, 2, 1, 3)
+    merge = lambda t: t.transpose(0, 2, 1, 3).reshape(B * S, d)
+    q, k, v, g = split(qkv[:, :d]), split(qkv[:, d:2 * d]), split(qkv[:, 2 * d:]), split(dout)
+    _, p = ops.attention_fwd(q, k, v, causal=bool(causal))
+    ds = p * (g @ np.swapaxes(v, -1, -2) - (g * split(host(o))).sum(-1, keepdims=True)) / np.sqrt(dh)
+    got = host(dqkv)
+    for name, a, ref in (("dq", got[:, :d], ds @ k), ("dk", got[:, d:2 * d], np.swapaxes(ds, -1, -2) @ q),
+                         ("dv", got[:, 2 * d:], np.swapaxes(p, -1, -2) @ g)):
+        ref = merge(ref)
+        rounding = relerr(ops.bf16_round(ref.astype(np.float32)), ref)
+        assert relerr(a, ref) <= 1.05 * rounding, (name, relerr(a, ref), rounding)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dh", [16, 32])
+def test_attention_small_heads_non_finite_launches_apart(K, dh, causal):
+    """As test_attention_small_heads_non_finite with 520 blocks of a kind: every sequence of the batch holds one infinity or
+    NaN, in q, k, v or the output's gradient, in an early, a middle or the last row, or none."""
+    rng = np.random.default_rng(dh)
+    B, S, H = 130, 150, 2
+    d = H * dh
+    qkv, dout = rnd(rng, (B, S, 3 * d), 1), rnd(rng, (B, S, d), 1)
+    cases = [(what, part, row) for what in (np.inf, -np.inf, np.nan) for part in range(4) for row in (5, 70, 149)]
+    for b, (what, part, row) in enumerate(cases):
+        (dout if part == 3 else qkv)[b, row, (0 if part == 3 else part * d) + dh + 3] = what
+    seen = []
+    for plain in (0, 1):
+        o, lse, delta = zeros(B * S, d).bfloat16(), zeros(B, H, S), zeros(B, H, S)
+        dqkv = zeros(B * S, 3 * d).bfloat16()
+        K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal, plain=plain)
+        K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal, plain=plain)
+        seen.append(host(dqkv).reshape(B, S, 3 * d))
+    for i in range(B):
+        a, b = seen[0][i], seen[1][i]
+        case = cases[i] if i < len(cases) else None
+        assert (np.isfinite(a) == np.isfinite(b)).all(), case
+        assert (np.isposinf(a) == np.isposinf(b)).all() and (np.isneginf(a) == np.isneginf(b)).all(), case
+        ok = np.isfinite(b)
+        assert np.abs(a[ok] - b[ok]).max(initial=0) <= 2.0 ** -6 * max(1.0, np.abs(b[ok]).max(initial=0)), case
+
+
 @pytest.mark.parametrize("a_kc,b_kc", [(0, 0), (1, 1), (1, 0)])
 @pytest.mark.parametrize("shape,pieces", [(s, p) for s in range(6) for p in (1, 3)] + [(-1, 1)])
 def test_grouped_products_every_tile(K, shape, pieces, a_kc, b_kc):
