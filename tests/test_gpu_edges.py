@@ -190,10 +190,11 @@ def test_batchnorm_any_channel_chunks(K, rows, C):
     assert relerr(host(dz), rdz) <= 4e-3 and relerr(host(dres), d) == 0
 
 
-@pytest.mark.parametrize("rows,C", [(1, 8), (2049, 8), (4096, 128), (4097, 128), (34816, 120), (34817, 120), (4096, 136)])
+@pytest.mark.parametrize("rows,C", [(1, 8), (2049, 8), (2048, 128), (2049, 128), (2312, 120), (2313, 120), (4096, 128), (4097, 128),
+                                    (34816, 120), (34817, 120), (4096, 136)])
 def test_batchnorm_few_slabs(K, rows, C):
-    """The slabs' sums added by the kernel that applies them (at most 128 channels and 4096 sums a plane: pairs of sizes on
-    both sides of each edge), against float64: fp32 sums of at most 2048 terms a slab, then sums of the slabs, 1e-5 of the
+    """The slabs' sums added by the kernel that applies them (at most 128 channels and 4096 sums a plane: 32 slabs of 64 rows of
+    128 channels and one more, 34 of 68 rows of 120 and one more, 136 channels), against float64: fp32 sums of at most 2048 terms a slab, then sums of the slabs, 1e-5 of the
     terms' magnitude; stored results to bf16's half step (4e-3). Gradients are added to what is there; twice: same bits."""
     import torch
     rng = np.random.default_rng(rows * 7 + C)
