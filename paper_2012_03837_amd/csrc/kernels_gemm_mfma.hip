@@ -81,8 +81,27 @@ static bool trace_on() {     // LP_GEMM_TRACE=1 prints the chosen kernel and pla
   if (v < 0) { const char* s = getenv("LP_GEMM_TRACE"); v = (s && s[0] == '1') ? 1 : 0; }
   return v != 0;
 }
-static const double kDmaStep[4] = {2796.0, 2300.0, 2300.0, 3900.0};      // 256 x 128 (two per CU), 256 x 256; 64-deep
+// (8192 cubed, 32-deep 256 x 256: 854 us, 64-deep: 806.)
+static const double kDmaStep[4] = {2796.0, 2050.0, 2050.0, 3900.0};      // 256 x 128 (two per CU), 256 x 256; 64-deep
 static const double kDmaFixed[4] = {7000.0, 9000.0, 9000.0, 9000.0};
+// Anything fused leaves this kernel's tiles in pieces of 16 bytes per lane, with its matrix cores idle: per tile, and once more
+// for every matrix that the epilogue reads or writes beside the output.  8192 x 3072 x 768, 256 x 256 tiles / one tile per
+// block: nothing fused 49 / 57 us, a bias 63 / 57, bias, GELU and pre-activation 78 / 63, residual 73 / 61; 8192 x 4096 x 1024
+// 66 / 72, 77 / 72, 114 / 80, 94 / 80.  So a layer's products with K <= 1024 go one tile per block although their plain
+// forms are faster here (all of them here: twelve layers of 768 25.2 -> 25.7 ms a step, 24 of 1024 34.9 -> 35.9).
+static const double kDmaFused[4] = {10400.0, 15600.0, 15600.0, 15600.0};
+// What a bf16 output takes at the rate it can leave at, in microseconds: the bound of short reductions over large outputs.  The
+// 256-wide shapes write whole lines past L2 where nothing is fused and rows are whole lines (8192 x 32000 x 32: 110 us, 4.8 TB/s),
+// and pieces of lines where they are not (8192 x 24008 x 32: 214 us); the others write pieces that L2 collects, up to the
+// memory-side cache's 256 MB at 4.2 TB/s (8192 x 8000 x 32: 31 us), beyond it slower (8192 x 32000 x 32: 142 us; with a bias 220
+// us, 203 us in 256-wide tiles).
+static double store_us(const GemmArgs& g, int kind, bool fused) {
+  if (g.c_f32) return 0.0;
+  const double mb = 2e-6 * g.M * g.N;
+  if (fused) return mb / (mb > 256.0 ? 2.5 : 4.2);
+  if (kind == 0 || kind == 2) return mb / (mb > 256.0 ? 3.5 : 4.2);
+  return mb / (g.ldc % 64 == 0 && ((uintptr_t)g.C & 127) == 0 ? 4.8 : 2.0);
+}
 
 static bool deep_auto() {     // LP_GEMM_K64=0 keeps the 64-deep k-tiles out of the automatic choice (for measurements)
   static int v = -1;
@@ -102,9 +121,11 @@ hipError_t gemm_mfma(const OpCtx& c, const GemmArgs& g) {
   else if (choice >= 13) force_kind = (choice - 13) / 2;
   else if (choice >= 9) { force_kind = choice - 9; force_cut = 2; }
   else if (choice >= 3) { force_kind = (choice - 3) / 2; force_cut = (choice - 3) % 2; }
-  // Short reductions over at most two waves of tiles (a layer's K = 768 products): a block that owns its CU
-  // has nothing to overlap its fused epilogue with and its pipeline never reaches steady state; one tile per block,
-  // two blocks per CU, measured 10-30 % faster there, so it takes them.
+  const int streams = (g.pre ? 1 : 0) + (g.dact != ACT_NONE ? 1 : 0) + (g.res ? 1 : 0) + (g.accumulate ? 1 : 0);
+  const bool fused = streams || g.bias || g.act != ACT_NONE;
+  // Short reductions over at most two waves of tiles (a layer's K = 768 products): with anything fused they go one tile per block
+  // at these prices too, and plain ones are within a tenth of each other (8192 x 3072 x 768 49 us here, 57 one tile per block;
+  // 2184 x 6408 x 832 32 and 30, 980 x 31144 x 312 44 and 38), so the search over this kernel's plans, half a microsecond on the host, is left out.
   const bool short_and_few = g.K <= 1024 && (long)((g.M + 255) / 256) * ((g.N + 255) / 256) <= 512;
   if (gemm_dma_ok(g) && choice != 2 && !(choice == 0 && short_and_few)) {
     for (int kind = 0; kind < 4; ++kind) {
@@ -114,7 +135,9 @@ hipError_t gemm_mfma(const OpCtx& c, const GemmArgs& g) {
         DmaGemmPlan d;
         if (!gemm_dma_plan(c, g, kind, cut, &d)) continue;
         if (cut == 1 && d.partial_bytes == 0 && force_cut < 0) continue;      // same as the uncut plan
-        double cycles = d.steps * kDmaStep[kind] + d.items * kDmaFixed[kind];
+        double cycles = d.steps * kDmaStep[kind] + d.items * (kDmaFixed[kind] + (fused ? (1 + streams) * kDmaFused[kind] : 0.0));
+        const double store = kCyclesPerUs * store_us(g, kind, fused);
+        if (store > cycles) cycles = store;
         if (d.partial_bytes > 0) cycles += 2.0 * d.partial_bytes / kPartialBytesPerCycle + kSecondLaunchCycles;
         // cut along k tile by tile, the tile columns of a row are at different k-steps and each fetches the
         // row's operand for itself: measured ~8 % slower than panel mode on a vocabulary head's gradients

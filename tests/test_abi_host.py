@@ -141,3 +141,22 @@ def test_filter_gradient_without_output_pixels_returns_on_the_host():
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"), capture_output=True,
                        text=True, timeout=300)
     assert r.returncode == 0 and int(r.stdout.split()[-1]) != 0, (r.returncode, r.stderr)
+
+
+def test_products_bound_by_their_output_choose_by_it():
+    """The kernel that a short reduction over a large output takes (printed in front of the launch, which fails without a
+    device): whole lines from 256-wide tiles where nothing is fused, one tile per block where something is (8192 x 16384 x 64:
+    64 and 89 us, and 102 and 147 us with the 256 x 128 tiles), and 128 x 128 tiles where they make one full round."""
+    import subprocess
+    import sys
+    code = ("import ctypes as C\nfrom paper_2012_03837_amd.binding import lib\n"
+            "v, n = C.c_void_p, C.c_int64\n"
+            "for M, N, K, bias in ((8192, 16384, 64, 0), (8192, 32000, 32, 0), (8192, 16384, 64, 4096), (528, 11648, 112, 0)):\n"
+            "    lib().lpk_gemm(1, v(4096), n(K), 1, v(8192), n(K), 1, v(16384), n(N), 0, M, N, K, v(bias), 0, v(0), v(0), 0, n(0),\n"
+            "                   v(0), n(0), 0, 0, v(0), C.c_size_t(0), v(0))\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=dict(os.environ, HIP_VISIBLE_DEVICES="-1", LP_GEMM_TRACE="1"),
+                       capture_output=True, text=True, timeout=300)
+    took = re.findall(r"\(11\): (persistent, kind \d|tiles, shape \d)", r.stderr)
+    assert r.returncode == 0 and len(took) == 4, r.stderr
+    assert took[0] in ("persistent, kind 1", "persistent, kind 3") and took[1] == "persistent, kind 1", took
+    assert took[2].startswith("tiles") and took[3] == "tiles, shape 2", took
