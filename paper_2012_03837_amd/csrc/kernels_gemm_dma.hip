@@ -286,44 +286,26 @@ __device__ __forceinline__ size_t slab_index(int wave, int ij, int c, int lane) 
   return ((((size_t)wave * (4 * TN) + ij) * 4 + c) * 64 + lane) * 4;
 }
 
-// Scheduling hint for one k-substep: NMF MFMAs, with the NDS LDS reads of the next substep spread over the
-// first three quarters of them (the last reads then have time to land before they are waited for) and
-// NVM direct-to-LDS loads spread over all of them.  A wave issues in order: a burst of loads that fills
-// the memory pipeline's queue would hold back the MFMAs behind it.
-template <int NMF, int NDS, int NVM>
-__device__ __forceinline__ void interleave_hint() {
-  constexpr int RD = NMF * 3 / 4;      // MFMAs over which the LDS reads are spread
+// One 16-deep substep: its matrix instructions, the next substep's fragment reads (READS; read1(r): the r-th of them, n side
+// first) between the first half of them and NL direct-to-LDS loads between the second.  The order is fixed here: a wave issues in
+// order, a burst of loads that fills the memory pipeline's queue holds back the matrix instructions behind it, and so do reads
+// that come too late to have landed.
+template <bool READS, int NL, int TN, class R, class L>
+__device__ __forceinline__ void substep(f32x16 (&acc)[TN][4], const bf16x8* fn, const bf16x8* fm, R read1, L load_at) {
+  constexpr int NMF = 4 * TN, NR = TN + 4, RD = NMF / 2;
 #pragma unroll
   for (int g = 0; g < NMF; ++g) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          // one MFMA
-    const int n = g < RD ? (NDS * (g + 1)) / RD - (NDS * g) / RD : 0;           // then this many LDS reads
-    if (n == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    else if (n == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    else if (n == 3) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-    const int m = (NVM * (g + 1)) / NMF - (NVM * g) / NMF;                      // and this many global loads
-    if (m == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-  }
-}
-
-// The same for a substep that also issues direct-to-LDS loads.  Those write LDS and the fragment reads
-// read it, so the scheduler keeps the two kinds in program order (reads first): the reads are spread over
-// the first half of the MFMAs and the loads over the second half.  Asking for an order that contradicts
-// the dependencies makes the scheduler drop the whole hint and emit both as one burst behind the first
-// MFMA, which stalls the MFMA pipe of both waves of a SIMD at once.
-template <int NMF, int NDS, int NVM>
-__device__ __forceinline__ void interleave_hint_loads() {
-  constexpr int RD = NMF / 2;
+    acc[g / 4][g % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fn[g / 4], fm[g % 4], acc[g / 4][g % 4], 0, 0, 0);
+    if (READS && g < RD) {
 #pragma unroll
-  for (int g = 0; g < NMF; ++g) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          // one MFMA
-    const int n = g < RD ? (NDS * (g + 1)) / RD - (NDS * g) / RD : 0;
-    if (n == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    else if (n == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    else if (n == 3) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-    else if (n == 4) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-    const int m = g >= RD ? (NVM * (g - RD + 1)) / (NMF - RD) - (NVM * (g - RD)) / (NMF - RD) : 0;
-    if (m == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    else if (m == 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+      for (int r = g * NR / RD; r < (g + 1) * NR / RD; ++r) read1(r);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (NL > 0 && g >= RD) {
+#pragma unroll
+      for (int l = (g - RD) * NL / RD; l < (g - RD + 1) * NL / RD; ++l) load_at(l);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
@@ -505,30 +487,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int x = 0; x < 16; ++x) acc[i][j][x] = 0.f;
-      // One 16-deep substep: its matrix instructions, the next substep's fragment reads (READS) between the first half of
-      // them and NL direct-to-LDS loads between the second.  The order is fixed here: a wave issues in order, a burst of
-      // loads that fills the memory pipeline's queue holds back the matrix instructions behind it, and so do reads that
-      // come too late to have landed.
-      auto sub = [&](auto reads, const bf16x8* fn, const bf16x8* fm, const char* as, const char* bs, int kk, bf16x8* gn, bf16x8* gm,
-                     auto nload, auto load_at) {
-        constexpr int NMF = 4 * TN, NR = TN + 4, RD = NMF / 2, NL = decltype(nload)::value;
-#pragma unroll
-        for (int g = 0; g < NMF; ++g) {
-          acc[g / 4][g % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fn[g / 4], fm[g % 4], acc[g / 4][g % 4], 0, 0, 0);
-          if (decltype(reads)::value && g < RD) {
-#pragma unroll
-            for (int r = g * NR / RD; r < (g + 1) * NR / RD; ++r) read1(as, bs, kk, r, gn, gm);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          if (NL > 0 && g >= RD) {
-#pragma unroll
-            for (int l = (g - RD) * NL / RD; l < (g - RD + 1) * NL / RD; ++l) load_at(l);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      };
-      typedef std::integral_constant<int, 0> None;
-      auto no_load = [](int) {};
+      auto none = [](int) {};
       // One 64-deep k-tile.  STEADY (1: first of a run, 2: later ones): the loader is two k-tiles ahead inside this
       // item, so everything is unconditional: the A half of k-tile t + 2 goes out in t's last substep (behind the
       // barrier), its B half in the first substep of t + 1, so that a wave's eight loads do not reach the memory
@@ -540,12 +499,12 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         if (ST == 2) {
           char* dst = smem + (lstage ^ 1) * STAGE_BYTES + A_BYTES;
           const int64_t off = pb.offset(lt - 1);
-          sub(std::true_type{}, fn0, fm0, as, bs, 1, fn1, fm1, std::integral_constant<int, BI>{}, [&](int l) { pb.issue1(l, dst, off); });
+          substep<true, BI>(acc, fn0, fm0, [&](int r) { read1(as, bs, 1, r, fn1, fm1); }, [&](int l) { pb.issue1(l, dst, off); });
         } else {
-          sub(std::true_type{}, fn0, fm0, as, bs, 1, fn1, fm1, None{}, no_load);
+          substep<true, 0>(acc, fn0, fm0, [&](int r) { read1(as, bs, 1, r, fn1, fm1); }, none);
         }
-        sub(std::true_type{}, fn1, fm1, as, bs, 2, fn0, fm0, None{}, no_load);
-        sub(std::true_type{}, fn0, fm0, as, bs, 3, fn1, fm1, None{}, no_load);
+        substep<true, 0>(acc, fn1, fm1, [&](int r) { read1(as, bs, 2, r, fn0, fm0); }, none);
+        substep<true, 0>(acc, fn0, fm0, [&](int r) { read1(as, bs, 3, r, fn1, fm1); }, none);
         // last substep: behind the barrier every wave has read all of this stage and the next k-tile has landed
         if (ST != 0) {
           wait_loads_and_barrier<0>();
@@ -553,8 +512,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
           const char* an = smem + cstage * STAGE_BYTES;
           char* dst = smem + lstage * STAGE_BYTES;
           const int64_t off = pa.offset(lt);
-          sub(std::true_type{}, fn1, fm1, an, an + A_BYTES, 0, fn0, fm0, std::integral_constant<int, AI>{},
-              [&](int l) { pa.issue1(l, dst, off); });
+          substep<true, AI>(acc, fn1, fm1, [&](int r) { read1(an, an + A_BYTES, 0, r, fn0, fm0); }, [&](int l) { pa.issue1(l, dst, off); });
           ++lt; --l_left;
           lstage ^= 1;
         } else {
@@ -570,7 +528,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
             if (tail_next) clear_counted(cstage);
             if (!last) read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
           }
-          sub(std::false_type{}, fn1, fm1, nullptr, nullptr, 0, fn0, fm0, None{}, no_load);
+          substep<false, 0>(acc, fn1, fm1, none, none);
         }
       };
       const int nt = C.ke - C.ks;
@@ -603,17 +561,19 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
     // vmcnt also counts the finished item's stores; whatever their completion order relative to the loads,
     // "at most n outstanding" then still implies that all but the youngest n loads have landed.  (Letting
     // the stores stay outstanding as well, by exact counting, measured no gain.)
-    auto read = [&](const char* as, const char* bs, int kk, bf16x8* fn, bf16x8* fm) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-        fn[i] = B_KC ? frag_kc(bs, wn + 32 * i + n_row, 2 * kk + hf)
-                     : frag_t<BN>(bs, wn + 32 * i + n_rowbase_t, 16 * kk + 8 * hf + kq);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        fm[j] = A_KC ? frag_kc(as, wm + 32 * j + li, 2 * kk + hf)
-                     : frag_t<BM>(as, wm + 32 * j + m_rowbase_t, 16 * kk + 8 * hf + kq);
+    auto read1 = [&](const char* as, int kk, int r, bf16x8* fn, bf16x8* fm) {       // fragment r of substep kk, n side first
+      const char* bs = as + A_BYTES;
+      if (r < TN)
+        fn[r] = B_KC ? frag_kc(bs, wn + 32 * r + n_row, 2 * kk + hf)
+                     : frag_t<BN>(bs, wn + 32 * r + n_rowbase_t, 16 * kk + 8 * hf + kq);
+      else
+        fm[r - TN] = A_KC ? frag_kc(as, wm + 32 * (r - TN) + li, 2 * kk + hf)
+                          : frag_t<BM>(as, wm + 32 * (r - TN) + m_rowbase_t, 16 * kk + 8 * hf + kq);
     };
-    constexpr int NDS = (A_KC ? 4 : 8) + (B_KC ? TN : 2 * TN);   // LDS read instructions per substep
+    auto read = [&](const char* as, int kk, bf16x8* fn, bf16x8* fm) {
+#pragma unroll
+      for (int r = 0; r < TN + 4; ++r) read1(as, kk, r, fn, fm);
+    };
     ItemIter L = first_item(), C = L;
     int lt = 0, l_left = 0;          // loader: next k-tile of its item, k-tiles of that item not yet issued
     int lstage = 0, cstage = 0;      // stage the next issued k-tile goes to; stage of the k-tile being multiplied
@@ -657,7 +617,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
     bf16x8 fn0[TN], fm0[4], fn1[TN], fm1[4];
     wait_oldest(inflight - 1);
     --inflight;
-    read(smem, smem + A_BYTES, 0, fn0, fm0);
+    read(smem, 0, fn0, fm0);
     for (;;) {
       f32x16 acc[TN][4];
 #pragma unroll
@@ -666,60 +626,45 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int x = 0; x < 16; ++x) acc[i][j][x] = 0.f;
-      auto mma = [&](const bf16x8* fn, const bf16x8* fm) {
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fn[i], fm[j], acc[i][j], 0, 0, 0);
-      };
-      // One k-tile.  STEADY: the pipeline is full and the loader is inside this item,
-      // so the wait is a constant and the loads are issued unconditionally: the second substep is then one
-      // basic block in which the scheduler can spread them between the MFMAs.  Otherwise everything that
-      // needs arithmetic is decided before the first MFMA.  `last`: the item's last k-tile; the next item's
-      // first fragments are read after this item is written, so that they are not live across the epilogue.
+      auto none = [](int) {};
+      // One k-tile.  STEADY (1: first of a run, 2: later ones): the pipeline is full and the loader is inside this item, so the
+      // wait is a constant and everything is unconditional.  Otherwise (0) what needs arithmetic is decided before the first
+      // matrix instruction.  `last`: the item's last k-tile; the next item's first fragments are read after this item is
+      // written, so that they are not live across the epilogue.
       auto step = [&](auto steady, bool last) {
-        constexpr bool STEADY = decltype(steady)::value != 0;
+        constexpr int ST = decltype(steady)::value;
         bool more = false, load = false;
-        if (!STEADY) {
+        if (ST == 0) {
           more = inflight > 0;                          // the stream has a k-tile after this one
           load = more && loader_ready();
           __builtin_amdgcn_sched_barrier(0);
         }
         const char* as = smem + cstage * STAGE_BYTES;
-        read(as, as + A_BYTES, 1, fn1, fm1);
-        if (STEADY && decltype(steady)::value == 2) {   // the B half of the k-tile whose A half went out one substep ago
-          const int ps = lstage == 0 ? NSTAGE - 1 : lstage - 1;
-          pb.issue(smem + ps * STAGE_BYTES + A_BYTES, lt - 1);
-          mma(fn0, fm0);
-          interleave_hint_loads<4 * TN, NDS, BI>();
+        if (ST == 2) {                                  // the B half of the k-tile whose A half went out one substep ago
+          char* dst = smem + (lstage == 0 ? NSTAGE - 1 : lstage - 1) * STAGE_BYTES + A_BYTES;
+          const int64_t off = pb.offset(lt - 1);
+          substep<true, BI>(acc, fn0, fm0, [&](int r) { read1(as, 1, r, fn1, fm1); }, [&](int l) { pb.issue1(l, dst, off); });
         } else {
-          mma(fn0, fm0);
-          interleave_hint<4 * TN, NDS, 0>();
+          substep<true, 0>(acc, fn0, fm0, [&](int r) { read1(as, 1, r, fn1, fm1); }, none);
         }
-        __builtin_amdgcn_sched_barrier(0);
         cstage = cstage + 1 == NSTAGE ? 0 : cstage + 1;
         const char* an = smem + cstage * STAGE_BYTES;
-        if (STEADY) {
+        if (ST != 0) {
           wait_loads_and_barrier<(NSTAGE - 3) * LPT>();
-          read(an, an + A_BYTES, 0, fn0, fm0);
           char* dst = smem + lstage * STAGE_BYTES;      // the stage that was read one k-tile ago
-          pa.issue(dst, lt);
+          const int64_t off = pa.offset(lt);
+          substep<true, AI>(acc, fn1, fm1, [&](int r) { read1(an, 0, r, fn0, fm0); }, [&](int l) { pa.issue1(l, dst, off); });
           ++lt; --l_left;
           lstage = lstage + 1 == NSTAGE ? 0 : lstage + 1;
-          mma(fn1, fm1);
-          interleave_hint_loads<4 * TN, NDS, AI>();
         } else {
           if (more) {
             wait_oldest(inflight - 1);
             --inflight;
             if (load) issue_tile();
-            if (!last) read(an, an + A_BYTES, 0, fn0, fm0);
+            if (!last) read(an, 0, fn0, fm0);
           }
-          mma(fn1, fm1);
-          interleave_hint<4 * TN, NDS, 0>();
+          substep<false, 0>(acc, fn1, fm1, none, none);
         }
-        __builtin_amdgcn_sched_barrier(0);
       };
       const int nt = C.ke - C.ks;
       int t = 0;
@@ -738,7 +683,7 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
       const bool have = advance(C);
       write_item(acc, done);
       if (!have) break;
-      read(smem + cstage * STAGE_BYTES, smem + cstage * STAGE_BYTES + A_BYTES, 0, fn0, fm0);
+      read(smem + cstage * STAGE_BYTES, 0, fn0, fm0);
     }
   } else {
     // Plain main loop, one item after the other.
