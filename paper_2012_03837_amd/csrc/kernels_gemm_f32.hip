@@ -53,16 +53,6 @@ __device__ __forceinline__ f4 load4(const bf16_t* p) {
   return r;
 }
 
-template <int N> __device__ __forceinline__ void load_rows(const float* p, float (&v)[N]) {
-  if constexpr (N == 4) { const f4 t = *reinterpret_cast<const f4*>(p); for (int e = 0; e < 4; ++e) v[e] = t[e]; }
-  else if constexpr (N == 2) { const float2 t = *reinterpret_cast<const float2*>(p); v[0] = t.x; v[1] = t.y; }
-  else v[0] = *p;
-}
-template <int N> __device__ __forceinline__ void load_rows(const bf16_t* p, float (&v)[N]) {
-  if constexpr (N == 4) { const f4 t = load4(p); for (int e = 0; e < 4; ++e) v[e] = t[e]; }
-  else if constexpr (N == 2) { const bf16x2 t = *reinterpret_cast<const bf16x2*>(p); v[0] = (float)t[0]; v[1] = (float)t[1]; }
-  else v[0] = (float)*p;
-}
 // Tile row that lane i's element of the t-th 16-row group is.
 template <int MODE, int TT> __device__ __forceinline__ int tile_row(int t, int i) { return MODE == F_ROWS ? TT * i + t : 16 * t + i; }
 
@@ -77,11 +67,11 @@ __device__ __forceinline__ void fetch_chunk(const T* const (&p)[TT], int64_t st,
       if (MASK && k >= K) r[t] = f4{0.f, 0.f, 0.f, 0.f};
     }
   } else if constexpr (MODE == F_ROWS) {
+    static_assert(TT == 4, "rows are read in fours");
     const T* q = p[0] + (int64_t)(MASK && k >= K ? K - 1 : k) * st;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float v[TT];
-      load_rows<TT>(q, v);
+      const f4 v = load4(q);
 #pragma unroll
       for (int t = 0; t < TT; ++t) r[t][j] = !MASK || k + j < K ? v[t] : 0.f;
       if (!MASK || k + j + 1 < K) q += st;
@@ -324,7 +314,7 @@ hipError_t gemm_f_t(const OpCtx& c, const GemmArgs* gs, int n) {
     FProblem<T>& p = grp.p[grp.n++];
     p.A = (const T*)g.A; p.B = (const T*)g.B; p.lda = g.lda; p.ldb = g.ldb;
     p.a_kc = g.a_kc; p.b_kc = g.b_kc;
-    auto mode = [&](const void* base, int64_t ld, int kc, int n) {      // rows: whole loads of four, so of fewer too
+    auto mode = [&](const void* base, int64_t ld, int kc, int n) {      // rows: whole loads of four
       if (ld % 4 || ((uintptr_t)base & al)) return F_ANY;
       return kc ? (g.K % 4 == 0 ? F_K4 : F_ANY) : (n % 4 == 0 ? F_ROWS : F_ANY);
     };
