@@ -209,19 +209,20 @@ hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
     bool ok = true;
     for (int i = 0; i < n; ++i) ok = ok && fast_ok(gs[i]);
     if (ok) {
+      // Up to four products of one reduction length and layout (a layer's weight gradients) share a launch of the tile kernel,
+      // alone against the persistent group and its fix-up: width 768 over 8192 rows 116 and 152 us, 1024 201 and 238, 448 over
+      // 2555 24 and 43; level where the work is largest (768 over 32768 rows 455 and 465, 2048 over 8192 703 and 714).  More of them,
+      // or unequal ones, go to that kernel.
       bool tiles = n <= kTileGroupMax;
-      double steps = 0.0, flops = 0.0;
+      double flops = 0.0;
       for (int i = 0; i < n; ++i) {
         const GemmArgs& g = gs[i];
         tiles = tiles && g.K == gs[0].K && g.a_kc == gs[0].a_kc && g.b_kc == gs[0].b_kc && !g.rowsum;
-        steps += (double)((g.M + 255) / 256) * ((g.N + 255) / 256) * ((g.K + 63) / 64);
         flops += 2.0 * g.M * g.N * g.K;
       }
-      // A persistent grouped launch and its fix-up: 25 us and 2.2 us for every 64 of k of 256 tiles of 256 x 256 (a layer's
-      // four weight gradients over 8192 rows: 140 us at width 768, 240 us at 1024).
       TilePlan plan;
       if (tiles) plan = gemm_tile_plan(c, gs, n);
-      if (tiles && plan.us < 25.0 + 2.2 * steps / 256.0) {
+      if (plan.shape >= 0) {
         ProfScope prof_(c, KC_GEMM, flops);
         return gemm_tile(c, gs, n, plan);
       }
