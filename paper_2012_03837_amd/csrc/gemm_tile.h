@@ -34,7 +34,8 @@ static __device__ const __attribute__((aligned(16))) unsigned kZeroPage[4] = {0,
 // ds_read_b64_tr_b16, so that a loop with a k-major operand never had a load in flight behind its matrix instructions
 // (persistent kernel, both operands k-major, alone: 32000 x 768 x 8192 449 -> 401 us, 8192 cubed 964 -> 851 us; a layer's
 // four weight gradients 159 -> 140 us at width 768, 256 -> 240 us at 1024).  Nothing is returned in registers; who reads the
-// LDS waits with a barrier that clobbers memory.
+// LDS waits with a barrier that clobbers memory.  m0 is a reserved register: the clobber draws a warning and protects nothing,
+// but no other instruction of these kernels uses it (LDS instructions do not need it, and nothing is indexed by a register).
 __device__ __forceinline__ void to_lds(const bf16_t* src, char* dst) {
   const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0");

@@ -508,7 +508,7 @@ k_bn_finish_wide(const float* __restrict__ partial, int nslab, int C, int rows, 
 // Forward statistics from the per-slab sums the convolution kernel left (ConvStats: slab t has its own pivot p_t, the
 // first of its slab_rows rows): every slab is shifted to slab 0's pivot P, with d = p_t - P
 //   sum (z - P) = s0_t + n d,   sum (z - P)^2 = s1_t + 2 d s0_t + n d^2,
-// the slabs are added in the order of k_bn_finish_v (16 groups of every 16th slab, then the groups in order), and the
+// the slabs are added in the order of k_bn_finish_v (1024 / CW groups, each every 1024 / CW-th slab, then bn_group_sums), and the
 // batch mean, 1 / sqrt(var + eps) and the running pair follow as there.
 template <int CW>
 __global__ void __launch_bounds__(kBnFinishThreads)
