@@ -791,9 +791,11 @@ def test_convolution_tiles(K, N, H, W, C, O, R, stride):
 TILES = {0: (64, 64), 1: (128, 64), 2: (128, 128), 3: (128, 128), 4: (256, 128), 6: (64, 128), 7: (256, 64), 8: (128, 32)}
 
 
+CONVS = [(5, 13, 11, 72, 136, 3, 1), (3, 11, 9, 64, 128, 3, 2), (11, 13, 11, 24, 32, 1, 1)]
+
+
 @pytest.mark.parametrize("pieces", [1, 2])
-@pytest.mark.parametrize("N,H,W,C,O,R,stride", [(5, 13, 11, 72, 136, 3, 1), (3, 11, 9, 64, 128, 3, 2), (11, 13, 11, 24, 32, 1, 1)])
-@pytest.mark.parametrize("shape", sorted(TILES))
+@pytest.mark.parametrize("shape,N,H,W,C,O,R,stride", [(s, *c) for s in sorted(TILES) for c in CONVS if s != 8 or c[3] <= 32])
 def test_convolution_every_tile(K, shape, N, H, W, C, O, R, stride, pieces):
     """Every tile shape, forward, data gradient (with an addend) and filter gradient (added to what is there), whole and cut
     along the reduction, with a remainder in every direction, against float64.  bf16 results: 4e-3; fp32 sums over at most
@@ -836,8 +838,7 @@ def test_convolution_every_tile(K, shape, N, H, W, C, O, R, stride, pieces):
             assert relerr(host(gw[:-1]).reshape(want.shape), times * want) <= 2e-6
             assert float(gw[-1]) == 3.0
         ran += 1
-    if not ran:
-        pytest.skip("no direction of this convolution takes the shape")
+    assert ran
 
 
 @pytest.mark.parametrize("shape", sorted(TILES))
