@@ -60,6 +60,15 @@ int lpk_gemm_grouped_tiles(int shape, int pieces, int n, const void* const* A, c
                            int a_kc, int b_kc, const float* const* bias, int act, const void* const* res, int accumulate,
                            float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
 
+/* The weight gradients of one layer with its bias gradients, as a step takes them: dw_i[M_i, N_i] (+)= dy_i^T x_i (bf16 dy_i
+ * [rows, M_i] and x_i [rows, N_i], fp32 out) and db_i[M_i] (+)= the column sums of dy_i (a null db_i: none), and in the same
+ * launch out[j] (+)= sum_b part[b, j], b < nblk, j < len (partial sums that an earlier kernel has left; len 0: none).  n up to 4,
+ * arrays as in lpk_gemm_grouped; shape and pieces as in lpk_gemm_grouped_tiles, or shape -1: chosen by the library. */
+int lpk_weight_grads(int shape, int pieces, int n, const void* const* dy, const int64_t* ld_dy, const void* const* x,
+                     const int64_t* ld_x, float* const* dw, float* const* db, const int* M, const int* N, int rows,
+                     int accumulate, const float* part, float* out, int nblk, int len, float* splitk_ws_dev,
+                     size_t splitk_ws_elems, void* stream);
+
 /* Causal (or full) multi-head attention of a decoder layer (appendix B.2).  qkv [B*S, 3*H*dh]
  * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch. */
 int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal,

@@ -98,9 +98,10 @@ struct Profiler {
 };
 
 // Partial sums that a chain of work has left and that one launch adds later (op_add_pending): the parameter gradients of a
-// layer's normalisations and its bias gradients, which nothing before the update reads.  A launch behind another one costs
-// 4.6 us however little it does (what a step of small layers gains; beside the products of another chain it waits for a compute
-// unit with sixteen free wave slots: 34 to 193 us for 11 MB, a layer of 768 over 8192 rows, by how the chains meet).
+// layer's normalisations, which nothing before the update reads, and where they are not taken with its weight gradients its bias
+// gradients.  A launch behind another one costs 4.6 us however little it does (what a step of small layers gains; beside the
+// products of another chain it waits for a compute unit with sixteen free wave slots: 34 to 193 us for 11 MB, a layer of 768
+// over 8192 rows, by how the chains meet), so they too go out with the weight gradients where those are bf16 tiles.
 constexpr int kMaxPending = 12;
 struct PendingSums {
   float* buf = nullptr;
@@ -128,6 +129,7 @@ struct OpCtx {
   float* splitk_ws = nullptr;   // fp32 workspace for split-K partial sums (may be null: no split-K)
   size_t splitk_elems = 0;
   PendingSums* pending = nullptr;   // where op_layernorm_bwd and op_colsum_batched may leave their sums (null: nowhere)
+  bool with_sums = false;           // op_gemm_grouped: the products' row sums and what is pending go out with their launch
 };
 
 // RAII bracket: records an event pair around the launches of one op when profiling is on.
@@ -149,7 +151,8 @@ struct ProfScope {
 // ---- ops (each enqueues on ctx.stream and returns a hipError_t) -------------------------------
 hipError_t op_gemm(const OpCtx& c, const GemmArgs& g);
 // n independent products in one launch where they qualify (bf16, same reduction length and operand layouts,
-// plain fp32 outputs: the weight gradients of one layer), otherwise one after the other.
+// plain fp32 outputs: the weight gradients of one layer), otherwise one after the other.  OpCtx::with_sums: one layer's
+// weight gradients, their bias gradients (GemmArgs::rowsum) and its pending sums, the sums in the same launch or ahead of it.
 hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n);
 hipError_t op_fill_f32(const OpCtx& c, float* p, size_t n, float v);
 // out[0] = <a, b> / (|a| |b|) over n floats (0 if either norm is 0); uses 3 * 128 floats of c.partial

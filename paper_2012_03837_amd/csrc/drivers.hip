@@ -189,7 +189,7 @@ int dec_backward_stage(lp_ctx* c, int li, int batch, const void* dout, void* dx,
   OpCtx o = c->op();
   int S = L.s.seq_len, d = L.s.width, H = L.s.n_heads, F = L.s.hidden, T = batch * S;
   bool has_emb = (li == 1 && c->spec.vocab > 0 && !L.in_override);
-  out->n = 0;
+  out->n = 0; out->sums = false;
   if (stage == 0) {            // FFN, second map
     L.wg[0] = lin_wgrad(c, dout, L.f, T, L.t["w2"], acc);
     GemmArgs gd = lin_dgrad(c, dout, T, L.t["w2"], c->dF);
@@ -217,13 +217,18 @@ int dec_backward_stage(lp_ctx* c, int li, int batch, const void* dout, void* dx,
                           params ? c->G32(L.t["ln1.g"]) : nullptr, params ? c->G32(L.t["ln1.b"]) : nullptr, T, d, acc));
     if (has_emb && params) DO(op_embed_bwd(o, ids, dh, c->G32(L.t["emb"]), T, c->spec.vocab, d, acc));
     if (params) {
-      // the four bias gradients: column sums of the same dY matrices the weight gradients read, in one pair of launches
+      // the four bias gradients: column sums of the same dY matrices the weight gradients read
       const void* dys[4] = {dout, c->dF, c->du, c->dqkv};
       const int64_t lds[4] = {d, F, d, 3 * d};
       float* outs[4] = {c->G32(L.t["b2"]), c->G32(L.t["b1"]), c->G32(L.t["bo"]), c->G32(L.t["bqkv"])};
       const int ns[4] = {d, F, d, 3 * d};
-      DO(op_colsum_batched(o, 4, dys, lds, outs, T, ns, acc));
-      DO(op_add_pending(o));         // these, both normalisations' gradients and, behind a head, its normalisation's
+      if (c->dt == BF16 && !c->lockstep) {       // with the weight gradients, and so do both normalisations' and, behind a head, its
+        out->sums = true;
+        for (int i = 0; i < 4; ++i) L.wg[i].rowsum = outs[i];
+      } else {
+        DO(op_colsum_batched(o, 4, dys, lds, outs, T, ns, acc));
+        DO(op_add_pending(o));
+      }
       for (int i = 0; i < 4; ++i) out->g[out->n++] = L.wg[i];
     }
   }
@@ -236,7 +241,9 @@ static int dec_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx
   for (int stage = 0; stage < kDecBwdStages; ++stage) {
     int st = dec_backward_stage(c, li, batch, dout, dx, need_dx, acc, ids, params, stage, &sg);
     if (st != LP_OK) return st;
-    DO(op_gemm_grouped(c->op(), sg.g, sg.n));
+    OpCtx o = c->op();
+    o.with_sums = sg.sums;
+    DO(op_gemm_grouped(o, sg.g, sg.n));
   }
   return LP_OK;
 }

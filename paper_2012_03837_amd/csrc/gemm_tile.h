@@ -133,11 +133,34 @@ struct Shape {
   static constexpr int LDS = NST * STAGE > NW * PATCH ? NST * STAGE : NW * PATCH;
 };
 
+// What is done with the m-side fragments of substep kk beside multiplying them: nothing.
+struct NoTap { template <int TM> __device__ __forceinline__ void operator()(int, const bf16x8 (&)[TM]) const {} };
+// Sums of the m side's rows over k (a weight gradient's bias gradient, from the fragments that are there anyway): lane
+// (li, hf) of row 32 j + li adds every other run of eight k, by dot products with ones (fp32 sums of exact products), of the
+// substeps in `mask` (wave-uniform): the waves that share rows deal the four of a k-tile out among them.
+template <int TM>
+struct RowSums {
+  static constexpr int CH = TM < 4 ? 2 : 1;      // chains
+  float s[CH][TM];
+  int mask;
+  __device__ __forceinline__ void operator()(int kk, const bf16x8 (&fm)[TM]) {
+    if (!(mask >> kk & 1)) return;
+    const bf16x2 ones = {(bf16_t)1.f, (bf16_t)1.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const bf16x2 v = {fm[j][2 * e], fm[j][2 * e + 1]};
+        s[e % CH][j] = __builtin_amdgcn_fdot2_f32_bf16(v, ones, s[e % CH][j], false);
+      }
+  }
+};
+
 // The k-tiles [t0, t1) of the tile at (m0, n0), K the length of the whole reduction; `before_last` runs in front of the last
 // k-tile's matrix instructions (all loads of operands are done by then).
-template <class SH, int WGN, int TM, int TN, int NST, class LA, class LB, class F>
+template <class SH, int WGN, int TM, int TN, int NST, class LA, class LB, class F, class TAP>
 __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n0, int t0, int t1, int K, char* smem,
-                                         f32x16 (&acc)[TN][TM], F before_last) {
+                                         f32x16 (&acc)[TN][TM], F before_last, TAP&& tap) {
   constexpr int BM = SH::BM, BN = SH::BN, AI = SH::AI, BI = SH::BI, LPT = SH::LPT, STAGE = SH::STAGE;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WGN) * 32 * TM, wn = (wave % WGN) * 32 * TN;
@@ -208,6 +231,7 @@ __device__ __forceinline__ void multiply(const LA& A, const LB& B, int m0, int n
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    tap((kk + 3) & 3, fm);
   };
   typedef std::integral_constant<int, 0> None;
   auto no_load = [](int) {};

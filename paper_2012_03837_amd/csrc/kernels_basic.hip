@@ -2,6 +2,7 @@
 // the fused optimizer update, and the weight initialiser.  64-wide wavefront reductions; every
 // reduction has a fixed order, so repeated runs are bit-identical.
 #include "common.h"
+#include "pending.h"
 #include "gemm_common.h"
 
 namespace lp {
@@ -487,21 +488,6 @@ __global__ void k_ln_bwd(const T* dy, const T* x, const float* mean, const float
     partial[(size_t)(nblk + blockIdx.x) * d + j] = bsum;
   }
 }
-// out[j] (+)= sum_b partial[b, j].  Block = 64 columns x 16 row groups; group q adds rows q, q+16, ... in
-// order (four independent loads in flight at a time) and the sixteen group sums are then added in order:
-// a fixed tree, so the result does not depend on the launch.
-constexpr int kReduceGroups = 16;
-__device__ __forceinline__ float group_sum(const float* __restrict__ partial, int nblk, int n, int j, int q) {
-  float a = 0.f;
-  int b = q;
-  for (; b + 3 * kReduceGroups < nblk; b += 4 * kReduceGroups) {
-    float v0 = partial[(size_t)b * n + j], v1 = partial[(size_t)(b + kReduceGroups) * n + j];
-    float v2 = partial[(size_t)(b + 2 * kReduceGroups) * n + j], v3 = partial[(size_t)(b + 3 * kReduceGroups) * n + j];
-    a += v0; a += v1; a += v2; a += v3;
-  }
-  for (; b < nblk; b += kReduceGroups) a += partial[(size_t)b * n + j];
-  return a;
-}
 __global__ void __launch_bounds__(64 * kReduceGroups)
 k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out, int accumulate,
                   float* out_y1 = nullptr) {
@@ -519,40 +505,15 @@ k_reduce_partials(const float* __restrict__ partial, int nblk, int n, float* out
     out[j] = accumulate ? out[j] + t : t;
   }
 }
-struct PendingTable { PendingSums::Sum s[kMaxPending]; int first[kMaxPending]; int count; };
 __global__ void __launch_bounds__(64 * kReduceGroups) k_add_pending(PendingTable t) {
   __shared__ float sh[kReduceGroups][64];
-  int p = 0;
-#pragma unroll
-  for (int i = 1; i < kMaxPending; ++i)
-    if (i < t.count && (int)blockIdx.x >= t.first[i]) p = i;
-  const float* part = t.s[p].part;
-  const int n = t.s[p].n, nblk = t.s[p].nblk;
-  const int lc = threadIdx.x & 63, q = threadIdx.x >> 6, j = (blockIdx.x - t.first[p]) * 64 + lc;
-  sh[q][lc] = j < n ? group_sum(part, nblk, n, j, q) : 0.f;
-  __syncthreads();
-  if (q == 0 && j < n) {
-    float v = 0.f;
-#pragma unroll
-    for (int g = 0; g < kReduceGroups; ++g) v += sh[g][lc];
-    float* out = t.s[p].out;
-    out[j] = t.s[p].accumulate ? out[j] + v : v;
-  }
+  add_pending_block<kReduceGroups>(t, blockIdx.x, sh);
 }
 hipError_t op_add_pending(const OpCtx& c) {
-  PendingSums* ps = c.pending;
-  if (!ps || ps->count == 0) return hipSuccess;
+  if (!c.pending || c.pending->count == 0) return hipSuccess;
   ProfScope prof_(c, KC_COLSUM);
-  PendingTable t = {};
-  int blocks = 0;
-  for (int i = 0; i < ps->count; ++i) {
-    t.s[i] = ps->s[i];
-    t.first[i] = blocks;
-    blocks += (ps->s[i].n + 63) / 64;
-  }
-  t.count = ps->count;
-  ps->count = 0; ps->used = 0;
-  k_add_pending<<<blocks, 64 * kReduceGroups, 0, c.stream>>>(t);
+  const PendingTable t = take_pending(c.pending);
+  k_add_pending<<<t.blocks, 64 * kReduceGroups, 0, c.stream>>>(t);
   return LP_LAUNCH_CHECK();
 }
 hipError_t op_reduce_partials(const OpCtx& c, const float* partial, int nblk, int n, float* out, int accumulate) {

@@ -221,7 +221,7 @@ k_conv_tile(LA A, LB B, Epilogue e, int M, int N, int K, int tiles_m, int tiles_
   f32x16 acc[TN][TM];
   RowStore<TM, TN> out;
   multiply<SH, WGN, TM, TN, NST>(A, B, tm * SH::BM, tn * SH::BN, t0, t1, K, smem, acc,
-                                 [&] { if (!raw) out.prefetch(e, mb, nb, M, N, lane); });
+                                 [&] { if (!raw) out.prefetch(e, mb, nb, M, N, lane); }, NoTap{});
   __syncthreads();
   ColumnSums<TN> cs;
   out.template store<STATS>(e, acc, smem + wave * SH::PATCH, mb, nb, M, N, lane, raw ? ws + (size_t)piece * M * N : nullptr, cs);

@@ -13,6 +13,7 @@
 // writes 16 bytes per lane.
 #include <stdio.h>
 #include <stdlib.h>
+#include <vector>
 #include "common.h"
 #include "gemm_common.h"
 
@@ -188,7 +189,7 @@ hipError_t op_gemm(const OpCtx& c, const GemmArgs& g) {
 hipError_t gemm_tile_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   if (n < 1 || n > kTileGroupMax || c.dt != BF16) return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i)
-    if (!fast_ok(gs[i]) || gs[i].K != gs[0].K || gs[i].a_kc != gs[0].a_kc || gs[i].b_kc != gs[0].b_kc || gs[i].rowsum) return hipErrorInvalidValue;
+    if (!fast_ok(gs[i]) || gs[i].K != gs[0].K || gs[i].a_kc != gs[0].a_kc || gs[i].b_kc != gs[0].b_kc || (gs[i].rowsum && !c.with_sums)) return hipErrorInvalidValue;
   return gemm_tile(c, gs, n, gemm_tile_plan(c, gs, n));
 }
 
@@ -217,7 +218,7 @@ hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
       double flops = 0.0;
       for (int i = 0; i < n; ++i) {
         const GemmArgs& g = gs[i];
-        tiles = tiles && g.K == gs[0].K && g.a_kc == gs[0].a_kc && g.b_kc == gs[0].b_kc && !g.rowsum;
+        tiles = tiles && g.K == gs[0].K && g.a_kc == gs[0].a_kc && g.b_kc == gs[0].b_kc && (!g.rowsum || (c.with_sums && !g.a_kc && !g.b_kc));
         flops += 2.0 * g.M * g.N * g.K;
       }
       TilePlan plan;
@@ -226,9 +227,24 @@ hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
         ProfScope prof_(c, KC_GEMM, flops);
         return gemm_tile(c, gs, n, plan);
       }
-      hipError_t e = gemm_dma_grouped(c, gs, n);
-      if (e != hipErrorInvalidValue) return e;          // launched (or failed for a reason of the device's)
+      if (!c.with_sums) {
+        hipError_t e = gemm_dma_grouped(c, gs, n);
+        if (e != hipErrorInvalidValue) return e;        // launched (or failed for a reason of the device's)
+      }
     }
+  }
+  if (c.with_sums) {                   // the sums by themselves, then the products
+    std::vector<const void*> dy(n);
+    std::vector<GemmArgs> plain(gs, gs + n);
+    std::vector<int64_t> ld(n);
+    std::vector<float*> out(n);
+    std::vector<int> m(n);
+    for (int i = 0; i < n; ++i) { dy[i] = gs[i].A; ld[i] = gs[i].lda; out[i] = gs[i].rowsum; m[i] = gs[i].M; plain[i].rowsum = nullptr; }
+    hipError_t e = op_colsum_batched(c, n, dy.data(), ld.data(), out.data(), gs[0].K, m.data(), gs[0].accumulate);
+    if (e == hipSuccess) e = op_add_pending(c);
+    OpCtx o = c;
+    o.with_sums = false;
+    return e == hipSuccess ? op_gemm_grouped(o, plain.data(), n) : e;
   }
   for (int i = 0; i < n; ++i) {
     hipError_t e = op_gemm(c, gs[i]);

@@ -77,6 +77,26 @@ extern "C" int lpk_gemm_grouped(int n, const void* const* A, const int64_t* lda,
   return lpk_gemm_grouped_tiles(-1, 1, n, A, lda, B, ldb, C, ldc, c_f32, M, N, K, a_kc, b_kc, bias, act, res, accumulate, splitk_ws,
                                 splitk_ws_elems, stream);
 }
+extern "C" int lpk_weight_grads(int shape, int pieces, int n, const void* const* dy, const int64_t* ld_dy, const void* const* x,
+                                const int64_t* ld_x, float* const* dw, float* const* db, const int* M, const int* N, int rows,
+                                int accumulate, const float* part, float* out, int nblk, int len, float* splitk_ws,
+                                size_t splitk_ws_elems, void* stream) {
+  if (n < 2 || n > 4 || !dy || !ld_dy || !x || !ld_x || !dw || !db || !M || !N || rows < 1) return (int)hipErrorInvalidValue;
+  GemmArgs g[4];
+  for (int i = 0; i < n; ++i) {
+    g[i].A = dy[i]; g[i].lda = ld_dy[i]; g[i].a_kc = 0; g[i].B = x[i]; g[i].ldb = ld_x[i]; g[i].b_kc = 0;
+    g[i].C = dw[i]; g[i].ldc = N[i]; g[i].c_f32 = 1; g[i].M = M[i]; g[i].N = N[i]; g[i].K = rows;
+    g[i].accumulate = accumulate; g[i].rowsum = db[i];
+  }
+  PendingSums pend;
+  if (len > 0) pend.add(part, out, nblk, len, accumulate);
+  OpCtx c = mk(BF16, stream);
+  c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws_elems;
+  c.pending = &pend; c.with_sums = true;
+  if (shape < 0) return (int)op_gemm_grouped(c, g, n);
+  c.tile_shape = shape; c.tile_pieces = pieces;
+  return (int)gemm_tile_grouped(c, g, n);
+}
 extern "C" int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh,
                                  int causal, int plain, void* stream) {
   OpCtx c = mk(dtype, stream);

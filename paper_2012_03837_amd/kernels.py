@@ -58,6 +58,19 @@ def lpk_gemm_grouped(As, Bs, Cs, Ms, Ns, K, a_kc, b_kc, accumulate, splitk_ws, b
         _ck(lib().lpk_gemm_grouped_tiles(_i(tiles[0]), _i(tiles[1]), *args), "lpk_gemm_grouped_tiles")
 
 
+def lpk_weight_grads(dys, xs, dws, dbs, accumulate=0, splitk_ws=None, part=None, out=None, tiles=(-1, 1)):
+    """dys [rows, M_i], xs [rows, N_i] (bf16), dws [M_i, N_i], dbs [M_i] or None (fp32); part [nblk, len] and out [len], or None."""
+    n, vp = len(dys), C.c_void_p * len(dys)
+    i64, ia = C.c_int64 * n, C.c_int * n
+    ptr = lambda t: 0 if t is None else t.data_ptr()
+    nblk, ln = (0, 0) if part is None else part.shape
+    _ck(lib().lpk_weight_grads(_i(tiles[0]), _i(tiles[1]), _i(n), vp(*map(ptr, dys)), i64(*[d.shape[1] for d in dys]),
+                               vp(*map(ptr, xs)), i64(*[x.shape[1] for x in xs]), vp(*map(ptr, dws)), vp(*map(ptr, dbs)),
+                               ia(*[w.shape[0] for w in dws]), ia(*[w.shape[1] for w in dws]), _i(dys[0].shape[0]), _i(accumulate),
+                               _p(part), _p(out), _i(nblk), _i(ln), _p(splitk_ws),
+                               _sz(0 if splitk_ws is None else splitk_ws.numel()), _stream()), "lpk_weight_grads")
+
+
 def lpk_attention_fwd(dtype, qkv, o, lse, B, S, H, dh, causal=1, plain=0):
     _ck(lib().lpk_attention_fwd(_i(dtype), _p(qkv), _p(o), _p(lse), _i(B), _i(S), _i(H), _i(dh), _i(causal), _i(plain),
                                 _stream()), "lpk_attention_fwd")
