@@ -214,8 +214,11 @@ hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float*
 constexpr int kMaxOptRanges = 8;
 struct OptRanges { size_t off[kMaxOptRanges], n[kMaxOptRanges]; float scale[kMaxOptRanges]; int count = 0; };
 struct MeanTable { const float* v[kMaxHeads]; float* out[kMaxHeads]; int rows = 0, count = 0; };
+// A matrix [rows][cols] of the buffers (cols a multiple of 8) that is updated with them and whose working copy is also written
+// transposed, to t [cols][ldt], columns rows .. ldt - 1 (ldt: rows rounded up to 64) zero.  rows 0: none.
+struct OptMatrix { size_t off = 0; int rows = 0, cols = 0, ldt = 0; void* t = nullptr; };
 hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
-                               const OptRanges& r, const MeanTable& mt);
+                               const OptRanges& r, const OptMatrix& x, const MeanTable& mt);
 
 hipError_t op_init_normal(const OpCtx& c, float* p, size_t n, float std, uint64_t seed, uint64_t stream_id);
 

@@ -844,16 +844,98 @@ hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, f
 // wave slot of the chip until the update is over (24 layers of 1024 in six chunks of four, ranges of 63 M elements in one
 // launch of 4096 looping blocks: a LayerNorm beside it 18 -> 37 us, the step 40.1 ms instead of 39.3).
 constexpr int kOptVecs = 2;
+struct OptScalars { float lr, mu, b1, b2, eps, wd, c1, c2; };
+template <int KIND>
+__device__ __forceinline__ void opt_update(const OptScalars& o, float gs, f32x4& pp, const f32x4& gg, f32x4& mm, f32x4& vv) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float gk = gg[k] * gs + o.wd * pp[k];
+    if (KIND == 0) pp[k] -= o.lr * gk;
+    else if (KIND == 1) { mm[k] = o.mu * mm[k] + gk; pp[k] -= o.lr * mm[k]; }
+    else {
+      mm[k] = o.b1 * mm[k] + (1.f - o.b1) * gk;
+      vv[k] = o.b2 * vv[k] + (1.f - o.b2) * gk * gk;
+      pp[k] -= o.lr * (mm[k] * o.c1) / (sqrtf(vv[k] * o.c2) + o.eps);
+    }
+  }
+}
+// N vectors (of index idx[u], where ok[u]) of a thread: all loads, the update, all stores; the new weights in pp.
+template <int KIND, bool LOWP, int N>
+__device__ __forceinline__ void opt_vectors(const OptScalars& o, float gs, float* p, const float* g, float* m, float* v, bf16_t* pl,
+                                            const size_t (&idx)[N], const bool (&ok)[N], bf16x4 (&low)[N]) {
+  f32x4 pp[N], gg[N], mm[N], vv[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+    if (ok[u]) {
+      pp[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + idx[u]);
+      gg[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g) + idx[u]);
+      if (KIND >= 1) mm[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(m) + idx[u]);
+      if (KIND == 2) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(v) + idx[u]);
+    }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (!ok[u]) continue;
+    opt_update<KIND>(o, gs, pp[u], gg[u], mm[u], vv[u]);
+    __builtin_nontemporal_store(pp[u], reinterpret_cast<f32x4*>(p) + idx[u]);
+    if (KIND >= 1) __builtin_nontemporal_store(mm[u], reinterpret_cast<f32x4*>(m) + idx[u]);
+    if (KIND == 2) __builtin_nontemporal_store(vv[u], reinterpret_cast<f32x4*>(v) + idx[u]);
+    if (LOWP) {
+      low[u] = bf16x4{static_cast<bf16_t>(pp[u][0]), static_cast<bf16_t>(pp[u][1]), static_cast<bf16_t>(pp[u][2]), static_cast<bf16_t>(pp[u][3])};
+      reinterpret_cast<bf16x4*>(pl)[idx[u]] = low[u];
+    }
+  }
+}
+constexpr int kXTile = 64, kXPitch = kXTile + 2;      // transposing tiles, LDS pitch in bf16
+// Column c0 + .. of the tile as rows of the transposed matrix: 16-byte stores of 8 rows gathered from the padded tile.
+__device__ __forceinline__ void store_transposed(const bf16_t* tile, bf16_t* dst, int r0, int c0, int C, int ldd) {
+  const int tr = threadIdx.x >> 3, tc = (threadIdx.x & 7) * 8;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = c0 + tr + 32 * i, r = r0 + tc;      // output row c, output columns r .. r+7
+    if (c < C && r < ldd) {       // rows past the source's are zeros in the tile
+      bf16x8 v;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] = tile[(tc + x) * kXPitch + tr + 32 * i];
+      *reinterpret_cast<bf16x8*>(dst + (size_t)c * ldd + r) = v;
+    }
+  }
+}
+// Grid: the ranges' blocks, 64 x 64 tiles of the matrix (the new weights are there in registers; with a transposing launch behind
+// the update instead: four layers of 128 with 8000 classes 1085 us a step, 1070 here, pipelined eight of 512 2010 and 1990, 24 of
+// 1024 33.99 and 33.69 ms), a block per mean.
 template <int KIND, bool LOWP>
 __global__ void __launch_bounds__(256) k_optimizer(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, bf16_t* __restrict__ pl, OptRanges rg, float lr,
-                            float mu, float b1, float b2, float eps, float wd, float c1, float c2,
-                            MeanTable mt) {
+                                                   float* __restrict__ v, bf16_t* __restrict__ pl, OptRanges rg, OptMatrix x,
+                                                   int tiles, OptScalars o, MeanTable mt) {
   __shared__ float sh[4];
-  const int blocks = gridDim.x - mt.count;
-  if ((int)blockIdx.x >= blocks) {
-    const int i = blockIdx.x - blocks;
+  __shared__ __attribute__((aligned(16))) bf16_t tile[LOWP ? kXTile * kXPitch : 1];
+  const int blocks = gridDim.x - mt.count - tiles;
+  if ((int)blockIdx.x >= blocks + tiles) {
+    const int i = blockIdx.x - blocks - tiles;
     block_mean_256(mt.v[i], mt.rows, mt.out[i], sh);
+    return;
+  }
+  if (LOWP && (int)blockIdx.x >= blocks) {
+    const int t = blockIdx.x - blocks, across = (x.cols + kXTile - 1) / kXTile;
+    const int r0 = t / across * kXTile, c0 = t % across * kXTile;
+    const int q = threadIdx.x & 15, tr = threadIdx.x >> 4;
+    size_t idx[4];
+    bool ok[4];
+    bf16x4 low[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = r0 + tr + 16 * u, c = c0 + 4 * q;
+      ok[u] = r < x.rows && c < x.cols;
+      idx[u] = (x.off + (size_t)r * x.cols + c) >> 2;
+      low[u] = bf16x4{(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+    }
+    opt_vectors<KIND, true>(o, 1.f, p, g, m, v, pl, idx, ok, low);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) *reinterpret_cast<bf16x2*>(tile + (tr + 16 * u) * kXPitch + 4 * q + 2 * k) = bf16x2{low[u][2 * k], low[u][2 * k + 1]};
+    __syncthreads();
+    store_transposed(tile, (bf16_t*)x.t, r0, c0, x.cols, x.ldt);
     return;
   }
   size_t first = (size_t)blockIdx.x * (256 * kOptVecs);      // vector of the ranges laid end to end, each from a block of its own
@@ -863,52 +945,27 @@ __global__ void __launch_bounds__(256) k_optimizer(float* __restrict__ p, const 
     if (first < whole) break;
     first -= whole;
   }
-  const float gs = rg.scale[r];
   const size_t end = (rg.off[r] + rg.n[r]) >> 2, i0 = (rg.off[r] >> 2) + first + threadIdx.x;
-  f32x4 pp[kOptVecs], gg[kOptVecs], mm[kOptVecs], vv[kOptVecs];
+  size_t idx[kOptVecs];
+  bool ok[kOptVecs];
+  bf16x4 low[kOptVecs];
 #pragma unroll
-  for (int u = 0; u < kOptVecs; ++u) {
-    const size_t i = i0 + 256 * u;
-    if (i < end) {
-      pp[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + i);
-      gg[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g) + i);
-      if (KIND >= 1) mm[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(m) + i);
-      if (KIND == 2) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(v) + i);
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kOptVecs; ++u) {
-    const size_t i = i0 + 256 * u;
-    if (i >= end) continue;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float gk = gg[u][k] * gs + wd * pp[u][k];
-      if (KIND == 0) pp[u][k] -= lr * gk;
-      else if (KIND == 1) { mm[u][k] = mu * mm[u][k] + gk; pp[u][k] -= lr * mm[u][k]; }
-      else {
-        mm[u][k] = b1 * mm[u][k] + (1.f - b1) * gk;
-        vv[u][k] = b2 * vv[u][k] + (1.f - b2) * gk * gk;
-        pp[u][k] -= lr * (mm[u][k] * c1) / (sqrtf(vv[u][k] * c2) + eps);
-      }
-    }
-    __builtin_nontemporal_store(pp[u], reinterpret_cast<f32x4*>(p) + i);
-    if (KIND >= 1) __builtin_nontemporal_store(mm[u], reinterpret_cast<f32x4*>(m) + i);
-    if (KIND == 2) __builtin_nontemporal_store(vv[u], reinterpret_cast<f32x4*>(v) + i);
-    if (LOWP) {
-      bf16x4 o = {static_cast<bf16_t>(pp[u][0]), static_cast<bf16_t>(pp[u][1]), static_cast<bf16_t>(pp[u][2]), static_cast<bf16_t>(pp[u][3])};
-      reinterpret_cast<bf16x4*>(pl)[i] = o;
-    }
-  }
+  for (int u = 0; u < kOptVecs; ++u) { idx[u] = i0 + 256 * u; ok[u] = idx[u] < end; }
+  opt_vectors<KIND, LOWP>(o, rg.scale[r], p, g, m, v, pl, idx, ok, low);
 }
 hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const float* g, float* m, float* v, void* p_lowp,
-                               const OptRanges& r, const MeanTable& mt) {
+                               const OptRanges& r, const OptMatrix& x, const MeanTable& mt) {
   ProfScope prof_(c, KC_OPTIMIZER);
-  size_t blocks = 0;
+  size_t blocks = 0, tiles = 0;
   for (int i = 0; i < r.count; ++i) {
     if (r.n[i] % 4 || r.off[i] % 4) return hipErrorInvalidValue;   // ranges are padded to 64 elements by the layout
     blocks += (r.n[i] / 4 + 256 * kOptVecs - 1) / (256 * kOptVecs);
   }
-  blocks += mt.count;
+  if (x.rows > 0) {
+    if (!p_lowp || x.off % 4 || x.cols % 8 || x.ldt % kXTile || x.ldt < x.rows || ((uintptr_t)x.t & 15)) return hipErrorInvalidValue;
+    tiles = (size_t)(x.ldt / kXTile) * ((x.cols + kXTile - 1) / kXTile);
+  }
+  blocks += tiles + mt.count;
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   float c1 = 1.f, c2 = 1.f;
@@ -917,7 +974,8 @@ hipError_t op_optimizer_ranges(const OpCtx& c, const OptArgs& o, float* p, const
     c2 = (float)(1.0 / (1.0 - pow((double)o.beta2, (double)o.t)));
   }
   bf16_t* pl = (bf16_t*)p_lowp;
-#define LP_OPT(K, L) k_optimizer<K, L><<<(unsigned)blocks, 256, 0, c.stream>>>(p, g, m, v, pl, r, o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2, mt)
+  const OptScalars os = {o.lr, o.momentum, o.beta1, o.beta2, o.eps, o.weight_decay, c1, c2};
+#define LP_OPT(K, L) k_optimizer<K, L><<<(unsigned)blocks, 256, 0, c.stream>>>(p, g, m, v, pl, r, x, (int)tiles, os, mt)
   if (o.kind == 0) { if (pl) LP_OPT(0, true); else LP_OPT(0, false); }
   else if (o.kind == 1) { if (pl) LP_OPT(1, true); else LP_OPT(1, false); }
   else { if (pl) LP_OPT(2, true); else LP_OPT(2, false); }
@@ -929,14 +987,14 @@ hipError_t op_optimizer(const OpCtx& c, const OptArgs& o, float* p, const float*
   if (n == 0) return hipSuccess;
   OptRanges r;
   r.off[0] = 0; r.n[0] = n; r.scale[0] = o.grad_scale; r.count = 1;
-  return op_optimizer_ranges(c, o, p, g, m, v, p_lowp, r, MeanTable());
+  return op_optimizer_ranges(c, o, p, g, m, v, p_lowp, r, OptMatrix(), MeanTable());
 }
 
 // ------------------------------------------------------------------------------------ transpose
-// 64 x 64 tiles through LDS: 16-byte loads of 8 columns, 16-byte stores of 8 rows gathered from a padded tile.
+// 64 x 64 tiles through LDS: 16-byte loads of 8 columns.
 __global__ void __launch_bounds__(256) k_transpose_bf16(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, int R, int C, int ldd) {
-  __shared__ bf16_t tile[64][64 + 2];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+  __shared__ bf16_t tile[kXTile * kXPitch];
+  const int r0 = blockIdx.y * kXTile, c0 = blockIdx.x * kXTile;
   const int tr = threadIdx.x >> 3, tc = (threadIdx.x & 7) * 8;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -948,19 +1006,10 @@ __global__ void __launch_bounds__(256) k_transpose_bf16(const bf16_t* __restrict
       for (int x = 0; x < 8; ++x) v[x] = (bf16_t)0.f;
     }
 #pragma unroll
-    for (int x = 0; x < 8; ++x) tile[tr + 32 * i][tc + x] = v[x];
+    for (int x = 0; x < 8; ++x) tile[(tr + 32 * i) * kXPitch + tc + x] = v[x];
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = c0 + tr + 32 * i, r = r0 + tc;      // output row c, output columns r .. r+7
-    if (c < C && r < ldd) {       // rows past R were fetched as zeros
-      bf16x8 v;
-#pragma unroll
-      for (int x = 0; x < 8; ++x) v[x] = tile[tc + x][tr + 32 * i];
-      *reinterpret_cast<bf16x8*>(dst + (size_t)c * ldd + r) = v;
-    }
-  }
+  store_transposed(tile, dst, r0, c0, C, ldd);
 }
 hipError_t op_transpose_bf16(const OpCtx& c, const void* src, void* dst, int R, int C, int ldd) {
   ProfScope prof_(c, KC_OTHER);

@@ -663,6 +663,7 @@ struct Updater {
   lp_ctx* c;
   OptArgs a;
   OptRanges r;
+  OptMatrix x;
   MeanTable mt;
   Updater(lp_ctx* ctx, int t) : c(ctx) {
     const lp_opt_spec& s = c->spec.opt;
@@ -670,8 +671,8 @@ struct Updater {
     a.weight_decay = s.weight_decay; a.t = t; a.grad_scale = 1.f;
   }
   int flush() {
-    CK(op_optimizer_ranges(c->op(), a, c->master, c->grads, c->mom, c->var, c->lowp, r, mt));
-    r.count = 0; mt.count = 0;
+    CK(op_optimizer_ranges(c->op(), a, c->master, c->grads, c->mom, c->var, c->lowp, r, x, mt));
+    r.count = 0; x.rows = 0; mt.count = 0;
     return LP_OK;
   }
   int add(size_t b, size_t e, float scale) {
@@ -706,14 +707,21 @@ static int update_block(lp_ctx* c, int hi, int t, F done) {
   int st = LP_OK;
   if (c->mean_rows > 0) st = u.mean(c->loss_rows, c->mean_rows, c->mean_out);
   c->mean_rows = 0;
-  if (st == LP_OK) st = u.add(Hd.p_begin, Hd.p_end, 1.f);
+  // a vocabulary head's weight as a matrix, which also refreshes its transposed copy
+  size_t from = Hd.p_begin;
+  const auto w = Hd.t.find("w");
+  if (w != Hd.t.end() && c->wt[w->second]) {
+    const Tensor& t = c->tensors[w->second];
+    u.x.off = t.off; u.x.rows = (int)t.shape[0]; u.x.cols = (int)t.shape[1]; u.x.ldt = lp_ctx::wt_ld(t); u.x.t = c->wt[w->second];
+    if (st == LP_OK && t.off > from) st = u.add(from, t.off, 1.f);
+    from = t.off + ((t.numel + 63) & ~(size_t)63);
+  }
+  if (st == LP_OK && Hd.p_end > from) st = u.add(from, Hd.p_end, 1.f);
   for (int lj = Hd.e; lj > Hd.s_lo && st == LP_OK; --lj) {
     float scale = 1.f;
     if (done(lj, &scale)) st = u.add(c->layers[lj].p_begin, c->layers[lj].p_end, scale);
   }
-  if (st == LP_OK) st = u.flush();
-  if (st != LP_OK) return st;
-  return c->lowp ? refresh_wt(c, Hd.p_begin, Hd.p_end - Hd.p_begin) : LP_OK;      // behind the update, on the same stream
+  return st == LP_OK ? u.flush() : st;
 }
 
 // A synchronous step of a residual MLP.  Its products are a few microseconds long, so what a step costs is the number of

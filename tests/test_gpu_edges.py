@@ -1084,3 +1084,28 @@ def test_weight_gradients_with_sums(K, shape, pieces):
                 assert np.abs(host(db[i][:-1]) - times * a.sum(0)).max() <= times * 2e-6 * np.abs(a).sum(0).max()
                 assert float(db[i][-1]) == 3.0
         assert relerr(host(out[:-1]), times * part.astype(np.float64).sum(0)) <= 2e-6 and float(out[-1]) == 3.0
+
+
+@pytest.mark.parametrize("vocab,heads", [(63, 3), (65, 1), (1003, 9)])
+@pytest.mark.parametrize("kind", ["sgd", "sgdm", "adam"])
+def test_update_keeps_the_transposed_head_weight(K, kind, vocab, heads):
+    """The transposed copy of a head's weight that the update writes: the next step's bits are those of a trainer that is given
+    the updated weights and so transposes them itself.  Vocabularies around whole tiles of 64, widths (8 a head) of one ragged
+    tile and of two."""
+    import paper_2012_03837_amd as lp
+    opt = dict(sgd=LI.configs.OptCfg("sgd", lr=0.05), sgdm=LI.configs.OptCfg("sgdm", lr=0.05, momentum=0.9), adam=LI.configs.OptCfg("adam", lr=1e-3))[kind]
+    cfg = LI.configs.decoder_config("t", n_layers=2, width=8 * heads, n_heads=heads, hidden=40, seq_len=19, batch=3, vocab=vocab, act="gelu", opt=opt)
+    a, b = lp.LocalTrainer(cfg), lp.LocalTrainer(cfg)
+    a.set_params(generic_params(cfg))
+    xd, yd = a.stage(*data_for(cfg))
+    a.step(xd, yd)
+    kept = {n: a.get(n) for k in a.names() for n in [k] + [k + m for m in dict(sgd=(), sgdm=(".m",), adam=(".m", ".v"))[kind]]}
+    for n, v in kept.items():
+        b.set(n, v)
+    lp.lp_set_step(b.ctx, lp.lp_get_step(a.ctx))
+    for tr in (a, b):
+        tr.step(xd, yd)
+    for k in a.names():
+        np.testing.assert_array_equal(a.get(k + ".grad"), b.get(k + ".grad"), err_msg=k)
+        np.testing.assert_array_equal(a.get(k), b.get(k), err_msg=k)
+    a.close(); b.close()
