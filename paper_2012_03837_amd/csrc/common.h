@@ -59,6 +59,7 @@ struct GemmArgs {
   const float* bias = nullptr;
   int act = ACT_NONE;
   void* pre = nullptr;
+  int drop_pre = 0;      // pre is not stored (the kernel is chosen as if it were: the same bits in C)
   const void* dact_src = nullptr; int dact = ACT_NONE; int64_t ldd = 0;
   const void* res = nullptr; int64_t ldr = 0;
   int accumulate = 0;

@@ -173,6 +173,7 @@ struct lp_ctx : lp_scratch {
   // forward pass of a layer waits only for the chains that read or update that layer (join_pending otherwise)
   int overlap_steps = 0;
   bool pending_join = false;
+  bool training = false;         // the pass in flight is a step: activations that only its backward pass reads are stored
   int step_t = 0;
   int last_batch = 0;
   // Replay of a captured synchronous step (lp_step_graph): the graph of the last captured call, the

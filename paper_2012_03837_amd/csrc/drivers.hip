@@ -161,6 +161,7 @@ int dec_forward_stage(lp_ctx* c, int li, int batch, const int32_t* ids, int stag
     GemmArgs g1 = lin_fwd(c, L.c, T, L.t["w1"], L.t["b1"], L.f);
     g1.act = L.s.act == LP_ACT_RELU ? ACT_RELU : ACT_GELU;
     g1.pre = L.fpre;
+    g1.drop_pre = !c->training;
     out->g[out->n++] = g1;
   } else {
     GemmArgs g2 = lin_fwd(c, L.f, T, L.t["w2"], L.t["b2"], L.out);

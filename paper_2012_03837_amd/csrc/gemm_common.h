@@ -32,7 +32,7 @@ struct Epilogue {
 
 static inline Epilogue make_epilogue(const GemmArgs& g) {
   Epilogue e;
-  e.bias = g.bias; e.act = g.act; e.pre = g.pre;
+  e.bias = g.bias; e.act = g.act; e.pre = g.drop_pre ? nullptr : g.pre;
   e.dact_src = g.dact_src; e.dact = g.dact; e.ldd = g.ldd;
   e.res = g.res; e.ldr = g.ldr;
   e.C = g.C; e.ldc = g.ldc; e.c_f32 = g.c_f32; e.accumulate = g.accumulate;
