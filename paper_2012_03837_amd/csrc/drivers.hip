@@ -423,6 +423,14 @@ int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bo
     for (int stage = 0; stage < kVocabHeadStages; ++stage) {
       int st = vocab_head_stage(c, hi, batch, y, loss_out, backward, dh, stage, &sg);
       if (st != LP_OK) return st;
+      if (stage == 0 && !backward) {
+        hipError_t e = op_gemm_loss(o, sg.g[0], y, c->loss_rows);
+        if (e == hipSuccess) {
+          DO(head_mean(c, batch * L.s.seq_len, loss_out, false));
+          return LP_OK;
+        }
+        if (e != hipErrorInvalidValue) DO(e);
+      }
       DO(op_gemm_grouped(c->op(), sg.g, sg.n));
     }
     return LP_OK;

@@ -1,10 +1,11 @@
 // Vectorised bf16 forms of the HBM-bound kernels: one global read and one global write per element,
 // 16 bytes per lane, all intermediate values in registers.
 //   LayerNorm forward / backward : rows of up to 1024 elements, one wavefront per row
-//   softmax cross-entropy        : rows of up to 32768 logits, one 256-thread block per row
+//   softmax cross-entropy        : rows of up to 32768 logits, a block of 256 or 512 threads per row
 // Shapes outside these limits (or unaligned) use the generic kernels.
 #include <type_traits>
 #include "common.h"
+#include "row_loss.h"
 
 namespace lp {
 
@@ -189,19 +190,25 @@ __global__ void __launch_bounds__(256) k_ln_bwd_v(const bf16_t* __restrict__ dy,
 // Softmax cross-entropy with the whole row in registers (<= 16 chunks of 8 logits per thread).  TAIL: n is not a
 // multiple of 8; the last chunk reaches into the row's padding, whose values count as -inf.  Chunks from n up to
 // pad_to are cleared together with the gradient's write (a padded dZ is read whole by the products behind it).
-constexpr int kCeChunks = 16;
-template <bool TAIL>
-__global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, int64_t ld, const int32_t* __restrict__ y,
-                                                        float* __restrict__ loss_rows, int n, int write_grad,
-                                                        float inv_rows, int pad_to) {
-  __shared__ float sh[8];
+// CH: chunks of a thread that there is room for, T threads.  Room for 8192 logits where a row has no more lets three times as
+// many rows into a compute unit as room for 32768 (8192 x 8000 53 -> 48 us, 2048 x 16000 29.4 -> 27.7; 8192 x 17000 103 us, 108 with 512 threads); rows of
+// more than 24576 take 512 threads (8192 x 32000 194 -> 187 us).
+constexpr int kCeMax = 32768;
+constexpr int ce_threads(int n) { return n <= 24576 ? 256 : 512; }
+template <bool TAIL, int CH, int T>
+__global__ void __launch_bounds__(T) k_softmax_ce_reg(bf16_t* __restrict__ z, int64_t ld, const int32_t* __restrict__ y,
+                                                      float* __restrict__ loss_rows, int n, int write_grad,
+                                                      float inv_rows, int pad_to) {
+  constexpr int W = T / 64;
+  __shared__ float sh[2 * W];
   const int row = blockIdx.x, nch = TAIL ? (n + 7) >> 3 : n >> 3;
   bf16_t* zr = z + (size_t)row * ld;
-  bf16x8 v[kCeChunks];
+  bf16x8 v[CH];
+  float gm[CH], gs[CH];      // of the group that this thread's chunk i is an eighth of
   float m = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kCeChunks; ++i) {
-    int c = threadIdx.x + 256 * i;
+  for (int i = 0; i < CH; ++i) {
+    int c = threadIdx.x + T * i;
     if (c < nch) {
       v[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(zr + 8 * c));
       if (TAIL) {
@@ -209,25 +216,33 @@ __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, 
         for (int e = 0; e < 8; ++e)
           if (8 * c + e >= n) v[i][e] = (bf16_t)(-INFINITY);
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) m = fmaxf(m, (float)v[i][e]);
     }
   }
+#pragma unroll
+  for (int i = 0; i < CH; ++i)
+    if (T * i < nch) {
+      float z8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) z8[e] = (int)threadIdx.x + T * i < nch ? (float)v[i][e] : -INFINITY;
+      group_stats(z8, gm[i], gs[i]);
+      m = fmaxf(m, gm[i]);
+    }
   m = wmax(m);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+#pragma unroll
+  for (int w = 0; w < W; ++w) m = fmaxf(m, sh[w]);
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kCeChunks; ++i)
-    if (threadIdx.x + 256 * i < nch) {
+  for (int i = 0; i < CH; ++i)
+    if (T * i < nch) s += gs[i] * __expf(gm[i] - m);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s += __expf((float)v[i][e] - m);
-    }
-  s = wsum(s);
-  if ((threadIdx.x & 63) == 0) sh[4 + (threadIdx.x >> 6)] = s;
+  for (int o = 8; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[W + (threadIdx.x >> 6)] = s;
   __syncthreads();
-  s = sh[4] + sh[5] + sh[6] + sh[7];
+  s = sh[W];
+#pragma unroll
+  for (int w = 1; w < W; ++w) s += sh[W + w];
   const float lse = m + __logf(s);
   const int yy = y[row];
   const bool y_ok = yy >= 0 && yy < n;
@@ -235,8 +250,8 @@ __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, 
   if (!write_grad) return;
   __syncthreads();   // the label's logit has been read before anything is overwritten
 #pragma unroll
-  for (int i = 0; i < kCeChunks; ++i) {
-    int c = threadIdx.x + 256 * i;
+  for (int i = 0; i < CH; ++i) {
+    int c = threadIdx.x + T * i;
     if (c < nch) {
       bf16x8 o;
 #pragma unroll
@@ -249,7 +264,36 @@ __global__ void __launch_bounds__(256) k_softmax_ce_reg(bf16_t* __restrict__ z, 
       __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(zr + 8 * c));
     }
   }
-  for (int j = 8 * nch + threadIdx.x; j < pad_to; j += 256) zr[j] = (bf16_t)0.f;
+  for (int j = 8 * nch + threadIdx.x; j < pad_to; j += T) zr[j] = (bf16_t)0.f;
+}
+
+// The rows' losses from their groups' pairs: NQ lanes a row (an eighth of the cross-entropy's threads), lane q the groups q, q + NQ, ...
+template <int NQ>
+__global__ void __launch_bounds__(256) k_ce_finish(GroupStats g, float* __restrict__ loss_rows, int rows, int n) {
+  const int row = blockIdx.x * (256 / NQ) + threadIdx.x / NQ, q = threadIdx.x % NQ;
+  if (row >= rows) return;
+  constexpr int I = NQ == 32 ? 12 : 8;
+  float2 p[I];
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    p[i] = q + NQ * i < g.groups ? g.pair[(size_t)row * g.groups + q + NQ * i] : float2{-INFINITY, 0.f};
+    m = fmaxf(m, p[i].x);
+  }
+#pragma unroll
+  for (int o = 1; o < NQ; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < I; ++i)
+    if (NQ * i < g.groups) s += p[i].y * __expf(p[i].x - m);
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o, 64);
+  const int first = threadIdx.x & 63 & ~(NQ - 1);
+  float t = __shfl(s, first, 64);
+#pragma unroll
+  for (int w = 8; w < NQ; w += 8) t += __shfl(s, first + w, 64);
+  const int yy = g.y[row];
+  if (q == 0) loss_rows[row] = m + __logf(t) - (yy >= 0 && yy < n ? g.zy[row] : 0.f);
 }
 
 bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -282,12 +326,25 @@ hipError_t ln_bwd_fast(const OpCtx& c, const void* dy, const void* x, const floa
   return hipGetLastError();
 }
 bool ce_fast_ok(const OpCtx& c, const void* z, int64_t ld, int n) {
-  return c.dt == BF16 && ld % 8 == 0 && n <= kCeChunks * 256 * 8 && al16(z);
+  return c.dt == BF16 && ld % 8 == 0 && n <= kCeMax && al16(z);
+}
+hipError_t ce_finish(const OpCtx& c, const GroupStats& g, float* loss_rows, int rows, int n) {
+  if (ce_threads(n) == 512) k_ce_finish<64><<<(rows + 3) / 4, 256, 0, c.stream>>>(g, loss_rows, rows, n);
+  else k_ce_finish<32><<<(rows + 7) / 8, 256, 0, c.stream>>>(g, loss_rows, rows, n);
+  return hipGetLastError();
 }
 hipError_t ce_fast(const OpCtx& c, void* z, int64_t ld, const int32_t* y, float* loss_rows, int rows, int n,
                    int write_grad, float inv_rows, int pad_to) {
-  if (n % 8) k_softmax_ce_reg<true><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
-  else k_softmax_ce_reg<false><<<rows, 256, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);
+#define LP_CE(CH, T)                                                                                                          \
+  do {                                                                                                                        \
+    if (n % 8) k_softmax_ce_reg<true, CH, T><<<rows, T, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to); \
+    else k_softmax_ce_reg<false, CH, T><<<rows, T, 0, c.stream>>>((bf16_t*)z, ld, y, loss_rows, n, write_grad, inv_rows, pad_to);     \
+  } while (0)
+  if (n <= 8192) LP_CE(4, 256);
+  else if (n <= 16384) LP_CE(8, 256);
+  else if (ce_threads(n) == 256) LP_CE(12, 256);
+  else LP_CE(8, 512);
+#undef LP_CE
   return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@
 #include <stdlib.h>
 #include <type_traits>
 #include "gemm_tile.h"
+#include "row_loss.h"
 
 namespace lp {
 
@@ -280,6 +281,52 @@ __device__ __forceinline__ void store_subtile(const Epilogue& e, const f32x16 (&
   }
 }
 
+// In the place of an output, the rows' group sums over a wave's 64 columns (row_loss.h), of the values that store_subtile would
+// store, turned around in the wave's LDS patch as there.
+__device__ __forceinline__ void stats_subtile(const GroupStats& gs, const f32x16 (&acc)[2][4], int m_base, int n_base, int li, int hf,
+                                              int M, int N, char* xs) {
+  const int lane = 32 * hf + li, rr = lane >> 3, rc = lane & 7, n = n_base + 8 * rc;
+  if (n_base >= N || m_base >= M) return;
+  int yy[16];
+#pragma unroll
+  for (int I = 0; I < 16; ++I) {
+    const int m = m_base + 8 * I + rr;
+    yy[I] = gs.y[m < M ? m : M - 1];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        bf16x8 w;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) w[x] = (bf16_t)acc[i][j][8 * q + x];
+        const int c = 4 * i + 2 * q + hf;
+        *reinterpret_cast<bf16x8*>(xs + li * 128 + ((c ^ ((li >> 1) & 7)) << 4)) = w;
+      }
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+      const int r = 8 * I + rr, m = m_base + 32 * j + r;
+      const bf16x8 w = *reinterpret_cast<const bf16x8*>(xs + r * 128 + ((rc ^ ((r >> 1) & 7)) << 4));
+      float z[8], gm, s;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) z[x] = n < N ? (float)w[x] : -INFINITY;
+      group_stats(z, gm, s);
+      if (m < M) {
+        if (rc == 0) gs.pair[(size_t)m * gs.groups + (n_base >> 6)] = float2{gm, s};
+        const int at = yy[4 * j + I] - n;
+        if (n < N && at >= 0 && at < 8) {
+          float v = z[0];
+#pragma unroll
+          for (int x = 1; x < 8; ++x) v = at == x ? z[x] : v;
+          gs.zy[m] = v;
+        }
+      }
+    }
+  }
+}
+
 // Partial-sum slab of one block tile, in accumulator order: 16 bytes per lane, 1 KB per wave store.
 template <int TN>
 __device__ __forceinline__ size_t slab_index(int wave, int ij, int c, int lane) {
@@ -309,9 +356,10 @@ __device__ __forceinline__ void substep(f32x16 (&acc)[TN][4], const bf16x8* fn, 
   }
 }
 
-template <bool A_KC, bool B_KC, int WNW, int TN, int NSTAGE, bool PIPE, int KT = 32>
+// STATS: no output; the rows' group sums instead (whole tiles only).
+template <bool A_KC, bool B_KC, int WNW, int TN, int NSTAGE, bool PIPE, int KT = 32, bool STATS = false>
 __global__ void __launch_bounds__(128 * WNW, (WNW * TN == 4) ? 2 : (WNW == 4 ? 2 : 1))
-k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, GroupTable gt) {
+k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, GroupTable gt, GroupStats gs) {
   constexpr int BN = 32 * TN * WNW, NWAVES = 2 * WNW;
   constexpr int A_BYTES = BM * KT * 2, B_BYTES = BN * KT * 2, STAGE_BYTES = A_BYTES + B_BYTES;
   constexpr int AI = (A_BYTES / 1024) / NWAVES, BI = (B_BYTES / 1024) / NWAVES, LPT = AI + BI;
@@ -385,7 +433,8 @@ k_gemm_dma(Operand A, Operand B, Epilogue e, int M, int N, SkPlan p, float* ws, 
         return;
       }
       plan_tile_coords(p, it.q, tm, tn);
-      store_subtile<TN>(e, acc, tm * BM + wm, tn * BN + wn, li, hf, M, N, xs);
+      if constexpr (STATS) stats_subtile(gs, acc, tm * BM + wm, tn * BN + wn, li, hf, M, N, xs);
+      else store_subtile<TN>(e, acc, tm * BM + wm, tn * BN + wn, li, hf, M, N, xs);
       return;
     }
     float* sp = ws + (size_t)(2 * v + (it.ks == 0 ? 1 : 0)) * (BM * BN);
@@ -832,7 +881,7 @@ hipError_t launch(const OpCtx& c, const GemmArgs& g, const SkPlan& p, bool parti
   const GroupTable& gt = grp ? *grp : no_group;
   {
     ProfScope one_(c, KC_GEMM_KERNEL, grp ? flops : 2.0 * g.M * g.N * g.K, 0, kname);
-    kern<<<dim3(p.G), 128 * WNW, smem, c.stream>>>(A, B, e, g.M, g.N, p, c.splitk_ws, gt);
+    kern<<<dim3(p.G), 128 * WNW, smem, c.stream>>>(A, B, e, g.M, g.N, p, c.splitk_ws, gt, GroupStats{});
     err = hipGetLastError();
   }
   if (err != hipSuccess || !partials) return err;
@@ -934,6 +983,25 @@ hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d) {
   if (!g.a_kc && g.b_kc) return LP_DMA(false, true);
   return LP_DMA(false, false);
 #undef LP_DMA
+}
+
+// The product of a head's logits for its loss alone (see GroupStats): both operands with k contiguous, N a multiple of 8, nothing
+// fused.  hipErrorInvalidValue, with nothing launched, where the plan is not whole 256 x 256 tiles of 64-deep k-tiles.
+hipError_t gemm_dma_stats(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d, const GroupStats& gs) {
+  if (d.kind != 3 || d.sib || d.partial_bytes > 0 || !g.a_kc || !g.b_kc || g.a_rows || g.b_rows) return hipErrorInvalidValue;
+  SkPlan p;
+  p.tiles_m = d.tiles_m; p.tiles_n = d.tiles_n; p.kt = d.kt; p.full = d.full; p.tail_tiles = d.tail_tiles;
+  p.upb = d.upb; p.G = d.G; p.sib = 0; p.ngrp = 0; p.K = g.K;
+  auto kern = k_gemm_dma<true, true, 4, 2, 2, true, 64, true>;
+  constexpr int smem = 2 * (BM + 256) * 64 * 2 + 8 * XPOSE_BYTES_PER_WAVE;
+  static LdsLimit limit;
+  hipError_t e = limit.raise(reinterpret_cast<const void*>(kern), smem);
+  if (e != hipSuccess) return e;
+  static const GroupTable no_group = {};
+  ProfScope one_(c, KC_GEMM_KERNEL, 2.0 * g.M * g.N * g.K, 0, "k_gemm_dma<true, true, 4, 2, 2, true, 64, true>");
+  kern<<<dim3(p.G), 512, smem, c.stream>>>(Operand{(const bf16_t*)g.A, g.lda, g.M}, Operand{(const bf16_t*)g.B, g.ldb, g.N}, make_epilogue(g), g.M,
+                                            g.N, p, nullptr, no_group, gs);
+  return hipGetLastError();
 }
 
 // Grouped launch of n products (see GroupTable).  Returns hipErrorInvalidValue, with nothing launched, if the set

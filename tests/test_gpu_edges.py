@@ -1109,3 +1109,33 @@ def test_update_keeps_the_transposed_head_weight(K, kind, vocab, heads):
         np.testing.assert_array_equal(a.get(k + ".grad"), b.get(k + ".grad"), err_msg=k)
         np.testing.assert_array_equal(a.get(k), b.get(k), err_msg=k)
     a.close(); b.close()
+
+
+@pytest.mark.parametrize("seq,batch,vocab,spoil", [(128, 64, 8000, None), (125, 61, 8008, None), (131, 59, 9000, None), (67, 32, 16392, None), (67, 32, 24584, None), (67, 32, 32000, None), (128, 64, 8000, "inf"),
+                                                   (128, 64, 8000, "-inf"), (128, 64, 8000, "nan"), (128, 64, 8000, "huge")])
+def test_evaluation_loss_without_logits(K, seq, batch, vocab, spoil):
+    """A large head's evaluation, whose product leaves the rows' group sums instead of logits: the bits of the losses that a step
+    reports, with ragged rows and classes past whole groups of 64; rows of infinite, very large and undefined logits; labels out of range."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=1, width=128, n_heads=2, hidden=64, seq_len=seq, batch=batch, vocab=vocab, act="gelu")
+    tr = lp.LocalTrainer(cfg)
+    P = generic_params(cfg)
+    if spoil:
+        w = P["H1.w"]
+        value = dict(inf=np.inf, nan=np.nan, huge=3e4).get(spoil, -np.inf)
+        w[130, 3] = value           # one class of the third group
+        if spoil == "-inf":         # every class of a group on one side of zero
+            w[192:256, 5] = value
+    tr.set_params(P)
+    x, y = data_for(cfg)
+    y = y.copy()
+    y[0, 0], y[1, 1], y[2, 2] = vocab, -1, vocab - 1
+    xd, yd = tr.stage(x, y)
+    lp.lp_profile_enable(tr.ctx, True)
+    ev = tr.eval(xd, yd).cpu().numpy().copy()
+    assert any(k["name"].endswith("64, true>") for k in lp.lp_profile_gemm_kernels(tr.ctx))
+    lp.lp_profile_enable(tr.ctx, False)
+    np.testing.assert_array_equal(tr.eval(xd, yd).cpu().numpy(), ev)
+    np.testing.assert_array_equal(tr.step(xd, yd).cpu().numpy(), ev)
+    if spoil in ("huge", None): assert np.isfinite(ev).all()
+    tr.close()
