@@ -70,7 +70,9 @@ int lpk_weight_grads(int shape, int pieces, int n, const void* const* dy, const 
                      size_t splitk_ws_elems, void* stream);
 
 /* Causal (or full) multi-head attention of a decoder layer (appendix B.2).  qkv [B*S, 3*H*dh]
- * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch. */
+ * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch.  plain 0: the library's
+ * choice; 1: the row-by-row kernels; for tests and measurements 2, 3, 4: the matrix kernels with a block's chain of tiles in
+ * one, two or four parts. */
 int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal,
                       int plain, void* stream);
 int lpk_attention_bwd(int dtype, const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv,

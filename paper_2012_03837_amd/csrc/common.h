@@ -127,6 +127,7 @@ struct OpCtx {
   Profiler* prof = nullptr;
   int gemm_variant = 0;         // 0: chosen by the cost model; otherwise a forced GEMM kernel (see lpk_gemm)
   int tile_shape = -1, tile_pieces = 1;   // one-tile-per-block products: a forced tile shape and cut (-1: by the cost model)
+  int attn_split = 0;           // attention: a block's chain in 1, 2 or 4 parts (0: by the number of blocks)
   float* splitk_ws = nullptr;   // fp32 workspace for split-K partial sums (may be null: no split-K)
   size_t splitk_elems = 0;
   PendingSums* pending = nullptr;   // where op_layernorm_bwd and op_colsum_batched may leave their sums (null: nowhere)

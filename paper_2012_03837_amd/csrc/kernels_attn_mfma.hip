@@ -21,6 +21,7 @@
 // read (ds_read_b64_tr_b16).  The next tile's global loads are issued before the current tile's MFMAs.
 // Layout: qkv [B*S, 3*H*DH] (q | k | v, head h at columns h*DH..), o [B*S, H*DH], lse [B, H, S].
 #include "common.h"
+#include "gemm_common.h"
 
 namespace lp {
 
@@ -193,21 +194,39 @@ __device__ __forceinline__ AttnBlock attn_block(int index, int H, int BH, int nb
   return a;
 }
 
+// P parts: where the blocks of 128 queries (or keys) are few, a block takes 64 or 32 of them, and the two or four waves that share
+// them every second or fourth key (query) tile, all brought to LDS together; their partial results are added through LDS.  A
+// chain of up to S / 64 tiles becomes one of a half or a quarter, on two or four times as many blocks (measured: see fwd_parts).
+// LDS of a block whose tiles take `tiles` bytes and whose four waves leave `values` partial values a lane over them.
+template <int P>
+constexpr int sum_bytes(int values, size_t tiles) { return P > 1 && 4 * values * 256 > (int)tiles ? 4 * values * 256 : (int)tiles; }
+template <int DH, int P>
+struct FwdLds {
+  static constexpr int NT = P;
+  __attribute__((aligned(16))) bf16_t k[NT][64][kAld<DH>], v[NT][64][kAld<DH>];
+  int bad[NT];
+  static constexpr int bytes() { return sum_bytes<P>(16 * ((DH + 31) / 32) + 2, sizeof(FwdLds)); }
+};
+// The waves' partial values, in the memory of the tiles: value i of lane `lane` of wave w at [(w * N + i) * 64 + lane].
+template <int N>
+__device__ __forceinline__ float& part(float* p, int wave, int i, int lane) { return p[(wave * N + i) * 64 + lane]; }
+
 // ================================================================================= forward
-template <int DH>
-__global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+template <int DH, int P>
+__global__ void __launch_bounds__(256, P > 1 ? 2 : 3) k_attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
                                                        float* __restrict__ lse, int S, int H, int BH, int causal) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[64][kAld<DH>];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[64][kAld<DH>];
-  __shared__ int bad;
+  constexpr int NT = P, QB = 128 / P;
+  constexpr bool SPLIT = P > 1;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  FwdLds<DH, P>& sm = *reinterpret_cast<FwdLds<DH, P>*>(smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
-  const AttnBlock ab = attn_block(blockIdx.x, H, BH, (S + 127) / 128, causal != 0);
+  const AttnBlock ab = attn_block(blockIdx.x, H, BH, (S + QB - 1) / QB, causal != 0);
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
   constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
-  const int q0 = bx * 128 + wave * 32, qi = q0 + n;
+  const int q0 = bx * QB + wave / P * 32, slot = wave % P, qi = q0 + n;
   bf16x8 qf[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk)
@@ -217,26 +236,36 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
 #pragma unroll
   for (int dh = 0; dh < ND; ++dh) zero16(oacc[dh]);
   const float c = kScale<DH> * kLog2e;
-  int q_hi = bx * 128 + 127;
+  int q_hi = bx * QB + QB - 1;
   if (q_hi > S - 1) q_hi = S - 1;
   const int n_tiles = causal ? q_hi / 64 + 1 : (S + 63) / 64;
-  TileRegs<DH> kr, vr;
-  kr.load(base + d + h * DH, ld, 0, S);
-  vr.load(base + 2 * d + h * DH, ld, 0, S);
-  if (DH < 64 && threadIdx.x == 0) bad = -1;
-  for (int jt = 0; jt < n_tiles; ++jt) {
-    const int k0 = jt * 64;
-    __syncthreads();
-    kr.store(Ks);
-    vr.store(Vs);
-    vr.mark(&bad, jt);
-    __syncthreads();
-    const bool slow = DH < 64 && bad == jt;
-    if (jt + 1 < n_tiles) {      // the next key tile's loads fly during this tile's MFMAs
-      kr.load(base + d + h * DH, ld, k0 + 64, S);
-      vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
+  TileRegs<DH> kr[NT], vr[NT];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= n_tiles) break;
+      kr[u].load(base + d + h * DH, ld, (t0 + u) * 64, S);
+      vr[u].load(base + 2 * d + h * DH, ld, (t0 + u) * 64, S);
     }
-    const bool active = q0 < S && (!causal || k0 <= q0 + 31);
+  };
+  load(0);
+  if (DH < 64 && threadIdx.x < NT) sm.bad[threadIdx.x] = -1;
+  auto& Ks = sm.k[slot];
+  auto& Vs = sm.v[slot];
+  for (int t0 = 0; t0 < n_tiles; t0 += NT) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= n_tiles) break;
+      kr[u].store(sm.k[u]);
+      vr[u].store(sm.v[u]);
+      vr[u].mark(&sm.bad[u], t0 + u);
+    }
+    __syncthreads();
+    const int jt = t0 + slot, k0 = jt * 64;
+    const bool slow = DH < 64 && sm.bad[slot] == jt;
+    if (t0 + NT < n_tiles) load(t0 + NT);      // the next key tiles' loads fly during these tiles' MFMAs
+    const bool active = q0 < S && jt < n_tiles && (!causal || k0 <= q0 + 31);
     if (!active) continue;
     f32x16 st[2];
 #pragma unroll
@@ -312,6 +341,46 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
       }
   }
   float lt = l + __shfl_xor(l, 32, 64);
+  if constexpr (SPLIT) {
+    constexpr int NV = 16 * ND + 2;
+    float* pt = reinterpret_cast<float*>(smem);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16 * ND; ++i) part<NV>(pt, wave, i, lane) = oacc[i / 16][i % 16];
+    part<NV>(pt, wave, 16 * ND, lane) = m;
+    part<NV>(pt, wave, 16 * ND + 1, lane) = lt;
+    __syncthreads();
+    float mw[P], M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int w = 0; w < P; ++w) { mw[w] = part<NV>(pt, wave - slot + w, 16 * ND, lane); M = fmaxf(M, mw[w]); }
+#pragma unroll
+    for (int w = 0; w < P; ++w) {
+      mw[w] = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);       // a wave without tiles has no sums
+      L += part<NV>(pt, wave - slot + w, 16 * ND + 1, lane) * mw[w];
+    }
+    if (qi < S) {                              // the waves take the 8-row groups of every output tile by turns
+      const float inv = 1.f / L;
+      bf16_t* op = o + ((size_t)b * S + qi) * d + h * DH;
+#pragma unroll
+      for (int dh = 0; dh < ND; ++dh)
+#pragma unroll
+        for (int x = 0; x < NG; x += P) {
+          const int g = x + slot;
+          if (NG < P && g >= NG) break;
+          bf16x4 r;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < P; ++w) v += part<NV>(pt, wave - slot + w, 16 * dh + 4 * g + j, lane) * mw[w];
+            r[j] = (bf16_t)(v * inv);
+          }
+          *reinterpret_cast<bf16x4*>(op + 32 * dh + 8 * g + 4 * hf) = r;
+        }
+      if (hf == 0 && slot == 0) lse[((size_t)b * H + h) * S + qi] = (M + log2f(L)) * kLn2;
+    }
+    return;
+  }
   if (qi < S) {
     float inv = 1.f / lt;
     bf16_t* op = o + ((size_t)b * S + qi) * d + h * DH;
@@ -330,28 +399,29 @@ __global__ void __launch_bounds__(256, 3) k_attn_fwd_mfma(const bf16_t* __restri
 
 // ================================================================================= backward
 // LDS of a backward block: its two streamed tiles (K and V, or Q and dO) and, for dK/dV, the rows' statistics.
-template <int DH>
+template <int DH, int P>
 struct BwdLds {
-  __attribute__((aligned(16))) bf16_t t0[64][kAld<DH>], t1[64][kAld<DH>];
-  __attribute__((aligned(16))) float lse2s[64], deltas[64];
-  int bad;
+  static constexpr int NT = P;
+  __attribute__((aligned(16))) bf16_t t0[NT][64][kAld<DH>], t1[NT][64][kAld<DH>];
+  __attribute__((aligned(16))) float lse2s[NT][64], deltas[NT][64];
+  int bad[NT];
+  static constexpr int bytes() { return sum_bytes<P>(32 * ((DH + 31) / 32), sizeof(BwdLds)); }
 };
 
 // ---------------------------------------------------------------------------------- dQ (and delta = rowsum(dO * O))
-template <int DH>
-__device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+template <int DH, int P>
+__device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH, P>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                             const float* __restrict__ lse, const bf16_t* __restrict__ dout,
                                             bf16_t* __restrict__ dqkv, float* __restrict__ delta, int S, int H, int causal) {
-  auto& Ks = sm.t0;
-  auto& Vs = sm.t1;
-  int& bad = sm.bad;
+  constexpr int NT = P, QB = 128 / P;
+  constexpr bool SPLIT = P > 1;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
   constexpr int NK = DH / 16, ND = (DH + 31) / 32, NG = DH >= 32 ? 4 : 2;   // k-steps of a score, output tiles, 8-row groups of one
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * S * ld;
-  const int q0 = bx * 128 + wave * 32, qi = q0 + n;
+  const int q0 = bx * QB + wave / P * 32, slot = wave % P, qi = q0 + n;
   bf16x8 qf[NK], dof[NK];
   float D = 0.f, lse2 = 0.f;
 #pragma unroll
@@ -371,32 +441,43 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH>& sm, 
   if (qi < S) {
     size_t si = ((size_t)b * H + h) * S + qi;
     lse2 = lse[si] * kLog2e;
-    if (hf == 0) delta[si] = D;
+    if (hf == 0 && slot == 0) delta[si] = D;
   }
   f32x16 dqa[ND];
 #pragma unroll
   for (int dh = 0; dh < ND; ++dh) zero16(dqa[dh]);
   const float scale = kScale<DH>, c = scale * kLog2e;
-  int q_hi = bx * 128 + 127;
+  int q_hi = bx * QB + QB - 1;
   if (q_hi > S - 1) q_hi = S - 1;
   const int n_tiles = causal ? q_hi / 64 + 1 : (S + 63) / 64;
-  TileRegs<DH> kr, vr;
-  kr.load(base + d + h * DH, ld, 0, S);
-  vr.load(base + 2 * d + h * DH, ld, 0, S);
-  if (DH < 64 && threadIdx.x == 0) bad = -1;
-  for (int jt = 0; jt < n_tiles; ++jt) {
-    const int k0 = jt * 64;
-    __syncthreads();
-    kr.store(Ks);
-    vr.store(Vs);
-    kr.mark(&bad, jt);
-    __syncthreads();
-    bool slow = DH < 64 && bad == jt;
-    if (jt + 1 < n_tiles) {
-      kr.load(base + d + h * DH, ld, k0 + 64, S);
-      vr.load(base + 2 * d + h * DH, ld, k0 + 64, S);
+  TileRegs<DH> kr[NT], vr[NT];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= n_tiles) break;
+      kr[u].load(base + d + h * DH, ld, (t0 + u) * 64, S);
+      vr[u].load(base + 2 * d + h * DH, ld, (t0 + u) * 64, S);
     }
-    const bool active = q0 < S && (!causal || k0 <= q0 + 31);
+  };
+  if (!SPLIT) load(0);
+  if (DH < 64 && threadIdx.x < NT) sm.bad[threadIdx.x] = -1;
+  auto& Ks = sm.t0[slot];
+  auto& Vs = sm.t1[slot];
+  for (int t0 = 0; t0 < n_tiles; t0 += NT) {
+    if (SPLIT) load(t0);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= n_tiles) break;
+      kr[u].store(sm.t0[u]);
+      vr[u].store(sm.t1[u]);
+      kr[u].mark(&sm.bad[u], t0 + u);
+    }
+    __syncthreads();
+    const int jt = t0 + slot, k0 = jt * 64;
+    bool slow = DH < 64 && sm.bad[slot] == jt;
+    if (!SPLIT && t0 + NT < n_tiles) load(t0 + NT);
+    const bool active = q0 < S && jt < n_tiles && (!causal || k0 <= q0 + 31);
     if (!active) continue;
     f32x16 st[2], dp[2];
 #pragma unroll
@@ -457,6 +538,34 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH>& sm, 
         for (int dh = 0; dh < ND; ++dh) dqa[dh] = mma_parts(frag_tr(Ks, 32 * i + 16 * kk, 32 * dh, lane), dsf, dqa[dh]);
       }
   }
+  if constexpr (SPLIT) {
+    constexpr int NV = 16 * ND;
+    float* pt = reinterpret_cast<float*>(&sm);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NV; ++i) part<NV>(pt, wave, i, lane) = dqa[i / 16][i % 16];
+    __syncthreads();
+    if (qi < S) {
+      bf16_t* dqp = dqkv + ((size_t)b * S + qi) * ld + h * DH;
+#pragma unroll
+      for (int dh = 0; dh < ND; ++dh)
+#pragma unroll
+        for (int x = 0; x < NG; x += P) {
+          const int g = x + slot;
+          if (NG < P && g >= NG) break;
+          bf16x4 r;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < P; ++w) v += part<NV>(pt, wave - slot + w, 16 * dh + 4 * g + j, lane);
+            r[j] = (bf16_t)(v * scale);
+          }
+          *reinterpret_cast<bf16x4*>(dqp + 32 * dh + 8 * g + 4 * hf) = r;
+        }
+    }
+    return;
+  }
   if (qi < S) {
     bf16_t* dqp = dqkv + ((size_t)b * S + qi) * ld + h * DH;
 #pragma unroll
@@ -474,16 +583,13 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnBlock ab, BwdLds<DH>& sm, 
 // ---------------------------------------------------------------------------------- dK, dV
 // OWN_DELTA: a query tile's deltas are taken from its dO and O rows as they come by (a read of O more per key block), so that
 // these blocks do not wait for the dQ blocks and both kinds can share a launch.
-template <int DH, bool OWN_DELTA>
-__device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+template <int DH, bool OWN_DELTA, int P>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH, P>& sm, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                              const float* __restrict__ lse, const float* __restrict__ delta,
                                              const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv, int S, int H,
                                              int causal) {
-  auto& Qs = sm.t0;
-  auto& dOs = sm.t1;
-  auto& lse2s = sm.lse2s;
-  auto& deltas = sm.deltas;
-  int& bad = sm.bad;
+  constexpr int NT = P, KB = 128 / P;
+  constexpr bool SPLIT = P > 1;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const int bx = ab.x;
   const int h = ab.h, b = ab.b, d = H * DH;
@@ -492,7 +598,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm,
   const bf16_t* base = qkv + (size_t)b * S * ld;
   const bf16_t* dob = dout + (size_t)b * S * d;
   const bf16_t* ob = o + (size_t)b * S * d;
-  const int k0w = bx * 128 + wave * 32, kj = k0w + n;
+  const int k0w = bx * KB + wave / P * 32, slot = wave % P, kj = k0w + n;
   bf16x8 kf[NK], vf[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
@@ -508,34 +614,47 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm,
 #pragma unroll
   for (int dh = 0; dh < ND; ++dh) { zero16(dka[dh]); zero16(dva[dh]); }
   const float scale = kScale<DH>, c = scale * kLog2e;
-  const int t_begin = causal ? (bx * 128) / 64 : 0;
+  const int t_begin = causal ? (bx * KB) / 64 : 0;
   const int t_end = (S + 63) / 64;
-  TileRegs<DH> qr, dor, orow;
-  qr.load(base + h * DH, ld, t_begin * 64, S);
-  dor.load(dob + h * DH, (size_t)d, t_begin * 64, S);
-  if (OWN_DELTA) orow.load(ob + h * DH, (size_t)d, t_begin * 64, S);
-  if (DH < 64 && threadIdx.x == 0) bad = -1;
-  for (int it = t_begin; it < t_end; ++it) {
-    const int q0 = it * 64;
-    __syncthreads();
-    qr.store(Qs);
-    dor.store(dOs);
-    qr.mark(&bad, it);
-    dor.mark(&bad, it);
-    if (OWN_DELTA) dor.row_dots(orow, deltas);
-    if (it + 1 < t_end) {
-      qr.load(base + h * DH, ld, q0 + 64, S);
-      dor.load(dob + h * DH, (size_t)d, q0 + 64, S);
-      if (OWN_DELTA) orow.load(ob + h * DH, (size_t)d, q0 + 64, S);
+  TileRegs<DH> qr[NT], dor[NT], orow[NT];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= t_end) break;
+      qr[u].load(base + h * DH, ld, (t0 + u) * 64, S);
+      dor[u].load(dob + h * DH, (size_t)d, (t0 + u) * 64, S);
+      if (OWN_DELTA) orow[u].load(ob + h * DH, (size_t)d, (t0 + u) * 64, S);
     }
-    if (threadIdx.x < 64) {
-      int q = q0 + threadIdx.x;
+  };
+  if (!SPLIT) load(t_begin);
+  if (DH < 64 && threadIdx.x < NT) sm.bad[threadIdx.x] = -1;
+  auto& Qs = sm.t0[slot];
+  auto& dOs = sm.t1[slot];
+  auto& lse2s = sm.lse2s[slot];
+  auto& deltas = sm.deltas[slot];
+  const int& bad = sm.bad[slot];
+  for (int t0 = t_begin; t0 < t_end; t0 += NT) {
+    if (SPLIT) load(t0);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (SPLIT && t0 + u >= t_end) break;
+      qr[u].store(sm.t0[u]);
+      dor[u].store(sm.t1[u]);
+      qr[u].mark(&sm.bad[u], t0 + u);
+      dor[u].mark(&sm.bad[u], t0 + u);
+      if (OWN_DELTA) dor[u].row_dots(orow[u], sm.deltas[u]);
+    }
+    if (!SPLIT && t0 + NT < t_end) load(t0 + NT);
+    if (threadIdx.x < 64 * NT) {
+      const int q = t0 * 64 + threadIdx.x;
       const size_t si = ((size_t)b * H + h) * S + q;
-      lse2s[threadIdx.x] = q < S ? lse[si] * kLog2e : 0.f;
-      if (!OWN_DELTA) deltas[threadIdx.x] = q < S ? delta[si] : 0.f;
+      sm.lse2s[threadIdx.x >> 6][threadIdx.x & 63] = q < S ? lse[si] * kLog2e : 0.f;
+      if (!OWN_DELTA) sm.deltas[threadIdx.x >> 6][threadIdx.x & 63] = q < S ? delta[si] : 0.f;
     }
     __syncthreads();
-    const bool active = k0w < S && (!causal || q0 + 63 >= k0w);
+    const int it = t0 + slot, q0 = it * 64;
+    const bool active = k0w < S && it < t_end && (!causal || q0 + 63 >= k0w);
     if (!active) continue;
     // the mask matters only where this wave's keys reach the tile's queries or either runs off the end
     const bool need_mask = q0 + 63 >= S || k0w + 31 >= S || (causal && k0w + 31 > q0);
@@ -611,6 +730,37 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm,
       }
     }
   }
+  if constexpr (SPLIT) {
+    constexpr int NV = 32 * ND;
+    float* pt = reinterpret_cast<float*>(&sm);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16 * ND; ++i) {
+      part<NV>(pt, wave, i, lane) = dka[i / 16][i % 16];
+      part<NV>(pt, wave, 16 * ND + i, lane) = dva[i / 16][i % 16];
+    }
+    __syncthreads();
+    if (kj < S) {
+      bf16_t* dkp = dqkv + ((size_t)b * S + kj) * ld + d + h * DH;
+#pragma unroll
+      for (int dh = 0; dh < 2 * ND; ++dh)         // dK, then dV
+#pragma unroll
+        for (int x = 0; x < NG; x += P) {
+          const int g = x + slot;
+          if (NG < P && g >= NG) break;
+          bf16x4 r;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < P; ++w) v += part<NV>(pt, wave - slot + w, 16 * dh + 4 * g + j, lane);
+            r[j] = (bf16_t)(dh < ND ? v * scale : v);
+          }
+          *reinterpret_cast<bf16x4*>(dkp + (dh < ND ? 32 * dh : d + 32 * (dh - ND)) + 8 * g + 4 * hf) = r;
+        }
+    }
+    return;
+  }
   if (kj < S) {
     bf16_t* dkp = dqkv + ((size_t)b * S + kj) * ld + d + h * DH;
     bf16_t* dvp = dkp + d;
@@ -634,12 +784,14 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnBlock ab, BwdLds<DH>& sm,
 // (4 x 2048, 16 heads of 64: 163 against 184): one kind's blocks share their tiles in L2.
 constexpr int kBwdTogether = 512;
 enum BwdKind { BWD_BOTH, BWD_DQ, BWD_DKV };
-template <int DH, BwdKind KIND>
-__global__ void __launch_bounds__(256, KIND == BWD_DQ ? (DH == 64 ? 2 : 3) : (DH == 16 ? 3 : 2))
+template <int DH, BwdKind KIND, int P>
+__global__ void __launch_bounds__(256, KIND == BWD_DQ ? (DH == 64 ? 2 : 3) : (DH == 16 && P == 1 ? 3 : 2))
 k_attn_bwd_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
                 const bf16_t* __restrict__ dout, bf16_t* __restrict__ dqkv, float* __restrict__ delta, int S, int H, int BH, int causal) {
-  __shared__ BwdLds<DH> sm;
-  const int nblk = (S + 127) / 128, n = nblk * BH, n8 = n & ~7, L = blockIdx.x;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  BwdLds<DH, P>& sm = *reinterpret_cast<BwdLds<DH, P>*>(smem);
+  constexpr int RB = 128 / P;
+  const int nblk = (S + RB - 1) / RB, n = nblk * BH, n8 = n & ~7, L = blockIdx.x;
   bool dq = KIND == BWD_DQ;
   int index = L;
   if (KIND == BWD_BOTH) {
@@ -653,35 +805,80 @@ k_attn_bwd_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, co
     }
   }
   if (KIND != BWD_DKV && dq)
-    attn_bwd_dq<DH>(attn_block(index, H, BH, nblk, causal != 0), sm, qkv, o, lse, dout, dqkv, delta, S, H, causal);
+    attn_bwd_dq<DH, P>(attn_block(index, H, BH, nblk, causal != 0), sm, qkv, o, lse, dout, dqkv, delta, S, H, causal);
   else if (KIND != BWD_DQ)
-    attn_bwd_dkv<DH, KIND == BWD_BOTH>(attn_block(index, H, BH, nblk, false), sm, qkv, o, lse, delta, dout, dqkv, S, H, causal);
+    attn_bwd_dkv<DH, KIND == BWD_BOTH, P>(attn_block(index, H, BH, nblk, false), sm, qkv, o, lse, delta, dout, dqkv, S, H, causal);
 }
 
-template <int DH>
+// Into how many parts a block's chain of tiles is split, n the number of whole blocks.  Alone, us, one / two / four parts:
+//            n   S x heads x size     forward               backward
+//           12   200 x 2 x 64         7.6   7.6   7.5       13.1    9.6    8.0
+//           64  2048 x 4 x 64        33.5  22.7  16.8       61.9   41.4   34.3
+//           90  1100 x 5 x 64        20.5  14.6  12.0       40.1   28.6   27.2
+//          128  2048 x 8 x 64        34.1  23.0  18.0       64.2   44.4   46.5
+//          128   256 x 8 x 64         7.9   7.1   7.2       13.7   11.3   18.2
+//          140   511 x 7 x 64        12.0   9.6  11.7       24.7   19.8   33.4
+//          243   300 x 9 x 64         8.4   8.1  12.8       19.3   21.3   37.0
+//          256  1024 x 8 x 64        19.6  14.8  19.5       37.5   38.1   55.5
+//          256   512 x 8 x 32        14.7   9.8  11.9       24.6   24.9   33.5
+//          768  1024 x 12 x 64       28.0  31.1  47.5       88.9  112.5  187.1
+// Short chains only where the blocks are very few: with another chain's products beside it the chip is not empty, and 128 blocks of
+// 256 x 8 x 64 in parts gain nothing (pipelined eight layers of 512: 2039 us in parts, 2009 whole).
+static int attn_parts(const OpCtx& c, int n, int S, int four, int two) {
+  if (c.attn_split) return c.attn_split;
+  if (S <= 256 ? n > 32 || S <= 64 : n > two) return 1;
+  return n <= four && S > 128 ? 4 : 2;
+}
+static int fwd_parts(const OpCtx& c, int n, int S) { return attn_parts(c, n, S, 128, 256); }
+static int bwd_parts(const OpCtx& c, int n, int S) { return attn_parts(c, n, S, 96, 176); }
+
+template <int DH, int P>
 static hipError_t attn_fwd_t(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
-  const int grid = ((S + 127) / 128) * H * B;
-  k_attn_fwd_mfma<DH><<<grid, 256, 0, c.stream>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, H, H * B, causal);
+  constexpr int QB = 128 / P, lds = FwdLds<DH, P>::bytes();
+  if (lds > 64 * 1024) {
+    static LdsLimit limit;
+    hipError_t e = limit.raise(reinterpret_cast<const void*>(k_attn_fwd_mfma<DH, P>), lds);
+    if (e != hipSuccess) return e;
+  }
+  k_attn_fwd_mfma<DH, P><<<((S + QB - 1) / QB) * H * B, 256, lds, c.stream>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, H, H * B, causal);
+  return hipGetLastError();
+}
+template <int DH, BwdKind KIND, int P>
+static hipError_t attn_bwd_launch(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
+                                  void* dqkv, float* delta, int B, int S, int H, int causal) {
+  constexpr int RB = 128 / P, lds = BwdLds<DH, P>::bytes();
+  if (lds > 64 * 1024) {
+    static LdsLimit limit;
+    hipError_t e = limit.raise(reinterpret_cast<const void*>(k_attn_bwd_mfma<DH, KIND, P>), lds);
+    if (e != hipSuccess) return e;
+  }
+  const int n = ((S + RB - 1) / RB) * H * B;
+  k_attn_bwd_mfma<DH, KIND, P><<<KIND == BWD_BOTH ? 2 * n : n, 256, lds, c.stream>>>(
+      (const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)dout, (bf16_t*)dqkv, delta, S, H, H * B, causal);
   return hipGetLastError();
 }
 template <int DH>
 static hipError_t attn_bwd_t(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                              void* dqkv, float* delta, int B, int S, int H, int causal) {
   const int n = ((S + 127) / 128) * H * B;
-  const bf16_t *q = (const bf16_t*)qkv, *out = (const bf16_t*)o, *dy = (const bf16_t*)dout;
-  if (n <= kBwdTogether) {
-    k_attn_bwd_mfma<DH, BWD_BOTH><<<2 * n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
-  } else {
-    k_attn_bwd_mfma<DH, BWD_DQ><<<n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
-    k_attn_bwd_mfma<DH, BWD_DKV><<<n, 256, 0, c.stream>>>(q, out, lse, dy, (bf16_t*)dqkv, delta, S, H, H * B, causal);
-  }
-  return hipGetLastError();
+  const int parts = bwd_parts(c, n, S);
+  if (parts == 4) return attn_bwd_launch<DH, BWD_BOTH, 4>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
+  if (parts == 2) return attn_bwd_launch<DH, BWD_BOTH, 2>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
+  if (n <= kBwdTogether) return attn_bwd_launch<DH, BWD_BOTH, 1>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
+  hipError_t e = attn_bwd_launch<DH, BWD_DQ, 1>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
+  return e == hipSuccess ? attn_bwd_launch<DH, BWD_DKV, 1>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal) : e;
+}
+template <int DH>
+static hipError_t attn_fwd_d(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
+  const int parts = fwd_parts(c, ((S + 127) / 128) * H * B, S);
+  return parts == 4 ? attn_fwd_t<DH, 4>(c, qkv, o, lse, B, S, H, causal)
+                    : (parts == 2 ? attn_fwd_t<DH, 2>(c, qkv, o, lse, B, S, H, causal) : attn_fwd_t<DH, 1>(c, qkv, o, lse, B, S, H, causal));
 }
 bool attn_mfma_ok(int dh) { return dh == 16 || dh == 32 || dh == 64; }
 hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal) {
   if (B * S == 0) return hipSuccess;
-  return dh == 64 ? attn_fwd_t<64>(c, qkv, o, lse, B, S, H, causal)
-                  : (dh == 32 ? attn_fwd_t<32>(c, qkv, o, lse, B, S, H, causal) : attn_fwd_t<16>(c, qkv, o, lse, B, S, H, causal));
+  return dh == 64 ? attn_fwd_d<64>(c, qkv, o, lse, B, S, H, causal)
+                  : (dh == 32 ? attn_fwd_d<32>(c, qkv, o, lse, B, S, H, causal) : attn_fwd_d<16>(c, qkv, o, lse, B, S, H, causal));
 }
 hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                          void* dqkv, float* delta, int B, int S, int H, int dh, int causal) {

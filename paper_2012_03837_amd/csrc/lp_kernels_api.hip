@@ -100,14 +100,16 @@ extern "C" int lpk_weight_grads(int shape, int pieces, int n, const void* const*
 extern "C" int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh,
                                  int causal, int plain, void* stream) {
   OpCtx c = mk(dtype, stream);
-  if (plain) return (int)attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
+  if (plain >= 2) c.attn_split = plain == 2 ? 1 : (plain == 3 ? 2 : 4);
+  if (plain == 1) return (int)attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
   return (int)op_attn_fwd(c, qkv, o, lse, B, S, H, dh, causal);
 }
 extern "C" int lpk_attention_bwd(int dtype, const void* qkv, const void* o, const float* lse, const void* dout,
                                  void* dqkv, float* delta, int B, int S, int H, int dh, int causal, int plain,
                                  void* stream) {
   OpCtx c = mk(dtype, stream);
-  if (plain) return (int)attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
+  if (plain >= 2) c.attn_split = plain == 2 ? 1 : (plain == 3 ? 2 : 4);
+  if (plain == 1) return (int)attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
   return (int)op_attn_bwd(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
 }
 extern "C" int lpk_layernorm_fwd(int dtype, const void* x, const float* g, const float* b, void* y, float* mean,

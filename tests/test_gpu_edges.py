@@ -1139,3 +1139,39 @@ def test_evaluation_loss_without_logits(K, seq, batch, vocab, spoil):
     np.testing.assert_array_equal(tr.step(xd, yd).cpu().numpy(), ev)
     if spoil in ("huge", None): assert np.isfinite(ev).all()
     tr.close()
+
+
+@pytest.mark.parametrize("parts", [1, 2, 4])
+@pytest.mark.parametrize("S,causal", [(1, 1), (31, 1), (33, 0), (64, 1), (65, 1), (97, 0), (129, 1), (257, 1), (300, 0), (449, 1)])
+@pytest.mark.parametrize("dh", [16, 32, 64])
+def test_attention_in_parts(K, dh, S, causal, parts):
+    """Blocks whose chain of tiles is taken by one, two or four waves: sequences around a wave's rows, a tile, a block and the
+    tiles that are brought together, parts without a tile.  Against float64; tolerances as in the kernels' own test (P, dS and
+    results of heads of 64 rounded to bf16; narrower heads only the results, 2^-9)."""
+    import torch
+    rng = np.random.default_rng(S + dh)
+    B, H = 2, 3
+    d = H * dh
+    qkv, dout = rnd(rng, (B * S, 3 * d), 1, scale=1.5), rnd(rng, (B * S, d), 1)
+    dq = dev(qkv, 1)
+    o, g = torch.zeros(B * S, d, device="cuda", dtype=torch.bfloat16), torch.full((B * S, 3 * d), 7.0, device="cuda", dtype=torch.bfloat16)
+    lse, delta = zeros(B * H * S), zeros(B * H * S)
+    K.lpk_attention_fwd(1, dq, o, lse, B, S, H, dh, causal, 1 + {1: 1, 2: 2, 4: 3}[parts])
+    K.lpk_attention_bwd(1, dq, o, lse, dev(dout, 1), g, delta, B, S, H, dh, causal, 1 + {1: 1, 2: 2, 4: 3}[parts])
+
+    def heads(t):
+        return t.reshape(B, S, H, dh).transpose(0, 2, 1, 3)
+    q64 = qkv.astype(np.float64)
+    q, k, v = heads(q64[:, :d]), heads(q64[:, d:2 * d]), heads(q64[:, 2 * d:])
+    ro, p = ops.attention_fwd(q, k, v, causal=bool(causal))
+    do = heads(dout.astype(np.float64))
+    dp = do @ np.swapaxes(v, -1, -2)
+    ds = p * (dp - (do * ro).sum(-1, keepdims=True)) / np.sqrt(dh)
+    back = lambda t: t.transpose(0, 2, 1, 3).reshape(B * S, d)
+    want = np.concatenate([back(ds @ k), back(np.swapaxes(ds, -1, -2) @ q), back(np.swapaxes(p, -1, -2) @ do)], 1)
+    assert relerr(host(o), back(ro)) <= (6e-3 if dh == 64 else 3e-3)
+    got = host(g)
+    for i in range(3):
+        ref = want[:, i * d:(i + 1) * d]
+        if np.abs(ref).max() > 1e-6:      # one key: no gradient of the scores
+            assert relerr(got[:, i * d:(i + 1) * d], ref) <= (1.5e-2 if dh == 64 else 6e-3), i
