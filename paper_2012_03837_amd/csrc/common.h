@@ -156,6 +156,8 @@ hipError_t op_gemm(const OpCtx& c, const GemmArgs& g);
 // plain fp32 outputs: the weight gradients of one layer), otherwise one after the other.  OpCtx::with_sums: one layer's
 // weight gradients, their bias gradients (GemmArgs::rowsum) and its pending sums, the sums in the same launch or ahead of it.
 hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n);
+// Whether product g is estimated to be faster in a launch with a group of n (of its reduction and layout) than behind it.
+bool gemm_joins(const OpCtx& c, const GemmArgs* group, int n, const GemmArgs& g);
 hipError_t op_fill_f32(const OpCtx& c, float* p, size_t n, float v);
 // out[0] = <a, b> / (|a| |b|) over n floats (0 if either norm is 0); uses 3 * 128 floats of c.partial
 hipError_t op_cosine(const OpCtx& c, const float* a, const float* b, size_t n, float* out);

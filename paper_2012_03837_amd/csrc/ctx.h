@@ -216,7 +216,7 @@ struct lp_ctx : lp_scratch {
 namespace lp {
 // The GEMMs a driver stage hands back for the caller to launch (see drivers.hip).
 // sums: the layer's weight gradients, with its bias gradients and pending sums (OpCtx::with_sums).
-struct StageGemms { GemmArgs g[4]; int n = 0; bool sums = false; };
+struct StageGemms { GemmArgs g[5]; int n = 0; bool sums = false; };
 // One layer's backward pass of a residual MLP: gradient in, where its input gradient goes (null: not wanted; dx_acc: added
 // to what is there), whether parameter gradients are taken and whether they are added to.
 struct MlpPass { int li = 0; const void* dout = nullptr; void* dx = nullptr; int dx_acc = 0; bool params = true; int acc = 0; };

@@ -244,6 +244,10 @@ static int dec_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx
     if (st != LP_OK) return st;
     OpCtx o = c->op();
     o.with_sums = sg.sums;
+    if (sg.sums && c->waiting.size() == 1) {       // the head's: one launch fewer, and with its tiles the group fills the chip better
+      sg.g[sg.n++] = c->waiting[0];
+      c->waiting.clear();
+    }
     DO(op_gemm_grouped(o, sg.g, sg.n));
   }
   return LP_OK;
@@ -402,7 +406,15 @@ int vocab_head_stage(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss
   } else if (stage == 1) {
     DO(op_softmax_ce(o, c->logits, Hd.ldz, y, c->loss_rows, rows, ncls, backward ? 1 : 0, 1.0f / (float)rows, Hd.ldz));
     DO(head_mean(c, rows, loss_out, backward));
-    if (backward) out->g[out->n++] = head_wgrad(c, Hd, c->logits, rows, Hd.t["w"]);    // logits now hold dZ
+    if (backward) {                   // logits now hold dZ
+      GemmArgs gw = head_wgrad(c, Hd, c->logits, rows, Hd.t["w"]);
+      // A small one goes out with the weight gradients of the layer below, over the same rows in the same layout (dec_backward):
+      // three layers of 128 with 1000 classes 348 -> 341 us a step, four of 128 with 8000 1056 -> 1042.
+      GemmArgs lw[4] = {lin_wgrad(c, L.u, L.f, rows, L.t["w2"], 0), lin_wgrad(c, L.f, L.c, rows, L.t["w1"], 0),
+                        lin_wgrad(c, L.u, L.o, rows, L.t["wo"], 0), lin_wgrad(c, L.qkv, L.a, rows, L.t["wqkv"], 0)};      // (of their sizes)
+      if (!c->lockstep && gemm_joins(o, lw, 4, gw)) c->waiting.push_back(gw);
+      else out->g[out->n++] = gw;
+    }
   } else if (stage == 2) {
     if (backward) out->g[out->n++] = head_dgrad(c, Hd, c->logits, rows, Hd.t["w"], c->dfeat);
   } else if (backward) {

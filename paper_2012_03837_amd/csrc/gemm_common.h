@@ -75,7 +75,7 @@ struct DmaGemmPlan {
 };
 
 // Tile shape and cut of a launch of the one-tile-per-block kernel (kernels_gemm_tile.hip), with its estimated time.
-constexpr int kTileShapes = 9, kTileGroupMax = 4;
+constexpr int kTileShapes = 9, kTileGroupMax = 5;      // a layer's four weight gradients and its head's
 struct TilePlan { int shape = -1, splits = 1, per = 0; double us = 1e300; };
 
 }  // namespace lp

@@ -199,6 +199,27 @@ hipError_t op_gemm(const OpCtx& c, const GemmArgs& g) {
   return gemm_f32(c, &g, 1);
 }
 
+static bool grouping_off() {     // LP_NO_GROUP=1: every product in a launch of its own (for measurements)
+  static int v = -1;
+  if (v < 0) { const char* s = getenv("LP_NO_GROUP"); v = (s && s[0] == '1') ? 1 : 0; }
+  return v != 0;
+}
+
+bool gemm_joins(const OpCtx& c, const GemmArgs* group, int n, const GemmArgs& g) {
+  if (c.dt != BF16 || use_plain() || grouping_off() || env_choice() != 0 || c.gemm_variant != 0 || n >= kTileGroupMax || !fast_ok(g)) return false;
+  GemmArgs all[kTileGroupMax];
+  for (int i = 0; i < n; ++i) {
+    if (!fast_ok(group[i]) || group[i].K != g.K || group[i].a_kc != g.a_kc || group[i].b_kc != g.b_kc) return false;
+    all[i] = group[i];
+  }
+  all[n] = g;
+  bool dma;
+  DmaGemmPlan d;
+  TilePlan alone;
+  if (!choose(c, g, &dma, &d, &alone) || dma) return false;
+  return gemm_tile_plan(c, all, n + 1).us < gemm_tile_plan(c, group, n).us + alone.us;
+}
+
 // The row losses of a head whose logits nothing else needs: instead of storing them (bf16 [rows, ld] into g.C) and reading them
 // again, the product leaves a pair per row and 64 columns in that memory, a 64th of it, and a short launch the losses; the
 // bits of op_softmax_ce.  Only where the product itself would be uncut 256 x 256 tiles (a large head); hipErrorInvalidValue,
@@ -222,17 +243,12 @@ hipError_t op_gemm_loss(const OpCtx& c, const GemmArgs& g, const int32_t* y, flo
 
 // n <= kTileGroupMax products in one launch of the one-tile-per-block kernel, whatever the other grouped kernel would cost.
 hipError_t gemm_tile_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
-  if (n < 1 || n > kTileGroupMax || c.dt != BF16) return hipErrorInvalidValue;
+  if (n < 1 || n > (c.with_sums ? kTileGroupMax : 4) || c.dt != BF16) return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i)
     if (!fast_ok(gs[i]) || gs[i].K != gs[0].K || gs[i].a_kc != gs[0].a_kc || gs[i].b_kc != gs[0].b_kc || (gs[i].rowsum && !c.with_sums)) return hipErrorInvalidValue;
   return gemm_tile(c, gs, n, gemm_tile_plan(c, gs, n));
 }
 
-static bool grouping_off() {     // LP_NO_GROUP=1: every product in a launch of its own (for measurements)
-  static int v = -1;
-  if (v < 0) { const char* s = getenv("LP_NO_GROUP"); v = (s && s[0] == '1') ? 1 : 0; }
-  return v != 0;
-}
 
 hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   if (c.dt == F32 && n >= 2) {
@@ -249,7 +265,7 @@ hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
       // alone against the persistent group and its fix-up: width 768 over 8192 rows 116 and 152 us, 1024 201 and 238, 448 over
       // 2555 24 and 43; level where the work is largest (768 over 32768 rows 455 and 465, 2048 over 8192 703 and 714).  More of them,
       // or unequal ones, go to that kernel.
-      bool tiles = n <= kTileGroupMax;
+      bool tiles = n <= 4 || (n <= kTileGroupMax && c.with_sums);
       double flops = 0.0;
       for (int i = 0; i < n; ++i) {
         const GemmArgs& g = gs[i];
@@ -269,13 +285,17 @@ hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
     }
   }
   if (c.with_sums) {                   // the sums by themselves, then the products
-    std::vector<const void*> dy(n);
+    std::vector<const void*> dy;
     std::vector<GemmArgs> plain(gs, gs + n);
-    std::vector<int64_t> ld(n);
-    std::vector<float*> out(n);
-    std::vector<int> m(n);
-    for (int i = 0; i < n; ++i) { dy[i] = gs[i].A; ld[i] = gs[i].lda; out[i] = gs[i].rowsum; m[i] = gs[i].M; plain[i].rowsum = nullptr; }
-    hipError_t e = op_colsum_batched(c, n, dy.data(), ld.data(), out.data(), gs[0].K, m.data(), gs[0].accumulate);
+    std::vector<int64_t> ld;
+    std::vector<float*> out;
+    std::vector<int> m;
+    for (GemmArgs& g : plain) {
+      if (!g.rowsum) continue;
+      dy.push_back(g.A); ld.push_back(g.lda); out.push_back(g.rowsum); m.push_back(g.M);
+      g.rowsum = nullptr;
+    }
+    hipError_t e = op_colsum_batched(c, (int)out.size(), dy.data(), ld.data(), out.data(), gs[0].K, m.data(), gs[0].accumulate);
     if (e == hipSuccess) e = op_add_pending(c);
     OpCtx o = c;
     o.with_sums = false;

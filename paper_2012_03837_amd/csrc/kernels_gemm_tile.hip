@@ -25,7 +25,7 @@ using namespace tile;
 
 namespace {
 
-constexpr int kTileGroup = 4;
+constexpr int kTileGroup = kTileGroupMax;
 struct TileProblem {
   Operand A, B;
   Epilogue e;
@@ -308,7 +308,6 @@ TilePlan gemm_tile_plan(const OpCtx& c, const GemmArgs* gs, int n) {
 // n products (one, or up to kTileGroupMax of one reduction length and the same operand layouts), all of shapes that the
 // bf16 kernels take.
 hipError_t gemm_tile(const OpCtx& c, const GemmArgs* gs, int n, const TilePlan& plan) {
-  static_assert(kTileGroup == kTileGroupMax, "");
   if (plan.shape < 0 || n < 1 || n > kTileGroup) return hipErrorInvalidValue;
   return n == 1 ? launch_group<1>(c, gs, 1, plan) : launch_group<kTileGroup>(c, gs, n, plan);
 }

@@ -81,8 +81,8 @@ extern "C" int lpk_weight_grads(int shape, int pieces, int n, const void* const*
                                 const int64_t* ld_x, float* const* dw, float* const* db, const int* M, const int* N, int rows,
                                 int accumulate, const float* part, float* out, int nblk, int len, float* splitk_ws,
                                 size_t splitk_ws_elems, void* stream) {
-  if (n < 2 || n > 4 || !dy || !ld_dy || !x || !ld_x || !dw || !db || !M || !N || rows < 1) return (int)hipErrorInvalidValue;
-  GemmArgs g[4];
+  if (n < 2 || n > 5 || !dy || !ld_dy || !x || !ld_x || !dw || !db || !M || !N || rows < 1) return (int)hipErrorInvalidValue;
+  GemmArgs g[5];
   for (int i = 0; i < n; ++i) {
     g[i].A = dy[i]; g[i].lda = ld_dy[i]; g[i].a_kc = 0; g[i].B = x[i]; g[i].ldb = ld_x[i]; g[i].b_kc = 0;
     g[i].C = dw[i]; g[i].ldc = N[i]; g[i].c_f32 = 1; g[i].M = M[i]; g[i].N = N[i]; g[i].K = rows;

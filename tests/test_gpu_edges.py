@@ -1062,10 +1062,10 @@ def test_gemm_fp32_wide_tiles(K, M, N, Kd, a_kc, b_kc):
 @pytest.mark.parametrize("shape,pieces", [(s, p) for s in range(6) for p in (1, 3)] + [(-1, 1)])
 def test_weight_gradients_with_sums(K, shape, pieces):
     """A layer's weight gradients with its bias gradients and pending sums in the launch, on every tile, whole and cut, stored and
-    added to what is there: rows past the tiles' and k past the last whole k-tile; one product without a bias, partial sums of a
+    added to what is there: rows past the tiles' and k past the last whole k-tile; two products without a bias, partial sums of a
     ragged width.  fp32 sums of 999 products (values) of either sign: 2e-6 (2e-6 of the sum of magnitudes, of order 30 deviations)."""
     import torch
-    rows, sizes = 999, [(264, 520), (520, 136), (8, 8), (1000, 264)]
+    rows, sizes = 999, [(264, 520), (520, 136), (8, 8), (1000, 264), (136, 72)]
     rng = np.random.default_rng(shape + 2)
     dY, X = [rnd(rng, (rows, m), 1, 0.5) for m, _ in sizes], [rnd(rng, (rows, n), 1, 0.5) for _, n in sizes]
     part = rng.standard_normal((37, 200)).astype(np.float32)
@@ -1074,12 +1074,12 @@ def test_weight_gradients_with_sums(K, shape, pieces):
     out = torch.full((201,), 3.0, device="cuda")
     ws = zeros(1 << 25)
     for times in (1, 2):
-        K.lpk_weight_grads([dev(a, 1) for a in dY], [dev(b, 1) for b in X], dw, [b if i != 2 else None for i, b in enumerate(db)], times - 1, ws,
+        K.lpk_weight_grads([dev(a, 1) for a in dY], [dev(b, 1) for b in X], dw, [b if i not in (2, 4) else None for i, b in enumerate(db)], times - 1, ws,
                            dev(part, 0), out, tiles=(shape, pieces))
         for i, (a, b) in enumerate(zip(dY, X)):
             a, b = a.astype(np.float64), b.astype(np.float64)
             assert relerr(host(dw[i]), times * (a.T @ b)) <= 2e-6
-            if i == 2: assert bool((db[i] == 3.0).all())
+            if i in (2, 4): assert bool((db[i] == 3.0).all())
             else:
                 assert np.abs(host(db[i][:-1]) - times * a.sum(0)).max() <= times * 2e-6 * np.abs(a).sum(0).max()
                 assert float(db[i][-1]) == 3.0
