@@ -143,6 +143,12 @@ int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x, float* dw
                            int R, int stride, int pad, int accumulate, float* splitk_ws_dev, size_t splitk_ws_elems,
                            void* stream);
 
+/* The filter gradients of a stage's convolutions, as its backward pass takes them: the pieces of all wait in the workspace and
+ * are added in one launch (in more where they do not fit together), with the bits of lpk_conv_bwd_weight_ws.  bf16; dims: n rows
+ * of N, H, W, C, O, R, stride, pad. */
+int lpk_conv_weight_grads(int n, const void* const* dout, const void* const* x, float* const* dw, const int* dims, int accumulate,
+                          float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
+
 /* A bf16 convolution on chosen tiles of the matrix-core kernel (for tests and measurements).  dir 0: out = conv(a = x, b = w);
  * 1: out = data gradient of (a = dout, b = w), plus `add` if given; 2: out (fp32) = filter gradient of (a = dout, b = x), added to
  * what is there if `accumulate`.  shape: rows x columns 0: 64 x 64, 1: 128 x 64, 2: 128 x 128 (two stages), 3: 128 x 128 (four),

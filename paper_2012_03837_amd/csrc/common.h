@@ -119,6 +119,15 @@ struct PendingSums {
   void add(const float* part, float* out, int nblk, int n, int accumulate) { s[count++] = Sum{part, out, nblk, n, accumulate}; }
 };
 
+// Filter gradients whose pieces' sums wait in the split-K workspace until one launch adds them (op_conv_add_pending): nothing
+// before the update reads them, and a launch of a few KB costs what any launch costs.  `used` floats of the workspace are taken.
+constexpr int kMaxFilters = 8;
+struct PendingFilters {
+  size_t used = 0;
+  int count = 0;
+  struct Filter { const float* ws; float* dw; int M, N, splits, accumulate; } f[kMaxFilters];
+};
+
 struct OpCtx {
   hipStream_t stream;
   int dt;              // compute dtype
@@ -131,6 +140,7 @@ struct OpCtx {
   float* splitk_ws = nullptr;   // fp32 workspace for split-K partial sums (may be null: no split-K)
   size_t splitk_elems = 0;
   PendingSums* pending = nullptr;   // where op_layernorm_bwd and op_colsum_batched may leave their sums (null: nowhere)
+  PendingFilters* filters = nullptr;   // where op_conv_bwd_weight may leave its pieces (null: nowhere)
   bool with_sums = false;           // op_gemm_grouped: the products' row sums and what is pending go out with their launch
 };
 
@@ -249,6 +259,8 @@ hipError_t op_conv_bwd_data(const OpCtx& c, const ConvArgs& a, const void* dout,
                             const void* add = nullptr);
 hipError_t op_conv_bwd_weight(const OpCtx& c, const ConvArgs& a, const void* dout, const void* x, float* dw,
                               int accumulate);
+// Adds what waits in c.filters, in one launch (the same bits as at once).
+hipError_t op_conv_add_pending(const OpCtx& c);
 // Running statistics of one batch normalisation (the evaluation form of the method appendix B.3 cites).
 // use == 0: the forward pass normalises with the batch's statistics and folds them in,
 //   mean <- (1 - momentum) mean + momentum mean_B,  var <- (1 - momentum) var + momentum var_B rows / (rows - 1);

@@ -75,8 +75,10 @@ hipError_t op_conv_bwd_weight(const OpCtx& c, const ConvArgs& a, const void* dou
                               int accumulate) {
   ProfScope prof_(c, KC_CONV, 2.0 * a.N * a.P * a.Q * a.O * a.R * a.S * a.C);
   if (!plain_conv() && conv_mfma_ok(c, a, dout, x, dw)) return conv_bwd_weight_mfma(c, a, dout, x, dw, accumulate);
+  hipError_t e = op_conv_add_pending(c);      // what follows uses the workspace from its start
+  if (e != hipSuccess) return e;
   if (!plain_conv() && conv_stem_ok(c, a, dout, dw)) {
-    hipError_t e = conv_stem_wgrad(c, a, dout, x, dw, accumulate);
+    e = conv_stem_wgrad(c, a, dout, x, dw, accumulate);
     if (e != hipErrorInvalidValue) return e;
   }
   return conv_bwd_weight_plain(c, a, dout, x, dw, accumulate);

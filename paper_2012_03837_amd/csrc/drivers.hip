@@ -268,8 +268,9 @@ static int unit_forward(lp_ctx* c, ConvUnit& u, const void* x, const void* res) 
 }
 // dy -> (dz in sZ) -> dw, and dx (+ dx_add, if given) if asked.  dres (if non-null) receives the ReLU-masked dy.
 static int unit_backward(lp_ctx* c, ConvUnit& u, const void* x, const void* dy, void* dres, void* dx, int acc,
-                         const void* dx_add = nullptr) {
+                         PendingFilters* later, const void* dx_add = nullptr) {
   OpCtx o = c->op();
+  o.filters = later;
   int rows = u.a.N * u.a.P * u.a.Q;
   const size_t es = dtype_size(c->dt);
   if (u.dy_keep) DO(hipMemcpyAsync(u.dy_keep, dy, (size_t)rows * u.a.O * es, hipMemcpyDeviceToDevice, o.stream));
@@ -310,6 +311,8 @@ static int res_forward(lp_ctx* c, int li, int batch) {
 static int res_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int acc) {
   LayerState& L = c->layers[li];
   OpCtx o = c->op();
+  PendingFilters later;          // the filter gradients' pieces: added in one launch at the end
+  o.filters = &later;
   const void* g = dout;
   int st;
   for (int bi = (int)L.blocks.size() - 1; bi >= 0; --bi) {
@@ -318,22 +321,26 @@ static int res_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx
     bool first_op = (bi == 0 && !L.has_stem);
     bool want_dx = need_dx || !first_op;
     // c2: dz2 -> dw2, dt (into sD1); masked upstream gradient ds -> sR
-    if ((st = unit_backward(c, b.c2, b.c1.y, g, c->sR, c->sD1, acc)) != LP_OK) return st;
+    if ((st = unit_backward(c, b.c2, b.c1.y, g, c->sR, c->sD1, acc, &later)) != LP_OK) return st;
     // c1, and the shortcut's share of the block input's gradient, added in the data-gradient epilogue that
     // finishes last: the identity shortcut's is the masked upstream gradient itself (sR), a projection's is its
     // own data gradient, which then takes c1's (sD1) as its addend
     void* dst = (first_op && need_dx) ? dx : c->sG;
     if (b.has_proj) {
-      if ((st = unit_backward(c, b.c1, bin, c->sD1, nullptr, want_dx ? c->sD1 : nullptr, acc)) != LP_OK) return st;
-      if ((st = unit_backward(c, b.proj, bin, c->sR, nullptr, want_dx ? dst : nullptr, acc, c->sD1)) != LP_OK) return st;
+      if ((st = unit_backward(c, b.c1, bin, c->sD1, nullptr, want_dx ? c->sD1 : nullptr, acc, &later)) != LP_OK) return st;
+      if ((st = unit_backward(c, b.proj, bin, c->sR, nullptr, want_dx ? dst : nullptr, acc, &later, c->sD1)) != LP_OK) return st;
     } else {
-      if ((st = unit_backward(c, b.c1, bin, c->sD1, nullptr, want_dx ? dst : nullptr, acc, c->sR)) != LP_OK) return st;
+      if ((st = unit_backward(c, b.c1, bin, c->sD1, nullptr, want_dx ? dst : nullptr, acc, &later, c->sR)) != LP_OK) return st;
     }
     g = dst;
   }
   if (L.has_stem) {
-    if ((st = unit_backward(c, L.stem, layer_input(c, li), g, nullptr, need_dx ? dx : nullptr, acc)) != LP_OK)
+    if ((st = unit_backward(c, L.stem, layer_input(c, li), g, nullptr, need_dx ? dx : nullptr, acc, &later)) != LP_OK)
       return st;
+  }
+  if (later.count) {
+    ProfScope prof_(o, KC_CONV);
+    DO(op_conv_add_pending(o));
   }
   return LP_OK;
 }

@@ -201,6 +201,20 @@ extern "C" int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x
   c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws ? splitk_ws_elems : 0;
   return (int)op_conv_bwd_weight(c, mkconv(N, H, W, C, O, R, stride, pad), dout, x, dw, accumulate);
 }
+extern "C" int lpk_conv_weight_grads(int n, const void* const* dout, const void* const* x, float* const* dw, const int* dims,
+                                     int accumulate, float* splitk_ws, size_t splitk_ws_elems, void* stream) {
+  if (n < 1 || !dout || !x || !dw || !dims) return (int)hipErrorInvalidValue;
+  PendingFilters later;
+  OpCtx c = mk(BF16, stream);
+  c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws ? splitk_ws_elems : 0;
+  c.filters = &later;
+  for (int i = 0; i < n; ++i) {
+    const int* d = dims + 8 * i;
+    hipError_t e = op_conv_bwd_weight(c, mkconv(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7]), dout[i], x[i], dw[i], accumulate);
+    if (e != hipSuccess) return (int)e;
+  }
+  return (int)op_conv_add_pending(c);
+}
 extern "C" int lpk_conv_plan(int dir, int N, int H, int W, int C, int O, int R, int stride, int pad, size_t splitk_ws_elems,
                              int* shape, int* pieces) {
   if (dir < 0 || dir > 2 || !shape || !pieces) return (int)hipErrorInvalidValue;

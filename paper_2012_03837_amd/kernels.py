@@ -146,6 +146,14 @@ def lpk_conv_bwd_weight_ws(dtype, dout, x, dw, N, H, W, Cin, O, R, stride, pad, 
                                      _stream()), "lpk_conv_bwd_weight_ws")
 
 
+def lpk_conv_weight_grads(douts, xs, dws, dims, splitk_ws, accumulate=0):
+    """dims: (N, H, W, C, O, R, stride, pad) of each convolution."""
+    n, vp = len(dws), C.c_void_p * len(dws)
+    ptrs = lambda ts: vp(*[t.data_ptr() for t in ts])
+    _ck(lib().lpk_conv_weight_grads(_i(n), ptrs(douts), ptrs(xs), ptrs(dws), (C.c_int * (8 * n))(*[v for d in dims for v in d]),
+                                    _i(accumulate), _p(splitk_ws), _sz(splitk_ws.numel()), _stream()), "lpk_conv_weight_grads")
+
+
 def lpk_conv_tile(direction, a, b, out, N, H, W, Cin, O, R, stride, pad, shape, pieces=1, add=None, accumulate=0, stats=None,
                   splitk_ws=None):
     """Returns the rows of a tile whose column sums were left in `stats` (0: none)."""

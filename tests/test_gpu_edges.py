@@ -788,6 +788,31 @@ def test_convolution_tiles(K, N, H, W, C, O, R, stride):
     assert relerr(host(gw), 2 * want) <= 2e-6
 
 
+FILTERS = [(50, 28, 28, 24, 24, 3, 1, 1), (3, 11, 9, 64, 128, 3, 2, 1), (5, 13, 11, 72, 136, 1, 1, 0), (2, 16, 16, 3, 64, 3, 1, 1),
+           (50, 7, 7, 96, 96, 3, 1, 1), (1, 3, 3, 8, 8, 3, 1, 1), (64, 4, 4, 256, 512, 3, 1, 1), (50, 14, 14, 24, 48, 1, 2, 0),
+           (40, 8, 8, 128, 128, 3, 1, 1), (50, 14, 14, 48, 48, 3, 1, 1), (6, 6, 6, 16, 8, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("elems", [1 << 18, 1 << 21, 1 << 25])
+@pytest.mark.parametrize("which", [slice(0, 1), slice(2, 7), slice(0, 11)])
+def test_filter_gradients_in_one_launch(K, which, elems):
+    """Pieces of several filter gradients that wait for one launch (in a workspace that holds all of them, some, or hardly one;
+    with a convolution among them that takes the workspace from its start): the bits of each alone."""
+    import torch
+    dims, rng = FILTERS[which], np.random.default_rng(7)
+    out = lambda d: ((d[1] + 2 * d[7] - d[5]) // d[6] + 1, (d[2] + 2 * d[7] - d[5]) // d[6] + 1)
+    xs = [dev(rnd(rng, d[:4], 1), 1) for d in dims]
+    dys = [dev(rnd(rng, (d[0], *out(d), d[4]), 1), 1) for d in dims]
+    ws = torch.full((elems,), float("nan"), device="cuda")
+    got, want = ([zeros(d[4], d[5], d[5], d[3]) for d in dims] for _ in range(2))
+    for acc in (0, 1):
+        K.lpk_conv_weight_grads(dys, xs, got, dims, ws, accumulate=acc)
+        for d, x, dy, w in zip(dims, xs, dys, want):
+            K.lpk_conv_bwd_weight_ws(1, dy, x, w, *d, ws, accumulate=acc)
+        for g, w in zip(got, want):
+            assert torch.isfinite(g).all() and torch.equal(g, w)
+
+
 TILES = {0: (64, 64), 1: (128, 64), 2: (128, 128), 3: (128, 128), 4: (256, 128), 6: (64, 128), 7: (256, 64), 8: (128, 32)}
 
 
