@@ -115,7 +115,10 @@ typedef struct {
                                them, default priority) as soon as the head's activation exists, while the
                                forward pass continues on the caller's stream; all of them are joined back
                                into the caller's stream before lp_local_step returns.  Results do not depend
-                               on n (every per-parameter accumulation keeps its order).  At most 8.  The
+                               on n (every per-parameter accumulation keeps its order).  At most 8.
+                               lp_eval_loss of a decoder with several heads uses them the same way for all
+                               heads but the last where they are large (and the caller's stream is not being
+                               captured), and joins them before it returns.  The
                                synchronous step of a residual MLP whose heads sit behind different layers does
                                not use them in fp32 (nor in bf16 with n = 1): its blocks walk their backward
                                passes together on the caller's stream, the products of all of them in shared

@@ -211,6 +211,7 @@ hipError_t op_softmax_ce(const OpCtx& c, void* z, int64_t ld, const int32_t* y, 
 // loss_rows of the logits that product g would store, without storing them; hipErrorInvalidValue (nothing launched) where that
 // form does not apply.
 hipError_t op_gemm_loss(const OpCtx& c, const GemmArgs& g, const int32_t* y, float* loss_rows);
+bool gemm_loss_ok(const OpCtx& c, const GemmArgs& g);      // whether it does
 hipError_t op_mean(const OpCtx& c, const float* v, int n, float* out);
 // Classifier heads of at most 32 classes on at most 1024 features, up to eight in one launch over the same rows and
 // labels: loss_rows, and if `backward` also dZ [rows, ncls] and dfeat = dZ w [rows, in] (and a second copy of it).

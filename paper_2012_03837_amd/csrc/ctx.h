@@ -234,6 +234,7 @@ int drv_forward(lp_ctx* c, int li, int batch, const int32_t* ids_or_null);
 // params == false: only the gradient with respect to the layer's input (no parameter gradient is touched).
 int drv_backward(lp_ctx* c, int li, int batch, const void* dout, void* dx, bool need_dx, int accumulate,
                  bool params = true);
+bool eval_beside(lp_ctx* c, int batch);
 int drv_head(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss_out, bool backward, void* dh);
 size_t layer_out_elems(const lp_layer_spec& s, int batch);
 }

@@ -987,8 +987,11 @@ hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d) {
 
 // The product of a head's logits for its loss alone (see GroupStats): both operands with k contiguous, N a multiple of 8, nothing
 // fused.  hipErrorInvalidValue, with nothing launched, where the plan is not whole 256 x 256 tiles of 64-deep k-tiles.
+bool gemm_dma_stats_ok(const GemmArgs& g, const DmaGemmPlan& d) {
+  return d.kind == 3 && !d.sib && d.partial_bytes <= 0 && g.a_kc && g.b_kc && !g.a_rows && !g.b_rows;
+}
 hipError_t gemm_dma_stats(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d, const GroupStats& gs) {
-  if (d.kind != 3 || d.sib || d.partial_bytes > 0 || !g.a_kc || !g.b_kc || g.a_rows || g.b_rows) return hipErrorInvalidValue;
+  if (!gemm_dma_stats_ok(g, d)) return hipErrorInvalidValue;
   SkPlan p;
   p.tiles_m = d.tiles_m; p.tiles_n = d.tiles_n; p.kt = d.kt; p.full = d.full; p.tail_tiles = d.tail_tiles;
   p.upb = d.upb; p.G = d.G; p.sib = 0; p.ngrp = 0; p.K = g.K;

@@ -24,6 +24,7 @@ hipError_t gemm_f32(const OpCtx& c, const GemmArgs* gs, int n);
 bool gemm_dma_ok(const GemmArgs& g);
 bool gemm_dma_plan(const OpCtx& c, const GemmArgs& g, int kind, int mode, DmaGemmPlan* out);
 hipError_t gemm_dma(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d);
+bool gemm_dma_stats_ok(const GemmArgs& g, const DmaGemmPlan& d);
 hipError_t gemm_dma_stats(const OpCtx& c, const GemmArgs& g, const DmaGemmPlan& d, const GroupStats& gs);
 bool ce_fast_ok(const OpCtx& c, const void* z, int64_t ld, int n);
 hipError_t ce_finish(const OpCtx& c, const GroupStats& g, float* loss_rows, int rows, int n);
@@ -225,17 +226,21 @@ bool gemm_joins(const OpCtx& c, const GemmArgs* group, int n, const GemmArgs& g)
 // bits of op_softmax_ce.  Only where the product itself would be uncut 256 x 256 tiles (a large head); hipErrorInvalidValue,
 // with nothing launched, where not.  Twelve layers of 768, 8192 rows, 32000 classes: 8.66 -> 7.72 ms an
 // evaluation.
+static bool loss_plan(const OpCtx& c, const GemmArgs& g, DmaGemmPlan* d) {
+  if (c.dt != BF16 || use_plain() || !fast_ok(g) || !ce_fast_ok(c, g.C, g.ldc, g.N)) return false;
+  if (g.bias || g.pre || g.act != ACT_NONE || g.dact != ACT_NONE || g.res || g.accumulate || g.c_f32 || g.rowsum) return false;
+  if (((size_t)8 * ((g.N + 63) / 64) + 4) > (size_t)2 * g.ldc) return false;
+  bool dma;
+  TilePlan t;
+  return choose(c, g, &dma, d, &t) && dma && gemm_dma_stats_ok(g, *d);
+}
+bool gemm_loss_ok(const OpCtx& c, const GemmArgs& g) { DmaGemmPlan d; return loss_plan(c, g, &d); }
 hipError_t op_gemm_loss(const OpCtx& c, const GemmArgs& g, const int32_t* y, float* loss_rows) {
-  if (c.dt != BF16 || use_plain() || !fast_ok(g) || !ce_fast_ok(c, g.C, g.ldc, g.N)) return hipErrorInvalidValue;
-  if (g.bias || g.pre || g.act != ACT_NONE || g.dact != ACT_NONE || g.res || g.accumulate || g.c_f32 || g.rowsum) return hipErrorInvalidValue;
+  DmaGemmPlan d;
+  if (!loss_plan(c, g, &d)) return hipErrorInvalidValue;
   GroupStats gs;
   gs.groups = (g.N + 63) / 64; gs.y = y;
   gs.pair = (float2*)g.C; gs.zy = (float*)(gs.pair + (size_t)g.M * gs.groups);
-  if (((size_t)8 * gs.groups + 4) > (size_t)2 * g.ldc) return hipErrorInvalidValue;
-  bool dma;
-  DmaGemmPlan d;
-  TilePlan t;
-  if (!choose(c, g, &dma, &d, &t) || !dma) return hipErrorInvalidValue;
   ProfScope prof_(c, KC_GEMM, 2.0 * g.M * g.N * g.K);
   hipError_t e = gemm_dma_stats(c, g, d, gs);
   return e == hipSuccess ? ce_finish(c, gs, loss_rows, g.M, g.N) : e;

@@ -1200,3 +1200,53 @@ def test_attention_in_parts(K, dh, S, causal, parts):
         ref = want[:, i * d:(i + 1) * d]
         if np.abs(ref).max() > 1e-6:      # one key: no gradient of the scores
             assert relerr(got[:, i * d:(i + 1) * d], ref) <= (1.5e-2 if dh == 64 else 6e-3), i
+
+
+@pytest.mark.parametrize("layers,seq,batch,vocab,scheme,chunk", [(4, 64, 1, 1000, "backprop", 1), (4, 64, 1, 1000, "greedy", 1), (8, 64, 1, 504, "chunk", 2)])
+def test_small_evaluations_do_not_pay_for_side_streams(K, layers, seq, batch, vocab, scheme, chunk):
+    """A small evaluation takes no longer in a trainer with side streams than in one without: the same launches on one stream.
+    The least of twelve alternating turns of twenty; with the heads on side streams it takes 1.2 to 1.4 times as long."""
+    import time
+    import torch
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=layers, width=128, n_heads=2, hidden=512, seq_len=seq, batch=batch, vocab=vocab, act="gelu", scheme=scheme, chunk=chunk)
+    trs = [lp.LocalTrainer(cfg, n_streams=n) for n in (0, 2)]
+    xd, yd = trs[0].stage(*data_for(cfg))
+    best = [1e9, 1e9]
+    for turn in range(13):                       # the first is not counted
+        for i, tr in enumerate(trs):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(20):
+                tr.eval(xd, yd)
+            torch.cuda.synchronize()
+            if turn: best[i] = min(best[i], time.perf_counter() - t0)
+    assert best[1] <= 1.12 * best[0], best
+    for tr in trs: tr.close()
+
+
+@pytest.mark.parametrize("layers,seq,batch,vocab,scheme,chunk,drop", [(3, 511, 4, 10003, "greedy", 1, 0), (4, 511, 4, 30003, "chunk", 2, 0), (3, 511, 5, 10003, "overlap", 1, 1)])
+def test_evaluation_beside_the_layers(K, layers, seq, batch, vocab, scheme, chunk, drop):
+    """Heads large enough to be evaluated on side streams (classes no multiple of 8, behind 25 GFLOP each and more): the losses' bits of
+    one stream, over again and between steps, with the labels and the inputs overwritten behind the call."""
+    import torch
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=layers, width=448, n_heads=7, hidden=1792, seq_len=seq, batch=batch, vocab=vocab, act="gelu", scheme=scheme, chunk=chunk)
+    x, y = data_for(cfg)
+    P, seen = generic_params(cfg), []
+    for n in (0, 2, 1):
+        tr = lp.LocalTrainer(cfg, n_streams=n)
+        tr.set_params(P)
+        out = []
+        for _ in range(2):
+            xd, yd = tr.stage(x, y)
+            for _ in range(3):
+                out.append(tr.eval(xd[:batch - drop], yd[:batch - drop]).clone())
+            xd.zero_(); yd.zero_()
+            xd, yd = tr.stage(x, y)
+            out.append(tr.step(xd[:batch - drop], yd[:batch - drop]).clone())
+        seen.append(torch.stack(out).cpu().numpy())
+        tr.close()
+    assert np.isfinite(seen[0]).all() and (seen[0][0] == seen[0][3]).all() and (seen[0][4] != seen[0][0]).any()
+    np.testing.assert_array_equal(seen[0], seen[1])
+    np.testing.assert_array_equal(seen[0], seen[2])
