@@ -70,13 +70,17 @@ int lpk_weight_grads(int shape, int pieces, int n, const void* const* dy, const 
                      size_t splitk_ws_elems, void* stream);
 
 /* Causal (or full) multi-head attention of a decoder layer (appendix B.2).  qkv [B*S, 3*H*dh]
- * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch.  plain 0: the library's
- * choice; 1: the row-by-row kernels; for tests and measurements 2, 3, 4: the matrix kernels with a block's chain of tiles in
- * one, two or four parts. */
+ * (q | k | v), o [B*S, H*dh], lse [B,H,S] = log-sum-exp of the scaled scores, delta [B,H,S] scratch.  plain != 0: the
+ * row-by-row kernels. */
 int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal,
                       int plain, void* stream);
 int lpk_attention_bwd(int dtype, const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv,
                       float* delta, int B, int S, int H, int dh, int causal, int plain, void* stream);
+/* The same in bf16 on the matrix kernels, heads of 16, 32 or 64, with a block's chain of tiles in 1, 2 or 4 parts (for tests and
+ * measurements); qkv, o, dout and dqkv on 16-byte boundaries.  Anything else is refused. */
+int lpk_attention_fwd_parts(const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal, int parts, void* stream);
+int lpk_attention_bwd_parts(const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv, float* delta, int B,
+                            int S, int H, int dh, int causal, int parts, void* stream);
 
 /* LayerNorm over the last dimension (eps 1e-5, biased variance); backward adds `add` to dx if given. */
 int lpk_layernorm_fwd(int dtype, const void* x, const float* g, const float* b, void* y, float* mean, float* rstd,

@@ -16,6 +16,10 @@ TilePlan conv_mfma_plan(const OpCtx& c, const ConvArgs& a, int dir);
 hipError_t attn_fwd_plain(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
 hipError_t attn_bwd_plain(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                           void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
+bool attn_mfma_ok(int dh);
+hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
+hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
+                         void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
 hipError_t conv_fwd_plain(const OpCtx& c, const ConvArgs& a, const void* x, const void* w, void* out);
 hipError_t conv_bwd_data_plain(const OpCtx& c, const ConvArgs& a, const void* dout, const void* w, void* dx,
                                const void* add = nullptr);
@@ -100,17 +104,30 @@ extern "C" int lpk_weight_grads(int shape, int pieces, int n, const void* const*
 extern "C" int lpk_attention_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int S, int H, int dh,
                                  int causal, int plain, void* stream) {
   OpCtx c = mk(dtype, stream);
-  if (plain >= 2) c.attn_split = plain == 2 ? 1 : (plain == 3 ? 2 : 4);
-  if (plain == 1) return (int)attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
+  if (plain) return (int)attn_fwd_plain(c, qkv, o, lse, B, S, H, dh, causal);
   return (int)op_attn_fwd(c, qkv, o, lse, B, S, H, dh, causal);
 }
 extern "C" int lpk_attention_bwd(int dtype, const void* qkv, const void* o, const float* lse, const void* dout,
                                  void* dqkv, float* delta, int B, int S, int H, int dh, int causal, int plain,
                                  void* stream) {
   OpCtx c = mk(dtype, stream);
-  if (plain >= 2) c.attn_split = plain == 2 ? 1 : (plain == 3 ? 2 : 4);
-  if (plain == 1) return (int)attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
+  if (plain) return (int)attn_bwd_plain(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
   return (int)op_attn_bwd(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
+}
+static bool parts_ok(int dh, int parts, uintptr_t bits) { return attn_mfma_ok(dh) && (parts == 1 || parts == 2 || parts == 4) && !(bits & 15); }
+extern "C" int lpk_attention_fwd_parts(const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal, int parts,
+                                       void* stream) {
+  if (!parts_ok(dh, parts, (uintptr_t)qkv | (uintptr_t)o)) return (int)hipErrorInvalidValue;
+  OpCtx c = mk(BF16, stream);
+  c.attn_split = parts;
+  return (int)attn_fwd_mfma(c, qkv, o, lse, B, S, H, dh, causal);
+}
+extern "C" int lpk_attention_bwd_parts(const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv, float* delta,
+                                       int B, int S, int H, int dh, int causal, int parts, void* stream) {
+  if (!parts_ok(dh, parts, (uintptr_t)qkv | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dqkv)) return (int)hipErrorInvalidValue;
+  OpCtx c = mk(BF16, stream);
+  c.attn_split = parts;
+  return (int)attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
 }
 extern "C" int lpk_layernorm_fwd(int dtype, const void* x, const float* g, const float* b, void* y, float* mean,
                                  float* rstd, int rows, int d, void* stream) {

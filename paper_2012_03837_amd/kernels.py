@@ -81,6 +81,16 @@ def lpk_attention_bwd(dtype, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal
                                 _i(dh), _i(causal), _i(plain), _stream()), "lpk_attention_bwd")
 
 
+def lpk_attention_fwd_parts(qkv, o, lse, B, S, H, dh, causal, parts):
+    _ck(lib().lpk_attention_fwd_parts(_p(qkv), _p(o), _p(lse), _i(B), _i(S), _i(H), _i(dh), _i(causal), _i(parts), _stream()),
+        "lpk_attention_fwd_parts")
+
+
+def lpk_attention_bwd_parts(qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal, parts):
+    _ck(lib().lpk_attention_bwd_parts(_p(qkv), _p(o), _p(lse), _p(dout), _p(dqkv), _p(delta), _i(B), _i(S), _i(H), _i(dh),
+                                      _i(causal), _i(parts), _stream()), "lpk_attention_bwd_parts")
+
+
 def lpk_layernorm_fwd(dtype, x, g, b, y, mean, rstd, rows, d):
     _ck(lib().lpk_layernorm_fwd(_i(dtype), _p(x), _p(g), _p(b), _p(y), _p(mean), _p(rstd), _i(rows), _i(d), _stream()),
         "lpk_layernorm_fwd")

@@ -1181,8 +1181,8 @@ def test_attention_in_parts(K, dh, S, causal, parts):
     dq = dev(qkv, 1)
     o, g = torch.zeros(B * S, d, device="cuda", dtype=torch.bfloat16), torch.full((B * S, 3 * d), 7.0, device="cuda", dtype=torch.bfloat16)
     lse, delta = zeros(B * H * S), zeros(B * H * S)
-    K.lpk_attention_fwd(1, dq, o, lse, B, S, H, dh, causal, 1 + {1: 1, 2: 2, 4: 3}[parts])
-    K.lpk_attention_bwd(1, dq, o, lse, dev(dout, 1), g, delta, B, S, H, dh, causal, 1 + {1: 1, 2: 2, 4: 3}[parts])
+    K.lpk_attention_fwd_parts(dq, o, lse, B, S, H, dh, causal, parts)
+    K.lpk_attention_bwd_parts(dq, o, lse, dev(dout, 1), g, delta, B, S, H, dh, causal, parts)
 
     def heads(t):
         return t.reshape(B, S, H, dh).transpose(0, 2, 1, 3)
@@ -1250,3 +1250,27 @@ def test_evaluation_beside_the_layers(K, layers, seq, batch, vocab, scheme, chun
     assert np.isfinite(seen[0]).all() and (seen[0][0] == seen[0][3]).all() and (seen[0][4] != seen[0][0]).any()
     np.testing.assert_array_equal(seen[0], seen[1])
     np.testing.assert_array_equal(seen[0], seen[2])
+
+
+@pytest.mark.parametrize("plain", [2, 3, 4, 7, -1])
+@pytest.mark.parametrize("dh", [16, 64])
+def test_attention_row_by_row_for_any_plain(K, dh, plain):
+    """Every value of `plain` but 0 is the row-by-row kernels: their bits.  Parts other than 1, 2 and 4 and other head sizes are
+    refused."""
+    import torch
+    B, S, H = 2, 150, 3
+    d, rng = H * dh, np.random.default_rng(dh)
+    qkv, dout = dev(rnd(rng, (B * S, 3 * d), 1), 1), dev(rnd(rng, (B * S, d), 1), 1)
+    seen = []
+    for p in (1, plain):
+        o, dq = zeros(B * S, d).bfloat16(), zeros(B * S, 3 * d).bfloat16()
+        lse, delta = zeros(B, H, S), zeros(B, H, S)
+        K.lpk_attention_fwd(1, qkv, o, lse, B, S, H, dh, 1, plain=p)
+        K.lpk_attention_bwd(1, qkv, o, lse, dout, dq, delta, B, S, H, dh, 1, plain=p)
+        seen.append((o, lse, dq, delta))
+    assert all(torch.equal(a, b) for a, b in zip(*seen))
+    for bad in ((dh, 0), (dh, 3), (dh, 8), (48, 1)):
+        with pytest.raises(K.KernelError):
+            K.lpk_attention_fwd_parts(qkv, o, lse, B, S, H, bad[0], 1, bad[1])
+        with pytest.raises(K.KernelError):
+            K.lpk_attention_bwd_parts(qkv, o, lse, dout, dq, delta, B, S, H, bad[0], 1, bad[1])
