@@ -81,6 +81,8 @@ int lpk_attention_bwd(int dtype, const void* qkv, const void* o, const float* ls
 int lpk_attention_fwd_parts(const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal, int parts, void* stream);
 int lpk_attention_bwd_parts(const void* qkv, const void* o, const float* lse, const void* dout, void* dqkv, float* delta, int B,
                             int S, int H, int dh, int causal, int parts, void* stream);
+/* The parts that the library chooses (needs no device); 0 for heads that are not 16, 32 or 64 wide. */
+int lpk_attention_parts(int B, int S, int H, int dh, int backward);
 
 /* LayerNorm over the last dimension (eps 1e-5, biased variance); backward adds `add` to dx if given. */
 int lpk_layernorm_fwd(int dtype, const void* x, const float* g, const float* b, void* y, float* mean, float* rstd,

@@ -196,7 +196,7 @@ __device__ __forceinline__ AttnBlock attn_block(int index, int H, int BH, int nb
 
 // P parts: where the blocks of 128 queries (or keys) are few, a block takes 64 or 32 of them, and the two or four waves that share
 // them every second or fourth key (query) tile, all brought to LDS together; their partial results are added through LDS.  A
-// chain of up to S / 64 tiles becomes one of a half or a quarter, on two or four times as many blocks (measured: see fwd_parts).
+// chain of up to S / 64 tiles becomes one of a half or a quarter, on two or four times as many blocks (measured: see parts_of).
 // LDS of a block whose tiles take `tiles` bytes and whose four waves leave `values` partial values a lane over them.
 template <int P>
 constexpr int sum_bytes(int values, size_t tiles) { return P > 1 && 4 * values * 256 > (int)tiles ? 4 * values * 256 : (int)tiles; }
@@ -815,6 +815,17 @@ k_attn_bwd_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, co
 //           12   200 x 2 x 64         7.6   7.6   7.5       13.1    9.6    8.0
 //           64  2048 x 4 x 64        33.5  22.7  16.8       61.9   41.4   34.3
 //           90  1100 x 5 x 64        20.5  14.6  12.0       40.1   28.6   27.2
+//           48   300 x 8 x 64         8.2   7.5   7.5       15.6   12.0   12.6
+//           63   300 x 7 x 64         8.3   7.2   7.3       15.6   12.0   12.9
+//           64   512 x 8 x 64        11.7   8.9   7.2       20.5   14.3   14.0
+//           80   512 x 10 x 64       11.8   9.0   7.9       20.6   16.2   17.8
+//           96   300 x 8 x 64         8.2   7.5   7.4       15.4   13.0   15.9
+//           96   768 x 8 x 64        15.6  11.3   9.6       27.5   21.3   23.3
+//           96  1024 x 12 x 64       19.3  13.6  10.9       34.7   25.8   26.0
+//           96  1536 x 8 x 64        26.6  18.1  14.6       48.7   34.4   32.0
+//           96   300 x 8 x 32         9.6   8.0   7.7       17.1   13.2   12.8
+//           96   512 x 12 x 16       13.1   9.7   7.8       22.2   15.8   15.9
+//          126   768 x 7 x 64        15.7  11.6  10.3       30.8   24.2   33.9
 //          128  2048 x 8 x 64        34.1  23.0  18.0       64.2   44.4   46.5
 //          128   256 x 8 x 64         7.9   7.1   7.2       13.7   11.3   18.2
 //          140   511 x 7 x 64        12.0   9.6  11.7       24.7   19.8   33.4
@@ -822,15 +833,19 @@ k_attn_bwd_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, co
 //          256  1024 x 8 x 64        19.6  14.8  19.5       37.5   38.1   55.5
 //          256   512 x 8 x 32        14.7   9.8  11.9       24.6   24.9   33.5
 //          768  1024 x 12 x 64       28.0  31.1  47.5       88.9  112.5  187.1
+// Four parts of the backward pass of 64-wide heads are 8 n blocks of both kinds, two to a compute unit: past n = 64 they no longer
+// go at once, which only long chains pay back (32 + S / 16, up to 96); the narrower heads' chains are longer.
 // Short chains only where the blocks are very few: with another chain's products beside it the chip is not empty, and 128 blocks of
 // 256 x 8 x 64 in parts gain nothing (pipelined eight layers of 512: 2039 us in parts, 2009 whole).
-static int attn_parts(const OpCtx& c, int n, int S, int four, int two) {
-  if (c.attn_split) return c.attn_split;
+static int parts_of(int n, int S, int four, int two) {
   if (S <= 256 ? n > 32 || S <= 64 : n > two) return 1;
   return n <= four && S > 128 ? 4 : 2;
 }
-static int fwd_parts(const OpCtx& c, int n, int S) { return attn_parts(c, n, S, 128, 256); }
-static int bwd_parts(const OpCtx& c, int n, int S) { return attn_parts(c, n, S, 96, 176); }
+int attn_parts(int B, int S, int H, int dh, bool backward) {
+  const int n = ((S + 127) / 128) * H * B;
+  if (!backward) return parts_of(n, S, 128, 256);
+  return parts_of(n, S, dh == 64 && S < 1024 ? 32 + S / 16 : 96, 176);
+}
 
 template <int DH, int P>
 static hipError_t attn_fwd_t(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
@@ -861,7 +876,7 @@ template <int DH>
 static hipError_t attn_bwd_t(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                              void* dqkv, float* delta, int B, int S, int H, int causal) {
   const int n = ((S + 127) / 128) * H * B;
-  const int parts = bwd_parts(c, n, S);
+  const int parts = c.attn_split ? c.attn_split : attn_parts(B, S, H, DH, true);
   if (parts == 4) return attn_bwd_launch<DH, BWD_BOTH, 4>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
   if (parts == 2) return attn_bwd_launch<DH, BWD_BOTH, 2>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
   if (n <= kBwdTogether) return attn_bwd_launch<DH, BWD_BOTH, 1>(c, qkv, o, lse, dout, dqkv, delta, B, S, H, causal);
@@ -870,7 +885,7 @@ static hipError_t attn_bwd_t(const OpCtx& c, const void* qkv, const void* o, con
 }
 template <int DH>
 static hipError_t attn_fwd_d(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int causal) {
-  const int parts = fwd_parts(c, ((S + 127) / 128) * H * B, S);
+  const int parts = c.attn_split ? c.attn_split : attn_parts(B, S, H, DH, false);
   return parts == 4 ? attn_fwd_t<DH, 4>(c, qkv, o, lse, B, S, H, causal)
                     : (parts == 2 ? attn_fwd_t<DH, 2>(c, qkv, o, lse, B, S, H, causal) : attn_fwd_t<DH, 1>(c, qkv, o, lse, B, S, H, causal));
 }

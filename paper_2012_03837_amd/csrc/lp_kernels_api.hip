@@ -17,6 +17,7 @@ hipError_t attn_fwd_plain(const OpCtx& c, const void* qkv, void* o, float* lse, 
 hipError_t attn_bwd_plain(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                           void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
 bool attn_mfma_ok(int dh);
+int attn_parts(int B, int S, int H, int dh, bool backward);
 hipError_t attn_fwd_mfma(const OpCtx& c, const void* qkv, void* o, float* lse, int B, int S, int H, int dh, int causal);
 hipError_t attn_bwd_mfma(const OpCtx& c, const void* qkv, const void* o, const float* lse, const void* dout,
                          void* dqkv, float* delta, int B, int S, int H, int dh, int causal);
@@ -128,6 +129,9 @@ extern "C" int lpk_attention_bwd_parts(const void* qkv, const void* o, const flo
   OpCtx c = mk(BF16, stream);
   c.attn_split = parts;
   return (int)attn_bwd_mfma(c, qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal);
+}
+extern "C" int lpk_attention_parts(int B, int S, int H, int dh, int backward) {
+  return attn_mfma_ok(dh) && B > 0 && S > 0 && H > 0 ? attn_parts(B, S, H, dh, backward != 0) : 0;
 }
 extern "C" int lpk_layernorm_fwd(int dtype, const void* x, const float* g, const float* b, void* y, float* mean,
                                  float* rstd, int rows, int d, void* stream) {

@@ -91,6 +91,10 @@ def lpk_attention_bwd_parts(qkv, o, lse, dout, dqkv, delta, B, S, H, dh, causal,
                                       _i(causal), _i(parts), _stream()), "lpk_attention_bwd_parts")
 
 
+def lpk_attention_parts(B, S, H, dh, backward):
+    return lib().lpk_attention_parts(_i(B), _i(S), _i(H), _i(dh), _i(backward))
+
+
 def lpk_layernorm_fwd(dtype, x, g, b, y, mean, rstd, rows, d):
     _ck(lib().lpk_layernorm_fwd(_i(dtype), _p(x), _p(g), _p(b), _p(y), _p(mean), _p(rstd), _i(rows), _i(d), _stream()),
         "lpk_layernorm_fwd")

@@ -32,6 +32,19 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(L, s), s
 
 
+@pytest.mark.parametrize("B,S,H,dh,backward,parts", [
+    (1, 64, 2, 64, 1, 1), (1, 65, 2, 64, 1, 2), (1, 129, 2, 64, 1, 4), (2, 256, 8, 64, 1, 4), (2, 256, 9, 64, 1, 1),
+    (4, 300, 8, 64, 1, 2), (4, 300, 8, 64, 0, 4), (4, 300, 8, 32, 1, 4), (2, 300, 8, 64, 1, 4), (3, 300, 7, 64, 1, 2),
+    (2, 512, 8, 64, 1, 4), (2, 512, 10, 64, 1, 2), (2, 768, 8, 64, 1, 2), (1, 1024, 12, 64, 1, 4), (1, 1536, 8, 64, 1, 4), (1, 2048, 7, 64, 1, 2),
+    (4, 512, 11, 64, 1, 2), (4, 512, 12, 64, 1, 1), (4, 512, 8, 64, 0, 4), (3, 512, 11, 64, 0, 2), (8, 512, 8, 16, 0, 2), (13, 512, 5, 16, 0, 1),
+    (1, 512, 8, 48, 0, 0), (0, 512, 8, 64, 0, 0)])
+def test_attention_parts_follow_the_measurements(B, S, H, dh, backward, parts):
+    """The rule at both sides of its limits.  Four parts of 64-wide heads' backward pass beyond them: 96 blocks of 300 positions
+    15.9 us, 15.4 whole and 13.0 in two."""
+    from paper_2012_03837_amd import kernels as K
+    assert K.lpk_attention_parts(B, S, H, dh, backward) == parts
+
+
 def test_query_sizes_all_configs():
     import numpy as np
     for name in LI.CONFIG_NAMES:
