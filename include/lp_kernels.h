@@ -63,7 +63,9 @@ int lpk_gemm_grouped_tiles(int shape, int pieces, int n, const void* const* A, c
 /* The weight gradients of one layer with its bias gradients, as a step takes them: dw_i[M_i, N_i] (+)= dy_i^T x_i (bf16 dy_i
  * [rows, M_i] and x_i [rows, N_i], fp32 out) and db_i[M_i] (+)= the column sums of dy_i (a null db_i: none), and in the same
  * launch out[j] (+)= sum_b part[b, j], b < nblk, j < len (partial sums that an earlier kernel has left; len 0: none).  n 2 to 5,
- * arrays as in lpk_gemm_grouped; shape and pieces as in lpk_gemm_grouped_tiles, or shape -1: chosen by the library. */
+ * arrays as in lpk_gemm_grouped; shape and pieces as in lpk_gemm_grouped_tiles, or shape -1: chosen by the library.  Where a width
+ * is no multiple of 8 or a matrix is not on a 16-byte boundary the sums go ahead of the products, through the workspace (at least
+ * (rows + 127) / 128 floats for every column of the widest dy_i); a forced shape refuses such matrices. */
 int lpk_weight_grads(int shape, int pieces, int n, const void* const* dy, const int64_t* ld_dy, const void* const* x,
                      const int64_t* ld_x, float* const* dw, float* const* db, const int* M, const int* N, int rows,
                      int accumulate, const float* part, float* out, int nblk, int len, float* splitk_ws_dev,

@@ -95,8 +95,9 @@ extern "C" int lpk_weight_grads(int shape, int pieces, int n, const void* const*
   }
   PendingSums pend;
   if (len > 0) pend.add(part, out, nblk, len, accumulate);
-  OpCtx c = mk(BF16, stream);
-  c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws_elems;
+  // column sums that do not go with the tiles are done with the workspace before the products take it
+  OpCtx c = mk(BF16, stream, splitk_ws, splitk_ws ? splitk_ws_elems : 0);
+  c.splitk_ws = splitk_ws; c.splitk_elems = splitk_ws ? splitk_ws_elems : 0;
   c.pending = &pend; c.with_sums = true;
   if (shape < 0) return (int)op_gemm_grouped(c, g, n);
   c.tile_shape = shape; c.tile_pieces = pieces;

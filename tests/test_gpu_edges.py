@@ -1274,3 +1274,33 @@ def test_attention_row_by_row_for_any_plain(K, dh, plain):
             K.lpk_attention_fwd_parts(qkv, o, lse, B, S, H, bad[0], 1, bad[1])
         with pytest.raises(K.KernelError):
             K.lpk_attention_bwd_parts(qkv, o, lse, dout, dq, delta, B, S, H, bad[0], 1, bad[1])
+
+
+@pytest.mark.parametrize("rows", [999, 100])
+@pytest.mark.parametrize("odd", [(1, 0), (0, 1), (2, 2)])
+def test_weight_gradients_of_odd_widths(K, odd, rows):
+    """A set with one width off a multiple of 8 goes out as column sums, waiting sums and products one after another; stored and
+    added to what is there.  2e-6 as for the tiles; a forced tile refuses it and writes nothing."""
+    import torch
+    sizes = [[264, 520], [520, 136], [8, 16], [72, 264]]
+    if odd[1] < 2: sizes[odd[0]][odd[1]] += 3
+    else: sizes[2] = [11, 13]
+    rng = np.random.default_rng(rows + odd[0])
+    dY, X = [rnd(rng, (rows, m), 1, 0.5) for m, _ in sizes], [rnd(rng, (rows, n), 1, 0.5) for _, n in sizes]
+    part = rng.standard_normal((37, 200)).astype(np.float32)
+    dw = [torch.full((m, n), 3.0, device="cuda") for m, n in sizes]
+    db = [torch.full((m + 1,), 3.0, device="cuda") if i != 3 else None for i, (m, _) in enumerate(sizes)]
+    out, ws = torch.full((201,), 3.0, device="cuda"), torch.full((1 << 22,), float("nan"), device="cuda")
+    args = lambda: ([dev(a, 1) for a in dY], [dev(b, 1) for b in X], dw, db)
+    with pytest.raises(K.KernelError):
+        K.lpk_weight_grads(*args(), 0, ws, dev(part, 0), out, tiles=(2, 1))
+    assert all(bool((t == 3.0).all()) for t in dw + db[:3] + [out])
+    for times in (1, 2):
+        K.lpk_weight_grads(*args(), times - 1, ws, dev(part, 0), out)
+        for i, (a, b) in enumerate(zip(dY, X)):
+            a, b = a.astype(np.float64), b.astype(np.float64)
+            assert relerr(host(dw[i]), times * (a.T @ b)) <= 2e-6
+            if db[i] is not None:
+                assert np.abs(host(db[i][:-1]) - times * a.sum(0)).max() <= times * 2e-6 * np.abs(a).sum(0).max()
+                assert float(db[i][-1]) == 3.0
+        assert relerr(host(out[:-1]), times * part.astype(np.float64).sum(0)) <= 2e-6 and float(out[-1]) == 3.0
