@@ -1136,24 +1136,40 @@ def test_update_keeps_the_transposed_head_weight(K, kind, vocab, heads):
     a.close(); b.close()
 
 
-@pytest.mark.parametrize("seq,batch,vocab,spoil", [(128, 64, 8000, None), (125, 61, 8008, None), (131, 59, 9000, None), (67, 32, 16392, None), (67, 32, 24584, None), (67, 32, 32000, None), (128, 64, 8000, "inf"),
-                                                   (128, 64, 8000, "-inf"), (128, 64, 8000, "nan"), (128, 64, 8000, "huge")])
+@pytest.mark.parametrize("seq,batch,vocab,spoil", [(128, 64, 8000, None), (125, 61, 8008, None), (131, 59, 9000, None), (67, 32, 16392, None), (67, 32, 24584, None), (67, 32, 32000, None),
+                                                   (128, 64, 8000, "inf"), (128, 64, 8000, "-inf"), (67, 32, 32000, "-inf"), (128, 64, 8000, "nan"), (128, 64, 8000, "huge"),
+                                                   (128, 64, 8000, "inf below"), (128, 64, 8000, "inf in a row")])
 def test_evaluation_loss_without_logits(K, seq, batch, vocab, spoil):
     """A large head's evaluation, whose product leaves the rows' group sums instead of logits: the bits of the losses that a step
-    reports, with ragged rows and classes past whole groups of 64; rows of infinite, very large and undefined logits; labels out of range."""
+    reports, with ragged rows and classes past whole groups of 64; labels out of range; very large logits.  A class of infinite or
+    undefined logits in every row, a whole group of 64 at -inf in every row ("-inf": the loss is that of the other classes), one
+    class at -inf ("inf below") that is +inf in a single row instead ("inf in a row": the mean is NaN).  The finite ones against
+    float64 over the same bf16 features and logits: fp32 exponentials and sums of losses of 9 (of 8000 where logits are very
+    large), 2e-5 + 1e-6; a class left out or counted twice is 3e-5 to 1e-4."""
     import paper_2012_03837_amd as lp
     cfg = LI.configs.decoder_config("t", n_layers=1, width=128, n_heads=2, hidden=64, seq_len=seq, batch=batch, vocab=vocab, act="gelu")
     tr = lp.LocalTrainer(cfg)
     P = generic_params(cfg)
-    if spoil:
-        w = P["H1.w"]
-        value = dict(inf=np.inf, nan=np.nan, huge=3e4).get(spoil, -np.inf)
-        w[130, 3] = value           # one class of the third group
-        if spoil == "-inf":         # every class of a group on one side of zero
-            w[192:256, 5] = value
-    tr.set_params(P)
     x, y = data_for(cfg)
-    y = y.copy()
+    x, y = x.copy(), y.copy()
+    w = P["H1.w"]
+    if spoil == "huge":
+        w[130, 3] = 3e4
+    elif spoil in ("inf below", "inf in a row"):
+        # the layer hands its input on, in which feature 5 is below the mean for every token but one
+        for k in ("L1.wo", "L1.bo", "L1.w2", "L1.b2"): P[k][...] = 0
+        P["L1.emb"][:, 5] = -10
+        P["L1.emb"][17, 5] = 10
+        P["H1.ln.g"][5], P["H1.ln.b"][5] = 1, 0
+        w[130, 5] = np.inf
+        x[x == 17] = 18
+        if spoil == "inf in a row": x[3, 9] = 17
+    elif spoil:
+        P["H1.ln.g"][5], P["H1.ln.b"][5] = 0, 1      # feature 5 is 1 in every row
+        if spoil == "-inf": w[192:256, 5] = -np.inf
+        else: w[130, 5] = np.inf if spoil == "inf" else np.nan
+    y[(y == 130) | ((y >= 192) & (y < 256))] = 7
+    tr.set_params(P)
     y[0, 0], y[1, 1], y[2, 2] = vocab, -1, vocab - 1
     xd, yd = tr.stage(x, y)
     lp.lp_profile_enable(tr.ctx, True)
@@ -1161,8 +1177,20 @@ def test_evaluation_loss_without_logits(K, seq, batch, vocab, spoil):
     assert any(k["name"].endswith("64, true>") for k in lp.lp_profile_gemm_kernels(tr.ctx))
     lp.lp_profile_enable(tr.ctx, False)
     np.testing.assert_array_equal(tr.eval(xd, yd).cpu().numpy(), ev)
+    if spoil in ("inf", "nan", "inf in a row"):
+        assert np.isnan(ev).all()
+    else:
+        h = tr.get("L1.out").astype(np.float64)
+        feat = (h - h.mean(1, keepdims=True)) / np.sqrt(h.var(1, keepdims=True) + 1e-5) * P["H1.ln.g"].astype(np.float64) + P["H1.ln.b"]
+        feat, wb, yy = ops.bf16_round(feat.astype(np.float32)).astype(np.float64), ops.bf16_round(w).astype(np.float64), y.reshape(-1)
+        total = 0.0
+        for r in range(0, len(yy), 1024):
+            z = ops.bf16_round((feat[r:r + 1024] @ wb.T).astype(np.float32)).astype(np.float64)
+            t, m = yy[r:r + 1024], z.max(1)
+            zy = np.where((t >= 0) & (t < vocab), np.take_along_axis(z, np.clip(t, 0, vocab - 1)[:, None], 1)[:, 0], 0.0)
+            total += (m + np.log(np.exp(z - m[:, None]).sum(1)) - zy).sum()
+        assert abs(ev[0] - total / len(yy)) <= 2e-5 + 1e-6 * abs(total / len(yy)), (ev, total / len(yy))
     np.testing.assert_array_equal(tr.step(xd, yd).cpu().numpy(), ev)
-    if spoil in ("huge", None): assert np.isfinite(ev).all()
     tr.close()
 
 
@@ -1304,3 +1332,114 @@ def test_weight_gradients_of_odd_widths(K, odd, rows):
                 assert np.abs(host(db[i][:-1]) - times * a.sum(0)).max() <= times * 2e-6 * np.abs(a).sum(0).max()
                 assert float(db[i][-1]) == 3.0
         assert relerr(host(out[:-1]), times * part.astype(np.float64).sum(0)) <= 2e-6 and float(out[-1]) == 3.0
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("parts", [1, 2, 4])
+@pytest.mark.parametrize("dh", [16, 32])
+def test_attention_parts_non_finite(K, dh, parts, causal):
+    """As test_attention_small_heads_non_finite in one, two and four parts, both kinds of the backward pass in one launch: every
+    sequence holds one infinity or NaN, in q, k, v or the output's gradient, in the first, second or third tile, or none."""
+    rng = np.random.default_rng(dh)
+    cases = [(what, part, row) for what in (np.inf, -np.inf, np.nan) for part in range(4) for row in (5, 70, 149)] + [None]
+    B, S, H = len(cases), 150, 2
+    d = H * dh
+    qkv, dout = rnd(rng, (B, S, 3 * d), 1), rnd(rng, (B, S, d), 1)
+    for b, (what, part, row) in enumerate(cases[:-1]):
+        (dout if part == 3 else qkv)[b, row, (0 if part == 3 else part * d) + dh + 3] = what
+    seen = []
+    for forced in (True, False):
+        o, lse, delta = zeros(B * S, d).bfloat16(), zeros(B, H, S), zeros(B, H, S)
+        dqkv = zeros(B * S, 3 * d).bfloat16()
+        if forced:
+            K.lpk_attention_fwd_parts(dev(qkv, 1), o, lse, B, S, H, dh, causal, parts)
+            K.lpk_attention_bwd_parts(dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal, parts)
+        else:
+            K.lpk_attention_fwd(1, dev(qkv, 1), o, lse, B, S, H, dh, causal, plain=1)
+            K.lpk_attention_bwd(1, dev(qkv, 1), o, lse, dev(dout, 1), dqkv, delta, B, S, H, dh, causal, plain=1)
+        seen.append([host(t).reshape(B, -1) for t in (o, lse, dqkv)])
+    for i, case in enumerate(cases):
+        for name, a, b in zip(("o", "lse", "dqkv"), (t[i] for t in seen[0]), (t[i] for t in seen[1])):
+            assert (np.isfinite(a) == np.isfinite(b)).all(), (case, name)
+            assert (np.isposinf(a) == np.isposinf(b)).all() and (np.isneginf(a) == np.isneginf(b)).all(), (case, name)
+            ok = np.isfinite(b)
+            assert np.abs(a[ok] - b[ok]).max(initial=0) <= 2.0 ** -6 * max(1.0, np.abs(b[ok]).max(initial=0)), (case, name)
+
+
+def test_more_filter_gradients_than_wait_at_once(K):
+    """Ten convolutions whose filter gradients are all cut, in a workspace that holds them all, two more than the table of those
+    that wait: it is emptied when it is full.  The bits of each alone."""
+    import torch
+    base = [(50, 28, 28, 24, 24, 3, 1, 1), (50, 14, 14, 48, 48, 3, 1, 1), (40, 8, 8, 128, 128, 3, 1, 1), (30, 14, 14, 64, 64, 3, 1, 1), (50, 7, 7, 96, 96, 3, 1, 1)]
+    dims, ws = [(d[0] - i, *d[1:]) for i in range(2) for d in base], torch.full((1 << 26,), float("nan"), device="cuda")
+    pieces = [K.lpk_conv_plan(2, *d, ws.numel())[1] for d in dims]
+    assert sum(p > 1 for p in pieces) > 8 and sum(p * d[4] * d[5] ** 2 * d[3] for p, d in zip(pieces, dims)) <= ws.numel()
+    rng = np.random.default_rng(3)
+    out = lambda d: ((d[1] + 2 * d[7] - d[5]) // d[6] + 1, (d[2] + 2 * d[7] - d[5]) // d[6] + 1)
+    xs = [dev(rnd(rng, d[:4], 1), 1) for d in dims]
+    dys = [dev(rnd(rng, (d[0], *out(d), d[4]), 1), 1) for d in dims]
+    got, want = ([zeros(d[4], d[5], d[5], d[3]) for d in dims] for _ in range(2))
+    for acc in (0, 1):
+        K.lpk_conv_weight_grads(dys, xs, got, dims, ws, accumulate=acc)
+        for d, x, dy, w in zip(dims, xs, dys, want):
+            K.lpk_conv_bwd_weight_ws(1, dy, x, w, *d, ws, accumulate=acc)
+        for g, w in zip(got, want):
+            assert torch.isfinite(g).all() and torch.equal(g, w)
+
+
+@pytest.mark.parametrize("rows", [1, 7, 63, 64, 65, 129])
+def test_weight_gradients_of_few_rows(K, rows):
+    """As test_weight_gradients_with_sums over a reduction of less than a k-tile, one, and a little more, on the library's choice."""
+    import torch
+    sizes = [(264, 520), (136, 72), (8, 8)]
+    rng = np.random.default_rng(rows)
+    dY, X = [rnd(rng, (rows, m), 1, 0.5) for m, _ in sizes], [rnd(rng, (rows, n), 1, 0.5) for _, n in sizes]
+    dw, db, ws = [zeros(m, n) for m, n in sizes], [zeros(m) for m, _ in sizes], torch.full((1 << 22,), float("nan"), device="cuda")
+    K.lpk_weight_grads([dev(a, 1) for a in dY], [dev(b, 1) for b in X], dw, db, 0, ws)
+    for a, b, w, s in zip(dY, X, dw, db):
+        a, b = a.astype(np.float64), b.astype(np.float64)
+        assert relerr(host(w), a.T @ b) <= 2e-6
+        assert np.abs(host(s) - a.sum(0)).max() <= 2e-6 * np.abs(a).sum(0).max()
+
+
+@pytest.mark.parametrize("n_streams", [0, 2])
+@pytest.mark.parametrize("layers,seq,batch,vocab", [(3, 511, 4, 10003), (2, 128, 16, 16000)])
+def test_captured_evaluation(K, layers, seq, batch, vocab, n_streams):
+    """An evaluation inside a caller's capture stays on the caller's stream also where it would use side streams (the first size)
+    and where a head's logits are not stored: replays after steps and changed inputs have the bits of eager evaluations."""
+    import torch
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=layers, width=448, n_heads=7, hidden=1792, seq_len=seq, batch=batch, vocab=vocab, act="gelu")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        tr = lp.LocalTrainer(cfg, stream=s, n_streams=n_streams)
+        tr.set_params(generic_params(cfg))
+        xd, yd = tr.stage(*data_for(cfg))
+        tr.eval(xd, yd)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            tr.eval(xd, yd)
+        for step in range(4):
+            x2, y2 = tr.stage(*data_for(cfg, step))
+            xd.copy_(x2); yd.copy_(y2)
+            want = tr.eval(xd, yd).clone()
+            tr.losses.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(tr.losses, want), step
+            tr.step(xd, yd)
+            torch.cuda.synchronize()
+    tr.close()
+
+
+@pytest.mark.parametrize("scheme,n_streams", [("greedy", 0), ("overlap", 2), ("backprop", 1)])
+def test_decoder_of_odd_hidden_width(K, scheme, n_streams):
+    """A hidden width off a multiple of 8: a layer's bias gradients and waiting sums cannot go with its weight gradients' tiles.
+    Two steps against the oracle."""
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=3, width=64, n_heads=2, hidden=100, seq_len=37, batch=4, vocab=203, act="gelu", scheme=scheme)
+    tr = lp.LocalTrainer(cfg, n_streams=n_streams)
+    x, y = data_for(cfg)
+    compare_step(tr, cfg, generic_params(cfg), x, y, n_steps=2, label=scheme)
+    tr.close()
