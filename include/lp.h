@@ -116,9 +116,9 @@ typedef struct {
                                forward pass continues on the caller's stream; all of them are joined back
                                into the caller's stream before lp_local_step returns.  Results do not depend
                                on n (every per-parameter accumulation keeps its order).  At most 8.
-                               lp_eval_loss of a decoder with several heads uses them the same way for all
-                               heads but the last where they are large (and the caller's stream is not being
-                               captured), and joins them before it returns.  The
+                               lp_eval_loss of a decoder with several large heads uses them the same way
+                               (unless the caller's stream is being captured), and joins them before it
+                               returns.  The
                                synchronous step of a residual MLP whose heads sit behind different layers does
                                not use them in fp32 (nor in bf16 with n = 1): its blocks walk their backward
                                passes together on the caller's stream, the products of all of them in shared

@@ -431,15 +431,16 @@ int vocab_head_stage(lp_ctx* c, int hi, int batch, const int32_t* y, float* loss
   return LP_OK;
 }
 
-// Whether an evaluation's vocabulary heads, all but the last, run on side streams beside the layers behind them.  Two events and
-// two waits a head cost the host 10 to 20 us, which shows where the device has less than that to do; behind large heads the
-// overlap fills the ends of launches, more so where the logits go through memory to a launch of their own (op_gemm_loss).  Priced
-// per head with its layers, in us: the products at 1 PFLOP/s and such logits at 4 TB/s.  Evaluations, price: on one stream / heads
-// beside, us.  Without logits: 4 x 256 over 2048 rows, 32000 classes, 37: 446 / 482; 4 x 512 over 2048, 32000, 80: 625 / 649; 4 x
-// 768 over 2048, 32000, 130: 902 / 910; 8 x 512 over 8192, 16000, 185: 2315 / 2282; 6 x 768 over 4096, 32000, 260: 2118 / 2049; 12 x
-// 768 over 8192, 32000, 520: 7708 / 7557.  With: 3 x 128 over 600, 1000, 1: 132 / 158; 4 x 256 over 2048, 8000, 28: 320 / 349; 8 x 256
-// in pairs over 2048, 10003, 37: 515 / 541; 6 x 448 over 2044, 10003, 48: 651 / 621; 6 x 768 over 2048, 5003, 55: 851 / 777; 8 x 512
-// in pairs over 2048, 16000, 92: 777 / 762; 4 x 64 over 8192, 20000, 185: 682 / 629.
+// Whether an evaluation's vocabulary heads run on side streams beside the layers behind them.  Two events and two waits a head
+// cost the host 10 to 20 us, which shows where the device has less than that to do; behind large heads the overlap fills the ends
+// of launches, more so where the logits go through memory to a launch of their own (op_gemm_loss), and most where their classes
+// end in a part of a 16-byte chunk.  Priced per head with its layers, in us: the products at 1 PFLOP/s and such logits at 4 TB/s.
+// Evaluations, price: on one stream / heads beside, us.  Without logits: 4 x 256 over 2048 rows, 32000 classes, 37: 446 / 486; 4 x
+// 512 over 2048, 32000, 80: 625 / 649; 4 x 768 over 2048, 32000, 130: 902 / 914; 8 x 512 over 8192, 16000, 185: 2315 / 2263; 6 x 768
+// over 4096, 32000, 260: 2118 / 2041; 12 x 768 over 8192, 32000, 520: 7708 / 7524.  With: 4 x 128 over 64, 1000, 0: 169 / 270; 4 x
+// 256 over 2048, 8000, 28: 320 / 358; 8 x 768 in pairs over 512, 32000, 56: 688 / 724; 4 x 768 over 2048, 8000, 70: 605 / 604; 8 x 512
+// in pairs over 2048, 16000, 92: 777 / 767; 4 x 64 over 8192, 20000, 185: 682 / 629.  With odd classes: 8 x 256 in pairs over 2048,
+// 10003, 37: 515 / 548; 6 x 448 over 2044, 10003, 48: 651 / 621; 6 x 768 over 2048, 5003, 55: 851 / 773.
 bool eval_beside(lp_ctx* c, int batch) {
   const int J = c->spec.n_heads;
   if (J < 2 || batch <= 0 || c->spec.vocab <= 0) return false;      // a single head has nothing to run beside
@@ -453,9 +454,9 @@ bool eval_beside(lp_ctx* c, int batch) {
     us += 2e-3 * n * h.s.in_dim / J;
     logits += n / J;
   }
-  if (us >= 100.0) return true;
-  if (us + logits < 45.0) return false;
   HeadState& h = c->heads[0];
+  if (us >= 100.0) return true;
+  if (us + logits < (h.s.n_classes % 8 ? 45.0 : 70.0)) return false;
   return h.s.kind != LP_HEAD_LN_LINEAR_CE || h.t.count("b") ||
          !gemm_loss_ok(c->op(), head_fwd(c, h, batch * c->layers[h.e].s.seq_len, h.t["w"], c->logits));
 }

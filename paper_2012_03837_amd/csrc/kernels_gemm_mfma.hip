@@ -115,6 +115,11 @@ static bool deep_auto() {     // LP_GEMM_K64=0 keeps the 64-deep k-tiles out of 
   return v != 0;
 }
 
+// Short reductions over at most two waves of tiles (a layer's K = 768 products): with anything fused they go one tile per block
+// at these prices too, and plain ones are within a tenth of each other (8192 x 3072 x 768 49 us here, 57 one tile per block;
+// 2184 x 6408 x 832 32 and 30, 980 x 31144 x 312 44 and 38), so the search over this kernel's plans, half a microsecond on the host, is left out.
+static bool short_and_few(const GemmArgs& g) { return g.K <= 1024 && (long)((g.M + 255) / 256) * ((g.N + 255) / 256) <= 512; }
+
 // The kernel and plan of a product; false where the kernel that is forced does not take it.
 static bool choose(const OpCtx& c, const GemmArgs& g, bool* dma, DmaGemmPlan* dma_plan, TilePlan* tile_plan) {
   const int choice = c.gemm_variant ? c.gemm_variant : env_choice();
@@ -129,11 +134,7 @@ static bool choose(const OpCtx& c, const GemmArgs& g, bool* dma, DmaGemmPlan* dm
   else if (choice >= 3) { force_kind = (choice - 3) / 2; force_cut = (choice - 3) % 2; }
   const int streams = (g.pre ? 1 : 0) + (g.dact != ACT_NONE ? 1 : 0) + (g.res ? 1 : 0) + (g.accumulate ? 1 : 0);
   const bool fused = streams || g.bias || g.act != ACT_NONE;
-  // Short reductions over at most two waves of tiles (a layer's K = 768 products): with anything fused they go one tile per block
-  // at these prices too, and plain ones are within a tenth of each other (8192 x 3072 x 768 49 us here, 57 one tile per block;
-  // 2184 x 6408 x 832 32 and 30, 980 x 31144 x 312 44 and 38), so the search over this kernel's plans, half a microsecond on the host, is left out.
-  const bool short_and_few = g.K <= 1024 && (long)((g.M + 255) / 256) * ((g.N + 255) / 256) <= 512;
-  if (gemm_dma_ok(g) && choice != 2 && !(choice == 0 && short_and_few)) {
+  if (gemm_dma_ok(g) && choice != 2 && !(choice == 0 && short_and_few(g))) {
     for (int kind = 0; kind < 4; ++kind) {
       if (force_kind >= 0 ? kind != force_kind : (kind == 2 || (kind == 3 && !deep_auto()))) continue;   // the 4-wave shape only when asked for
       for (int cut = 0; cut < 3; ++cut) {                 // tail whole / cut along k / panel mode
@@ -230,6 +231,7 @@ static bool loss_plan(const OpCtx& c, const GemmArgs& g, DmaGemmPlan* d) {
   if (c.dt != BF16 || use_plain() || !fast_ok(g) || !ce_fast_ok(c, g.C, g.ldc, g.N)) return false;
   if (g.bias || g.pre || g.act != ACT_NONE || g.dact != ACT_NONE || g.res || g.accumulate || g.c_f32 || g.rowsum) return false;
   if (((size_t)8 * ((g.N + 63) / 64) + 4) > (size_t)2 * g.ldc) return false;
+  if (c.gemm_variant == 0 && env_choice() == 0 && short_and_few(g)) return false;      // without pricing it: small evaluations wait for the host
   bool dma;
   TilePlan t;
   return choose(c, g, &dma, d, &t) && dma && gemm_dma_stats_ok(g, *d);

@@ -1000,7 +1000,6 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
   const int32_t* ids = c->spec.vocab > 0 ? (const int32_t*)x : nullptr;
   if (train && c->mlp_lockstep) return run_mlp(c, y, batch, losses);
   int hj = 0, chain = 0;
-  const int n_beside = train ? J : J - 1;      // heads on side streams, if any are; an evaluation ends with its last head
   c->use(0);
   for (int li = 1; li <= L; ++li) {
     c->use(0);
@@ -1012,11 +1011,11 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
         if (c->heads[j].s_lo <= li && li <= c->heads[j].e) CK(hipStreamWaitEvent(c->stream, c->ev_chain[j], 0));
     }
     if ((st = drv_forward(c, li, batch, ids)) != LP_OK) return st;
-    if (side && hj < n_beside && c->heads[hj].e == li) CK(hipEventRecord(c->ev_fwd[li], c->stream));
+    if (side && hj < J && c->heads[hj].e == li) CK(hipEventRecord(c->ev_fwd[li], c->stream));
     // every head attached after this layer runs as soon as the activation exists
     for (; hj < J && c->heads[hj].e == li; ++hj) {
       HeadState& Hd = c->heads[hj];
-      const int set = side && hj < n_beside ? 1 + (chain++ % c->n_side) : 0;
+      const int set = side ? 1 + (chain++ % c->n_side) : 0;
       c->use(set);
       if (set) CK(hipStreamWaitEvent(c->cur_stream, c->ev_fwd[li], 0));
       if ((st = drv_head(c, hj, batch, y, losses + hj, train, c->dA)) != LP_OK) return st;
@@ -1068,7 +1067,7 @@ static int run(lp_ctx* c, const void* x, const int32_t* y, int batch, float* los
   if (overlap) {
     c->pending_join = true;        // joined by the next call that is not an overlapped step
   } else if (side) {
-    for (int j = 0; j < n_beside; ++j) CK(hipStreamWaitEvent(c->stream, c->ev_chain[j], 0));
+    for (int j = 0; j < J; ++j) CK(hipStreamWaitEvent(c->stream, c->ev_chain[j], 0));
     c->pending_join = false;
   }
   return LP_OK;
