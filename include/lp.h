@@ -255,7 +255,7 @@ int lp_profile_enable(lp_ctx* ctx, int on);
 int lp_profile_gemm_shapes(lp_ctx* ctx, char* out, size_t cap);
 /* The main kernel of every bf16 GEMM op (and of every convolution run as implicit GEMM) since profiling was enabled, grouped by kernel instance, as text into
  * the host buffer `out`: one line per instance, "name<TAB>launches<TAB>total_ms<TAB>algorithmic_flops", where the
- * name is the kernel's name as a profiler prints it ("k_gemm_dma<true, true, 4, 2, 4, true>") and the time is
+ * name is the kernel's name as a profiler prints it ("k_gemm_dma<true, true, 4, 2, 2, true, 64, false>") and the time is
  * that of the one launch (an event pair around it; the op's partial-sum fix-up kernel, if any, is outside).
  * LP_ESHAPE if the buffer is too small. */
 int lp_profile_gemm_kernels(lp_ctx* ctx, char* out, size_t cap);

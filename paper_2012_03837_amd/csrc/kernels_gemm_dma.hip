@@ -874,8 +874,8 @@ hipError_t launch(const OpCtx& c, const GemmArgs& g, const SkPlan& p, bool parti
   Epilogue e = make_epilogue(g);
   static char kname[64];
   if (!kname[0])
-    snprintf(kname, sizeof kname, KT == 32 ? "k_gemm_dma<%s, %s, %d, %d, %d, %s>" : "k_gemm_dma<%s, %s, %d, %d, %d, %s, 64>",
-             A_KC ? "true" : "false", B_KC ? "true" : "false", WNW, TN, NSTAGE, PIPE ? "true" : "false");
+    snprintf(kname, sizeof kname, "k_gemm_dma<%s, %s, %d, %d, %d, %s, %d, false>", A_KC ? "true" : "false", B_KC ? "true" : "false", WNW, TN,
+             NSTAGE, PIPE ? "true" : "false", KT);
   hipError_t err;
   static const GroupTable no_group = {};
   const GroupTable& gt = grp ? *grp : no_group;

@@ -1443,3 +1443,18 @@ def test_decoder_of_odd_hidden_width(K, scheme, n_streams):
     x, y = data_for(cfg)
     compare_step(tr, cfg, generic_params(cfg), x, y, n_steps=2, label=scheme)
     tr.close()
+
+
+def test_profiled_kernel_names_are_whole(K):
+    """Products of the persistent kernel are listed under the name that a profiler prints: with every template argument."""
+    import re
+    import paper_2012_03837_amd as lp
+    cfg = LI.configs.decoder_config("t", n_layers=1, width=128, n_heads=2, hidden=64, seq_len=128, batch=64, vocab=32000, act="gelu")
+    tr = lp.LocalTrainer(cfg)
+    xd, yd = tr.stage(*data_for(cfg))
+    lp.lp_profile_enable(tr.ctx, True)
+    tr.step(xd, yd)
+    names = [k["name"] for k in lp.lp_profile_gemm_kernels(tr.ctx) if k["name"].startswith("k_gemm_dma")]
+    lp.lp_profile_enable(tr.ctx, False)
+    assert names and all(re.fullmatch(r"k_gemm_dma<(true|false), (true|false), \d, \d, \d, (true|false), (32|64), (true|false)>", n) for n in names), names
+    tr.close()
