@@ -62,7 +62,8 @@ int lpk_gemm_grouped_tiles(int shape, int pieces, int n, const void* const* A, c
 
 /* The weight gradients of one layer with its bias gradients, as a step takes them: dw_i[M_i, N_i] (+)= dy_i^T x_i (bf16 dy_i
  * [rows, M_i] and x_i [rows, N_i], fp32 out) and db_i[M_i] (+)= the column sums of dy_i (a null db_i: none), and in the same
- * launch out[j] (+)= sum_b part[b, j], b < nblk, j < len (partial sums that an earlier kernel has left; len 0: none).  n 2 to 5,
+ * launch out[j] (+)= sum_b part[b, j], b < nblk, j < len (partial sums that an earlier kernel has left; len 0: none); no output
+ * overlaps another.  n 2 to 5,
  * arrays as in lpk_gemm_grouped; shape and pieces as in lpk_gemm_grouped_tiles, or shape -1: chosen by the library.  Where a width
  * is no multiple of 8 or a matrix is not on a 16-byte boundary the sums go ahead of the products, through the workspace (at least
  * (rows + 127) / 128 floats for every column of the widest dy_i); a forced shape refuses such matrices. */
@@ -153,7 +154,7 @@ int lpk_conv_bwd_weight_ws(int dtype, const void* dout, const void* x, float* dw
 
 /* The filter gradients of a stage's convolutions, as its backward pass takes them: the pieces of all wait in the workspace and
  * are added in one launch (in more where they do not fit together), with the bits of lpk_conv_bwd_weight_ws.  bf16; dims: n rows
- * of N, H, W, C, O, R, stride, pad. */
+ * of N, H, W, C, O, R, stride, pad; no dw overlaps another. */
 int lpk_conv_weight_grads(int n, const void* const* dout, const void* const* x, float* const* dw, const int* dims, int accumulate,
                           float* splitk_ws_dev, size_t splitk_ws_elems, void* stream);
 

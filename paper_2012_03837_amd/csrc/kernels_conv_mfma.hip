@@ -287,8 +287,9 @@ unsigned reduce_blocks(int M, int N, int lanes) { return (unsigned)(((size_t)M *
 
 // The same for the filter gradients of a stage's backward pass, each in its own blocks (first[i]: the first of gradient i's).
 // Alone each is a few KB to a few MB of sums, bound by a launch and two memory latencies (5 us) in the middle of the chain of a
-// backward pass; together they cost one such launch a stage, with the same bits.  A step: four stages of batch 256 (64 channels)
-// 2621 -> 2598 us, three stages of 24 channels on 28 x 28, whose launches the host issues as fast as they run, 624 -> 584 us.
+// backward pass; together they cost one such launch a stage, with the same bits.  A step, before and after in turn on one card: four
+// stages of batch 256 (64 channels) 2620 and 2598 us (runs of one side 0.1 % apart), with batch 128 and one head 2308 and 2257; of
+// three stages of 24 channels on 28 x 28 it is lost in the noise of the host's issue (6 to 10 %).
 struct FilterTable { PendingFilters::Filter f[kMaxFilters]; int lanes[kMaxFilters], first[kMaxFilters]; int count; };
 __global__ void __launch_bounds__(256) k_conv_reduce_filters(FilterTable t) {
   int p = 0;

@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(256) k_ln_bwd_v(const bf16_t* __restrict__ dy,
   }
 }
 
-// Softmax cross-entropy with the whole row in registers (<= 16 chunks of 8 logits per thread).  TAIL: n is not a
+// Softmax cross-entropy with the whole row in registers (4 to 12 chunks of 8 logits per thread).  TAIL: n is not a
 // multiple of 8; the last chunk reaches into the row's padding, whose values count as -inf.  Chunks from n up to
 // pad_to are cleared together with the gradient's write (a padded dZ is read whole by the products behind it).
 // CH: chunks of a thread that there is room for, T threads.  Room for 8192 logits where a row has no more lets three times as

@@ -223,10 +223,10 @@ bool gemm_joins(const OpCtx& c, const GemmArgs* group, int n, const GemmArgs& g)
 }
 
 // The row losses of a head whose logits nothing else needs: instead of storing them (bf16 [rows, ld] into g.C) and reading them
-// again, the product leaves a pair per row and 64 columns in that memory, a 64th of it, and a short launch the losses; the
-// bits of op_softmax_ce.  Only where the product itself would be uncut 256 x 256 tiles (a large head); hipErrorInvalidValue,
-// with nothing launched, where not.  Twelve layers of 768, 8192 rows, 32000 classes: 8.66 -> 7.72 ms an
-// evaluation.
+// again, the product leaves a pair per row and 64 columns in that memory, a 16th of it (and the label's logit per row), and a
+// short launch the losses; the bits of op_softmax_ce.  Only where the product itself would be uncut 256 x 256 tiles (a large
+// head); hipErrorInvalidValue, with nothing launched, where not.  Twelve layers of 768, 8192 rows, 32000 classes: 8.66 -> 7.72 ms
+// an evaluation.
 static bool loss_plan(const OpCtx& c, const GemmArgs& g, DmaGemmPlan* d) {
   if (c.dt != BF16 || use_plain() || !fast_ok(g) || !ce_fast_ok(c, g.C, g.ldc, g.N)) return false;
   if (g.bias || g.pre || g.act != ACT_NONE || g.dact != ACT_NONE || g.res || g.accumulate || g.c_f32 || g.rowsum) return false;
@@ -255,7 +255,6 @@ hipError_t gemm_tile_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
     if (!fast_ok(gs[i]) || gs[i].K != gs[0].K || gs[i].a_kc != gs[0].a_kc || gs[i].b_kc != gs[0].b_kc || (gs[i].rowsum && !c.with_sums)) return hipErrorInvalidValue;
   return gemm_tile(c, gs, n, gemm_tile_plan(c, gs, n));
 }
-
 
 hipError_t op_gemm_grouped(const OpCtx& c, const GemmArgs* gs, int n) {
   if (c.dt == F32 && n >= 2) {
